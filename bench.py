@@ -660,16 +660,17 @@ def phase_of_kernel(name: str):
     for the launch variants with work counters, which run only to count)."""
     import re
 
-    simple = (("scan_tags_kernel", "scan_tags"), ("scan_counts_kernel", "scan_slots"),
+    simple = (("scan_tags_kernel", "scan_tags"), ("scan_slots_kernel", "scan_slots"),
+              ("list_kernel", "bisect_write"), ("list_small_kernel", "bisect_write"),
               ("scan_counts_dev_kernel", "scan_records"), ("finish_kernel", "finish"))
     for key, phase in simple:
         if f"sx::{key}(" in name:
             return phase
     if re.search(r"sx::record_kernel(<(true|false)>)?\(", name):
         return "records"
-    m = re.search(r"sx::bisect_kernel<(true|false), (true|false), \d+>", name)
+    m = re.search(r"sx::bisect_kernel<(true|false), \d+>", name)
     if m:
-        return None if m.group(2) == "true" else ("bisect_write" if m.group(1) == "true" else "bisect_count")
+        return None if m.group(1) == "true" else "bisect_count"
     m = re.search(r"sx::slot_kernel<\d+, (true|false)(, (true|false))?>", name)
     if m:
         return None if m.group(1) == "true" else "pieces"

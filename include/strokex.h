@@ -295,8 +295,10 @@ int sx_debug_piece_stats(sx_ctx *ctx, const sx_scene *scene, float tolerance, in
 /* The phases of sx_expand_async, one kernel each, for per-kernel timing:
  *   SX_PHASE_SCAN_TAGS     tag-monoid scan (Section 8.2)
  *   SX_PHASE_BISECT_COUNT  Algorithm 2 per segment: slots per tag (pieces + 1)
- *   SX_PHASE_SCAN_SLOTS    exclusive scan of the slot counts (slot bases)
- *   SX_PHASE_BISECT_WRITE  Algorithm 2 again: each piece's slot at its base
+ *   SX_PHASE_SCAN_SLOTS    exclusive scan of the slot counts (slot bases; a
+ *                          small scene's are part of the next phase, and
+ *                          this one launches nothing)
+ *   SX_PHASE_BISECT_WRITE  the piece list: each piece at its canonical place
  *   SX_PHASE_PIECES        per piece slot: Euler spiral, parallel curves and
  *                          counts (Sections 4-6) as emission items, and the
  *                          slot's record count

@@ -261,10 +261,10 @@ hipError_t reserve_scene(sx_scene* s, uint32_t n_tags, uint32_t n_pts, uint32_t 
         regrow(s->d_tags, ntag_pad);
         regrow(s->d_mon, 4 * (size_t)sx::mon_stride_of(c) * sizeof(uint32_t));
         regrow(s->d_nslots, ((size_t)c + 16) * sizeof(uint32_t));
-        // kept piece codes: keep_codes_of(n) x mon_stride_of(n) words for any
-        // n <= c (at most 2^25, or kKeepCodes rows of c)
-        regrow(s->d_codes, std::max<size_t>((size_t)1 << 25, (size_t)sx::mon_stride_of(c) * sx::kKeepCodes) *
-                               sizeof(uint32_t));
+        // kept piece codes: n x keep_codes_of(n) words for any n <= c (at
+        // most 2^25, or kKeepCodes per tag)
+        regrow(s->d_codes, std::min<size_t>(std::max<size_t>((size_t)1 << 25, (size_t)c * sx::kKeepCodes),
+                                            (size_t)c * 1024) * sizeof(uint32_t));
         regrow(s->d_base, ((size_t)c + 1) * sizeof(uint64_t));
         regrow(s->d_status_tags, sx::scan_status_bytes(c));
         regrow(s->d_status_nslots, sx::scan_status_bytes(c));
@@ -338,14 +338,14 @@ hipError_t run_one(const sx_ctx* ctx, const sx_scene* s, const sx::Cfg& cfg, int
                                         st);
         case kPhBisectCount:
             return sx::launch_bisect(view(s), cfg, t.bisect_range, sx::keep_codes_of(s->n_tags), (int)t.bisect_waves,
-                                     false, s->d_nslots,
-                                     s->d_codes, nullptr, nullptr, 0, stats, st);
+                                     s->d_nslots, s->d_codes, stats, st);
         case kPhScanSlots:
-            return sx::launch_scan_counts(s->d_nslots, s->n_tags, s->d_base, ctl_block(s, 1), s->d_status_nslots, st);
+            // (a small scene's bases are part of the next phase)
+            if (sx::list_is_small(s->n_tags)) return hipSuccess;
+            return sx::launch_scan_slots(s->d_nslots, s->n_tags, s->d_base, ctl_block(s, 1), s->d_status_nslots, st);
         case kPhBisectWrite:
-            return sx::launch_bisect(view(s), cfg, t.bisect_range, sx::keep_codes_of(s->n_tags), (int)t.bisect_waves,
-                                     true, s->d_nslots,
-                                     s->d_codes, s->d_base, s->d_slots, s->slot_cap, nullptr, st);
+            return sx::launch_list(view(s), cfg, sx::keep_codes_of(s->n_tags), s->d_nslots, s->d_codes, s->d_base,
+                                   s->d_slots, s->slot_cap, st);
         case kPhPieces:
             return sx::launch_slots(view(s), cfg, workspace(s), s->d_slots, n_slots_dev(s), s->slot_cap, s->d_rc,
                                     (int)t.piece_waves, stats, st);

@@ -1364,6 +1364,13 @@ SX_FN Tan sample_q(const Seg& s, double t) {
     return Tan{q, ql};
 }
 
+// the second and third differences of the control points
+SX_FN void seg_diffs(Seg& s) {
+    s.A2 = s.D2_ - s.D1 * 2.0;
+    s.B2 = s.D3 - s.D2_ * 2.0 + s.D1;
+    s.C3 = s.D3 - s.D2_ * 3.0 + s.D1 * 3.0;
+}
+
 // ------------------------------------------------------ segment fetch
 // linear part of the transform applied to a difference vector (FP64 from FP32)
 SX_FN D2 xf_vec(const float* X, double dx, double dy) {
@@ -1477,9 +1484,7 @@ SX_HD inline void fetch_tag(const SceneView& sv, uint32_t i, TagInfo& ti, Seg& s
         s.D2_ = e1;
         s.D3 = e2;
     }
-    s.A2 = s.D2_ - s.D1 * 2.0;
-    s.B2 = s.D3 - s.D2_ * 2.0 + s.D1;
-    s.C3 = s.D3 - s.D2_ * 3.0 + s.D1 * 3.0;
+    seg_diffs(s);
     // end tangents: the first nonzero difference from each end (r_c - r_{c-1-j})
     const float2 q0 = (c == 1) ? r0 : ((c == 2) ? r1 : r2);  // r_{c-1}
     const float2 q1 = (c == 2) ? r0 : r1;                    // r_{c-2}
@@ -1581,6 +1586,32 @@ SX_HD inline bool bisect_step(Bisect& b, const Seg& s, const Cfg& cfg, bool line
     b.t0_u *= 2;
     b.depth += 1;
     return false;
+}
+
+// One node of the bisection tree on its own: whether [t0, t0 + 2^-depth]
+// (t0 = t0_u 2^-depth) of a curve is accepted by the fit.  The same
+// operations on the same values as bisect_step, whose carried samples are
+// functions of t alone (q at t = 0 and 1 is D1 and D3 - D2 exactly), so the
+// tree's leaves are the segment's pieces in whatever order its nodes are
+// tried.
+SX_FN Tan tan_at(const Seg& s, double t, D2 q) {
+    double ql = len(q);
+    if (t == 0.0) return Tan{s.ts, ql};
+    if (t == 1.0) return Tan{s.te, ql};
+    if (ql < kEpsQ * s.lpoly) {
+        q = cubic_q(s, (t + kDeltaT < 1.0) ? t + kDeltaT : t - kDeltaT);
+        ql = len(q);
+    }
+    return Tan{q, ql};
+}
+SX_HD inline bool node_accepted(const Seg& s, const Cfg& cfg, uint32_t t0_u, uint32_t depth) {
+    const double dt = depth_dt(depth);
+    const double t0 = (double)t0_u * dt;
+    const double t1 = t0 + dt;
+    const D2 q0 = cubic_q(s, t0);
+    const Tan last_q = tan_at(s, t0, q0);
+    const Tan next_q = tan_at(s, t1, cubic_q(s, t1));
+    return trial(s, cfg, false, dt, last_q, next_q, cubic_chord(s, t0, dt, q0)).ok;
 }
 
 // The accepted piece [t0, t0 + 2^-depth] of the segment (accepted by the

@@ -3,14 +3,16 @@
 //  scan_tags_kernel       tag-monoid prefix scan (Section 8.2): single pass,
 //                         wave64 shuffle scan + LDS block scan + decoupled
 //                         look-back over dynamically numbered tiles.
-//  bisect_kernel          Algorithm 2 in FP64 with lane refill (a wave owns a
-//                         range of tags; a lane whose tag is done takes the
-//                         next).  Count pass: slots per tag (pieces + 1 tail)
-//                         and the codes of the first pieces; write pass: every
-//                         piece {tag, code} at its canonical position in the
-//                         piece list.
+//  bisect_kernel          Algorithm 2 in FP64 over the bisection trees' open
+//                         nodes (a wave owns a range of tags and tries 64
+//                         nodes at a time): slots per tag (pieces + 1 tail)
+//                         and the codes of the pieces found.
+//  list_kernel            every piece {tag, code} at its canonical position
+//  list_small_kernel      in the piece list (small scenes: with the scan of
+//                         the slot counts).
 //  scan_counts_kernel     exclusive scan of u32 counts into u64 offsets (slot
-//  scan_counts_dev_kernel bases; record offsets, with the count read on the
+//  scan_slots_kernel      bases; record offsets, with the count read on the
+//  scan_counts_dev_kernel
 //                         device).  Replaces the paper's atomic bump
 //                         allocation: the output order is canonical.
 //  slot_kernel            per piece, the Euler spiral, parallel curves,
@@ -179,6 +181,7 @@ constexpr int kScanBlock = 256;
 constexpr int kTagItems = 16;    // tags per thread of the tag-monoid scan
 constexpr int kCountItems = 32;  // counts per thread of the count scans
 constexpr int kRecCountItems = 64;  // counts per thread of the record-count scan (one round of tiles)
+constexpr uint32_t kCountLine = 0x80000000u;  // bit of a slot-count word: a line segment
 
 __device__ __forceinline__ Pair tag_inc(uint32_t t) {
     uint64_t pts = (t & kTagCount) + ((t & kTagEnd) ? 1u : 0u);
@@ -324,13 +327,19 @@ __global__ __launch_bounds__(kScanBlock) void scan_tags_kernel(const uint8_t* __
 }
 
 // exclusive scan of u32 counts into u64 offsets; out[n] = total
-template <int Items>
+// (Mask: the bits of an input word that count)
+template <int Items, uint32_t Mask = ~0u>
 __device__ __forceinline__ void scan_u32_body(const uint32_t* __restrict__ in, uint32_t n, uint64_t* __restrict__ out,
                                               ScanCtl* ctl, TileStatus* st);
 __global__ __launch_bounds__(kScanBlock) void scan_counts_kernel(const uint32_t* __restrict__ in, uint32_t n,
                                                                  uint64_t* __restrict__ out, ScanCtl* ctl,
                                                                  TileStatus* st) {
     scan_u32_body<kCountItems>(in, n, out, ctl, st);
+}
+__global__ __launch_bounds__(kScanBlock) void scan_slots_kernel(const uint32_t* __restrict__ in, uint32_t n,
+                                                                uint64_t* __restrict__ out, ScanCtl* ctl,
+                                                                TileStatus* st) {
+    scan_u32_body<kCountItems, ~kCountLine>(in, n, out, ctl, st);
 }
 // the same with n read from device memory (clamped to the buffers' capacity);
 // the grid covers the capacity
@@ -342,7 +351,7 @@ __global__ __launch_bounds__(kScanBlock) void scan_counts_dev_kernel(const uint3
     if (nd == 0 && blockIdx.x == 0 && threadIdx.x == 0) out[0] = 0;
     scan_u32_body<kRecCountItems>(in, nd < cap ? (uint32_t)nd : cap, out, ctl, st);
 }
-template <int Items>
+template <int Items, uint32_t Mask>
 __device__ __forceinline__ void scan_u32_body(const uint32_t* __restrict__ in, uint32_t n, uint64_t* __restrict__ out,
                                               ScanCtl* ctl, TileStatus* st) {
     auto load = [&](uint64_t base, Pair* item) {
@@ -350,14 +359,14 @@ __device__ __forceinline__ void scan_u32_body(const uint32_t* __restrict__ in, u
 #pragma unroll
             for (int j = 0; j < Items; j += 4) {
                 uint4 v = *reinterpret_cast<const uint4*>(in + base + j);
-                item[j] = Pair{v.x, 0};
-                item[j + 1] = Pair{v.y, 0};
-                item[j + 2] = Pair{v.z, 0};
-                item[j + 3] = Pair{v.w, 0};
+                item[j] = Pair{v.x & Mask, 0};
+                item[j + 1] = Pair{v.y & Mask, 0};
+                item[j + 2] = Pair{v.z & Mask, 0};
+                item[j + 3] = Pair{v.w & Mask, 0};
             }
         } else {
 #pragma unroll
-            for (int j = 0; j < Items; j++) item[j] = Pair{(base + j < n) ? (uint64_t)in[base + j] : 0ull, 0};
+            for (int j = 0; j < Items; j++) item[j] = Pair{(base + j < n) ? (uint64_t)(in[base + j] & Mask) : 0ull, 0};
         }
     };
     auto store = [&](uint64_t base, const Pair* incl, Pair pre) {
@@ -372,140 +381,331 @@ __device__ __forceinline__ void scan_u32_body(const uint32_t* __restrict__ in, u
 }
 
 // --------------------------------------------------------- bisection
-// One wave per workgroup owns `range` consecutive tags.  Every lane runs the
-// bisection of one segment at a time (Algorithm 2, one trial per loop turn);
-// a lane whose segment is done takes the wave's next tag (lane refill), so
-// the wave is busy until its range is exhausted instead of waiting for its
-// longest segment.  The count pass writes, per tag, its slot count (accepted
-// pieces + 1 tail) and keeps the codes of its first `keep` pieces (code
-// q of tag i at codes[q * stride + i], so the lanes of a wave, holding
-// consecutive tags, read and write consecutive words); the
-// write pass, after the scan of those counts, writes each tag's pieces into
-// the scene's piece list (canonical order; the piece of ordinal p of tag i
-// has slot p + i, since every tag before it owns one tail slot besides its
-// pieces): copied from the kept codes, or, for the few segments with more
-// pieces, from a second run of the bisection.
+// Algorithm 2 as a tree: a node is an interval [t0, t0 + 2^-depth] of one
+// curve, tried on its own (node_accepted); an accepted one is a piece, any
+// other is replaced by its two halves.  One wave per workgroup owns `range`
+// consecutive tags and keeps the open nodes of up to 64 of their curves on a
+// stack in LDS (the curves' control polygons beside it); every turn its lanes
+// try the 64 deepest open nodes, and idle lanes take the range's next curves
+// once there are kRefillLanes of them.  A curve's trials run side by side, so
+// the wave's time follows its number of trials and the depth of its trees,
+// not its longest curve's trials in sequence: with one curve per lane and its
+// trials in order, 24 random cubics took 293 us (one lane's 180 trials), now
+// 28 us; 1,000 of them 371 -> 41 us; 20,000 stress cubics 1,154 us, 10,007 of
+// them now 129 us; the map scene of 1M segments 277 -> 178 us (23 of 64 lanes
+// were active).  Bound by the FP64 latency of a trial (about 2 us per turn of
+// a wave) on small scenes and by FP64 issue on large ones.
+// Pieces are found in no particular order: the q-th one found of tag i is
+// kept at codes[i * keep + q] (the first `keep` of each tag), and the write
+// pass orders them by their start.
 constexpr int kBisectBlock = 64;
 constexpr uint32_t kBisectMaxRange = 1024;  // tags per wave (the autotuner's largest range)
-constexpr int kRefillLanes = 8;  // idle lanes that trigger a refill (on the map scene 8 and 12 beat 4, 16 and 32)
+constexpr uint32_t kRefillLanes = 16;       // idle lanes that trigger a refill
+constexpr uint32_t kNodeSegs = 64;          // curves with open nodes (a refilling wave holds fewer than 64 nodes)
+// Open nodes of a wave.  The stack is ordered by depth (deepest on top) and a
+// turn takes the top 64: nodes of one depth are pushed at most 128 at a time
+// and at most 64 of them stay behind when deeper ones are pushed over them,
+// for each depth up to kMaxDepth.
+constexpr uint32_t kNodeStack = 64u * (uint32_t)(kMaxDepth + 1);
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
-template <bool Write, bool Stats, int MinWaves>
-__global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(
-    SceneView sv, Cfg cfg, uint32_t range, uint32_t keep, uint32_t* __restrict__ nslots, uint32_t* __restrict__ codes,
-    const uint64_t* __restrict__ base, Slot* __restrict__ pcs, uint64_t slot_cap,
-    unsigned long long* __restrict__ stats) {
+template <bool Stats, int MinWaves>
+__global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneView sv, Cfg cfg, uint32_t range,
+                                                                        uint32_t keep, uint32_t* __restrict__ nslots,
+                                                                        uint32_t* __restrict__ codes,
+                                                                        unsigned long long* __restrict__ stats) {
+    __shared__ double s_seg[12][kNodeSegs];      // D1, D2, D3, end tangents, width, polygon length
+    __shared__ uint32_t s_node[kNodeStack];      // segment << 21 | depth << 16 | t0
+    __shared__ uint32_t s_tag[kNodeSegs];        // tag of a segment
+    __shared__ uint32_t s_open[kNodeSegs];       // its open nodes
+    __shared__ uint32_t s_found[kNodeSegs];      // its pieces so far
+    __shared__ uint32_t s_free[kNodeSegs];       // unused segments
+    __shared__ uint32_t s_curve[128];            // ring of curves not yet taken
     const uint32_t lane = threadIdx.x;
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const size_t cstride = mon_stride_of(sv.n_tags);  // row stride of the kept codes
     const uint32_t a = blockIdx.x * range;
     const uint32_t b = min(sv.n_tags, a + range);
     uint32_t n_trials = 0, n_lines = 0;
-    // Count pass: lines (one straight piece each, reading G32), markers and
-    // invalid tags need no bisection.  They are settled for the whole range
-    // first, 64 consecutive tags at a time, and only the curves are listed
-    // (in LDS) for the refill loop, so that a refill does not spend rounds
-    // of scattered loads on tags that take no trial.
-    __shared__ uint32_t s_curve[kBisectMaxRange];
-    uint32_t n_curve = 0;
-    if (!Write) {
-        for (uint32_t t0 = a; t0 < b; t0 += 64u) {
-            const uint32_t it = t0 + lane;
-            bool curve = false;
-            if (it < b) {
-                bool line;
-                const int kind = tag_kind(sv, it, line);
-                if (kind == kTagSegment && !line) {
-                    curve = true;
-                } else if (kind == kTagSegment) {
-                    nslots[it] = 2u;
-                    codes[it] = slot_code(0u, 0u, false) | kCodeLine;
-                    if (Stats) n_lines++;
-                } else {
-                    nslots[it] = 1u;  // markers and invalid tags own only their tail slot
-                }
-            }
-            const uint64_t m = __ballot(curve);
-            if (curve) s_curve[n_curve + (uint32_t)__popcll(m & below)] = it;
-            n_curve += (uint32_t)__popcll(m);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    // the refill loop's work list: the range's curves (count pass) or its tags
-    uint32_t cursor = Write ? a : 0u;  // next unassigned entry (wave-uniform)
-    const uint32_t cend = Write ? b : n_curve;
-    bool busy = false;
-    uint32_t i = 0, seq = 0;
-    uint64_t bi = 0;  // piece ordinal of the lane's tag's first piece (write pass)
-    TagInfo ti;
-    Seg s;
-    Bisect bs;
+    uint32_t at = a;                       // next tag to look at
+    uint32_t c_lo = 0, c_hi = 0;           // the ring's entries
+    uint32_t n_free = kNodeSegs, n_node = 0;
+    s_free[lane] = lane;
+    wave_lds_sync();
     for (;;) {
-        // refill idle lanes with the next tags of the range, once kRefillLanes
-        // lanes are idle (a refill fetches segments: its latency is shared by
-        // the lanes it serves) or the wave has nothing left to run
-        const uint64_t idle = __ballot(!busy);
-        if (idle && cursor < cend && (__popcll(idle) >= kRefillLanes || __ballot(busy) == 0ull)) {
-            const uint32_t ni = cursor + (uint32_t)__popcll(idle & below);
-            cursor += (uint32_t)__popcll(idle);
-            if (!busy && ni < cend) {
-                i = Write ? ni : s_curve[ni];
-                seq = 0;
-                bool copied = false;
-                if (Write) {
-                    bi = base[i] - i;  // pieces of the tags before this one
-                    const uint32_t np = nslots[i] - 1u;
-                    if (np <= keep) {
-                        // pieces known from the count pass: copy them
-                        for (uint32_t q = 0; q < np; q++)
-                            if (bi + q < slot_cap) pcs[bi + q] = Slot{i, codes[q * cstride + i]};
-                        copied = true;
+        // this turn's nodes: the top of the stack on the first lanes
+        const uint32_t n_pop = min(n_node, 64u);
+        uint32_t take = 0;
+        if (64u - n_pop >= kRefillLanes || n_pop == 0u) {
+            // the next curves of the range.  Lines (one straight piece each,
+            // reading G32), markers and invalid tags need no bisection and
+            // are settled here, 64 consecutive tags at a time.
+            while (c_hi - c_lo < 64u - n_pop && at < b) {
+                const uint32_t i = at + lane;
+                bool curve = false;
+                if (i < b) {
+                    bool line;
+                    const int kind = tag_kind(sv, i, line);
+                    curve = kind == kTagSegment && !line;
+                    if (kind == kTagSegment && line) {
+                        nslots[i] = 2u | kCountLine;
+                        if (Stats) n_lines++;
+                    } else if (!curve) {
+                        nslots[i] = 1u;  // only the tail slot
                     }
                 }
-                if (!copied) fetch_tag(sv, i, ti, s);
-                if (copied) {
-                    // done with this tag
-                } else if (!Write && ti.kind == kTagSegment && ti.line) {
-                    // a line is one straight piece (reading G32): no bisection
-                    nslots[i] = 2u;
-                    codes[i] = slot_code(0u, 0u, false) | kCodeLine;
-                    if (Stats) n_lines++;
-                } else if (ti.kind == kTagSegment) {
-                    bisect_init(bs, s);
-                    busy = true;
-                } else if (!Write) {
-                    nslots[i] = 1u;  // markers and invalid tags own only their tail slot
-                }
+                const uint64_t m = __ballot(curve);
+                if (curve) s_curve[(c_hi + (uint32_t)__popcll(m & below)) & 127u] = i;
+                c_hi += (uint32_t)__popcll(m);
+                at += 64u;
             }
-            continue;  // refill again until no idle lane can take a tag
+            take = min(min(64u - n_pop, c_hi - c_lo), n_free);
+            wave_lds_sync();
         }
-        if (__ballot(busy) == 0ull) break;
-        if (busy) {
-            uint32_t t0u = 0, depth = 0;
-            bool done = false, pivot = false;
-            if (Stats) {
-                if (ti.line) n_lines++;
-                else n_trials++;
+        const uint32_t n_now = n_pop + take;
+        if (n_now == 0u) break;
+        const bool act = lane < n_now;
+        Seg s;
+        uint32_t sg = 0, depth = 0, t0u = 0;
+        if (lane < n_pop) {
+            const uint32_t w = s_node[n_node - 1u - lane];
+            sg = w >> 21;
+            depth = (w >> 16) & 31u;
+            t0u = w & 0xffffu;
+        } else if (act) {
+            const uint32_t i = s_curve[(c_lo + (lane - n_pop)) & 127u];
+            sg = s_free[n_free - 1u - (lane - n_pop)];
+            TagInfo ti;
+            fetch_tag(sv, i, ti, s);
+            s_seg[0][sg] = s.D1.x;
+            s_seg[1][sg] = s.D1.y;
+            s_seg[2][sg] = s.D2_.x;
+            s_seg[3][sg] = s.D2_.y;
+            s_seg[4][sg] = s.D3.x;
+            s_seg[5][sg] = s.D3.y;
+            s_seg[6][sg] = s.ts.x;
+            s_seg[7][sg] = s.ts.y;
+            s_seg[8][sg] = s.te.x;
+            s_seg[9][sg] = s.te.y;
+            s_seg[10][sg] = s.w;
+            s_seg[11][sg] = s.lpoly;
+            s_tag[sg] = i;
+            s_open[sg] = 1u;
+            s_found[sg] = 0u;
+        }
+        n_node -= n_pop;
+        c_lo += take;
+        n_free -= take;
+        wave_lds_sync();
+        bool split = false, done = false;
+        if (act) {
+            s.D1 = d2(s_seg[0][sg], s_seg[1][sg]);
+            s.D2_ = d2(s_seg[2][sg], s_seg[3][sg]);
+            s.D3 = d2(s_seg[4][sg], s_seg[5][sg]);
+            s.ts = d2(s_seg[6][sg], s_seg[7][sg]);
+            s.te = d2(s_seg[8][sg], s_seg[9][sg]);
+            s.w = s_seg[10][sg];
+            s.lpoly = s_seg[11][sg];
+            seg_diffs(s);
+            const bool ok = node_accepted(s, cfg, t0u, depth);
+            if (Stats) n_trials++;
+            split = !ok && depth < (uint32_t)kMaxDepth;
+            if (!split) {
+                const uint32_t q = atomicAdd(&s_found[sg], 1u);
+                if (q < keep) codes[(size_t)s_tag[sg] * keep + q] = slot_code(t0u, depth, !ok);
             }
-            if (bisect_step(bs, s, cfg, ti.line, t0u, depth, pivot, done)) {
-                if (Write) {
-                    const uint64_t at = bi + seq;
-                    if (at < slot_cap) pcs[at] = Slot{i, slot_code(t0u, depth, pivot)};
-                } else if (seq < keep) {
-                    codes[seq * cstride + i] = slot_code(t0u, depth, pivot);
-                }
-                seq++;
-                if (done) {
-                    if (!Write) nslots[i] = seq + 1u;
-                    busy = false;
-                }
+            // the lane that closes a segment's last open node finishes its tag
+            done = atomicAdd(&s_open[sg], split ? 1u : ~0u) == 1u && !split;
+            if (done) nslots[s_tag[sg]] = s_found[sg] + 1u;
+        }
+        // the halves of this turn's nodes, the deepest (lane 0's) on top
+        const uint64_t m_split = __ballot(split), m_done = __ballot(done);
+        const uint32_t n_split = (uint32_t)__popcll(m_split);
+        if (split) {
+            const uint32_t to = n_node + 2u * (n_split - 1u - (uint32_t)__popcll(m_split & below));
+            const uint32_t w = (sg << 21) | ((depth + 1u) << 16) | (2u * t0u);
+            if (to + 1u < kNodeStack) {
+                s_node[to] = w;
+                s_node[to + 1u] = w + 1u;
             }
         }
+        n_node += 2u * n_split;
+        if (done) s_free[n_free + (uint32_t)__popcll(m_done & below)] = sg;
+        n_free += (uint32_t)__popcll(m_done);
+        wave_lds_sync();
     }
     if (Stats) {
         atomicAdd(&stats[kStTrials], (unsigned long long)n_trials);
         atomicAdd(&stats[kStLines], (unsigned long long)n_lines);
+    }
+}
+
+// The piece list: every piece {tag, code} at its canonical position (pieces
+// in t order; the piece of ordinal p of tag i has slot p + i, since every tag
+// before it owns one tail slot besides its pieces).  One thread per piece: a
+// tag's piece count says nothing of its neighbours' (a stress cubic has
+// hundreds, a line one), so blocks of tags would wait for their richest tag.
+// The thread finds its tag from the slot bases and takes its place among the
+// tag's kept codes by counting the ones that start before it (the lanes of a
+// tag read its row together).  A tag with more pieces than codes kept runs
+// its bisection again, in order, on the thread of its first piece.
+constexpr int kListBlock = 256;
+constexpr uint32_t kListPieces = 1024;      // pieces of a block's turn (list_kernel)
+constexpr uint32_t kListSpan = 2048;        // tags of a turn whose bases are staged in LDS
+constexpr uint32_t kSmallTags = 16384;      // scenes whose blocks scan all counts themselves
+constexpr uint32_t kSmallBlocks = 512;      // their grid cap
+
+__device__ __forceinline__ uint32_t code_start(uint32_t code) {
+    return code_t0u(code) << ((uint32_t)kMaxDepth - code_depth(code));
+}
+// Piece q of the np pieces of tag i, whose first piece has ordinal `first`.
+__device__ __forceinline__ void list_piece(const SceneView& sv, const Cfg& cfg, uint32_t keep,
+                                           const uint32_t* __restrict__ codes, bool line, uint32_t i, uint32_t q,
+                                           uint32_t np, uint64_t first, Slot* __restrict__ pcs, uint64_t slot_cap) {
+    if (np > keep) {
+        if (q != 0u) return;
+        TagInfo ti;
+        Seg s;
+        fetch_tag(sv, i, ti, s);
+        Bisect bs;
+        bisect_init(bs, s);
+        for (bool done = false; !done;) {
+            uint32_t t0u = 0, depth = 0;
+            bool pivot = false;
+            if (bisect_step(bs, s, cfg, false, t0u, depth, pivot, done)) {
+                if (first < slot_cap) pcs[first] = Slot{i, slot_code(t0u, depth, pivot)};
+                first++;
+            }
+        }
+        return;
+    }
+    uint32_t code = slot_code(0u, 0u, false) | kCodeLine, rank = 0;
+    if (!line) {
+        const uint32_t* row = codes + (size_t)i * keep;
+        code = row[q];
+        const uint32_t start = code_start(code);
+        for (uint32_t r = 0; r < np; r += 4u) {
+            const uint4 v = *reinterpret_cast<const uint4*>(row + r);
+            rank += (code_start(v.x) < start ? 1u : 0u) + (r + 1u < np && code_start(v.y) < start ? 1u : 0u) +
+                    (r + 2u < np && code_start(v.z) < start ? 1u : 0u) +
+                    (r + 3u < np && code_start(v.w) < start ? 1u : 0u);
+        }
+    }
+    if (first + rank < slot_cap) pcs[first + rank] = Slot{i, code};
+}
+
+// From the scanned slot bases; a block takes kListPieces pieces at a time.
+__global__ __launch_bounds__(kListBlock) void list_kernel(SceneView sv, Cfg cfg, uint32_t keep,
+                                                          const uint32_t* __restrict__ nslots,
+                                                          const uint32_t* __restrict__ codes,
+                                                          const uint64_t* __restrict__ base, Slot* __restrict__ pcs,
+                                                          uint64_t slot_cap) {
+    __shared__ uint32_t s_tag[2];
+    __shared__ uint32_t s_off[kListSpan];  // pieces of the turn before each of its tags
+    const uint32_t n = sv.n_tags, t = threadIdx.x, lane = t & 63u, wv = t >> 6;
+    const uint64_t n_pieces = base[n] - n;
+    // (piece ordinal of tag i: base[i] - i)
+    for (uint64_t p0 = (uint64_t)blockIdx.x * kListPieces; p0 < n_pieces; p0 += (uint64_t)gridDim.x * kListPieces) {
+        const uint64_t p1 = min(p0 + kListPieces, n_pieces);
+        // the tags of the turn's first and last piece: the last tag whose
+        // pieces start at or before it, 64 probes at a time
+        if (wv < 2u) {
+            const uint64_t p = wv == 0u ? p0 : p1 - 1u;
+            uint32_t lo = 0, cnt = n;  // the answer is in [lo, lo + cnt)
+            while (cnt > 1u) {
+                const uint32_t step = (cnt + 63u) / 64u;
+                const uint32_t off = lane * step;
+                const bool le = off < cnt && base[lo + off] - (lo + off) <= p;
+                const uint32_t last = 63u - (uint32_t)__builtin_clzll(__ballot(le));  // (lane 0 always is)
+                lo += last * step;
+                cnt = min(step, cnt - last * step);
+            }
+            if (lane == 0u) s_tag[wv] = lo;
+        }
+        __syncthreads();
+        const uint32_t tag0 = s_tag[0], tag1 = s_tag[1];
+        const uint64_t f0 = base[tag0] - tag0;
+        const bool staged = tag1 - tag0 < kListSpan;
+        if (staged)
+            for (uint32_t k = t; k <= tag1 - tag0; k += kListBlock)
+                s_off[k] = (uint32_t)(base[tag0 + k] - (tag0 + k) - f0);
+        __syncthreads();
+        for (uint64_t p = p0 + t; p < p1; p += kListBlock) {
+            uint32_t lo = 0, cnt = tag1 - tag0 + 1u;
+            while (cnt > 1u) {
+                const uint32_t half = cnt / 2u;
+                const uint64_t off = staged ? s_off[lo + half] : base[tag0 + lo + half] - (tag0 + lo + half) - f0;
+                const bool le = off <= p - f0;
+                lo = le ? lo + half : lo;
+                cnt = le ? cnt - half : half;
+            }
+            const uint32_t i = tag0 + lo, w = nslots[i];
+            const uint64_t first = staged ? f0 + s_off[lo] : base[i] - i;
+            list_piece(sv, cfg, keep, codes, (w & kCountLine) != 0u, i, (uint32_t)(p - first), (w & ~kCountLine) - 1u,
+                       first, pcs, slot_cap);
+        }
+        __syncthreads();  // s_tag and s_off are reused
+    }
+}
+
+// Small scenes: every block scans all slot counts into LDS (n_tags words), so
+// bases and list take one launch without a wait between blocks.
+__global__ __launch_bounds__(kListBlock) void list_small_kernel(SceneView sv, Cfg cfg, uint32_t keep,
+                                                                const uint32_t* __restrict__ nslots,
+                                                                const uint32_t* __restrict__ codes,
+                                                                uint64_t* __restrict__ base, Slot* __restrict__ pcs,
+                                                                uint64_t slot_cap) {
+    extern __shared__ uint32_t s_end[];  // pieces of tags 0..i; bit 31: a line
+    __shared__ uint32_t s_wave[kListBlock / 64];
+    const uint32_t n = sv.n_tags, t = threadIdx.x, lane = t & 63u, wv = t >> 6;
+    // each thread's consecutive tags (a multiple of 4 of them), 16 bytes at a time
+    const uint32_t per = ((n + kListBlock - 1u) / kListBlock + 3u) & ~3u;
+    const uint32_t i0 = min(t * per, n), i1 = min(i0 + per, n);
+    uint32_t mine = 0;
+    for (uint32_t i = i0; i < i1; i += 4u) {
+        const uint4 v = *reinterpret_cast<const uint4*>(nslots + i);
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (uint32_t j = 0; j < 4u; j++)
+            if (i + j < i1) {
+                mine += (w[j] & ~kCountLine) - 1u;
+                s_end[i + j] = mine | (w[j] & kCountLine);
+            }
+    }
+    uint32_t v = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t u = __shfl_up(v, d, 64);
+        if ((int)lane >= d) v += u;
+    }
+    if (lane == 63u) s_wave[wv] = v;
+    __syncthreads();
+    uint32_t before = v - mine, run = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kListBlock / 64; k++) {
+        if (k < wv) before += s_wave[k];
+        run += s_wave[k];
+    }
+    for (uint32_t i = i0; i < i1; i++) s_end[i] += before;
+    __syncthreads();
+    for (uint32_t i = blockIdx.x * kListBlock + t; i < n; i += gridDim.x * kListBlock) {
+        base[i] = (uint64_t)(i ? s_end[i - 1u] & ~kCountLine : 0u) + i;
+        if (i == n - 1u) base[n] = (uint64_t)run + n;
+    }
+    for (uint32_t p = blockIdx.x * kListBlock + t; p < run; p += gridDim.x * kListBlock) {
+        uint32_t i = 0, cnt = n;  // the first tag whose pieces end after p
+        while (cnt > 1u) {
+            const uint32_t half = cnt / 2u;
+            const bool le = (s_end[i + half - 1u] & ~kCountLine) <= p;
+            i = le ? i + half : i;
+            cnt = le ? cnt - half : half;
+        }
+        const uint32_t first = i ? s_end[i - 1u] & ~kCountLine : 0u, e = s_end[i];
+        list_piece(sv, cfg, keep, codes, (e & kCountLine) != 0u, i, p - first, (e & ~kCountLine) - first, first, pcs,
+                   slot_cap);
     }
 }
 
@@ -1085,6 +1285,11 @@ hipError_t launch_scan_counts(const uint32_t* in, uint32_t n, uint64_t* out, voi
     scan_counts_kernel<<<count_scan_tiles(n), kScanBlock, 0, s>>>(in, n, out, (ScanCtl*)ctl, (TileStatus*)st);
     return hipGetLastError();
 }
+hipError_t launch_scan_slots(const uint32_t* nslots, uint32_t n, uint64_t* base, void* ctl, void* st, hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    scan_slots_kernel<<<count_scan_tiles(n), kScanBlock, 0, s>>>(nslots, n, base, (ScanCtl*)ctl, (TileStatus*)st);
+    return hipGetLastError();
+}
 __global__ void zero_u64_kernel(uint64_t* out) {
     if (threadIdx.x == 0) out[0] = 0ull;
 }
@@ -1099,37 +1304,44 @@ hipError_t launch_scan_counts_dev(const uint32_t* in, const uint64_t* n_dev, uin
     return hipGetLastError();
 }
 
-template <bool Write, bool Stats>
+template <bool Stats>
 static void bisect_launch(uint32_t g, hipStream_t s, int waves, const SceneView& sv, const Cfg& cfg, uint32_t range,
-                          uint32_t keep, uint32_t* nslots, uint32_t* codes, const uint64_t* base, Slot* pcs,
-                          uint64_t cap, unsigned long long* stats) {
+                          uint32_t keep, uint32_t* nslots, uint32_t* codes, unsigned long long* stats) {
     if (waves <= 2)
-        bisect_kernel<Write, Stats, 2><<<g, kBisectBlock, 0, s>>>(sv, cfg, range, keep, nslots, codes, base, pcs, cap,
-                                                                stats);
+        bisect_kernel<Stats, 2><<<g, kBisectBlock, 0, s>>>(sv, cfg, range, keep, nslots, codes, stats);
     else if (waves == 3)
-        bisect_kernel<Write, Stats, 3><<<g, kBisectBlock, 0, s>>>(sv, cfg, range, keep, nslots, codes, base, pcs, cap,
-                                                                stats);
+        bisect_kernel<Stats, 3><<<g, kBisectBlock, 0, s>>>(sv, cfg, range, keep, nslots, codes, stats);
     else
-        bisect_kernel<Write, Stats, 4><<<g, kBisectBlock, 0, s>>>(sv, cfg, range, keep, nslots, codes, base, pcs, cap,
-                                                                stats);
+        bisect_kernel<Stats, 4><<<g, kBisectBlock, 0, s>>>(sv, cfg, range, keep, nslots, codes, stats);
 }
-hipError_t launch_bisect(const SceneView& sv, const Cfg& cfg, uint32_t range, uint32_t keep, int waves, bool write,
-                         uint32_t* nslots, uint32_t* codes, const uint64_t* base, Slot* pcs, uint64_t slot_cap,
-                         unsigned long long* stats, hipStream_t s) {
+hipError_t launch_bisect(const SceneView& sv, const Cfg& cfg, uint32_t range, uint32_t keep, int waves,
+                         uint32_t* nslots, uint32_t* codes, unsigned long long* stats, hipStream_t s) {
     if (sv.n_tags == 0) return hipSuccess;
-    if (range == 0 || range % 64u || range > kBisectMaxRange || keep < (uint32_t)kKeepCodes)
+    if (range == 0 || range % 64u || range > kBisectMaxRange || keep < (uint32_t)kKeepCodes || keep % 4u)
         return hipErrorInvalidValue;
-    // a scene too small to give every SIMD a wave at this range takes
-    // shorter ranges (down to one tag per lane)
-    const uint32_t fill = ((sv.n_tags / 4096u + 63u) / 64u) * 64u;
-    if (fill < range) range = fill < 64u ? 64u : fill;
+    // a scene too small to give every SIMD its waves at this range takes
+    // shorter ranges, down to one tag per wave
+    const uint32_t fill = (sv.n_tags + 4095u) / 4096u;
+    if (fill < range) range = fill;
     const uint32_t g = (sv.n_tags + range - 1) / range;
-    if (write)
-        bisect_launch<true, false>(g, s, waves, sv, cfg, range, keep, nslots, codes, base, pcs, slot_cap, stats);
-    else if (stats)
-        bisect_launch<false, true>(g, s, waves, sv, cfg, range, keep, nslots, codes, base, pcs, slot_cap, stats);
+    if (stats)
+        bisect_launch<true>(g, s, waves, sv, cfg, range, keep, nslots, codes, stats);
     else
-        bisect_launch<false, false>(g, s, waves, sv, cfg, range, keep, nslots, codes, base, pcs, slot_cap, stats);
+        bisect_launch<false>(g, s, waves, sv, cfg, range, keep, nslots, codes, stats);
+    return hipGetLastError();
+}
+bool list_is_small(uint32_t n_tags) { return n_tags <= kSmallTags; }
+hipError_t launch_list(const SceneView& sv, const Cfg& cfg, uint32_t keep, const uint32_t* nslots,
+                       const uint32_t* codes, uint64_t* base, Slot* pcs, uint64_t slot_cap, hipStream_t s) {
+    if (sv.n_tags == 0) return hipSuccess;
+    if (list_is_small(sv.n_tags)) {
+        const uint32_t g = (uint32_t)std::min<uint64_t>(kSmallBlocks, (slot_cap + kListBlock - 1) / kListBlock);
+        list_small_kernel<<<g, kListBlock, sv.n_tags * sizeof(uint32_t), s>>>(sv, cfg, keep, nslots, codes, base, pcs,
+                                                                             slot_cap);
+    } else {
+        const uint32_t g = (uint32_t)std::min<uint64_t>(4096, (slot_cap + kListPieces - 1) / kListPieces);
+        list_kernel<<<g, kListBlock, 0, s>>>(sv, cfg, keep, nslots, codes, base, pcs, slot_cap);
+    }
     return hipGetLastError();
 }
 template <bool Newton>

@@ -1,0 +1,106 @@
+"""The bisection and the piece list at the edges of their dispatch (GPU, through
+the C ABI): scenes at the tag count where the list kernel changes, tags with
+more pieces than the bisection keeps codes for, and runs of tags without
+pieces longer than the list kernel stages.  Against the FP64 oracle at the
+parity bars (or bit for bit against the same paths expanded without the empty
+ones)."""
+import numpy as np
+import pytest
+
+import oracle as O
+import parity as P
+from paper_2405_00127_amd import scenes as S
+
+pytestmark = pytest.mark.gpu
+
+SMALL_TAGS = 16384  # kSmallTags of the list kernels
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+
+    from paper_2405_00127_amd import binding as B
+
+    torch.cuda.set_device(0)
+    c = B.Context(0)
+    yield c
+    c.close()
+
+
+def _with_tags(n_tags):
+    """A map-shaped scene of exactly n_tags tags: one of 40% fewer segments,
+    then open paths of two lines (3 tags) and of one line (2 tags)."""
+    base = S.scene_map(11, n_tags * 3 // 5, max(1, n_tags // 125))
+    rest = n_tags - len(O.encode(base).tags)
+    assert rest >= 3
+    b = S.SceneBuilder()
+    for k in range(base.n_paths):
+        b.add_path(*base.path(k), int(base.style_ix[k]), 0)
+    while rest:
+        m = 2 if rest % 2 else 1
+        x = float(rest % 1000)
+        b.add_path([S.MOVE] + [S.LINE] * m, [[x, 5.0], [x + 3.0, 9.0], [x + 7.0, 4.0]][: m + 1], 0, 0)
+        rest -= m + 1
+    sc = b.build(base.styles, base.xforms, tolerance=0.25)
+    assert len(O.encode(sc).tags) == n_tags
+    return sc
+
+
+def _check(ctx, sc):
+    from paper_2405_00127_amd import binding as B
+
+    ref = O.expand(sc)
+    scene = ctx.encode(sc)
+    recs, _, _ = ctx.expand(scene, sc.tolerance, sc.output_mode)
+    counts = ctx.counts(scene, sc.tolerance, sc.output_mode).cpu().numpy().astype(np.uint32)
+    rep = P.compare(counts, B.records_to_numpy(recs, sc.output_mode), ref, sc.output_mode)
+    assert rep.ok(), rep
+    scene.release()
+
+
+@pytest.mark.parametrize("n_tags", [12, 255, 257, 4095, 4097, SMALL_TAGS, SMALL_TAGS + 1])
+def test_tag_counts_at_the_edges(ctx, n_tags):
+    _check(ctx, _with_tags(n_tags))
+
+
+@pytest.mark.parametrize("n_cubics,extra", [(6, 0), (6, SMALL_TAGS)])
+def test_more_pieces_than_codes_kept(ctx, n_cubics, extra):
+    """About 1,400 pieces per cubic (1,024 codes are kept at most): the
+    tag's bisection runs again in the list kernel, small and general."""
+    sc = S.scene_c1(5, n_paths=2, n_cubics=n_cubics, tolerance=1e-5)
+    if extra:
+        b = S.SceneBuilder()
+        for k in range(sc.n_paths):
+            b.add_path(*sc.path(k), int(sc.style_ix[k]), 0)
+        for j in range(extra // 2):
+            b.add_path([S.MOVE, S.LINE], [[j % 997, 1.0], [j % 997 + 2.5, 8.0]], 0, 0)
+        sc = b.build(sc.styles, sc.xforms, tolerance=1e-5)
+    assert len(O.expand(sc).pieces) > 1024 * n_cubics
+    _check(ctx, sc)
+
+
+def test_long_runs_of_tags_without_pieces(ctx):
+    """9,000 paths whose dashes draw nothing (two empty subpaths each) between
+    solid ones: a turn of the list kernel spans more tags than it stages."""
+    from paper_2405_00127_amd import binding as B
+
+    solid = S.scene_c1(7, n_paths=4, n_cubics=40)
+    b = S.SceneBuilder()
+    keep = S.SceneBuilder()
+    n_st = len(solid.styles)
+    for k in range(4):
+        b.add_path(*solid.path(k), k, 0)
+        keep.add_path(*solid.path(k), k, 0)
+        for j in range(2250):
+            b.add_path([S.MOVE, S.LINE], [[j, 0.0], [j + 1.0, 3.0]], n_st, 0)
+    styles = np.concatenate([solid.styles, solid.styles[:1]])
+    sc = b.build(styles, solid.xforms)
+    sc.dashes = [None] * n_st + [(np.array([0.0, 10.0], np.float32), 0.0)]
+    ref = keep.build(styles, solid.xforms)
+    got, n, _ = ctx.expand(ctx.encode(sc), 0.25, S.OUT_LINES)
+    want, m, _ = ctx.expand(ctx.encode(ref), 0.25, S.OUT_LINES)
+    got, want = (B.records_to_numpy(x, S.OUT_LINES).copy() for x in (got, want))
+    assert n == m
+    want["path"] *= 2251
+    assert np.array_equal(got, want)
