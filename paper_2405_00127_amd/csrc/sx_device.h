@@ -90,6 +90,55 @@ SX_FN V2 f32(D2 a) { return v2((float)a.x, (float)a.y); }
 // offset point p + N h, rounded once
 SX_FN V2 offs(D2 p, D2 n, double h) { return f32(p + n * h); }
 
+// ------------------------------------------- elementary functions, FP64
+// Reciprocal and reciprocal square root from the hardware's estimates
+// (relative error e of about 2^-24) and one step of third order: 1 / x =
+// y (1 + e + e^2) with e = 1 - x y, x^-1/2 = y (1 + e / 2 + 3 e^2 / 8) with
+// e = 1 - x y^2, both to rounding (within 2 ulp), for normal x > 0 (squares
+// and products of FP32 inputs stay far inside the range).  The library's
+// division and square root rescale their arguments and round correctly at
+// two to four times the instructions.  x = 0 gives NaN: callers guard it.
+SX_FN double rcp_d(double x) {
+#ifdef __HIP_DEVICE_COMPILE__
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+#else
+    return 1.0 / x;
+#endif
+}
+SX_FN double rsqrt_d(double x) {
+#ifdef __HIP_DEVICE_COMPILE__
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+#else
+    return 1.0 / sqrt(x);
+#endif
+}
+// atan(t) for |t| <= 1: t P(t^2), P the minimax polynomial of degree 19 for
+// atan(sqrt z) / sqrt z on [0, 1] (relative error 2.7e-17), even and odd
+// powers apart for two chains of half the length
+SX_FN double atan_1(double t) {
+    const double z = t * t, y = z * z;
+    double p = fma(z, -2.0018481170597968e-05, 0.00022068613385287154);
+    p = fma(y, p, fma(z, -0.0011535800179158506, 0.003827137827562648));
+    p = fma(y, p, fma(z, -0.00913031107637468, 0.016904037711967242));
+    p = fma(y, p, fma(z, -0.025751147940759618, 0.03400872948686186));
+    p = fma(y, p, fma(z, -0.04089077361869093, 0.04672287883449064));
+    p = fma(y, p, fma(z, -0.05238634041897263, 0.05877142358486348));
+    p = fma(y, p, fma(z, -0.06665825855864474, 0.07692207609177779));
+    p = fma(y, p, fma(z, -0.09090900647665989, 0.11111110634357174));
+    p = fma(y, p, fma(z, -0.142857142691963, 0.1999999999969631));
+    return t * fma(y, p, fma(z, -0.3333333333333111, 1.0));
+}
+// The angle of the unit vector (cs, sn), inv = 1 / (1 + |cs|): sn inv is the
+// tangent of half the angle to the nearer end of the cosine axis.
+SX_FN double unit_angle(double sn, double cs, double inv) {
+    const double a = 2.0 * atan_1(sn * inv);
+    return cs >= 0.0 ? a : copysign(kPi, sn) - a;
+}
+
 // ------------------------------------------------------- Euler spirals
 // Appendix A: k1 and chord / arc-length ratio as 7th-order polynomials in
 // k = th0 + th1 and D = th1 - th0.
@@ -114,20 +163,22 @@ SX_FN double es_chord(double th0, double th1) {
 
 // Section 7.1: chord-normalised distance estimate between a cubic with end
 // angles th0, th1 and arms d0, d1 and the Euler spiral with those angles
-// (sn0, c0, sn1, c1: the sines and cosines of th0 and th1).
-SX_FN double fit_estimate_sc(double th0, double th1, double sn0, double c0, double sn1, double c1, double d0,
-                             double d1) {
+// (sn0, c0, sn1, c1: the sines and cosines of th0 and th1; v0, v1:
+// 1 / (1 + c0) and 1 / (1 + c1)).
+SX_FN double fit_estimate_sc(double th0, double th1, double sn0, double c0, double sn1, double c1, double v0,
+                             double v1, double d0, double d1) {
     double s = fabs(th0 + th1), df = fabs(th0 - th1);
     double s2 = s * s;
     double e0 = 4.6255e-6 * (s2 * s2 * s) + 7.5e-3 * s2 * df;
     const double sn01 = sn0 * c1 + c0 * sn1;
-    double db0 = 2.0 / (3.0 * (1.0 + c0)), db1 = 2.0 / (3.0 * (1.0 + c1));
+    double db0 = (2.0 / 3.0) * v0, db1 = (2.0 / 3.0) * v1;
     // area(d0,d1) - area(db0,db1), area = 3/20 (2 d0 sin th0 + 2 d1 sin th1 - d0 d1 sin(th0+th1))
     double a_src = 2.0 * d0 * sn0 + 2.0 * d1 * sn1 - d0 * d1 * sn01;
     double a_es = 2.0 * db0 * sn0 + 2.0 * db1 * sn1 - db0 * db1 * sn01;
     double ea = 1.55 * 0.15 * fabs(a_src - a_es);
     double x0 = db0 - d0, x1 = db1 - d1;
-    double ei = (0.005 * s + 0.07 * df) * sqrt(x0 * x0 + x1 * x1);
+    const double xx = x0 * x0 + x1 * x1;
+    double ei = (0.005 * s + 0.07 * df) * (xx > 0.0 ? xx * rsqrt_d(xx) : 0.0);
     return e0 + ea + ei;
 }
 
@@ -1364,13 +1415,6 @@ SX_FN Tan sample_q(const Seg& s, double t) {
     return Tan{q, ql};
 }
 
-// the second and third differences of the control points
-SX_FN void seg_diffs(Seg& s) {
-    s.A2 = s.D2_ - s.D1 * 2.0;
-    s.B2 = s.D3 - s.D2_ * 2.0 + s.D1;
-    s.C3 = s.D3 - s.D2_ * 3.0 + s.D1 * 3.0;
-}
-
 // ------------------------------------------------------ segment fetch
 // linear part of the transform applied to a difference vector (FP64 from FP32)
 SX_FN D2 xf_vec(const float* X, double dx, double dy) {
@@ -1484,7 +1528,9 @@ SX_HD inline void fetch_tag(const SceneView& sv, uint32_t i, TagInfo& ti, Seg& s
         s.D2_ = e1;
         s.D3 = e2;
     }
-    seg_diffs(s);
+    s.A2 = s.D2_ - s.D1 * 2.0;
+    s.B2 = s.D3 - s.D2_ * 2.0 + s.D1;
+    s.C3 = s.D3 - s.D2_ * 3.0 + s.D1 * 3.0;
     // end tangents: the first nonzero difference from each end (r_c - r_{c-1-j})
     const float2 q0 = (c == 1) ? r0 : ((c == 2) ? r1 : r2);  // r_{c-1}
     const float2 q1 = (c == 2) ? r0 : r1;                    // r_{c-2}
@@ -1498,120 +1544,113 @@ SX_HD inline void fetch_tag(const SceneView& sv, uint32_t i, TagInfo& ti, Seg& s
 }
 
 // ------------------------------------------- Algorithm 2: the bisection
-// One candidate piece [t0, t0 + dt] of the segment: its chord, end angles and
-// the accept test (Section 7.1 estimate with reading G2, the hodograph test
-// of reading G29; a line is its own piece and skips the test).
-struct Trial {
-    D2 chord;
-    double cl, th0, th1;
-    bool ok;
+// The bisection of a curve is a binary tree over its parameter: a node is an
+// interval [t0, t0 + 2^-depth] (t0 = t0_u 2^-depth), tried on its own; an
+// accepted node is a piece, any other is replaced by its halves.  What a
+// trial needs of the curve: q(t) = B'(t) / 3 = D1 + t (2 A2 + t C3), the
+// unit tangents at its ends (us, ue) and |q(1)| (m1; exactly 0 where the last
+// two control points meet), the half-width and the near-zero test's bound.
+struct NodeSeg {
+    D2 D1, A2, C3, us, ue;
+    double m1, w, eps;
 };
-SX_HD inline Trial trial(const Seg& s, const Cfg& cfg, bool line, double dt, const Tan& last_q, const Tan& next_q,
-                         D2 chord) {
-    Trial r;
-    r.chord = chord;
-    r.cl = len(chord);
-    r.th0 = 0.0;
-    r.th1 = 0.0;
-    r.ok = true;
-    if (line) return r;
-    // the end angles, and their sines and cosines from the same cross and
-    // dot products (a zero vector gives angle 0)
-    const double x0 = cross(last_q.dir, chord), y0 = dot(last_q.dir, chord);
-    const double x1 = cross(chord, next_q.dir), y1 = dot(chord, next_q.dir);
-    r.th0 = atan2(x0, y0);
-    r.th1 = atan2(x1, y1);
-    const double h0 = sqrt(x0 * x0 + y0 * y0), h1 = sqrt(x1 * x1 + y1 * y1);
-    const double r0 = 1.0 / h0, r1 = 1.0 / h1, rcl = dt / r.cl;
-    const double sn0 = h0 > 0.0 ? x0 * r0 : 0.0, c0 = h0 > 0.0 ? y0 * r0 : 1.0;
-    const double sn1 = h1 > 0.0 ? x1 * r1 : 0.0, c1 = h1 > 0.0 ? y1 * r1 : 1.0;
-    const double d0 = last_q.mag * rcl, d1 = next_q.mag * rcl;
-    const double est = fit_estimate_sc(r.th0, r.th1, sn0, c0, sn1, c1, d0, d1);
-    const double err = cfg.paper_fit ? est * r.cl : est * (r.cl + kFitK * s.w) * kFitS;
-    const bool len_ok = r.cl > 0.0;
+SX_FN NodeSeg node_seg(const Seg& s) {
+    return NodeSeg{s.D1, s.A2, s.C3, unit(s.ts), unit(s.te), len(s.D3 - s.D2_), s.w, kEpsQ * s.lpoly};
+}
+SX_FN D2 node_q(const NodeSeg& n, double t) {
+    return d2(fma(t, fma(t, n.C3.x, 2.0 * n.A2.x), n.D1.x), fma(t, fma(t, n.C3.y, 2.0 * n.A2.y), n.D1.y));
+}
+SX_FN double depth_dt(uint32_t depth) { return ldexp(1.0, -(int)depth); }  // 2^-depth, exact
+// unit direction (zero for a zero vector) and magnitude of the tangent
+// sample q at an interior t; a near-zero q is replaced by a sample beside it
+// (Section 7.3)
+SX_FN double node_tan(const NodeSeg& n, double t, D2 q, D2& u) {
+    double ss = dot(q, q);
+    if (!(ss >= n.eps * n.eps) || !(ss > 0.0)) {
+        q = node_q(n, (t + kDeltaT < 1.0) ? t + kDeltaT : t - kDeltaT);
+        ss = dot(q, q);
+    }
+    const double r = ss > 0.0 ? rsqrt_d(ss) : 0.0;
+    u = q * r;
+    return ss * r;
+}
+// Whether a node is accepted: the Section 7.1 estimate with reading G2 and
+// the hodograph test of reading G29.
+SX_HD inline bool node_accepted(const NodeSeg& n, const Cfg& cfg, uint32_t t0_u, uint32_t depth) {
+    const double dt = depth_dt(depth);
+    const double t0 = (double)t0_u * dt;
+    const double t1 = t0 + dt;
+    const D2 q0 = node_q(n, t0);
+    D2 u0 = n.us, u1 = n.ue;
+    double m0, m1 = n.m1;
+    if (t0_u == 0u) {
+        const double ss = dot(q0, q0);
+        m0 = ss > 0.0 ? ss * rsqrt_d(ss) : 0.0;
+    } else {
+        m0 = node_tan(n, t0, q0, u0);
+    }
+    if (t1 != 1.0) m1 = node_tan(n, t1, node_q(n, t1), u1);
+    // B(t0 + dt) - B(t0) = dt (3 q0 + dt (3 (A2 + t0 C3) + dt C3))
+    const D2 h = d2(fma(dt, n.C3.x, 3.0 * fma(t0, n.C3.x, n.A2.x)), fma(dt, n.C3.y, 3.0 * fma(t0, n.C3.y, n.A2.y)));
+    const D2 chord = d2(dt * fma(dt, h.x, 3.0 * q0.x), dt * fma(dt, h.y, 3.0 * q0.y));
+    const double cc = dot(chord, chord);
+    if (!(cc > 0.0)) return false;
+    const double rcl = rsqrt_d(cc), cl = cc * rcl;
+    // sines and cosines of the end angles (a zero vector: angle 0)
+    const double sn0 = cross(u0, chord) * rcl, sn1 = cross(chord, u1) * rcl;
+    double c0 = dot(u0, chord) * rcl, c1 = dot(chord, u1) * rcl;
+    if (is_zero(u0)) c0 = 1.0;
+    if (is_zero(u1)) c1 = 1.0;
+    // 1 / (1 + |c0|), 1 / (1 + |c1|) by one reciprocal
+    const double e0 = 1.0 + fabs(c0), e1 = 1.0 + fabs(c1), r = rcp_d(e0 * e1), i0 = r * e1, i1 = r * e0;
+    const double th0 = unit_angle(sn0, c0, i0), th1 = unit_angle(sn1, c1, i1);
+    const double v0 = c0 >= 0.0 ? i0 : 1.0 / (1.0 + c0), v1 = c1 >= 0.0 ? i1 : 1.0 / (1.0 + c1);
+    const double ma = m0 * dt, mc = m1 * dt;
+    const double est = fit_estimate_sc(th0, th1, sn0, c0, sn1, c1, v0, v1, ma * rcl, mc * rcl);
+    const double err = cfg.paper_fit ? est * cl : est * (cl + kFitK * n.w) * kFitS;
     bool hodo_ok = true;
     {
-        const double ma = last_q.mag * dt, mc = next_q.mag * dt;
-        const D2 a = unit(last_q.dir) * ma, c = unit(next_q.dir) * mc;
-        const D2 b = chord - a - c;
+        const D2 a = u0 * ma, c = u1 * mc, b = chord - a - c;
         // a middle vector that is zero up to rounding leaves only the turn from a to c (< pi)
-        if (ma > 0.0 && mc > 0.0 && len(b) > 1e-9 * (ma + mc)) hodo_ok = (dot(a, b) * mc + dot(b, c) * ma) > 0.0;
+        const double lim = 1e-9 * (ma + mc);
+        if (ma > 0.0 && mc > 0.0 && dot(b, b) > lim * lim) hodo_ok = (dot(a, b) * mc + dot(b, c) * ma) > 0.0;
     }
-    r.ok = len_ok && hodo_ok && (err <= cfg.tau_fit);
-    return r;
+    return hodo_ok && (err <= cfg.tau_fit);
 }
 
-// The bisection state of one segment: the two-word stack (t0_u, depth with
-// dt = 2^-depth) and the samples at t0.
+// The tree of one segment in parameter order: the two-word stack (t0_u,
+// depth).
 struct Bisect {
     uint32_t t0_u, depth;
-    Tan last_q;
-    D2 last_qtrue;
+    NodeSeg n;
 };
 SX_FN void bisect_init(Bisect& b, const Seg& s) {
     b.t0_u = 0;
     b.depth = 0;
-    b.last_q = sample_q(s, 0.0);
-    b.last_qtrue = s.D1;
+    b.n = node_seg(s);
 }
-SX_FN double depth_dt(uint32_t depth) { return ldexp(1.0, -(int)depth); }  // 2^-depth, exact
-
-// One trial of the bisection.  Returns true when [t0, t0 + dt] is accepted
-// (its t0_u and depth are reported before the stack pops); *done is set when
-// the segment is fully covered.
-SX_HD inline bool bisect_step(Bisect& b, const Seg& s, const Cfg& cfg, bool line, uint32_t& acc_t0u,
+// One trial.  Returns true when [t0, t0 + dt] is accepted (its t0_u and depth
+// are reported before the stack pops; a line is its own piece); *done is set
+// when the segment is fully covered.
+SX_HD inline bool bisect_step(Bisect& b, const Seg&, const Cfg& cfg, bool line, uint32_t& acc_t0u,
                               uint32_t& acc_depth, bool& acc_pivot, bool& done) {
-    const double dt = depth_dt(b.depth);
-    const double t0 = (double)b.t0_u * dt;
-    const double t1 = t0 + dt;
-    const Tan next_q = line ? b.last_q : sample_q(s, t1);
-    const D2 chord = line ? s.D3 : cubic_chord(s, t0, dt, b.last_qtrue);
-    const Trial tr = trial(s, cfg, line, dt, b.last_q, next_q, chord);
-    const bool forced = b.depth >= (uint32_t)kMaxDepth;
+    const bool ok = line || node_accepted(b.n, cfg, b.t0_u, b.depth);
     done = false;
-    if (tr.ok || forced) {
+    if (ok || b.depth >= (uint32_t)kMaxDepth) {
         acc_t0u = b.t0_u;
         acc_depth = b.depth;
-        acc_pivot = !tr.ok;
+        acc_pivot = !ok;
         // pop: count trailing zeros
         b.t0_u += 1;
         const uint32_t sh = __builtin_ctz(b.t0_u);
         b.t0_u >>= sh;
         b.depth -= sh;
-        b.last_q = next_q;
-        b.last_qtrue = (t1 == 1.0) ? s.D3 - s.D2_ : cubic_q(s, t1);
-        done = (double)b.t0_u * depth_dt(b.depth) == 1.0;
+        done = b.t0_u == 1u && b.depth == 0u;
         return true;
     }
     b.t0_u *= 2;
     b.depth += 1;
     return false;
-}
-
-// One node of the bisection tree on its own: whether [t0, t0 + 2^-depth]
-// (t0 = t0_u 2^-depth) of a curve is accepted by the fit.  The same
-// operations on the same values as bisect_step, whose carried samples are
-// functions of t alone (q at t = 0 and 1 is D1 and D3 - D2 exactly), so the
-// tree's leaves are the segment's pieces in whatever order its nodes are
-// tried.
-SX_FN Tan tan_at(const Seg& s, double t, D2 q) {
-    double ql = len(q);
-    if (t == 0.0) return Tan{s.ts, ql};
-    if (t == 1.0) return Tan{s.te, ql};
-    if (ql < kEpsQ * s.lpoly) {
-        q = cubic_q(s, (t + kDeltaT < 1.0) ? t + kDeltaT : t - kDeltaT);
-        ql = len(q);
-    }
-    return Tan{q, ql};
-}
-SX_HD inline bool node_accepted(const Seg& s, const Cfg& cfg, uint32_t t0_u, uint32_t depth) {
-    const double dt = depth_dt(depth);
-    const double t0 = (double)t0_u * dt;
-    const double t1 = t0 + dt;
-    const D2 q0 = cubic_q(s, t0);
-    const Tan last_q = tan_at(s, t0, q0);
-    const Tan next_q = tan_at(s, t1, cubic_q(s, t1));
-    return trial(s, cfg, false, dt, last_q, next_q, cubic_chord(s, t0, dt, q0)).ok;
 }
 
 // The accepted piece [t0, t0 + 2^-depth] of the segment (accepted by the
@@ -1629,14 +1668,11 @@ SX_HD void piece_es(Sink& k, const Cfg& cfg, const Seg& s, bool line, uint32_t t
     const D2 last_qtrue = (t0 == 0.0) ? s.D1 : cubic_q(s, t0);
     const Tan next_q = line ? last_q : sample_q(s, t1);
     const D2 chord = line ? s.D3 : cubic_chord(s, t0, dt, last_qtrue);
-    Trial tr;
-    tr.chord = chord;
-    tr.cl = len(chord);
-    tr.th0 = 0.0;
-    tr.th1 = 0.0;
+    const double cl = len(chord);
+    double th0 = 0.0, th1 = 0.0;
     if (!line && !pivot) {
-        tr.th0 = atan2(cross(last_q.dir, chord), dot(last_q.dir, chord));
-        tr.th1 = atan2(cross(chord, next_q.dir), dot(chord, next_q.dir));
+        th0 = atan2(cross(last_q.dir, chord), dot(last_q.dir, chord));
+        th1 = atan2(cross(chord, next_q.dir), dot(chord, next_q.dir));
     }
     if constexpr (Sink::kStats) k.st[kStPieces]++;
     es.pivot = pivot;
@@ -1658,9 +1694,9 @@ SX_HD void piece_es(Sink& k, const Cfg& cfg, const Seg& s, bool line, uint32_t t
         c = es_chord(0.5 * es.k0, 0.5 * es.k0);
         base = atan2(last_q.dir.y, last_q.dir.x) + 0.5 * es.k0;
     } else {
-        es.k0 = tr.th0 + tr.th1;
-        es.k1 = es_k1(tr.th0, tr.th1);
-        c = es_chord(tr.th0, tr.th1);
+        es.k0 = th0 + th1;
+        es.k1 = es_k1(th0, th1);
+        c = es_chord(th0, th1);
         // rotation chord / Z(1) in FP32: it only places the per-point work
         const V2 z1 = es_integral1_f((float)es.k0, (float)es.k1);
         const V2 ch = f32(chord);
@@ -1670,7 +1706,7 @@ SX_HD void piece_es(Sink& k, const Cfg& cfg, const Seg& s, bool line, uint32_t t
         base = (double)atan2f(fr.y, fr.x);
     }
     if (!(c > kCMin)) c = kCMin;
-    es.L = tr.cl / c;
+    es.L = cl / c;
     es.fp0 = f32(es.p0);
     es.fd = f32(es.p1 - es.p0);
     es.frot = f32(rot);

@@ -393,8 +393,10 @@ __device__ __forceinline__ void scan_u32_body(const uint32_t* __restrict__ in, u
 // trials in order, 24 random cubics took 293 us (one lane's 180 trials), now
 // 28 us; 1,000 of them 371 -> 41 us; 20,000 stress cubics 1,154 us, 10,007 of
 // them now 129 us; the map scene of 1M segments 277 -> 178 us (23 of 64 lanes
-// were active).  Bound by the FP64 latency of a trial (about 2 us per turn of
-// a wave) on small scenes and by FP64 issue on large ones.
+// were active).  A trial on unit vectors with its own reciprocals, square
+// roots and arctangents (node_accepted), instead of the library's: 28 -> 20.5
+// us, 41 -> 28 us, 129 -> 78 us, 178 -> 123 us.  Bound by the FP64 latency of
+// a trial on small scenes and by FP64 issue on large ones.
 // Pieces are found in no particular order: the q-th one found of tag i is
 // kept at codes[i * keep + q] (the first `keep` of each tag), and the write
 // pass orders them by their start.
@@ -418,7 +420,7 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
                                                                         uint32_t keep, uint32_t* __restrict__ nslots,
                                                                         uint32_t* __restrict__ codes,
                                                                         unsigned long long* __restrict__ stats) {
-    __shared__ double s_seg[12][kNodeSegs];      // D1, D2, D3, end tangents, width, polygon length
+    __shared__ double s_seg[13][kNodeSegs];      // NodeSeg
     __shared__ uint32_t s_node[kNodeStack];      // segment << 21 | depth << 16 | t0
     __shared__ uint32_t s_tag[kNodeSegs];        // tag of a segment
     __shared__ uint32_t s_open[kNodeSegs];       // its open nodes
@@ -468,7 +470,6 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
         const uint32_t n_now = n_pop + take;
         if (n_now == 0u) break;
         const bool act = lane < n_now;
-        Seg s;
         uint32_t sg = 0, depth = 0, t0u = 0;
         if (lane < n_pop) {
             const uint32_t w = s_node[n_node - 1u - lane];
@@ -479,19 +480,22 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
             const uint32_t i = s_curve[(c_lo + (lane - n_pop)) & 127u];
             sg = s_free[n_free - 1u - (lane - n_pop)];
             TagInfo ti;
+            Seg s;
             fetch_tag(sv, i, ti, s);
-            s_seg[0][sg] = s.D1.x;
-            s_seg[1][sg] = s.D1.y;
-            s_seg[2][sg] = s.D2_.x;
-            s_seg[3][sg] = s.D2_.y;
-            s_seg[4][sg] = s.D3.x;
-            s_seg[5][sg] = s.D3.y;
-            s_seg[6][sg] = s.ts.x;
-            s_seg[7][sg] = s.ts.y;
-            s_seg[8][sg] = s.te.x;
-            s_seg[9][sg] = s.te.y;
-            s_seg[10][sg] = s.w;
-            s_seg[11][sg] = s.lpoly;
+            const NodeSeg e = node_seg(s);
+            s_seg[0][sg] = e.D1.x;
+            s_seg[1][sg] = e.D1.y;
+            s_seg[2][sg] = e.A2.x;
+            s_seg[3][sg] = e.A2.y;
+            s_seg[4][sg] = e.C3.x;
+            s_seg[5][sg] = e.C3.y;
+            s_seg[6][sg] = e.us.x;
+            s_seg[7][sg] = e.us.y;
+            s_seg[8][sg] = e.ue.x;
+            s_seg[9][sg] = e.ue.y;
+            s_seg[10][sg] = e.m1;
+            s_seg[11][sg] = e.w;
+            s_seg[12][sg] = e.eps;
             s_tag[sg] = i;
             s_open[sg] = 1u;
             s_found[sg] = 0u;
@@ -502,15 +506,10 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
         wave_lds_sync();
         bool split = false, done = false;
         if (act) {
-            s.D1 = d2(s_seg[0][sg], s_seg[1][sg]);
-            s.D2_ = d2(s_seg[2][sg], s_seg[3][sg]);
-            s.D3 = d2(s_seg[4][sg], s_seg[5][sg]);
-            s.ts = d2(s_seg[6][sg], s_seg[7][sg]);
-            s.te = d2(s_seg[8][sg], s_seg[9][sg]);
-            s.w = s_seg[10][sg];
-            s.lpoly = s_seg[11][sg];
-            seg_diffs(s);
-            const bool ok = node_accepted(s, cfg, t0u, depth);
+            const NodeSeg e{d2(s_seg[0][sg], s_seg[1][sg]), d2(s_seg[2][sg], s_seg[3][sg]),
+                            d2(s_seg[4][sg], s_seg[5][sg]), d2(s_seg[6][sg], s_seg[7][sg]),
+                            d2(s_seg[8][sg], s_seg[9][sg]), s_seg[10][sg], s_seg[11][sg], s_seg[12][sg]};
+            const bool ok = node_accepted(e, cfg, t0u, depth);
             if (Stats) n_trials++;
             split = !ok && depth < (uint32_t)kMaxDepth;
             if (!split) {
