@@ -662,9 +662,9 @@ def phase_of_kernel(name: str):
 
     simple = (("scan_tags_kernel", "scan_tags"), ("scan_slots_kernel", "scan_slots"),
               ("list_kernel", "bisect_write"), ("list_small_kernel", "bisect_write"),
-              ("scan_counts_dev_kernel", "scan_records"), ("finish_kernel", "finish"))
+              ("scan_counts_dev_kernel", "scan_records"))
     for key, phase in simple:
-        if f"sx::{key}(" in name:
+        if re.search(rf"sx::{key}(<\d+>)?\(", name):
             return phase
     if re.search(r"sx::record_kernel(<(true|false)>)?\(", name):
         return "records"

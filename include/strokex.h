@@ -366,9 +366,10 @@ int sx_batch_expand(sx_ctx *ctx, sx_batch *batch, float tolerance, int output_mo
  *   piece_waves   1..3: waves per SIMD the slot kernel's register
  *                 allocation allows (more waves hide more latency but spill);
  *   chunk_k       1..255: records per emission item chunk (work per thread
- *                 of the record kernel);
+ *                 of the record kernel; scenes of few pieces take at most 4);
  *   bisect_range  tags per bisection wave, a multiple of 64 up to 1024
- *                 (0 = 256): longer ranges keep lanes refilled longer;
+ *                 (0 = 256): longer ranges keep lanes refilled longer (small
+ *                 scenes take shorter ones, one wave per SIMD slot);
  *   bisect_waves  2, 3 or 4 (0 = 2): waves per SIMD of the bisection kernels.
  * Defaults {2, 16, 256, 2}.  Errors: SX_EINVAL (out of range). */
 typedef struct {

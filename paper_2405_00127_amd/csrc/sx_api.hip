@@ -322,16 +322,26 @@ bool make_cfg(const sx_ctx* ctx, float tol, int mode, sx::Cfg& cfg) {
     return true;
 }
 
+// A scene of few pieces cannot fill the chip with threads of chunk_k records
+// each, which then follow one another: it takes chunks of at most
+// kSmallChunk.  (At 2^17 slots and two records per slot, chunks of 4 still
+// make no more threads than the chip holds at two waves per SIMD.)
+constexpr uint64_t kSmallSlots = 1ull << 17;
+constexpr uint32_t kSmallChunk = 4;
+
 const uint64_t* n_slots_dev(const sx_scene* s) { return s->d_base + s->n_tags; }
 
 // Pipeline phases (each one kernel, in this order on one stream).
 enum { kPhScanTags, kPhBisectCount, kPhScanSlots, kPhBisectWrite, kPhPieces, kPhTails, kPhScanRecords, kPhRecords,
        kPhN };
 
-hipError_t run_one(const sx_ctx* ctx, const sx_scene* s, const sx::Cfg& cfg, int ph, void* out, uint64_t cap_records,
-                   unsigned long long* stats, hipStream_t st) {
+// (the last one puts {records, 0 or 1 = workspace too small} into dst, when given)
+hipError_t run_one(const sx_ctx* ctx, const sx_scene* s, const sx::Cfg& conf, int ph, void* out, uint64_t cap_records,
+                   unsigned long long* stats, hipStream_t st, uint64_t* dst = nullptr) {
     const sx_tuning& t = ctx->tune;
     if (s->n_tags == 0) return hipSuccess;
+    sx::Cfg cfg = conf;
+    if (s->slot_cap <= kSmallSlots) cfg.K = std::min(cfg.K, kSmallChunk);
     switch (ph) {
         case kPhScanTags:
             return sx::launch_scan_tags(s->d_tags, s->n_tags, s->d_mon, ctl_block(s, 0), s->d_status_tags, s->d_ws_ctl,
@@ -356,28 +366,17 @@ hipError_t run_one(const sx_ctx* ctx, const sx_scene* s, const sx::Cfg& cfg, int
                                               ctl_block(s, 2), s->d_status_rc, st);
         case kPhRecords:
             return sx::launch_records(view(s), workspace(s), cfg, s->d_roff, s->d_slots, n_slots_dev(s), s->slot_cap,
-                                      out, cap_records, st);
+                                      out, cap_records, dst, st);
     }
     return hipErrorInvalidValue;
-}
-
-// phases [0, last) of the pipeline
-int run_phases(sx_ctx* ctx, const sx_scene* s, const sx::Cfg& cfg, int last, void* out, uint64_t cap_records,
-               hipStream_t st) {
-    for (int ph = 0; ph < last; ph++) {
-        hipError_t e = run_one(ctx, s, cfg, ph, out, cap_records, nullptr, st);
-        if (e != hipSuccess) return hip_fail(ctx, e, "pipeline launch");
-    }
-    return SX_OK;
 }
 
 // the whole pipeline; dst (device) receives {records, 0 or 1 = workspace too small}
 int run_all(sx_ctx* ctx, const sx_scene* s, const sx::Cfg& cfg, void* out, uint64_t cap_records, uint64_t* dst,
             hipStream_t st) {
-    int r = run_phases(ctx, s, cfg, kPhN, out, cap_records, st);
-    if (r != SX_OK) return r;
-    hipError_t e = sx::launch_finish(s->d_roff, n_slots_dev(s), s->slot_cap, s->n_tags, workspace(s), dst, st);
-    return e == hipSuccess ? SX_OK : hip_fail(ctx, e, "finish launch");
+    hipError_t e = s->n_tags == 0 ? sx::launch_no_records(dst, st) : hipSuccess;
+    for (int ph = 0; ph < kPhN && e == hipSuccess; ph++) e = run_one(ctx, s, cfg, ph, out, cap_records, nullptr, st, dst);
+    return e == hipSuccess ? SX_OK : hip_fail(ctx, e, "pipeline launch");
 }
 
 // Synchronous expansion with workspace growth: runs the pipeline, and when

@@ -81,8 +81,12 @@ hipError_t launch_slots(const SceneView& sv, const Cfg& cfg, const ItemWs& ws, c
 // tail slots (one thread per tag), after launch_slots
 hipError_t launch_tails(const SceneView& sv, const Cfg& cfg, const ItemWs& ws, const uint64_t* base,
                         uint64_t slot_cap, uint32_t* rc, unsigned long long* stats, hipStream_t s);
+// dst (or null) receives {records, 0 or 1 = the workspace was too small}.
 hipError_t launch_records(const SceneView& sv, const ItemWs& ws, const Cfg& cfg, const uint64_t* roff, const Slot* pcs,
-                          const uint64_t* n_slots_dev, uint64_t slot_cap, void* out, uint64_t cap, hipStream_t s);
+                          const uint64_t* n_slots_dev, uint64_t slot_cap, void* out, uint64_t cap, uint64_t* dst,
+                          hipStream_t s);
+// dst = {0, 0}: an empty scene's result
+hipError_t launch_no_records(uint64_t* dst, hipStream_t s);
 // Single-pass expansion into an unordered line soup (one thread per tag;
 // records reserved with atomic adds on *counter, which ends at the total the
 // scene needs even when it exceeds cap_records).
@@ -92,8 +96,6 @@ hipError_t launch_gather(const GatherDesc* descs, uint32_t n_scenes, uint8_t* ta
                          float* xforms, uint32_t* path_map, hipStream_t s);
 hipError_t launch_scene_offsets(const uint64_t* base, const uint64_t* roff, uint64_t slot_cap, const GatherDesc* descs,
                                 uint32_t n_scenes, uint32_t n_tags, uint64_t* scene_offsets, hipStream_t s);
-hipError_t launch_finish(const uint64_t* roff, const uint64_t* n_slots_dev, uint64_t slot_cap, uint32_t n_tags,
-                         const ItemWs& ws, uint64_t* dst, hipStream_t s);
 hipError_t launch_tag_records(const uint64_t* base, const uint64_t* roff, uint64_t slot_cap, uint32_t n_tags,
                               uint32_t* counts, uint64_t* offs, hipStream_t s);
 

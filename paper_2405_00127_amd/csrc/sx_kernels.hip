@@ -181,6 +181,8 @@ constexpr int kScanBlock = 256;
 constexpr int kTagItems = 16;    // tags per thread of the tag-monoid scan
 constexpr int kCountItems = 32;  // counts per thread of the count scans
 constexpr int kRecCountItems = 64;  // counts per thread of the record-count scan (one round of tiles)
+constexpr int kRecCountSmall = 16;  // the same for scenes of at most kRecSmallSlots slots
+constexpr uint32_t kRecSmallSlots = 1u << 20;
 constexpr uint32_t kCountLine = 0x80000000u;  // bit of a slot-count word: a line segment
 
 __device__ __forceinline__ Pair tag_inc(uint32_t t) {
@@ -343,13 +345,14 @@ __global__ __launch_bounds__(kScanBlock) void scan_slots_kernel(const uint32_t* 
 }
 // the same with n read from device memory (clamped to the buffers' capacity);
 // the grid covers the capacity
+template <int Items>
 __global__ __launch_bounds__(kScanBlock) void scan_counts_dev_kernel(const uint32_t* __restrict__ in,
                                                                      const uint64_t* __restrict__ n_dev, uint32_t cap,
                                                                      uint64_t* __restrict__ out, ScanCtl* ctl,
                                                                      TileStatus* st) {
     const uint64_t nd = *n_dev;
     if (nd == 0 && blockIdx.x == 0 && threadIdx.x == 0) out[0] = 0;
-    scan_u32_body<kRecCountItems>(in, nd < cap ? (uint32_t)nd : cap, out, ctl, st);
+    scan_u32_body<Items>(in, nd < cap ? (uint32_t)nd : cap, out, ctl, st);
 }
 template <int Items, uint32_t Mask>
 __device__ __forceinline__ void scan_u32_body(const uint32_t* __restrict__ in, uint32_t n, uint64_t* __restrict__ out,
@@ -715,9 +718,11 @@ constexpr int kTailBlock = 256;   // tags per tail-kernel workgroup
 constexpr int kTailGrid = 8192;   // grid cap of the tail kernel (tags stride by it)
 constexpr int kTailWin = 64;      // slot tiles a tail-kernel block counts in LDS
 constexpr int kRecBlock = 256;
-constexpr int kRecGrid = 8192;    // persistent grid of the record kernel
+constexpr uint32_t kRecGrid = 8192;  // grid cap of the record kernel (tiles stride by it)
 constexpr uint32_t kStageWords = 6400;  // LDS words staging a tile's records (25 KB)
-constexpr int kOvfBlocks = 512;   // record-kernel blocks striding over the overflow slots
+constexpr uint32_t kRecSplit = 8;     // most blocks of a tile (scenes of few tiles)
+constexpr uint32_t kRecSplitGrid = 1024;  // record-kernel blocks that a small scene spreads over
+constexpr uint32_t kOvfBlocks = 512;  // most record-kernel blocks striding over the overflow units
 
 // Unit allocation of the piece launch.  A piece's items are first counted
 // by a dry run of its puts (CountAlloc: nothing is written); the lane then
@@ -793,7 +798,7 @@ __global__ __launch_bounds__(kSlotBlock, MinWaves) void slot_kernel(SceneView sv
     __shared__ RangeRes s_res[2 * kSlotBlock];
     __shared__ RangeRes s_first[2][kSlotBlock];    // each side's first range
     const uint64_t n_slots = *n_slots_dev;
-    if (n_slots > slot_cap) return;  // reported by the finish kernel
+    if (n_slots > slot_cap) return;  // reported by the record kernel
     const uint64_t n_pieces = n_slots - sv.n_tags;
     const uint32_t n_tiles = piece_tile_count(n_pieces);
     // groups of kPieceGroup tiles, then the last kSingleTiles tiles one at a
@@ -1008,7 +1013,7 @@ __global__ __launch_bounds__(kTailBlock, 3) void tail_kernel(SceneView sv, Cfg c
     __shared__ uint32_t s_at[kTailWin];
     __shared__ uint32_t s_asked;
     const uint32_t n = sv.n_tags;
-    if (base[n] > slot_cap) return;  // reported by the finish kernel
+    if (base[n] > slot_cap) return;  // reported by the record kernel
     const uint32_t t = threadIdx.x;
     if (t == 0) s_asked = 0u;
     uint32_t asked = 0, joins = 0;
@@ -1088,19 +1093,34 @@ __device__ __forceinline__ void record_item(const SceneView& sv, const ItemWs& w
 }
 
 // Per item chunk, the FP32 per-point work: records at
-// roff[slot] + the chunk's position within its slot.
+// roff[slot] + the chunk's position within its slot.  A tile is one block's
+// turn; a scene of few tiles gives each to several blocks (every split-th
+// round of 256 units), since a block's rounds of records follow one another
+// and a chunk's records too: 24 cubics (10 tiles of about 750 units) took 27
+// us with a block per tile and chunks of 16, 14 us with 4 blocks a tile and
+// chunks of 4.  The first block also publishes dst[0] = records and dst[1] =
+// 0 when everything fit, else 1 (slots or items were dropped: the workspace
+// must grow; the counters stay in ws.ctl), for which a launch of its own
+// took 4.6 us.
 template <bool Newton>
 __global__ __launch_bounds__(kRecBlock, Newton ? 3 : 6) void record_kernel(SceneView sv, ItemWs ws, int arcs,
                                                            const uint64_t* __restrict__ roff,
                                                            const Slot* __restrict__ pcs,
                                                            const uint64_t* __restrict__ n_slots_dev, uint64_t slot_cap,
-                                                           float* __restrict__ out, uint64_t cap_records, XIncF xi) {
+                                                           float* __restrict__ out, uint64_t cap_records, XIncF xi,
+                                                           uint32_t ovf_blocks, uint64_t* __restrict__ dst) {
     const uint64_t n_slots = *n_slots_dev;
+    const bool fit = n_slots <= slot_cap && ws.ctl->ovf_n <= ws.ovf_cap;
+    if (dst && blockIdx.x == 0u && threadIdx.x == 0u) {
+        dst[0] = n_slots <= slot_cap ? roff[n_slots] : 0ull;
+        dst[1] = fit ? 0ull : 1ull;
+        ws.ctl->slots_total = n_slots;
+    }
     // nothing is written when the records exceed the capacity, or slots or items were dropped
-    if (n_slots > slot_cap || roff[n_slots] > cap_records || ws.ctl->ovf_n > ws.ovf_cap) return;
+    if (!fit || roff[n_slots] > cap_records) return;
     const uint32_t n_tiles = piece_tile_count(n_slots - sv.n_tags);
-    const uint32_t b = blockIdx.x;
-    if (b < kRecGrid) {
+    const uint32_t b = blockIdx.x, n_main = gridDim.x - ovf_blocks;
+    if (b < n_main) {
         // a tile's units, one per thread (units in any order: every record's
         // position comes from the scans)
         // the tile's slots own one contiguous output range: records in its
@@ -1108,7 +1128,10 @@ __global__ __launch_bounds__(kRecBlock, Newton ? 3 : 6) void record_kernel(Scene
         // coalesced stores once the tile is done
         __shared__ float s_stage[kStageWords];
         const uint32_t words = arcs ? 6u : 5u;
-        for (uint32_t tile = b; tile < n_tiles; tile += kRecGrid) {
+        // blocks per tile (a split tile's blocks write their records directly)
+        const uint32_t split = max(1u, min(kRecSplit, min(n_main, kRecSplitGrid) / n_tiles));
+        for (uint32_t turn = b; turn < n_tiles * split; turn += n_main) {
+            const uint32_t tile = turn / split, part = turn % split;
             const uint32_t cnt = ws.tile_n[tile] < ws.region_cap ? ws.tile_n[tile] : ws.region_cap;
             const Unit* base = ws.units + (uint64_t)tile * ws.region_cap;
             const uint64_t s_lo = tile_first_slot(pcs, tile, n_tiles, n_slots);
@@ -1117,22 +1140,23 @@ __global__ __launch_bounds__(kRecBlock, Newton ? 3 : 6) void record_kernel(Scene
             const uint64_t n_rec = roff[s_hi] - lo;
             // (a tile whose items spilled into the overflow area is not
             // staged: those records are written by the overflow blocks)
-            const uint64_t n_st = ws.tile_n[tile] > ws.region_cap ? 0u
+            const uint64_t n_st = ws.tile_n[tile] > ws.region_cap || split > 1u ? 0u
                                   : (n_rec < kStageWords / words ? n_rec : kStageWords / words);
-            for (uint32_t s2 = threadIdx.x; s2 < cnt; s2 += kRecBlock)
+            for (uint32_t s2 = part * kRecBlock + threadIdx.x; s2 < cnt; s2 += split * kRecBlock)
                 record_item<Newton>(sv, ws, base + s2, roff, n_slots, out, cap_records, arcs, xi, s_stage, lo,
                                     lo + n_st);
+            if (split > 1u) continue;
             __syncthreads();
-            uint32_t* dst = reinterpret_cast<uint32_t*>(out) + lo * words;
+            uint32_t* dst32 = reinterpret_cast<uint32_t*>(out) + lo * words;
             const uint32_t* src = reinterpret_cast<const uint32_t*>(s_stage);
-            for (uint32_t d = threadIdx.x; d < (uint32_t)n_st * words; d += kRecBlock) dst[d] = src[d];
+            for (uint32_t d = threadIdx.x; d < (uint32_t)n_st * words; d += kRecBlock) dst32[d] = src[d];
             __syncthreads();
         }
     } else {
         const uint64_t cnt = ws.ctl->ovf_n;
         const Unit* base = ws.units + ws.ovf_base;
-        for (uint64_t s = (uint64_t)(b - kRecGrid) * kRecBlock + threadIdx.x; s < cnt;
-             s += (uint64_t)kOvfBlocks * kRecBlock)
+        for (uint64_t s = (uint64_t)(b - n_main) * kRecBlock + threadIdx.x; s < cnt;
+             s += (uint64_t)ovf_blocks * kRecBlock)
             record_item<Newton>(sv, ws, base + s, roff, n_slots, out, cap_records, arcs, xi);
     }
 }
@@ -1195,24 +1219,6 @@ hipError_t launch_soup(const SceneView& sv, const Cfg& cfg, void* out, uint64_t 
     const uint32_t blocks = (sv.n_tags + 255u) / 256u;
     soup_kernel<<<blocks < 16384u ? blocks : 16384u, 256, 0, s>>>(sv, cfg, xi, (float*)out, cap_records, counter);
     return hipGetLastError();
-}
-
-// dst[0] = records, dst[1] = 0 when everything fit, else 1 (slots or items
-// were dropped: the workspace must grow); the counters stay in ws.ctl.
-__global__ void finish_kernel(const uint64_t* __restrict__ roff, const uint64_t* __restrict__ n_slots_dev,
-                              uint64_t slot_cap, uint32_t n_tags, const ItemWs ws, uint64_t* __restrict__ dst) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        if (n_tags == 0) {
-            dst[0] = 0;
-            dst[1] = 0;
-            return;
-        }
-        const uint64_t ns = *n_slots_dev;
-        const bool slots_ok = ns <= slot_cap;
-        dst[0] = slots_ok ? roff[ns] : 0ull;
-        dst[1] = (!slots_ok || ws.ctl->ovf_n > ws.ovf_cap) ? 1ull : 0ull;
-        ws.ctl->slots_total = ns;
-    }
 }
 
 // Per-tag record counts and offsets (verification exports):
@@ -1298,8 +1304,15 @@ hipError_t launch_zero_u64(uint64_t* out, hipStream_t s) {
 }
 hipError_t launch_scan_counts_dev(const uint32_t* in, const uint64_t* n_dev, uint32_t cap, uint64_t* out, void* ctl,
                                   void* st, hipStream_t s) {
-    const int g = count_scan_tiles(cap > 0 ? cap : 1, kRecCountItems);
-    scan_counts_dev_kernel<<<g, kScanBlock, 0, s>>>(in, n_dev, cap, out, (ScanCtl*)ctl, (TileStatus*)st);
+    // a small scene's tiles are short: its one or two tiles' loads and stores
+    // would follow one another (24 cubics: 64 counts per thread 8.7 us, 16
+    // 4.1 us); a large one's are long, one round of tiles
+    if (cap <= kRecSmallSlots)
+        scan_counts_dev_kernel<kRecCountSmall><<<count_scan_tiles(cap > 0 ? cap : 1, kRecCountSmall), kScanBlock, 0, s>>>(
+            in, n_dev, cap, out, (ScanCtl*)ctl, (TileStatus*)st);
+    else
+        scan_counts_dev_kernel<kRecCountItems><<<count_scan_tiles(cap, kRecCountItems), kScanBlock, 0, s>>>(
+            in, n_dev, cap, out, (ScanCtl*)ctl, (TileStatus*)st);
     return hipGetLastError();
 }
 
@@ -1377,17 +1390,23 @@ hipError_t launch_tails(const SceneView& sv, const Cfg& cfg, const ItemWs& ws, c
     return hipGetLastError();
 }
 hipError_t launch_records(const SceneView& sv, const ItemWs& ws, const Cfg& cfg, const uint64_t* roff, const Slot* pcs,
-                          const uint64_t* n_slots_dev, uint64_t slot_cap, void* out, uint64_t cap, hipStream_t s) {
+                          const uint64_t* n_slots_dev, uint64_t slot_cap, void* out, uint64_t cap, uint64_t* dst,
+                          hipStream_t s) {
     if (sv.n_tags == 0) return hipSuccess;
     XIncF xi;
     for (int k = 0; k < 5; k++) xi.v[k] = (float)cfg.xinc[k];
+    // a block per tile that the slot buffers can hold; small scenes: several
+    // per tile, up to kRecSplitGrid in all (the kernel takes what there is)
+    const uint32_t tiles = std::min<uint32_t>(kRecGrid, std::max<uint32_t>(1u, slot_tiles(slot_cap)));
+    const uint32_t g = std::max<uint32_t>(tiles, std::min<uint32_t>(tiles * kRecSplit, kRecSplitGrid));
+    const uint32_t go = std::min<uint32_t>(kOvfBlocks, std::max<uint32_t>(1u, g / 16u));
     // exact-density items exist only with line output in the Newton mode
     if (cfg.newton && !cfg.arcs)
-        record_kernel<true><<<kRecGrid + kOvfBlocks, kRecBlock, 0, s>>>(sv, ws, cfg.arcs, roff, pcs, n_slots_dev,
-                                                                        slot_cap, (float*)out, cap, xi);
+        record_kernel<true><<<g + go, kRecBlock, 0, s>>>(sv, ws, cfg.arcs, roff, pcs, n_slots_dev, slot_cap,
+                                                         (float*)out, cap, xi, go, dst);
     else
-        record_kernel<false><<<kRecGrid + kOvfBlocks, kRecBlock, 0, s>>>(sv, ws, cfg.arcs, roff, pcs, n_slots_dev,
-                                                                         slot_cap, (float*)out, cap, xi);
+        record_kernel<false><<<g + go, kRecBlock, 0, s>>>(sv, ws, cfg.arcs, roff, pcs, n_slots_dev, slot_cap,
+                                                          (float*)out, cap, xi, go, dst);
     return hipGetLastError();
 }
 hipError_t launch_gather(const GatherDesc* descs, uint32_t n_scenes, uint8_t* tags, float2* pts, StyleD* styles,
@@ -1403,9 +1422,11 @@ hipError_t launch_scene_offsets(const uint64_t* base, const uint64_t* roff, uint
                                                                     scene_offsets);
     return hipGetLastError();
 }
-hipError_t launch_finish(const uint64_t* roff, const uint64_t* n_slots_dev, uint64_t slot_cap, uint32_t n_tags,
-                         const ItemWs& ws, uint64_t* dst, hipStream_t s) {
-    finish_kernel<<<1, 64, 0, s>>>(roff, n_slots_dev, slot_cap, n_tags, ws, dst);
+__global__ void zero2_u64_kernel(uint64_t* out) {
+    if (threadIdx.x < 2) out[threadIdx.x] = 0ull;
+}
+hipError_t launch_no_records(uint64_t* dst, hipStream_t s) {
+    zero2_u64_kernel<<<1, 64, 0, s>>>(dst);
     return hipGetLastError();
 }
 hipError_t launch_tag_records(const uint64_t* base, const uint64_t* roff, uint64_t slot_cap, uint32_t n_tags,

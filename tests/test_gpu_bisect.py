@@ -1,6 +1,7 @@
-"""The bisection and the piece list at the edges of their dispatch (GPU, through
-the C ABI): scenes at the tag count where the list kernel changes, tags with
-more pieces than the bisection keeps codes for, and runs of tags without
+"""The bisection, the piece list and the record launch at the edges of their
+dispatch (GPU, through the C ABI): scenes at the tag counts where the list
+kernel, the record chunks (2^17 slots, four per tag at first) and the record
+scan (2^20 slots) change, tags with more pieces than the bisection keeps codes for, and runs of tags without
 pieces longer than the list kernel stages.  Against the FP64 oracle at the
 parity bars (or bit for bit against the same paths expanded without the empty
 ones)."""
@@ -59,7 +60,7 @@ def _check(ctx, sc):
     scene.release()
 
 
-@pytest.mark.parametrize("n_tags", [12, 255, 257, 4095, 4097, SMALL_TAGS, SMALL_TAGS + 1])
+@pytest.mark.parametrize("n_tags", [12, 255, 257, 4095, 4097, SMALL_TAGS, SMALL_TAGS + 1, 32768, 32769, 262145])
 def test_tag_counts_at_the_edges(ctx, n_tags):
     _check(ctx, _with_tags(n_tags))
 
