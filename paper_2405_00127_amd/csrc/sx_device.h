@@ -59,37 +59,6 @@ struct StyleD {
 // a fill: flattened at offset 0 (half_width 0), one side, no joins or caps
 constexpr uint32_t kStyleFill = 1u << 24;
 
-// ---------------------------------------------------------- small vectors
-struct V2 {  // FP32 (per-point work, outputs)
-    float x, y;
-};
-struct D2 {  // FP64 (decisions)
-    double x, y;
-};
-SX_FN V2 v2(float x, float y) { return V2{x, y}; }
-SX_FN V2 operator+(V2 a, V2 b) { return v2(a.x + b.x, a.y + b.y); }
-SX_FN V2 operator-(V2 a, V2 b) { return v2(a.x - b.x, a.y - b.y); }
-SX_FN V2 operator*(V2 a, float s) { return v2(a.x * s, a.y * s); }
-SX_FN float len(V2 a) { return sqrtf(a.x * a.x + a.y * a.y); }
-
-SX_FN D2 d2(double x, double y) { return D2{x, y}; }
-SX_FN D2 operator+(D2 a, D2 b) { return d2(a.x + b.x, a.y + b.y); }
-SX_FN D2 operator-(D2 a, D2 b) { return d2(a.x - b.x, a.y - b.y); }
-SX_FN D2 operator*(D2 a, double s) { return d2(a.x * s, a.y * s); }
-SX_FN double dot(D2 a, D2 b) { return a.x * b.x + a.y * b.y; }
-SX_FN double cross(D2 a, D2 b) { return a.x * b.y - a.y * b.x; }
-SX_FN double len(D2 a) { return sqrt(a.x * a.x + a.y * a.y); }
-SX_FN bool is_zero(D2 a) { return a.x == 0.0 && a.y == 0.0; }
-SX_FN D2 unit(D2 a) {
-    const double r = 1.0 / len(a);
-    return d2(a.x * r, a.y * r);
-}
-// right normal N = (T_y, -T_x); N' = kappa T
-SX_FN D2 rnormal(D2 t) { return d2(t.y, -t.x); }
-SX_FN V2 f32(D2 a) { return v2((float)a.x, (float)a.y); }
-// offset point p + N h, rounded once
-SX_FN V2 offs(D2 p, D2 n, double h) { return f32(p + n * h); }
-
 // ------------------------------------------- elementary functions, FP64
 // Reciprocal and reciprocal square root from the hardware's estimates
 // (relative error e of about 2^-24) and one step of third order: 1 / x =
@@ -116,6 +85,18 @@ SX_FN double rsqrt_d(double x) {
     return 1.0 / sqrt(x);
 #endif
 }
+SX_FN double sqrt_d(double x) { return x > 0.0 ? x * rsqrt_d(x) : 0.0; }
+// Cube root of x >= 0: an FP32 estimate and one Halley step (third order).
+SX_FN double cbrt_d(double x) {
+#ifdef __HIP_DEVICE_COMPILE__
+    if (!(x > 1e-30 && x < 1e30)) return cbrt(x);
+    const double y = (double)exp2f(log2f((float)x) * (1.0f / 3.0f));
+    const double c = y * y * y;
+    return y * fma(2.0, x, c) * rcp_d(fma(2.0, c, x));
+#else
+    return cbrt(x);
+#endif
+}
 // atan(t) for |t| <= 1: t P(t^2), P the minimax polynomial of degree 19 for
 // atan(sqrt z) / sqrt z on [0, 1] (relative error 2.7e-17), even and odd
 // powers apart for two chains of half the length
@@ -139,26 +120,57 @@ SX_FN double unit_angle(double sn, double cs, double inv) {
     return cs >= 0.0 ? a : copysign(kPi, sn) - a;
 }
 
+// ---------------------------------------------------------- small vectors
+struct V2 {  // FP32 (per-point work, outputs)
+    float x, y;
+};
+struct D2 {  // FP64 (decisions)
+    double x, y;
+};
+SX_FN V2 v2(float x, float y) { return V2{x, y}; }
+SX_FN V2 operator+(V2 a, V2 b) { return v2(a.x + b.x, a.y + b.y); }
+SX_FN V2 operator-(V2 a, V2 b) { return v2(a.x - b.x, a.y - b.y); }
+SX_FN V2 operator*(V2 a, float s) { return v2(a.x * s, a.y * s); }
+SX_FN float len(V2 a) { return sqrtf(a.x * a.x + a.y * a.y); }
+
+SX_FN D2 d2(double x, double y) { return D2{x, y}; }
+SX_FN D2 operator+(D2 a, D2 b) { return d2(a.x + b.x, a.y + b.y); }
+SX_FN D2 operator-(D2 a, D2 b) { return d2(a.x - b.x, a.y - b.y); }
+SX_FN D2 operator*(D2 a, double s) { return d2(a.x * s, a.y * s); }
+SX_FN double dot(D2 a, D2 b) { return a.x * b.x + a.y * b.y; }
+SX_FN double cross(D2 a, D2 b) { return a.x * b.y - a.y * b.x; }
+SX_FN double len(D2 a) { return sqrt_d(a.x * a.x + a.y * a.y); }
+SX_FN bool is_zero(D2 a) { return a.x == 0.0 && a.y == 0.0; }
+SX_FN D2 unit(D2 a) {
+    const double r = rsqrt_d(a.x * a.x + a.y * a.y);
+    return d2(a.x * r, a.y * r);
+}
+// right normal N = (T_y, -T_x); N' = kappa T
+SX_FN D2 rnormal(D2 t) { return d2(t.y, -t.x); }
+SX_FN V2 f32(D2 a) { return v2((float)a.x, (float)a.y); }
+// offset point p + N h, rounded once
+SX_FN V2 offs(D2 p, D2 n, double h) { return f32(p + n * h); }
+
 // ------------------------------------------------------- Euler spirals
 // Appendix A: k1 and chord / arc-length ratio as 7th-order polynomials in
 // k = th0 + th1 and D = th1 - th0.
 SX_FN double es_k1(double th0, double th1) {
     double k = th0 + th1, d = th1 - th0;
     double k2 = k * k, d2_ = d * d;
-    double a = 6.0 + d2_ * (-1.0 / 70.0 + d2_ * (-1.0 / 10780.0 + d2_ * 2.769178184818219e-7));
-    double b = -0.1 + d2_ * (1.0 / 4200.0 + d2_ * 1.6959677820260655e-5);
-    double c = -1.0 / 1400.0 + d2_ * 6.84915970574303e-5;
+    double a = fma(d2_, fma(d2_, fma(d2_, 2.769178184818219e-7, -1.0 / 10780.0), -1.0 / 70.0), 6.0);
+    double b = fma(d2_, fma(d2_, 1.6959677820260655e-5, 1.0 / 4200.0), -0.1);
+    double c = fma(d2_, 6.84915970574303e-5, -1.0 / 1400.0);
     double e = -7.936475029053326e-6;
-    return d * (a + k2 * (b + k2 * (c + k2 * e)));
+    return d * fma(k2, fma(k2, fma(k2, e, c), b), a);
 }
 SX_FN double es_chord(double th0, double th1) {
     double k = th0 + th1, d = th1 - th0;
     double k2 = k * k, d2_ = d * d;
-    double a = 1.0 + d2_ * (-1.0 / 40.0 + d2_ * (0.00034226190482569864 - d2_ * 1.9349474568904524e-6));
-    double b = -1.0 / 24.0 + d2_ * (0.0024702380951963226 - d2_ * 3.7297408997537985e-5);
-    double c = 1.0 / 1920.0 - d2_ * 4.87350869747975e-5;
+    double a = fma(d2_, fma(d2_, fma(d2_, -1.9349474568904524e-6, 0.00034226190482569864), -1.0 / 40.0), 1.0);
+    double b = fma(d2_, fma(d2_, -3.7297408997537985e-5, 0.0024702380951963226), -1.0 / 24.0);
+    double c = fma(d2_, -4.87350869747975e-5, 1.0 / 1920.0);
     double e = -3.1001936068463107e-6;
-    return a + k2 * (b + k2 * (c + k2 * e));
+    return fma(k2, fma(k2, fma(k2, e, c), b), a);
 }
 
 // Section 7.1: chord-normalised distance estimate between a cubic with end
@@ -213,11 +225,6 @@ SX_FN float es_phi_f(float k0, float k1, float u) {
     float v = u - 0.5f;
     return v * (k0 + 0.5f * k1 * v);
 }
-SX_FN double es_phi(double k0, double k1, double u) {
-    double v = u - 0.5;
-    return v * (k0 + 0.5 * k1 * v);
-}
-
 // Z(u) = int_0^u exp(i phi(v)) dv by 4-point Gauss-Legendre on [0, u] (FP32).
 SX_FN V2 es_integral_f(float k0, float k1, float u) {
     const float gx[4] = {-0.8611363115940526f, -0.3399810435848563f, 0.3399810435848563f, 0.8611363115940526f};
@@ -238,8 +245,8 @@ SX_FN V2 es_integral_f(float k0, float k1, float u) {
 // Z(1) (once per piece): 8-point Gauss-Legendre on v = u - 1/2.  The nodes
 // come in pairs +-v, and exp(i phi(v)) + exp(i phi(-v)) = 2 cos(k0 v)
 // exp(i k1 v^2 / 2), so each pair costs one sincos and one cos.  Z(1) only
-// places the piece for the per-point work (p0 + chord / Z(1) * Z(u)), so the
-// pipeline takes it in FP32; the FP64 form serves host checks.
+// places the piece for the per-point work (p0 + chord / Z(1) * Z(u)), so it
+// is taken in FP32.
 SX_FN V2 es_integral1_f(float k0, float k1) {
     float sx = 0.0f, sy = 0.0f;
     if (fabsf(k0) + fabsf(k1) < 1.5f) {
@@ -274,21 +281,6 @@ SX_FN V2 es_integral1_f(float k0, float k1) {
     }
     return v2(sx, sy);
 }
-SX_FN D2 es_integral1(double k0, double k1) {
-    const double gx[4] = {0.1834346424956498, 0.5255324099163290, 0.7966664774136267, 0.9602898564975363};
-    const double gw[4] = {0.3626837833783620, 0.3137066458778873, 0.2223810344533745, 0.1012285362903763};
-    double sx = 0.0, sy = 0.0;
-    for (int i = 0; i < 4; i++) {
-        const double v = 0.5 * gx[i];
-        double sn, cs;
-        sincos(0.5 * k1 * v * v, &sn, &cs);
-        const double c = gw[i] * cos(k0 * v);
-        sx += c * cs;
-        sy += c * sn;
-    }
-    return d2(sx, sy);
-}
-
 struct ES {
     D2 p0, p1, n0, n1;  // exact end points and end normals
     double k0, k1, L;   // curvature params and arc length (px)
@@ -327,7 +319,7 @@ SX_FN V2 evolute_end(const ES& es, bool at_end) {
     // read on reversed ranges, where kappa is not 0)
     D2 p = at_end ? es.p1 : es.p0, n = at_end ? es.n1 : es.n0;
     double kn = es_kn(es, at_end ? 1.0 : 0.0);
-    return f32(p - n * (es.L / kn));
+    return f32(p - n * (es.L * rcp_d(kn)));
 }
 // the rounded end points of the spiral's sides and evolute (see ES)
 SX_FN void es_ends(ES& es, double w) {
@@ -335,8 +327,12 @@ SX_FN void es_ends(ES& es, double w) {
     es.P1A = offs(es.p1, es.n1, w);
     es.P0B = offs(es.p0, es.n0, -w);
     es.P1B = offs(es.p1, es.n1, -w);
-    es.E0 = evolute_end(es, false);
-    es.E1 = evolute_end(es, true);
+    // the evolute's only where rho = 1 + h kappa can be negative
+    es.E0 = es.E1 = v2(0.0f, 0.0f);
+    if (w * fmax(fabs(es_kn(es, 0.0)), fabs(es_kn(es, 1.0))) > 0.999999 * es.L) {
+        es.E0 = evolute_end(es, false);
+        es.E1 = evolute_end(es, true);
+    }
 }
 
 // FP32 copies of an ES for the record pass: p0, chord / Z(1) (or p1 - p0 for
@@ -372,97 +368,95 @@ SX_FN XPT<T> bp_xp(T x) { return XPT<T>{x, absT(x) - T(1)}; }
 // branch of f_approx by |x|: 0 [0,0.8) sin, 1 [0.8,1.25) 1.5-power, 2 [1.25,2.1) and 3 quadratics
 template <class T>
 SX_FN int branch_of(T ax) { return ax < T(0.8) ? 0 : (ax < T(1.25) ? 1 : (ax < T(2.1) ? 2 : 3)); }
-SX_FN double pow15(double a) { return a * sqrt(a); }
+SX_FN double pow15(double a) { return a * sqrt_d(a); }
 SX_FN float pow15f(float a) { return a * sqrtf(a); }
 
 // Divided difference (F(b) - F(a)) / (b - a) of f_approx over one branch,
 // in a cancellation-free form; dx = b - a given precisely.
-template <class T>
-SX_HD inline T branch_dd(int br, XPT<T> a, XPT<T> b, T dx) {
+SX_HD inline double branch_dd(int br, XP a, XP b, double dx) {
     if (br == 0) {
         // cos(c1 m) sin(hz) / hz.  A piece of this branch lies in
         // [-0.8, 0.8], so |c1 m| < 0.88 and |hz| <= 0.8 c1 < 0.88: both by
         // their Taylor series (truncation below 1e-18 relative for |hz| < 1).
-        const T m = T(0.5) * (a.x + b.x);
-        const T hz = T(0.5) * T(kC1) * dx;
-        const T z = T(kC1) * m;
-        const T h2 = hz * hz;
-        const T sc = T(1) + h2 * (T(-1.0 / 6) + h2 * (T(1.0 / 120) + h2 * (T(-1.0 / 5040) + h2 * (T(1.0 / 362880) +
-                     h2 * (T(-1.0 / 39916800) + h2 * (T(1.0 / 6227020800.0) + h2 * (T(-1.0 / 1307674368000.0) +
-                     h2 * (T(1.0 / 355687428096000.0) + h2 * (T(-1.0 / 121645100408832000.0) +
-                     h2 * T(1.0 / 51090942171709440000.0))))))))));
-        const T z2 = z * z;
-        const T cz = T(1) + z2 * (T(-1.0 / 2) + z2 * (T(1.0 / 24) + z2 * (T(-1.0 / 720) + z2 * (T(1.0 / 40320) +
-                     z2 * (T(-1.0 / 3628800) + z2 * (T(1.0 / 479001600.0) + z2 * (T(-1.0 / 87178291200.0) +
-                     z2 * (T(1.0 / 20922789888000.0) + z2 * (T(-1.0 / 6402373705728000.0) +
-                     z2 * T(1.0 / 2432902008176640000.0))))))))));
-        return cz * sc;
+        const double z = (0.5 * kC1) * (a.x + b.x), hz = (0.5 * kC1) * dx;
+        const double h2 = hz * hz, z2 = z * z;
+        double sc = fma(h2, 1.0 / 51090942171709440000.0, -1.0 / 121645100408832000.0);
+        double cz = fma(z2, 1.0 / 2432902008176640000.0, -1.0 / 6402373705728000.0);
+        sc = fma(h2, sc, 1.0 / 355687428096000.0);
+        cz = fma(z2, cz, 1.0 / 20922789888000.0);
+        sc = fma(h2, sc, -1.0 / 1307674368000.0);
+        cz = fma(z2, cz, -1.0 / 87178291200.0);
+        sc = fma(h2, sc, 1.0 / 6227020800.0);
+        cz = fma(z2, cz, 1.0 / 479001600.0);
+        sc = fma(h2, sc, -1.0 / 39916800);
+        cz = fma(z2, cz, -1.0 / 3628800);
+        sc = fma(h2, sc, 1.0 / 362880);
+        cz = fma(z2, cz, 1.0 / 40320);
+        sc = fma(h2, sc, -1.0 / 5040);
+        cz = fma(z2, cz, -1.0 / 720);
+        sc = fma(h2, sc, 1.0 / 120);
+        cz = fma(z2, cz, 1.0 / 24);
+        sc = fma(h2, sc, -1.0 / 6);
+        cz = fma(z2, cz, -1.0 / 2);
+        return fma(z2, cz, 1.0) * fma(h2, sc, 1.0);
     }
     if (br == 1) {
-        const T ea = absT(a.e), eb = absT(b.e);
-        if (a.e * b.e >= T(0)) {
-            const T ra = sqrt(ea), rb = sqrt(eb);
-            const T den = ra + rb;
-            if (den == T(0)) return T(0);
-            return T(kA2) * (ea + ra * rb + eb) / den;
-        }
-        return T(kA2) * (ea * sqrt(ea) + eb * sqrt(eb)) / (ea + eb);
+        const double ea = fabs(a.e), eb = fabs(b.e);
+        const double ra = sqrt_d(ea), rb = sqrt_d(eb);
+        const bool same = a.e * b.e >= 0.0;
+        const double num = same ? fma(ra, rb, ea + eb) : fma(ea, ra, eb * rb);
+        const double den = same ? ra + rb : ea + eb;
+        return den > 0.0 ? kA2 * num * rcp_d(den) : 0.0;
     }
-    const T aa = absT(a.x), ab = absT(b.x);
-    if (br == 2) return T(0.6406) * (aa + ab) - T(0.81);
-    return T(0.5) * (aa + ab) - T(0.156);
+    const double aa = fabs(a.x), ab = fabs(b.x);
+    if (br == 2) return 0.6406 * (aa + ab) - 0.81;
+    return 0.5 * (aa + ab) - 0.156;
 }
 
-// Range of the x axis split at the branch breaks of f_approx.
-template <class T>
-struct XSegT {
-    XPT<T> a;
-    T len;  // signed x length
-    T dF;   // F increment over the piece
-    T G;    // dF / len (the piece's divided difference)
-    int br;
+// The branch breaks of f_approx on the x axis and its increments from the
+// first of them to each (by the divided differences of the pieces between).
+constexpr double kXBreak[6] = {-2.1, -1.25, -0.8, 0.8, 1.25, 2.1};
+struct XTab {
+    double b[6], c[6];
 };
-using XSeg = XSegT<double>;
+SX_HD inline void set_xtab(XTab& t, const double* xinc) {
+    double sum = 0.0;
+    for (int k = 0; k < 6; k++) {
+        t.b[k] = kXBreak[k];
+        t.c[k] = sum;
+        if (k < 5) sum += xinc[k];
+    }
+}
+// the branch of the region between breaks r - 1 and r
+SX_FN int region_branch(int r) { return r < 3 ? 3 - r : r - 3; }
 // Total F increment over [xa, xb], split at the branch breaks of f_approx
 // (each piece within one branch, by its divided difference).  Pieces
-// between two breaks have fixed increments (xinc, see set_break_increments),
-// so at most the two end pieces are evaluated.  *dF0 and *len0 receive the
-// first piece's increment and x length, *xbits the split: breaks crossed
-// (bits 0-2), index of the first one crossed (bits 3-5), walking up the x
-// axis (bit 6).
-constexpr double kXBreak[6] = {-2.1, -1.25, -0.8, 0.8, 1.25, 2.1};
-SX_HD inline double split_x_sum(XP xa, XP xb, double dx_total, const double* xinc, double* dF0, double* len0,
+// between two breaks have fixed increments (the table), so at most the two
+// end pieces are evaluated.  *dF0 and *len0 receive the first piece's
+// increment and x length, *xbits the split: breaks crossed (bits 0-2), index
+// of the first one crossed (bits 3-5), walking up the x axis (bit 6).
+SX_HD inline double split_x_sum(XP xa, XP xb, double dx_total, const XTab& T, double* dF0, double* len0,
                                 uint32_t* xbits) {
     const bool up = xb.x > xa.x;
-    // the breaks strictly between xa and xb are consecutive ones: walk them
-    // from xa, summing the fixed increments between them
-    int n = 0, kf = 0;
-    double bf = 0.0, bl = 0.0, mid = 0.0;
+    const double lo = up ? xa.x : xb.x, hi = up ? xb.x : xa.x;
+    // the breaks strictly between are [k_lo, k_hi)
+    int k_lo = 0, k_hi = 0;
 #pragma unroll
-    for (int kk = 0; kk < 6; kk++) {
-        const double b = up ? kXBreak[kk] : kXBreak[5 - kk];
-        const bool in = up ? (b > xa.x && b < xb.x) : (b < xa.x && b > xb.x);
-        if (in) {
-            if (n == 0) {
-                bf = b;
-                kf = up ? kk : 5 - kk;
-            } else if (kk > 0) {
-                mid += up ? xinc[kk - 1] : -xinc[5 - kk];
-            }
-            bl = b;
-            n++;
-        }
+    for (int k = 0; k < 6; k++) {
+        k_lo += kXBreak[k] <= lo ? 1 : 0;
+        k_hi += kXBreak[k] < hi ? 1 : 0;
     }
-    const bool cross = n > 0;
-    const double l1 = cross ? bf - xa.x : dx_total;
-    const int br1 = cross ? branch_of(fabs(xa.x + 0.5 * l1)) : branch_of(fabs(0.5 * (xa.x + xb.x)));
-    double dF = branch_dd(br1, xa, cross ? bp_xp(bf) : xb, l1) * l1;
+    const int n = k_hi > k_lo ? k_hi - k_lo : 0;
+    const int kf = n == 0 ? 0 : (up ? k_lo : k_hi - 1);
+    const double l1 = n ? T.b[kf] - xa.x : dx_total;
+    double dF = branch_dd(region_branch(up || n == 0 ? k_lo : k_hi), xa, n ? bp_xp(T.b[kf]) : xb, l1) * l1;
     *dF0 = dF;
     *len0 = l1;
-    if (cross) {
-        const double l2 = xb.x - bl;
-        dF += mid;
-        dF += branch_dd(branch_of(fabs(bl + 0.5 * l2)), bp_xp(bl), xb, l2) * l2;
+    if (n) {
+        const int kl = up ? k_hi - 1 : k_lo;
+        const double bl = T.b[kl], l2 = xb.x - bl;
+        dF += T.c[kl] - T.c[kf];
+        dF += branch_dd(region_branch(up ? k_hi : k_lo), bp_xp(bl), xb, l2) * l2;
     }
     *xbits = (uint32_t)n | ((uint32_t)kf << 3) | (up ? 64u : 0u);
     return dF;
@@ -472,9 +466,19 @@ SX_HD inline double split_x_sum(XP xa, XP xb, double dx_total, const double* xin
 SX_HD inline void set_break_increments(double* xinc) {
     for (int k = 0; k < 5; k++) {
         const double a = kXBreak[k], b = kXBreak[k + 1], l = b - a;
-        xinc[k] = branch_dd(branch_of(fabs(a + 0.5 * l)), bp_xp(a), bp_xp(b), l) * l;
+        xinc[k] = branch_dd(region_branch(k + 1), bp_xp(a), bp_xp(b), l) * l;
     }
 }
+
+// One branch piece of a range of the x axis.
+template <class T>
+struct XSegT {
+    XPT<T> a;
+    T len;  // signed x length
+    T dF;   // F increment over the piece
+    T G;    // dF / len (the piece's divided difference)
+    int br;
+};
 
 // Fraction of a branch segment at which F has risen by f * seg.dF
 // (local, cancellation-free inverse of f_approx; FP32 per output point).
@@ -781,67 +785,77 @@ struct RangeRes {
     float dF0, len0, alpha;  // increment and x length of its first branch piece; evolute point split
     uint32_t n, ne, place, xbits;  // xbits: the split at the branch breaks (split_x_sum)
 };
+// A piece's terms that its ranges share: hl = w / L, and isc with the line
+// count of a range I = |dF| isc (general regime: I = |dF| L^2 / (4 |h k1|
+// sqrt|h|) sqrt(1 / (8 tau)), from |dF| / (4 |kappa'| |h|^1.5)).
+struct PieceK {
+    double k0, k1, L, w, hl, isc;
+};
+SX_FN PieceK piece_k(const Cfg& cfg, double k0, double k1, double L, double w) {
+    PieceK p{k0, k1, L, w, 0.0, 0.0};
+    if (!cfg.arcs && k1 != 0.0 && w != 0.0) {
+        const double wk = w * fabs(k1);
+        p.hl = w * rcp_d(L);
+        p.isc = L * L * rcp_d(4.0 * wk) * rsqrt_d(w) * cfg.inv_sqrt8tf;
+    }
+    return p;
+}
 // Newton: the build that can count with the exact integral (cfg.newton);
 // the default build leaves that code out.
 template <bool Newton = true>
-SX_FN RangeRes range_count(const Cfg& cfg, double k0, double k1, double L, double h, double ua, double ub,
+SX_FN RangeRes range_count(const Cfg& cfg, const XTab& T, const PieceK& p, int side, double ua, double ub,
                            bool reversed) {
     RangeRes r;
+    const double k0 = p.k0, k1 = p.k1, L = p.L, h = side ? -p.w : p.w;
     const double du = ub - ua;
-    const double kna = k0 + k1 * (ua - 0.5), knb = k0 + k1 * (ub - 0.5);
+    const double kna = fma(k1, ua - 0.5, k0), knb = fma(k1, ub - 0.5, k0);
     r.dF = 0.0f;
     r.dF0 = 0.0f;
     r.len0 = 0.0f;
     r.place = 0;
     r.xbits = 0;
     if (!cfg.arcs) {
-        double I;
+        double I;  // lines of the range, before rounding up
         if (k1 == 0.0) {
-            I = du * sqrt(fabs(k0) * fabs(L + h * k0));
+            I = k0 != 0.0 ? du * sqrt_d(fabs(k0) * fabs(L + h * k0)) * cfg.inv_sqrt8tf : 0.0;
         } else if (h == 0.0) {
             r.place = kIfPlaceES;
             double aa = fabs(kna), ab = fabs(knb);
-            if (kna * knb >= 0.0) {
-                r.place |= kIfKSame;
-                double den = pow15(aa) + pow15(ab);
-                I = den > 0.0 ? (2.0 / 3.0) * du * sqrt(L) * (aa * aa + aa * ab + ab * ab) / den : 0.0;
-            } else {
-                I = (2.0 / 3.0) * du * sqrt(L) * (pow15(aa) + pow15(ab)) / (aa + ab);
-            }
-        } else if (Newton && cfg.newton) {
-            // the exact integral (counts) and the range's x in FP64 (placement)
-            r.place = kIfNewton;
-            const double hL = h / L;
-            const double xa = -1.0 - 2.0 * (hL * kna), xb = -1.0 - 2.0 * (hL * knb);
-            const double dx = -2.0 * hL * k1 * du;
-            const double D = dens_int_d(xa, xb);
-            uint64_t xw;
-            memcpy(&xw, &xa, 8);
-            r.len0 = bits_f((uint32_t)xw);
-            r.dF0 = bits_f((uint32_t)(xw >> 32));
-            r.dF = (float)dx;
-            I = (dx != 0.0) ? fabs(D) * L * L / (4.0 * fabs(h * k1) * sqrt(fabs(h))) : 0.0;
+            const double pa = pow15(aa), pb = pow15(ab);
+            const bool same = kna * knb >= 0.0;
+            if (same) r.place |= kIfKSame;
+            const double num = same ? fma(aa, aa, fma(aa, ab, ab * ab)) : pa + pb, den = same ? pa + pb : aa + ab;
+            I = den > 0.0 ? (2.0 / 3.0) * du * sqrt_d(L) * num * rcp_d(den) * cfg.inv_sqrt8tf : 0.0;
         } else {
-            r.place = kIfPlaceF;
-            const double hL = h / L;
-            const double hka = hL * kna, hkb = hL * knb;
+            const double hL = side ? -p.hl : p.hl;
             const double dx = -2.0 * hL * k1 * du;
-            double d0, l0;
-            const double dF = split_x_sum(make_xp(hka), make_xp(hkb), dx, cfg.xinc, &d0, &l0, &r.xbits);
-            r.dF = (float)dF;
-            r.dF0 = (float)d0;
-            r.len0 = (float)l0;
-            // I = |dF| / (4 |kappa'| |h|^1.5) = |dF/dx| L_r / (2 sqrt|h|)
-            // (dx = -2 h k1 du / L, so |dF/dx| du L = |dF| L^2 / (2 |h k1|))
-            I = (dx != 0.0) ? fabs(dF) * L * L / (4.0 * fabs(h * k1) * sqrt(fabs(h))) : 0.0;
+            if (Newton && cfg.newton) {
+                // the exact integral (counts) and the range's x in FP64 (placement)
+                r.place = kIfNewton;
+                const double xa = -1.0 - 2.0 * (hL * kna), xb = -1.0 - 2.0 * (hL * knb);
+                const double D = dens_int_d(xa, xb);
+                uint64_t xw;
+                memcpy(&xw, &xa, 8);
+                r.len0 = bits_f((uint32_t)xw);
+                r.dF0 = bits_f((uint32_t)(xw >> 32));
+                r.dF = (float)dx;
+                I = (dx != 0.0) ? fabs(D) * p.isc : 0.0;
+            } else {
+                r.place = kIfPlaceF;
+                double d0, l0;
+                const double dF = split_x_sum(make_xp(hL * kna), make_xp(hL * knb), dx, T, &d0, &l0, &r.xbits);
+                r.dF = (float)dF;
+                r.dF0 = (float)d0;
+                r.len0 = (float)l0;
+                I = (dx != 0.0) ? fabs(dF) * p.isc : 0.0;
+            }
         }
-        r.n = ceil_count(I * cfg.inv_sqrt8tf);
+        r.n = ceil_count(I);
     } else {
         double n_est = 0.0;
         if (k1 != 0.0) {
-            double Lr = du * L;
-            double kp = k1 / (L * L);
-            n_est = Lr * cbrt(fabs(kp) * (1.0 + 0.4 * fabs(h * Lr * kp))) * cfg.cbrt_inv120tf;
+            const double Lr = du * L, rL = rcp_d(L), kp = fabs(k1) * rL * rL;
+            n_est = Lr * cbrt_d(kp * fma(0.4, fabs(h) * Lr * kp, 1.0)) * cfg.cbrt_inv120tf;
         }
         r.n = ceil_count(n_est);
         double sweep = fmax(fabs(kna), fabs(knb)) * du * (1.0 / kHalfPi);
@@ -852,10 +866,11 @@ SX_FN RangeRes range_count(const Cfg& cfg, double k0, double k1, double L, doubl
     r.alpha = 0.5f;
     if (reversed) {
         // evolute: density |s - s0|^-1/2 (Section 6); lines in both modes
-        const double ra = sqrt(fabs(kna)), rb = sqrt(fabs(knb));
-        double Iev = (k1 != 0.0 && ra + rb > 0.0) ? 2.0 * du * sqrt(fabs(k1) * L) / (ra + rb) : 0.0;
+        const double ra = sqrt_d(fabs(kna)), rb = sqrt_d(fabs(knb)), sum = ra + rb;
+        const double inv = sum > 0.0 ? rcp_d(sum) : 0.0;
+        double Iev = 2.0 * du * sqrt_d(fabs(k1) * L) * inv;
         r.ne = ceil_count(Iev * cfg.inv_sqrt8tf);
-        if (ra + rb > 0.0) r.alpha = (float)(ra / (ra + rb));
+        if (sum > 0.0) r.alpha = (float)(ra * inv);
     }
     return r;
 }
@@ -896,13 +911,6 @@ SX_FN void range_put(Sink& k, const Cfg& cfg, const ES& es, double h, double ua,
     }
 }
 
-template <class Sink>
-SX_FN void emit_range(Sink& k, const Cfg& cfg, const ES& es, double h, double ua, double ub, bool reversed,
-                      bool end_a_piece, bool end_b_piece, V2 Pa, V2 Pb) {
-    range_put(k, cfg, es, h, ua, ub, reversed, end_a_piece, end_b_piece, Pa, Pb,
-              range_count(cfg, es.k0, es.k1, es.L, h, ua, ub, reversed));
-}
-
 // One side (h = +w for side 0, -w for side 1) of a piece: rho = 1 + h kappa
 // changes sign at most once along it (kappa is linear in u), splitting the
 // side at the parallel-curve cusp tc into two ranges (reading G9).
@@ -918,7 +926,7 @@ SX_FN SideGeo side_geo(const ES& es, double w, int side) {
     g.P0 = side == 0 ? es.P0A : es.P0B;
     g.P1 = side == 0 ? es.P1A : es.P1B;
     g.split = r0 * r1 < 0.0;
-    g.tc = g.split ? r0 / (r0 - r1) : 1.0;
+    g.tc = g.split ? r0 * rcp_d(r0 - r1) : 1.0;
     g.Pc = g.split ? offset_point_f(es, (float)g.h, (float)g.tc) : g.P1;
     g.rev1 = g.split ? r0 < 0.0 : (r0 < 0.0 || r1 < 0.0);
     g.rev2 = r1 < 0.0;
@@ -927,21 +935,27 @@ SX_FN SideGeo side_geo(const ES& es, double w, int side) {
 
 template <class Sink>
 SX_FN void emit_sides(Sink& k, const Cfg& cfg, const ES& es, double w, bool fill) {
+    XTab T;
+    set_xtab(T, cfg.xinc);
+    const PieceK p = piece_k(cfg, es.k0, es.k1, es.L, w);
     for (int side = 0; side < (fill ? 1 : 2); side++) {
         const SideGeo g = side_geo(es, w, side);
-        emit_range(k, cfg, es, g.h, 0.0, g.tc, g.rev1, true, !g.split, g.P0, g.Pc);
-        if (g.split) emit_range(k, cfg, es, g.h, g.tc, 1.0, g.rev2, false, true, g.Pc, g.P1);
+        range_put(k, cfg, es, g.h, 0.0, g.tc, g.rev1, true, !g.split, g.P0, g.Pc,
+                  range_count(cfg, T, p, side, 0.0, g.tc, g.rev1));
+        if (g.split)
+            range_put(k, cfg, es, g.h, g.tc, 1.0, g.rev2, false, true, g.Pc, g.P1,
+                      range_count(cfg, T, p, side, g.tc, 1.0, g.rev2));
     }
 }
 
 // ----------------------------------------------------- joins and caps
+// 2 acos(1 - tau_flat / w), from 1 - c without cancellation
 SX_FN double round_step(double w, double tau_flat) {
-    double c = 1.0 - tau_flat / w;
-    c = fmin(fmax(c, -1.0), 1.0);
-    return 2.0 * acos(c);
+    const double v = w > 0.0 ? fmin(tau_flat * rcp_d(w), 2.0) : 2.0, c = 1.0 - v;
+    return 2.0 * unit_angle(sqrt_d(v * (2.0 - v)), c, rcp_d(1.0 + fabs(c)));
 }
 SX_FN uint32_t round_count(const Cfg& cfg, double w, double sweep) {
-    return cfg.arcs ? ceil_count(fabs(sweep) * (1.0 / kHalfPi)) : ceil_count(fabs(sweep) / round_step(w, cfg.tau_flat));
+    return cfg.arcs ? ceil_count(fabs(sweep) * (1.0 / kHalfPi)) : ceil_count(fabs(sweep) * rcp_d(round_step(w, cfg.tau_flat)));
 }
 SX_FN uint32_t inner_count(uint32_t inner) { return inner == kInPivot ? 2u : (inner == kInSmooth ? 1u : 0u); }
 SX_FN uint32_t outer_count(uint32_t outer, uint32_t n_round) {
@@ -1007,7 +1021,7 @@ SX_HD void emit_join(Sink& k, const Cfg& cfg, int join, double miter_limit, D2 p
     jp.fx = fi.x; jp.fy = fi.y; jp.px = fp.x; jp.py = fp.y; jp.tx = ti.x; jp.ty = ti.y;
     uint32_t outer = kOutLine1;
     if (join == kJoinRound) {
-        double dphi = atan2(cr, dp);  // FP64: it decides the count
+        double dphi = unit_angle(cr, dp, rcp_d(1.0 + fabs(dp)));  // FP64: it decides the count
         jp.a0 = atan2f((float)(from.y - p.y), (float)(from.x - p.x));
         jp.sweep = (float)fabs(dphi); jp.w = (float)w;
         jp.n_outer = round_count(cfg, w, fabs(dphi));
@@ -1015,7 +1029,7 @@ SX_HD void emit_join(Sink& k, const Cfg& cfg, int join, double miter_limit, D2 p
     } else if (join == kJoinMiter) {
         double crit = miter_limit * miter_limit * (1.0 + dp);
         if (crit >= 2.0) {
-            V2 M = offs(p, Na + Nb, h_out / (1.0 + dp));
+            V2 M = offs(p, Na + Nb, h_out * rcp_d(1.0 + dp));
             jp.ax = M.x; jp.ay = M.y;
             outer = kOutLine2;
         }
@@ -1367,52 +1381,61 @@ SX_HD inline void emit_item(const uint32_t* it, const float* es_rec, const XIncF
 struct Seg {
     D2 P0w, P3w;      // world end points (bit-identical with the neighbours')
     D2 D1, D2_, D3;   // world offsets of the elevated control points from P0w
-    D2 A2, B2, C3;    // D2 - 2 D1, D3 - 2 D2 + D1, D3 - 3 D2 + 3 D1
+    D2 A2, C3;        // D2 - 2 D1, D3 - 3 D2 + 3 D1
     D2 ts, te;        // end tangents (transformed raw differences)
-    double w, lpoly;
+    double w;
     bool fill;        // one side at offset 0 (the path itself)
 };
 
-struct Tan {
-    D2 dir;
-    double mag;
-};
-
-// B(t) - P0
-SX_FN D2 cubic_rel(const Seg& s, double t) {
-    double mt = 1.0 - t;
-    double b = 3.0 * mt * mt * t, c = 3.0 * mt * t * t, d = t * t * t;
-    return d2(b * s.D1.x + c * s.D2_.x + d * s.D3.x, b * s.D1.y + c * s.D2_.y + d * s.D3.y);
-}
+// B(t) = P0 + t (3 D1 + t (3 A2 + t C3))
 SX_FN D2 cubic_world(const Seg& s, double t) {
     if (t == 0.0) return s.P0w;
     if (t == 1.0) return s.P3w;
-    return s.P0w + cubic_rel(s, t);
+    return d2(fma(t, fma(t, fma(t, s.C3.x, 3.0 * s.A2.x), 3.0 * s.D1.x), s.P0w.x),
+              fma(t, fma(t, fma(t, s.C3.y, 3.0 * s.A2.y), 3.0 * s.D1.y), s.P0w.y));
 }
-// q = B'/3
-SX_FN D2 cubic_q(const Seg& s, double t) {
-    double mt = 1.0 - t;
-    D2 a = s.D1, b = s.D2_ - s.D1, c = s.D3 - s.D2_;
-    double wa = mt * mt, wb = 2.0 * t * mt, wc = t * t;
-    return d2(wa * a.x + wb * b.x + wc * c.x, wa * a.y + wb * b.y + wc * c.y);
+// q = B'/3 = D1 + t (2 A2 + t C3)
+SX_FN D2 cubic_q(D2 D1, D2 A2, D2 C3, double t) {
+    return d2(fma(t, fma(t, C3.x, 2.0 * A2.x), D1.x), fma(t, fma(t, C3.y, 2.0 * A2.y), D1.y));
 }
-// B(t0 + dt) - B(t0) by the (terminating) Taylor expansion of the cubic
-SX_FN D2 cubic_chord(const Seg& s, double t0, double dt, D2 q0) {
-    double mt = 1.0 - t0;
-    D2 b2 = d2(mt * s.A2.x + t0 * s.B2.x, mt * s.A2.y + t0 * s.B2.y);
-    double e1 = 3.0 * dt, e2 = 3.0 * dt * dt, e3 = dt * dt * dt;
-    return d2(e1 * q0.x + e2 * b2.x + e3 * s.C3.x, e1 * q0.y + e2 * b2.y + e3 * s.C3.y);
+// B(t0 + dt) - B(t0) = dt (3 q0 + dt (3 (A2 + t0 C3) + dt C3)), q0 = q(t0)
+SX_FN D2 cubic_chord(D2 A2, D2 C3, double t0, double dt, D2 q0) {
+    const D2 h = d2(fma(dt, C3.x, 3.0 * fma(t0, C3.x, A2.x)), fma(dt, C3.y, 3.0 * fma(t0, C3.y, A2.y)));
+    return d2(dt * fma(dt, h.x, 3.0 * q0.x), dt * fma(dt, h.y, 3.0 * q0.y));
 }
-SX_FN Tan sample_q(const Seg& s, double t) {
-    if (t == 0.0) return Tan{s.ts, len(s.D1)};
-    if (t == 1.0) return Tan{s.te, len(s.D3 - s.D2_)};
-    D2 q = cubic_q(s, t);
-    double ql = len(q);
-    if (ql < kEpsQ * s.lpoly) {
-        q = cubic_q(s, (t + kDeltaT < 1.0) ? t + kDeltaT : t - kDeltaT);
-        ql = len(q);
+// length of the control polygon
+SX_FN double poly_len(const Seg& s) { return len(s.D1) + len(s.D2_ - s.D1) + len(s.D3 - s.D2_); }
+// The unit tangent at t (Section 7.3: a near-zero q at an interior t is
+// replaced by a sample beside it; the polygon's length, three square roots,
+// is needed only below its bound by coordinate sums).
+SX_FN D2 unit_tan(const Seg& s, double t, D2 q) {
+    if (t == 0.0) return unit(s.ts);
+    if (t == 1.0) return unit(s.te);
+    const D2 e = s.D2_ - s.D1, f = s.D3 - s.D2_;
+    const double sum = fabs(s.D1.x) + fabs(s.D1.y) + fabs(e.x) + fabs(e.y) + fabs(f.x) + fabs(f.y);
+    const double ss = dot(q, q), most = kEpsQ * sum;
+    if (!(ss >= most * most)) {
+        const double eps = kEpsQ * poly_len(s);
+        if (!(ss >= eps * eps)) q = cubic_q(s.D1, s.A2, s.C3, (t + kDeltaT < 1.0) ? t + kDeltaT : t - kDeltaT);
     }
-    return Tan{q, ql};
+    return unit(q);
+}
+
+// q at t in Bernstein form, with Section 7.3's replacement: the tangents that
+// a pivot turns between.  At an exact reversal the turn is pi either way and
+// its sign is that of a cross product of two opposite vectors, rounding
+// alone; this is the form whose rounding the oracle shares.
+SX_FN D2 pivot_tan(const Seg& s, double t) {
+    if (t == 0.0) return s.ts;
+    if (t == 1.0) return s.te;
+    const D2 a = s.D1, b = s.D2_ - s.D1, c = s.D3 - s.D2_;
+    auto at = [&](double x) {
+        const double mt = 1.0 - x, wa = mt * mt, wb = 2.0 * x * mt, wc = x * x;
+        return d2(wa * a.x + wb * b.x + wc * c.x, wa * a.y + wb * b.y + wc * c.y);
+    };
+    D2 q = at(t);
+    if (len(q) < kEpsQ * poly_len(s)) q = at((t + kDeltaT < 1.0) ? t + kDeltaT : t - kDeltaT);
+    return q;
 }
 
 // ------------------------------------------------------ segment fetch
@@ -1490,7 +1513,7 @@ SX_HD inline void fetch_tag(const SceneView& sv, uint32_t i, TagInfo& ti, Seg& s
     const uint32_t xfi = sv.mon[3 * (size_t)sv.mon_stride + i];
     const StyleD st = sv.styles[sty];
     const float* X = sv.xforms + 6 * (size_t)xfi;
-    const double scale = sqrt(fabs((double)X[0] * X[3] - (double)X[1] * X[2]));
+    const double scale = sqrt_d(fabs((double)X[0] * X[3] - (double)X[1] * X[2]));
     ti.tag = tag;
     ti.off = off;
     ti.X = X;
@@ -1529,7 +1552,6 @@ SX_HD inline void fetch_tag(const SceneView& sv, uint32_t i, TagInfo& ti, Seg& s
         s.D3 = e2;
     }
     s.A2 = s.D2_ - s.D1 * 2.0;
-    s.B2 = s.D3 - s.D2_ * 2.0 + s.D1;
     s.C3 = s.D3 - s.D2_ * 3.0 + s.D1 * 3.0;
     // end tangents: the first nonzero difference from each end (r_c - r_{c-1-j})
     const float2 q0 = (c == 1) ? r0 : ((c == 2) ? r1 : r2);  // r_{c-1}
@@ -1540,7 +1562,6 @@ SX_HD inline void fetch_tag(const SceneView& sv, uint32_t i, TagInfo& ti, Seg& s
     const D2 one = d2(1.0, 0.0);
     s.ts = !is_zero(e0) ? e0 : (c >= 2 && !is_zero(e1)) ? e1 : (c >= 3 && !is_zero(e2)) ? e2 : one;
     s.te = !is_zero(ce0) ? ce0 : (c >= 2 && !is_zero(ce1)) ? ce1 : (c >= 3 && !is_zero(ce2)) ? ce2 : one;
-    s.lpoly = len(s.D1) + len(s.D2_ - s.D1) + len(s.D3 - s.D2_);
 }
 
 // ------------------------------------------- Algorithm 2: the bisection
@@ -1555,11 +1576,9 @@ struct NodeSeg {
     double m1, w, eps;
 };
 SX_FN NodeSeg node_seg(const Seg& s) {
-    return NodeSeg{s.D1, s.A2, s.C3, unit(s.ts), unit(s.te), len(s.D3 - s.D2_), s.w, kEpsQ * s.lpoly};
+    return NodeSeg{s.D1, s.A2, s.C3, unit(s.ts), unit(s.te), len(s.D3 - s.D2_), s.w, kEpsQ * poly_len(s)};
 }
-SX_FN D2 node_q(const NodeSeg& n, double t) {
-    return d2(fma(t, fma(t, n.C3.x, 2.0 * n.A2.x), n.D1.x), fma(t, fma(t, n.C3.y, 2.0 * n.A2.y), n.D1.y));
-}
+SX_FN D2 node_q(const NodeSeg& n, double t) { return cubic_q(n.D1, n.A2, n.C3, t); }
 SX_FN double depth_dt(uint32_t depth) { return ldexp(1.0, -(int)depth); }  // 2^-depth, exact
 // unit direction (zero for a zero vector) and magnitude of the tangent
 // sample q at an interior t; a near-zero q is replaced by a sample beside it
@@ -1584,15 +1603,12 @@ SX_HD inline bool node_accepted(const NodeSeg& n, const Cfg& cfg, uint32_t t0_u,
     D2 u0 = n.us, u1 = n.ue;
     double m0, m1 = n.m1;
     if (t0_u == 0u) {
-        const double ss = dot(q0, q0);
-        m0 = ss > 0.0 ? ss * rsqrt_d(ss) : 0.0;
+        m0 = len(q0);
     } else {
         m0 = node_tan(n, t0, q0, u0);
     }
     if (t1 != 1.0) m1 = node_tan(n, t1, node_q(n, t1), u1);
-    // B(t0 + dt) - B(t0) = dt (3 q0 + dt (3 (A2 + t0 C3) + dt C3))
-    const D2 h = d2(fma(dt, n.C3.x, 3.0 * fma(t0, n.C3.x, n.A2.x)), fma(dt, n.C3.y, 3.0 * fma(t0, n.C3.y, n.A2.y)));
-    const D2 chord = d2(dt * fma(dt, h.x, 3.0 * q0.x), dt * fma(dt, h.y, 3.0 * q0.y));
+    const D2 chord = cubic_chord(n.A2, n.C3, t0, dt, q0);
     const double cc = dot(chord, chord);
     if (!(cc > 0.0)) return false;
     const double rcl = rsqrt_d(cc), cl = cc * rcl;
@@ -1664,22 +1680,17 @@ SX_HD void piece_es(Sink& k, const Cfg& cfg, const Seg& s, bool line, uint32_t t
     const double dt = depth_dt(depth);
     const double t0 = (double)t0_u * dt;
     const double t1 = t0 + dt;
-    const Tan last_q = sample_q(s, t0);
-    const D2 last_qtrue = (t0 == 0.0) ? s.D1 : cubic_q(s, t0);
-    const Tan next_q = line ? last_q : sample_q(s, t1);
-    const D2 chord = line ? s.D3 : cubic_chord(s, t0, dt, last_qtrue);
-    const double cl = len(chord);
-    double th0 = 0.0, th1 = 0.0;
-    if (!line && !pivot) {
-        th0 = atan2(cross(last_q.dir, chord), dot(last_q.dir, chord));
-        th1 = atan2(cross(chord, next_q.dir), dot(chord, next_q.dir));
-    }
+    const D2 q0 = line ? s.D1 : cubic_q(s.D1, s.A2, s.C3, t0);
+    const D2 u0 = unit_tan(s, t0, q0);
+    const D2 u1 = line ? u0 : unit_tan(s, t1, cubic_q(s.D1, s.A2, s.C3, t1));
+    const D2 chord = line ? s.D3 : cubic_chord(s.A2, s.C3, t0, dt, q0);
+    const double cc = dot(chord, chord), rcl = cc > 0.0 ? rsqrt_d(cc) : 0.0, cl = cc * rcl;
     if constexpr (Sink::kStats) k.st[kStPieces]++;
     es.pivot = pivot;
     es.p0 = cubic_world(s, t0);
     es.p1 = cubic_world(s, t1);
-    es.n0 = rnormal(unit(last_q.dir));
-    es.n1 = rnormal(unit(next_q.dir));
+    es.n0 = rnormal(u0);
+    es.n1 = rnormal(u1);
     double c, base;
     D2 rot = d2(0.0, 0.0);
     if (line) {
@@ -1689,11 +1700,17 @@ SX_HD void piece_es(Sink& k, const Cfg& cfg, const Seg& s, bool line, uint32_t t
         rot = chord;
         base = atan2(rot.y, rot.x);
     } else if (pivot) {
-        es.k0 = atan2(cross(last_q.dir, next_q.dir), dot(last_q.dir, next_q.dir));
+        const D2 a = pivot_tan(s, t0), b = pivot_tan(s, t1);
+        es.k0 = atan2(cross(a, b), dot(a, b));
         es.k1 = 0.0;
         c = es_chord(0.5 * es.k0, 0.5 * es.k0);
-        base = atan2(last_q.dir.y, last_q.dir.x) + 0.5 * es.k0;
+        base = atan2(a.y, a.x) + 0.5 * es.k0;
     } else {
+        // the end angles between the tangents and the chord
+        const double sn0 = cross(u0, chord) * rcl, sn1 = cross(chord, u1) * rcl;
+        const double c0 = dot(u0, chord) * rcl, c1 = dot(chord, u1) * rcl;
+        const double e0 = 1.0 + fabs(c0), e1 = 1.0 + fabs(c1), r = rcp_d(e0 * e1);
+        const double th0 = unit_angle(sn0, c0, r * e1), th1 = unit_angle(sn1, c1, r * e0);
         es.k0 = th0 + th1;
         es.k1 = es_k1(th0, th1);
         c = es_chord(th0, th1);
@@ -1706,7 +1723,7 @@ SX_HD void piece_es(Sink& k, const Cfg& cfg, const Seg& s, bool line, uint32_t t
         base = (double)atan2f(fr.y, fr.x);
     }
     if (!(c > kCMin)) c = kCMin;
-    es.L = cl / c;
+    es.L = cl * rcp_d(c);
     es.fp0 = f32(es.p0);
     es.fd = f32(es.p1 - es.p0);
     es.frot = f32(rot);

@@ -783,6 +783,10 @@ __device__ __forceinline__ uint64_t tail_tile(const uint64_t* base, uint32_t i) 
 // (the piece's k0, k1, L, width and cusp go through the wave's part of LDS,
 // so no block barrier is needed), and then each thread writes its piece's
 // items in canonical order.
+// Bound by FP64 issue (about 155 us of the map scene's 279, 1M segments) and by
+// the items' 0.5 GB written after it.  With the library's divisions, square
+// roots and arctangents, separate multiplies and adds in the polynomials, and
+// all six branch breaks walked per range: 362 us.
 template <int MinWaves, bool Stats, bool Newton>
 __global__ __launch_bounds__(kSlotBlock, MinWaves) void slot_kernel(SceneView sv, Cfg cfg, ItemWs ws,
                                                                     const Slot* __restrict__ pcs,
@@ -794,6 +798,7 @@ __global__ __launch_bounds__(kSlotBlock, MinWaves) void slot_kernel(SceneView sv
     __shared__ uint32_t s_hist[kPieceGroup][kSlotBlock / 64][2];
     __shared__ uint32_t s_task[2 * kSlotBlock];     // owner thread << 2 | side << 1 | reversed
     __shared__ double s_own[kSlotBlock][4];        // k0, k1, L, w of the owner's piece
+    __shared__ XTab s_xtab;
     __shared__ double s_tc[kSlotBlock][2];         // cusp u of each side
     __shared__ RangeRes s_res[2 * kSlotBlock];
     __shared__ RangeRes s_first[2][kSlotBlock];    // each side's first range
@@ -808,6 +813,7 @@ __global__ __launch_bounds__(kSlotBlock, MinWaves) void slot_kernel(SceneView sv
     const uint32_t t = threadIdx.x, lane = t & 63u, wv = t >> 6;
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     uint32_t st[kStN] = {0, 0, 0, 0, 0, 0};
+    if (t == 0u) set_xtab(s_xtab, cfg.xinc);  // (read after the first barrier)
     for (uint32_t grp = blockIdx.x; grp < n_groups; grp += gridDim.x) {
         const uint32_t tile0 = grp < n_multi ? grp * kPieceGroup : n_multi * kPieceGroup + (grp - n_multi);
         const uint32_t n_gt = grp < n_multi ? kPieceGroup : 1u;  // tiles of this group
@@ -886,13 +892,14 @@ __global__ __launch_bounds__(kSlotBlock, MinWaves) void slot_kernel(SceneView sv
                     g0 = side_geo(es, sg.w, 0);
                     g1 = side_geo(es, sg.w, 1);
                     g1.split = g1.split && side1;
-                    s_first[0][t] = range_count<Newton>(cfg, es.k0, es.k1, es.L, g0.h, 0.0, g0.tc, g0.rev1);
-                    if (side1) s_first[1][t] = range_count<Newton>(cfg, es.k0, es.k1, es.L, g1.h, 0.0, g1.tc, g1.rev1);
+                    const PieceK pk = piece_k(cfg, es.k0, es.k1, es.L, sg.w);
+                    s_first[0][t] = range_count<Newton>(cfg, s_xtab, pk, 0, 0.0, g0.tc, g0.rev1);
+                    if (side1) s_first[1][t] = range_count<Newton>(cfg, s_xtab, pk, 1, 0.0, g1.tc, g1.rev1);
                     if (g0.split || g1.split) {
-                        s_own[t][0] = es.k0;
-                        s_own[t][1] = es.k1;
-                        s_own[t][2] = es.L;
-                        s_own[t][3] = sg.w;
+                        s_own[t][0] = pk.k0;
+                        s_own[t][1] = pk.k1;
+                        s_own[t][2] = pk.L;
+                        s_own[t][3] = pk.w;
                         s_tc[t][0] = g0.tc;
                         s_tc[t][1] = g1.tc;
                     }
@@ -918,9 +925,8 @@ __global__ __launch_bounds__(kSlotBlock, MinWaves) void slot_kernel(SceneView sv
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             for (uint32_t q = lane; q < n_task; q += 64u) {
                 const uint32_t task = w_task[q], own = task >> 2, side = (task >> 1) & 1u;
-                const double w = s_own[own][3];
-                w_res[q] = range_count<Newton>(cfg, s_own[own][0], s_own[own][1], s_own[own][2], side ? -w : w,
-                                               s_tc[own][side], 1.0, (task & 1u) != 0u);
+                const PieceK pk = piece_k(cfg, s_own[own][0], s_own[own][1], s_own[own][2], s_own[own][3]);
+                w_res[q] = range_count<Newton>(cfg, s_xtab, pk, (int)side, s_tc[own][side], 1.0, (task & 1u) != 0u);
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
