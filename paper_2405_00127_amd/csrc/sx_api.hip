@@ -6,9 +6,11 @@
 #include <cstdio>
 #include <cstddef>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "strokex.h"
@@ -16,12 +18,119 @@
 #include "sx_encode.h"
 #include "sx_kernels.h"
 
+// Device memory of a context's scenes.  Large blocks that a scene gives back
+// are kept for the next one, up to kPoolBytes in kPoolBlocks blocks: a
+// document opened, drawn and closed maps and frees 200 MB otherwise (closing
+// took 0.84 ms at 50,000 segments).  Blocks below kPoolMin cost the runtime
+// almost nothing and are not kept.  A block is given back with the device
+// idle, as hipFree would wait for it, so it has no user on any stream.
+// Shared by the context and its scenes (a scene may be released after its
+// context; nothing is kept then).
+class DevPool {
+   public:
+    explicit DevPool(int device) : device_(device) {}
+    DevPool(const DevPool&) = delete;
+    DevPool& operator=(const DevPool&) = delete;
+    ~DevPool() { close(); }
+    // Waits for the device; false when that failed (a stream being captured).
+    bool idle() {
+        int cur = device_;
+        (void)hipGetDevice(&cur);
+        if (cur != device_ && hipSetDevice(device_) != hipSuccess) return false;
+        const bool ok = hipDeviceSynchronize() == hipSuccess;
+        if (!ok) (void)hipGetLastError();
+        if (cur != device_) (void)hipSetDevice(cur);
+        return ok;
+    }
+    hipError_t take(void** p, size_t bytes) {
+        std::lock_guard<std::mutex> lk(mu_);
+        *p = nullptr;
+        bytes = (std::max<size_t>(bytes, 16) + 255) & ~(size_t)255;
+        if (bytes >= kPoolMin) {
+            // the smallest block that holds it, at most twice its size
+            size_t best = held_.size();
+            for (size_t i = 0; i < held_.size(); i++)
+                if (held_[i].bytes >= bytes && held_[i].bytes / 2 <= bytes &&
+                    (best == held_.size() || held_[i].bytes < held_[best].bytes))
+                    best = i;
+            if (best < held_.size()) {
+                const Blk b = held_[best];
+                held_.erase(held_.begin() + (ptrdiff_t)best);
+                total_ -= b.bytes;
+                out_[b.p] = b.bytes;
+                *p = b.p;
+                return hipSuccess;
+            }
+        }
+        hipError_t e = hipMalloc(p, bytes);
+        if (e == hipErrorOutOfMemory && !held_.empty()) {
+            (void)hipGetLastError();
+            trim(0);
+            e = hipMalloc(p, bytes);
+        }
+        if (e == hipSuccess && bytes >= kPoolMin) out_[*p] = bytes;
+        return e;
+    }
+    // Gives a block back; is_idle: idle() was called and held.
+    void give(void* p, bool is_idle) {
+        if (!p) return;
+        std::lock_guard<std::mutex> lk(mu_);
+        const auto it = out_.find(p);
+        const size_t bytes = it == out_.end() ? 0 : it->second;
+        if (bytes) out_.erase(it);
+        if (bytes && bytes <= kPoolBytes && is_idle && !closed_) {
+            held_.push_back(Blk{p, bytes});
+            total_ += bytes;
+            trim(kPoolBytes);
+        } else {
+            (void)hipFree(p);
+        }
+    }
+    void close() {
+        std::lock_guard<std::mutex> lk(mu_);
+        closed_ = true;
+        trim(0);
+    }
+
+   private:
+    static constexpr size_t kPoolMin = (size_t)256 << 10, kPoolBytes = (size_t)384 << 20, kPoolBlocks = 48;
+    struct Blk {
+        void* p;
+        size_t bytes;
+    };
+    // frees the oldest blocks until at most `most` bytes are held
+    void trim(size_t most) {
+        while (!held_.empty() && (total_ > most || held_.size() > kPoolBlocks)) {
+            (void)hipFree(held_.front().p);
+            total_ -= held_.front().bytes;
+            held_.erase(held_.begin());
+        }
+    }
+    const int device_;
+    std::mutex mu_;
+    std::vector<Blk> held_;                  // oldest first
+    std::unordered_map<void*, size_t> out_;  // large blocks in use
+    size_t total_ = 0;
+    bool closed_ = false;
+};
+
+static void* pinned_get(size_t bytes) {
+    void* p = nullptr;
+    return hipHostMalloc(&p, bytes, hipHostMallocDefault) == hipSuccess ? p : nullptr;
+}
+static void pinned_put(void* p) { (void)hipHostFree(p); }
+// Scenes of up to this many verbs are encoded into the context's pinned
+// buffers (a few MB, kept); larger ones into pageable memory of their own.
+constexpr uint32_t kPinnedVerbs = 1u << 18;
+
 struct sx_ctx {
     int device = 0;
     sx_config cfg = {SX_FIT_OFFSET, SX_DENSITY_APPROX, SX_CONSTANTS_VERSION, 0u};
     std::string err;
     sx_tuning tune = {2u, 16u, 256u, 2u};
-    uint64_t* pinned_total = nullptr;  // host-pinned 2 x u64: record count, status
+    sx::WsCtl* pinned = nullptr;       // host-pinned counters of the last synchronous expansion
+    std::shared_ptr<DevPool> pool;
+    sx::HostEncoding enc{{pinned_get, pinned_put}};  // a scene's host streams while it is encoded (memory reused)
     void* scratch = nullptr;           // device address of `scratch` on this device
 };
 
@@ -33,6 +142,7 @@ struct SoupTerm {
 
 struct sx_scene {
     sx_ctx* ctx = nullptr;
+    std::shared_ptr<DevPool> pool;  // the context's
     uint32_t n_tags = 0, n_pts = 0, n_paths = 0, n_styles = 0, n_xforms = 0;
     // encoded streams
     uint8_t* d_tags = nullptr;
@@ -123,18 +233,15 @@ int hip_fail(sx_ctx* ctx, hipError_t e, const char* what) {
     return fail(ctx, e == hipErrorOutOfMemory ? SX_ENOMEM : SX_EDEVICE, m);
 }
 
-template <class T>
-hipError_t dalloc(T** p, size_t bytes) {
-    return hipMalloc((void**)p, bytes ? bytes : 16);
-}
-template <class T>
-void dfree(T*& p) {
-    if (p) (void)hipFree((void*)p);
-    p = nullptr;
-}
-
+// The scene's large blocks go back to its context's pool: the device is idle
+// then (hipFree would wait for it too).
 void free_scene(sx_scene* s) {
     if (!s) return;
+    const bool idle = s->pool->idle();
+    auto dfree = [&](auto*& p) {
+        s->pool->give((void*)p, idle);
+        p = nullptr;
+    };
     dfree(s->d_tags);
     dfree(s->d_pts);
     dfree(s->d_styles);
@@ -217,6 +324,12 @@ hipError_t size_slots(sx_scene* s, uint64_t slot_cap, uint32_t region_per_piece,
     auto A = [&](hipError_t r) {
         if (e == hipSuccess) e = r;
     };
+    const bool idle = (s->d_slots || s->d_items) && s->pool->idle();  // (a new scene has nothing to give back)
+    auto dfree = [&](auto*& p) {
+        s->pool->give((void*)p, idle);
+        p = nullptr;
+    };
+    auto dalloc = [&](auto** p, size_t bytes) { return s->pool->take((void**)p, bytes); };
     if (slot_cap != s->slot_cap || !s->d_slots) {
         dfree(s->d_slots);
         dfree(s->d_rc);
@@ -230,7 +343,8 @@ hipError_t size_slots(sx_scene* s, uint64_t slot_cap, uint32_t region_per_piece,
         A(dalloc(&s->d_roff, (slot_cap + 1) * sizeof(uint64_t)));
         A(dalloc(&s->d_status_rc, sx::scan_status_bytes((uint32_t)slot_cap)));
         A(dalloc(&s->d_tile_n, (size_t)sx::slot_tiles(slot_cap) * sizeof(uint32_t)));
-        if (e == hipSuccess) A(hipMemsetAsync(s->d_status_rc, 0, sx::scan_status_bytes((uint32_t)slot_cap), st));
+        if (e == hipSuccess)
+            A(sx::launch_zero({{s->d_status_rc, sx::scan_status_bytes((uint32_t)slot_cap)}}, st));
         if (e != hipSuccess) return e;
         s->slot_cap = slot_cap;
     }
@@ -245,36 +359,50 @@ hipError_t size_slots(sx_scene* s, uint64_t slot_cap, uint32_t region_per_piece,
 // contents are rewritten by the caller).  Ordered on st; allocation is
 // synchronous.
 hipError_t reserve_scene(sx_scene* s, uint32_t n_tags, uint32_t n_pts, uint32_t n_styles, uint32_t n_xforms,
-                         uint32_t n_paths, hipStream_t st) {
+                         uint32_t n_paths, hipStream_t st, bool streams_only = false) {
     hipError_t e = hipSuccess;
     auto A = [&](hipError_t r) {
         if (e == hipSuccess) e = r;
     };
+    const bool first = !s->allocated;
+    bool idle = first;  // (nothing to give back)
+    auto dalloc = [&](auto** p, size_t bytes) { return s->pool->take((void**)p, bytes); };
     auto regrow = [&](auto*& p, size_t bytes) {
-        dfree(p);
+        if (!idle) idle = s->pool->idle();
+        s->pool->give((void*)p, idle);
+        p = nullptr;
         A(dalloc(&p, bytes));
     };
-    const bool first = !s->allocated;
     if (first || n_tags > s->cap_tags) {
         const uint32_t c = n_tags;
         const size_t ntag_pad = ((size_t)c + 16 + 15) & ~(size_t)15;
         regrow(s->d_tags, ntag_pad);
         regrow(s->d_mon, 4 * (size_t)sx::mon_stride_of(c) * sizeof(uint32_t));
-        regrow(s->d_nslots, ((size_t)c + 16) * sizeof(uint32_t));
+        regrow(s->d_status_tags, sx::scan_status_bytes(c));
+        if (!streams_only) regrow(s->d_nslots, ((size_t)c + 16) * sizeof(uint32_t));
         // kept piece codes: n x keep_codes_of(n) words for any n <= c (at
         // most 2^25, or kKeepCodes per tag)
-        regrow(s->d_codes, std::min<size_t>(std::max<size_t>((size_t)1 << 25, (size_t)c * sx::kKeepCodes),
-                                            (size_t)c * 1024) * sizeof(uint32_t));
-        regrow(s->d_base, ((size_t)c + 1) * sizeof(uint64_t));
-        regrow(s->d_status_tags, sx::scan_status_bytes(c));
-        regrow(s->d_status_nslots, sx::scan_status_bytes(c));
+        if (!streams_only) {
+            regrow(s->d_codes, std::min<size_t>(std::max<size_t>((size_t)1 << 25, (size_t)c * sx::kKeepCodes),
+                                                (size_t)c * 1024) * sizeof(uint32_t));
+            regrow(s->d_base, ((size_t)c + 1) * sizeof(uint64_t));
+            regrow(s->d_status_nslots, sx::scan_status_bytes(c));
+        }
+        if (first) {
+            A(dalloc(&s->d_scan_ctl, 3 * sx::scan_ctl_bytes()));
+            A(dalloc(&s->d_ws_ctl, sizeof(sx::WsCtl)));
+        }
         if (e != hipSuccess) return e;
         s->cap_tags = c;
-        A(hipMemsetAsync(s->d_tags, 0, ntag_pad, st));
-        A(hipMemsetAsync(s->d_status_tags, 0, sx::scan_status_bytes(c), st));
-        A(hipMemsetAsync(s->d_status_nslots, 0, sx::scan_status_bytes(c), st));
+        // the tag padding, the scans' status words (epoch 0: not ready) and counters
+        A(sx::launch_zero({{s->d_tags, ntag_pad},
+                           {s->d_status_tags, sx::scan_status_bytes(c)},
+                           {s->d_status_nslots, streams_only ? 0 : sx::scan_status_bytes(c)},
+                           {s->d_scan_ctl, first ? 3 * sx::scan_ctl_bytes() : 0},
+                           {s->d_ws_ctl, first ? sizeof(sx::WsCtl) : 0}},
+                          st));
         const uint64_t want = std::max<uint64_t>((uint64_t)c * kSlotsPerTag, kMinSlots);
-        if (want > s->slot_cap) {
+        if (!streams_only && want > s->slot_cap) {
             const uint32_t region = s->region_per_piece ? s->region_per_piece : kRegionPerPiece;
             A(size_slots(s, std::min<uint64_t>(want, kMaxSlotCap), region,
                          std::max<uint64_t>(std::max<uint64_t>(want, s->ovf_cap), kMinOverflow), st));
@@ -295,12 +423,6 @@ hipError_t reserve_scene(sx_scene* s, uint32_t n_tags, uint32_t n_pts, uint32_t 
     if (first || n_paths > s->cap_paths) {
         regrow(s->d_path_map, (size_t)n_paths * sizeof(uint32_t));
         s->cap_paths = n_paths;
-    }
-    if (first) {
-        A(dalloc(&s->d_scan_ctl, 3 * sx::scan_ctl_bytes()));
-        A(dalloc(&s->d_ws_ctl, sizeof(sx::WsCtl)));
-        A(hipMemsetAsync(s->d_scan_ctl, 0, 3 * sx::scan_ctl_bytes(), st));
-        A(hipMemsetAsync(s->d_ws_ctl, 0, sizeof(sx::WsCtl), st));
     }
     if (e == hipSuccess) s->allocated = true;
     return e;
@@ -389,10 +511,10 @@ int run_sized(sx_ctx* ctx, sx_scene* s, const sx::Cfg& cfg, void* out, uint64_t 
         uint64_t* dst = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(s->d_ws_ctl) + offsetof(sx::WsCtl, result));
         int r = run_all(ctx, s, cfg, out, cap_records, dst, st);
         if (r != SX_OK) return r;
-        sx::WsCtl w;
-        hipError_t e = hipMemcpyAsync(&w, s->d_ws_ctl, sizeof(w), hipMemcpyDeviceToHost, st);
+        hipError_t e = hipMemcpyAsync(ctx->pinned, s->d_ws_ctl, sizeof(sx::WsCtl), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return hip_fail(ctx, e, "count readback");
+        const sx::WsCtl w = *ctx->pinned;
         *n_records = w.result[0];
         if (w.result[1] == 0) return SX_OK;
         if (w.slots_total > s->slot_cap) {
@@ -433,8 +555,9 @@ int sx_ctx_create(int device, const sx_config* cfg, sx_ctx** out) {
     if (!c) return SX_ENOMEM;
     c->device = device;
     c->cfg = conf;
+    c->pool = std::make_shared<DevPool>(device);
     if (hipSetDevice(device) != hipSuccess) { delete c; return SX_EDEVICE; }
-    if (hipHostMalloc((void**)&c->pinned_total, 2 * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void**)&c->pinned, sizeof(sx::WsCtl), hipHostMallocDefault) != hipSuccess) {
         delete c;
         return SX_ENOMEM;
     }
@@ -446,7 +569,8 @@ int sx_ctx_create(int device, const sx_config* cfg, sx_ctx** out) {
 
 int sx_ctx_destroy(sx_ctx* ctx) {
     if (!ctx) return SX_OK;
-    if (ctx->pinned_total) (void)hipHostFree(ctx->pinned_total);
+    if (ctx->pinned) (void)hipHostFree(ctx->pinned);
+    ctx->pool->close();
     delete ctx;
     return SX_OK;
 }
@@ -490,6 +614,8 @@ enum { kEstCurve = 1, kEstLine = 2, kEstMarker = 4, kEstFill = 8, kEstRound = 16
 static void soup_terms(const sx::HostEncoding& enc, const sx_style* styles, const sx_affine* xforms,
                        std::vector<SoupTerm>& est) {
     const size_t n = enc.tags.size();
+    // (squares of FP32 values stay in range: no need of hypot's scaling)
+    auto norm = [](double x, double y) { return std::sqrt(x * x + y * y); };
     est.assign(n, SoupTerm{});
     uint32_t off = 0;
     int sty = -1, xfi = -1;
@@ -521,9 +647,9 @@ static void soup_terms(const sx::HostEncoding& enc, const sx_style* styles, cons
             }
             double M = 0.0;
             for (uint32_t j = 0; j + 2 <= c; j++)
-                M = std::max(M, std::hypot(px[j + 2] - 2.0 * px[j + 1] + px[j], py[j + 2] - 2.0 * py[j + 1] + py[j]));
+                M = std::max(M, norm(px[j + 2] - 2.0 * px[j + 1] + px[j], py[j + 2] - 2.0 * py[j + 1] + py[j]));
             const double dd = (double)(c * (c - 1));
-            const double ch = std::hypot(px[c] - px[0], py[c] - py[0]);
+            const double ch = norm(px[c] - px[0], py[c] - py[0]);
             a = std::sqrt(dd * M / 8.0);
             b = std::sqrt(1.0 + (ch > 0.0 ? w * dd * M / (ch * ch) : 0.0));
         }
@@ -534,7 +660,7 @@ static void soup_terms(const sx::HostEncoding& enc, const sx_style* styles, cons
 
 static int encode_impl(sx_ctx* ctx, const sx_paths* paths, const sx_style* styles, uint32_t n_styles,
                        const sx_affine* xforms, uint32_t n_xforms, void* stream, sx_scene** out,
-                       std::vector<uint32_t>* style_stream) {
+                       std::vector<uint32_t>* style_stream, bool streams_only = false) {
     if (!ctx || !out) return SX_EINVAL;
     *out = nullptr;
     if (!paths || (paths->n_paths && (!paths->verbs || !paths->verb_off || !paths->pts || !paths->pt_off ||
@@ -542,9 +668,14 @@ static int encode_impl(sx_ctx* ctx, const sx_paths* paths, const sx_style* style
         return fail(ctx, SX_EINVAL, "null path arrays");
     if ((n_styles && !styles) || (n_xforms && !xforms)) return fail(ctx, SX_EINVAL, "null style/transform table");
     if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, SX_EDEVICE, "hipSetDevice");
-    sx::HostEncoding enc;
+    sx::HostEncoding own;
+    sx::HostEncoding& enc = paths->n_paths && paths->verb_off[paths->n_paths] > kPinnedVerbs ? own : ctx->enc;
     std::string err;
-    if (!sx::encode_paths(*paths, styles, n_styles, n_xforms, enc, err)) return fail(ctx, SX_EINVAL, err);
+    try {
+        if (!sx::encode_paths(*paths, styles, n_styles, n_xforms, enc, err)) return fail(ctx, SX_EINVAL, err);
+    } catch (const std::bad_alloc&) {
+        return fail(ctx, SX_ENOMEM, "host encoding");
+    }
     // validate the styles and transforms that are actually used
     std::vector<sx::StyleD> sd(enc.style_stream.size());
     for (size_t i = 0; i < enc.style_stream.size(); i++) {
@@ -581,13 +712,14 @@ static int encode_impl(sx_ctx* ctx, const sx_paths* paths, const sx_style* style
     sx_scene* s = new (std::nothrow) sx_scene();
     if (!s) return fail(ctx, SX_ENOMEM, "scene alloc");
     s->ctx = ctx;
+    s->pool = ctx->pool;
     s->n_tags = (uint32_t)enc.tags.size();
     s->n_pts = (uint32_t)(enc.data.size() / 2);
     s->n_paths = (uint32_t)enc.path_map.size();
     s->n_styles = (uint32_t)sd.size();
     s->n_xforms = (uint32_t)enc.xform_stream.size();
     hipStream_t st = (hipStream_t)stream;
-    hipError_t e = reserve_scene(s, s->n_tags, s->n_pts, s->n_styles, s->n_xforms, s->n_paths, st);
+    hipError_t e = reserve_scene(s, s->n_tags, s->n_pts, s->n_styles, s->n_xforms, s->n_paths, st, streams_only);
     if (e != hipSuccess) {
         free_scene(s);
         return hip_fail(ctx, e, "scene allocation");
@@ -609,7 +741,7 @@ static int encode_impl(sx_ctx* ctx, const sx_paths* paths, const sx_style* style
         free_scene(s);
         return hip_fail(ctx, e, "scene upload");
     }
-    soup_terms(enc, styles, xforms, s->est);
+    if (!streams_only) soup_terms(enc, styles, xforms, s->est);
     if (style_stream) *style_stream = enc.style_stream;
     s->last_stream = st;
     *out = s;
@@ -657,7 +789,7 @@ int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* s
     hipStream_t st = (hipStream_t)stream;
     std::vector<uint32_t> sstream;
     sx_scene* src = nullptr;
-    int r = encode_impl(ctx, paths, styles, n_styles, xforms, n_xforms, stream, &src, &sstream);
+    int r = encode_impl(ctx, paths, styles, n_styles, xforms, n_xforms, stream, &src, &sstream, true);
     if (r != SX_OK) return r;
     const uint32_t n = src->n_tags;
     // per style entry of the scene: its user style's pattern
@@ -683,6 +815,12 @@ int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* s
         if (e == hipSuccess) e = x;
     };
     sx::DashBufs b{};
+    bool idle = false;  // the device has been waited for
+    auto dalloc = [&](auto** p, size_t bytes) { return ctx->pool->take((void**)p, bytes); };
+    auto dfree = [&](auto*& p) {
+        ctx->pool->give((void*)p, idle);
+        p = nullptr;
+    };
     sx_scene* dst = nullptr;
     // device time of the three dashing phases (the host reads the sizes and
     // allocates between them)
@@ -710,12 +848,13 @@ int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* s
         e = hipMemcpyAsync(b.desc, desc.data(), desc.size() * sizeof(sx::DashDesc), hipMemcpyHostToDevice, st);
     if (e == hipSuccess && !pat.empty())
         e = hipMemcpyAsync(b.pat, pat.data(), pat.size() * sizeof(int64_t), hipMemcpyHostToDevice, st);
-    A(hipMemsetAsync(b.ctl0, 0, sx::scan_ctl_bytes(), st));
-    A(hipMemsetAsync(b.ctl1, 0, sx::scan_ctl_bytes(), st));
-    A(hipMemsetAsync(b.ctl2, 0, sx::scan_ctl_bytes(), st));
-    A(hipMemsetAsync(b.st0, 0, sx::scan_status_bytes(n), st));
-    A(hipMemsetAsync(b.st1, 0, sx::scan_status_bytes(n), st));
-    A(hipMemsetAsync(b.flag, 0, sizeof(uint32_t), st));
+    A(sx::launch_zero({{b.ctl0, sx::scan_ctl_bytes()},
+                       {b.ctl1, sx::scan_ctl_bytes()},
+                       {b.ctl2, sx::scan_ctl_bytes()},
+                       {b.st0, sx::scan_status_bytes(n)},
+                       {b.st1, sx::scan_status_bytes(n)},
+                       {b.flag, sizeof(uint32_t)}},
+                      st));
     if (e == hipSuccess && n)
         e = sx::launch_scan_tags(src->d_tags, n, src->d_mon, ctl_block(src, 0), src->d_status_tags, nullptr, st);
     // phase 0: lengths, positions, subpath starts, chunks per tag and their scan
@@ -736,7 +875,7 @@ int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* s
         A(dalloc(&b.otag, nc * sizeof(uint64_t)));
         A(dalloc(&b.opt, nc * sizeof(uint64_t)));
         A(dalloc(&b.st2, sx::scan_status_bytes(b.n_ch)));
-        A(hipMemsetAsync(b.st2, 0, sx::scan_status_bytes(b.n_ch), st));
+        A(sx::launch_zero({{b.st2, sx::scan_status_bytes(b.n_ch)}}, st));
         A(hipEventRecord(ev[2], st));
         if (e == hipSuccess) e = sx::launch_dash(view(src), b, 1, nullptr, nullptr, st);
         A(hipEventRecord(ev[3], st));
@@ -753,6 +892,7 @@ int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* s
     // phase 2: the write pass into the result scene
     if (e == hipSuccess && r == SX_OK) {
         dst->ctx = ctx;
+        dst->pool = ctx->pool;
         dst->n_tags = (uint32_t)tot_t;
         dst->n_pts = (uint32_t)tot_p;
         dst->n_paths = src->n_paths;
@@ -778,6 +918,7 @@ int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* s
             hipEventElapsedTime(&ms[2], ev[4], ev[5]) == hipSuccess)
             dst->dash_ms = ms[0] + ms[1] + ms[2];
     }
+    idle = ctx->pool->idle();
     dfree(b.desc);
     dfree(b.pat);
     dfree(b.panels);
@@ -906,6 +1047,7 @@ int sx_batch_create(sx_ctx* ctx, sx_batch** out) {
         return fail(ctx, SX_ENOMEM, "batch alloc");
     }
     b->arena->ctx = ctx;
+    b->arena->pool = ctx->pool;
     b->arena->batch_arena = true;
     hipError_t e = hipEventCreateWithFlags(&b->staged, hipEventDisableTiming);
     if (e == hipSuccess) e = reserve_scene(b->arena, 0, 0, 0, 0, 0, nullptr);

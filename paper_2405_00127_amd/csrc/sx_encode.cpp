@@ -29,16 +29,26 @@ struct SubpathState {
 };
 
 inline bool same(float ax, float ay, float bx, float by) { return ax == bx && ay == by; }
+inline bool finite_f(float v) {
+    uint32_t u;
+    memcpy(&u, &v, 4);
+    return (u & 0x7f800000u) != 0x7f800000u;
+}
 }  // namespace
 
 bool encode_paths(const sx_paths& in, const sx_style* styles, uint32_t n_styles, uint32_t n_xforms,
                   HostEncoding& out, std::string& err) {
-    out = HostEncoding{};
-    out.tags.reserve(in.verb_off ? in.verb_off[in.n_paths] + in.n_paths : 0);
+    out.clear();
+    if (in.n_paths) {
+        // about what comes out: a marker and three points per path besides
+        // the input's (room() below covers whatever there is)
+        out.tags.room((size_t)in.verb_off[in.n_paths] + 2 * (size_t)in.n_paths);
+        out.data.room(2 * ((size_t)in.pt_off[in.n_paths] + 4 * (size_t)in.n_paths));
+    }
     int64_t prev_style = -1, prev_xf = -1;
     auto put_pt = [&](float x, float y) {
-        out.data.push_back(x);
-        out.data.push_back(y);
+        out.data.put(x);
+        out.data.put(y);
     };
     for (uint32_t k = 0; k < in.n_paths; k++) {
         if (in.style_ix[k] >= n_styles) { err = "style index out of range"; return false; }
@@ -55,7 +65,7 @@ bool encode_paths(const sx_paths& in, const sx_style* styles, uint32_t n_styles,
         SubpathState sp;
         auto close_line = [&]() {
             if (!same(sp.cx, sp.cy, sp.sx, sp.sy)) {
-                out.tags.push_back((uint8_t)(1u | kF32));
+                out.tags.put((uint8_t)(1u | kF32));
                 put_pt(sp.sx, sp.sy);
                 sp.cx = sp.sx;
                 sp.cy = sp.sy;
@@ -67,7 +77,7 @@ bool encode_paths(const sx_paths& in, const sx_style* styles, uint32_t n_styles,
                     close_line();
                     sp.closed = true;
                 }
-                out.tags.push_back((uint8_t)(2u | kEnd | kF32 | (sp.closed ? kClosedBit : 0u)));
+                out.tags.put((uint8_t)(2u | kEnd | kF32 | (sp.closed ? kClosedBit : 0u)));
                 if (!sp.has_dir) { sp.dx = sp.sx + 1.0f; sp.dy = sp.sy; }
                 put_pt(sp.sx, sp.sy);
                 put_pt(sp.dx, sp.dy);
@@ -75,6 +85,32 @@ bool encode_paths(const sx_paths& in, const sx_style* styles, uint32_t n_styles,
         };
         for (uint32_t vi = in.verb_off[k]; vi < in.verb_off[k + 1]; vi++) {
             const uint8_t v = in.verbs[vi];
+            // a verb adds at most a closing line and a marker, or its own points and a start
+            out.tags.room(4);
+            out.data.room(16);
+            if (v - 1u < 3u && pi + 3 <= np && sp.has_dir) {
+                const uint32_t c = v;
+                // inside a path every segment reads three points and
+                // advances by its own, with no branch on its degree (the
+                // degrees of a drawing are not predictable: 13 ns a
+                // segment with a loop over its points)
+                const float* q = P + 2 * (size_t)pi;
+                const bool two = c >= 2, three = c == 3;
+                const bool f1 = finite_f(q[0]) & finite_f(q[1]), f2 = finite_f(q[2]) & finite_f(q[3]),
+                           f3 = finite_f(q[4]) & finite_f(q[5]);
+                if (!(f1 & (f2 | !two) & (f3 | !three))) { err = "non-finite coordinate"; return false; }
+                const bool m1 = (q[0] != sp.cx) | (q[1] != sp.cy), m2 = (q[2] != sp.cx) | (q[3] != sp.cy),
+                           m3 = (q[4] != sp.cx) | (q[5] != sp.cy);
+                pi += c;
+                if (!(m1 | (m2 & two) | (m3 & three))) continue;  // zero-length segment
+                memcpy(out.data.end(), q, 24);
+                out.data.add(2 * c);
+                out.tags.put((uint8_t)(c | kF32));
+                sp.cx = q[2 * c - 2];
+                sp.cy = q[2 * c - 1];
+                sp.nseg++;
+                continue;
+            }
             if (v == SX_MOVE) {
                 finish();
                 if (pi + 1 > np) { err = "point count mismatch"; return false; }
@@ -121,7 +157,7 @@ bool encode_paths(const sx_paths& in, const sx_style* styles, uint32_t n_styles,
                     }
                 }
                 for (uint32_t j = 0; j < c; j++) put_pt(P[2 * (pi + j)], P[2 * (pi + j) + 1]);
-                out.tags.push_back((uint8_t)(c | kF32));
+                out.tags.put((uint8_t)(c | kF32));
                 sp.cx = P[2 * (pi + c - 1)];
                 sp.cy = P[2 * (pi + c - 1) + 1];
                 pi += c;
@@ -131,6 +167,8 @@ bool encode_paths(const sx_paths& in, const sx_style* styles, uint32_t n_styles,
                 return false;
             }
         }
+        out.tags.room(4);
+        out.data.room(16);
         finish();
         if (pi != np) { err = "point count mismatch"; return false; }
         if (out.tags.size() > first_tag) {

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 #include "sx_device.h"
 
 namespace sx {
@@ -38,6 +40,23 @@ struct GatherDesc {
     uint32_t tag_base, pt_base, style_base, xform_base, path_base;
     uint32_t pad;
 };
+
+// Zeroes up to kZeroParts blocks of device memory (each a multiple of 4
+// bytes, 4-byte aligned; 0 bytes: none) in one launch.
+constexpr int kZeroParts = 6;
+struct ZeroPart {
+    void* p;
+    size_t bytes;
+};
+struct ZeroList {
+    ZeroPart part[kZeroParts] = {};
+    ZeroList(std::initializer_list<ZeroPart> l) {
+        int n = 0;
+        for (const ZeroPart& x : l)
+            if (n < kZeroParts) part[n++] = x;
+    }
+};
+hipError_t launch_zero(const ZeroList& list, hipStream_t s);
 
 int scan_tiles(uint32_t n);
 uint32_t piece_tiles(uint32_t n, uint32_t tile);

@@ -1428,6 +1428,19 @@ hipError_t launch_scene_offsets(const uint64_t* base, const uint64_t* roff, uint
                                                                     scene_offsets);
     return hipGetLastError();
 }
+__global__ __launch_bounds__(256) void zero_kernel(ZeroList l) {
+    for (int k = 0; k < kZeroParts; k++) {
+        uint32_t* p = static_cast<uint32_t*>(l.part[k].p);
+        for (size_t i = blockIdx.x * 256u + threadIdx.x; i < l.part[k].bytes / 4u; i += gridDim.x * 256u) p[i] = 0u;
+    }
+}
+hipError_t launch_zero(const ZeroList& list, hipStream_t s) {
+    size_t most = 0;
+    for (const ZeroPart& x : list.part) most = std::max(most, x.bytes);
+    if (most == 0) return hipSuccess;
+    zero_kernel<<<(uint32_t)std::min<size_t>(1024, most / 4 / 256 + 1), 256, 0, s>>>(list);
+    return hipGetLastError();
+}
 __global__ void zero2_u64_kernel(uint64_t* out) {
     if (threadIdx.x < 2) out[threadIdx.x] = 0ull;
 }
