@@ -1862,7 +1862,7 @@ SX_FN double bez_speed_c(const D2* P, double t) {
         dx = 3.0 * (a * (P[1].x - P[0].x) + b * (P[2].x - P[1].x) + e * (P[3].x - P[2].x));
         dy = 3.0 * (a * (P[1].y - P[0].y) + b * (P[2].y - P[1].y) + e * (P[3].y - P[2].y));
     }
-    return hypot(dx, dy);
+    return sqrt_d(dx * dx + dy * dy);  // (coordinates are within 2^24: no scaling needed)
 }
 // 8-node Gauss-Legendre of |B'| over [a, b]
 template <int C>
@@ -2056,6 +2056,9 @@ struct DashIn {
 // first chunk also opens the path, the last one ends it), so the chunks'
 // outputs in order are the tag's.
 constexpr int64_t kDashChunk = 16;
+constexpr int64_t kDashChunkFine = 2;    // few source tags: more, shorter chunks
+constexpr uint32_t kDashFineTags = 1u << 17;  // scenes of at most this many
+constexpr int64_t kDashFineMost = 64;    // chunks of kDashChunk up to which a segment's are cut finer
 constexpr uint32_t kDashMaxChunks = 1u << 20;  // per segment; more is refused
 struct DashSpan {
     int64_t S0, S1, Stot, base;  // the segment on its subpath (grid units)
@@ -2075,7 +2078,16 @@ SX_HD inline DashSpan dash_span(const DashIn& in, uint32_t i, const DashDesc& dd
     const int64_t span = dash_m_hi(sp.S1, dd.period, dd.phase) - sp.mlo + 1;
     const int64_t dashes = (int64_t)(dd.n / 2u);
     sp.per = dashes >= kDashChunk ? 1 : kDashChunk / dashes;
-    const int64_t nq = (span + sp.per - 1) / sp.per;
+    int64_t nq = (span + sp.per - 1) / sp.per;
+    // A small scene does not fill the chip with threads of 16 dashes each,
+    // which follow one another (20,011 segments: write pass 330 us with 16
+    // dashes a chunk, 194 with 4, 138 with 2, 157 with 1).  (What is refused stays a matter of chunks
+    // of kDashChunk: only segments of few of those are cut finer, so that
+    // the chunks of such a scene stay below 2^27.)
+    if (in.sv.n_tags <= kDashFineTags && nq <= kDashFineMost) {
+        sp.per = dashes >= kDashChunkFine ? 1 : kDashChunkFine / dashes;
+        nq = (span + sp.per - 1) / sp.per;
+    }
     sp.nq = nq > (int64_t)kDashMaxChunks ? kDashMaxChunks + 1u : (uint32_t)nq;
     return sp;
 }
