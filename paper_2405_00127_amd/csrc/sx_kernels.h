@@ -76,9 +76,9 @@ constexpr int kKeepCodes = 32;  // fewest piece codes kept per tag by the bisect
 // Piece codes the bisection keeps per tag for n tags: a budget of 2^25 words
 // shared by the tags, at least kKeepCodes and at most 1024 per tag (a tag with
 // more pieces runs its bisection a second time, in the list kernel), a
-// multiple of 4 (rows are read as uint4).
+// multiple of 16 (rows are read as four uint4).
 inline uint32_t keep_codes_of(uint32_t n) {
-    const uint64_t k = ((1ull << 25) / ((uint64_t)n + 1u)) & ~3ull;
+    const uint64_t k = ((1ull << 25) / ((uint64_t)n + 1u)) & ~15ull;
     return (uint32_t)(k < (uint64_t)kKeepCodes ? kKeepCodes : (k > 1024u ? 1024u : k));
 }
 // Slots per tag (pieces + 1; bit 31 marks a line) and, in no defined order,

@@ -178,11 +178,18 @@ __device__ Pair look_back(TileStatus* st, uint32_t tile, uint32_t epoch, int lan
 
 // --------------------------------------------------------- tag monoid
 constexpr int kScanBlock = 256;
+// Items per thread of a scan, by the number of items.  A tile's loads and
+// stores follow one another (a thread's items are consecutive), so a small
+// scene takes short tiles; a large one long tiles, for its look-back chain.
 constexpr int kTagItems = 16;    // tags per thread of the tag-monoid scan
+constexpr int kTagItemsSmall = 4;
+constexpr uint32_t kTagSmall = 1u << 16;
 constexpr int kCountItems = 32;  // counts per thread of the count scans
+constexpr int kCountItemsSmall = 8;
+constexpr uint32_t kCountSmall = 1u << 18;
 constexpr int kRecCountItems = 64;  // counts per thread of the record-count scan (one round of tiles)
-constexpr int kRecCountSmall = 16;  // the same for scenes of at most kRecSmallSlots slots
-constexpr uint32_t kRecSmallSlots = 1u << 20;
+constexpr int kRecCountMid = 16, kRecCountSmall = 8;  // the same for fewer slots
+constexpr uint32_t kRecMidSlots = 1u << 20, kRecSmallSlots = 1u << 17;
 constexpr uint32_t kCountLine = 0x80000000u;  // bit of a slot-count word: a line segment
 
 __device__ __forceinline__ Pair tag_inc(uint32_t t) {
@@ -266,6 +273,7 @@ __device__ void scan_tile(Load load, Store store, uint32_t n, ScanCtl* ctl, Tile
     if (tid == 0) finish_scan(ctl, s_epoch);
 }
 
+template <int Items>
 __global__ __launch_bounds__(kScanBlock) void scan_tags_kernel(const uint8_t* __restrict__ tags, uint32_t n,
                                                                uint32_t* __restrict__ mon, ScanCtl* ctl,
                                                                TileStatus* st, WsCtl* ws_reset) {
@@ -275,21 +283,26 @@ __global__ __launch_bounds__(kScanBlock) void scan_tags_kernel(const uint8_t* __
         ws_reset->items_total = 0;
     }
     auto load = [&](uint64_t base, Pair* item) {
-        if (base + kTagItems <= n) {
-            uint4 raw = *reinterpret_cast<const uint4*>(tags + base);
-            uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+        if (base + Items <= n) {
+            uint32_t w[Items / 4];
+            if constexpr (Items == 16) {
+                const uint4 raw = *reinterpret_cast<const uint4*>(tags + base);
+                w[0] = raw.x, w[1] = raw.y, w[2] = raw.z, w[3] = raw.w;
+            } else {
+                w[0] = *reinterpret_cast<const uint32_t*>(tags + base);
+            }
 #pragma unroll
-            for (int j = 0; j < kTagItems; j++) item[j] = tag_inc((w[j >> 2] >> (8 * (j & 3))) & 0xffu);
+            for (int j = 0; j < Items; j++) item[j] = tag_inc((w[j >> 2] >> (8 * (j & 3))) & 0xffu);
         } else {
 #pragma unroll
-            for (int j = 0; j < kTagItems; j++) item[j] = (base + j < n) ? tag_inc(tags[base + j]) : Pair{0, 0};
+            for (int j = 0; j < Items; j++) item[j] = (base + j < n) ? tag_inc(tags[base + j]) : Pair{0, 0};
         }
     };
     auto store = [&](uint64_t base, const Pair* incl, Pair pre) {
         // item j: exclusive = pre + incl[j-1]; style/xform stored inclusive - 1
-        uint32_t o_off[kTagItems], o_pth[kTagItems], o_sty[kTagItems], o_xf[kTagItems];
+        uint32_t o_off[Items], o_pth[Items], o_sty[Items], o_xf[Items];
 #pragma unroll
-        for (int j = 0; j < kTagItems; j++) {
+        for (int j = 0; j < Items; j++) {
             Pair ex = pre;
             if (j > 0) ex = ex + incl[j - 1];
             Pair in = pre + incl[j];
@@ -299,15 +312,15 @@ __global__ __launch_bounds__(kScanBlock) void scan_tags_kernel(const uint8_t* __
             o_xf[j] = (uint32_t)(in.b >> 32) - 1u;
         }
         // rows of mon_stride_of(n) words: 16-byte aligned, so a full run of
-        // 16 tags (base a multiple of 16) stores as four uint4 per row
+        // tags (base a multiple of Items) stores as uint4
         const size_t stride = mon_stride_of(n);
         uint32_t* m0 = mon;
         uint32_t* m1 = mon + stride;
         uint32_t* m2 = mon + 2 * stride;
         uint32_t* m3 = mon + 3 * stride;
-        if (base + kTagItems <= n) {
+        if (base + Items <= n) {
 #pragma unroll
-            for (int j = 0; j < kTagItems; j += 4) {
+            for (int j = 0; j < Items; j += 4) {
                 *reinterpret_cast<uint4*>(m0 + base + j) = make_uint4(o_off[j], o_off[j + 1], o_off[j + 2], o_off[j + 3]);
                 *reinterpret_cast<uint4*>(m1 + base + j) = make_uint4(o_pth[j], o_pth[j + 1], o_pth[j + 2], o_pth[j + 3]);
                 *reinterpret_cast<uint4*>(m2 + base + j) = make_uint4(o_sty[j], o_sty[j + 1], o_sty[j + 2], o_sty[j + 3]);
@@ -315,7 +328,7 @@ __global__ __launch_bounds__(kScanBlock) void scan_tags_kernel(const uint8_t* __
             }
         } else {
 #pragma unroll
-            for (int j = 0; j < kTagItems; j++) {
+            for (int j = 0; j < Items; j++) {
                 if (base + j < n) {
                     m0[base + j] = o_off[j];
                     m1[base + j] = o_pth[j];
@@ -325,7 +338,7 @@ __global__ __launch_bounds__(kScanBlock) void scan_tags_kernel(const uint8_t* __
             }
         }
     };
-    scan_tile<kTagItems>(load, store, n, ctl, st);
+    scan_tile<Items>(load, store, n, ctl, st);
 }
 
 // exclusive scan of u32 counts into u64 offsets; out[n] = total
@@ -338,10 +351,11 @@ __global__ __launch_bounds__(kScanBlock) void scan_counts_kernel(const uint32_t*
                                                                  TileStatus* st) {
     scan_u32_body<kCountItems>(in, n, out, ctl, st);
 }
+template <int Items>
 __global__ __launch_bounds__(kScanBlock) void scan_slots_kernel(const uint32_t* __restrict__ in, uint32_t n,
                                                                 uint64_t* __restrict__ out, ScanCtl* ctl,
                                                                 TileStatus* st) {
-    scan_u32_body<kCountItems, ~kCountLine>(in, n, out, ctl, st);
+    scan_u32_body<Items, ~kCountLine>(in, n, out, ctl, st);
 }
 // the same with n read from device memory (clamped to the buffers' capacity);
 // the grid covers the capacity
@@ -555,15 +569,24 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
 // tag read its row together).  A tag with more pieces than codes kept runs
 // its bisection again, in order, on the thread of its first piece.
 constexpr int kListBlock = 256;
-constexpr uint32_t kListPieces = 1024;      // pieces of a block's turn (list_kernel)
-constexpr uint32_t kListSpan = 2048;        // tags of a turn whose bases are staged in LDS
-constexpr uint32_t kSmallTags = 16384;      // scenes whose blocks scan all counts themselves
-constexpr uint32_t kSmallBlocks = 512;      // their grid cap
+// pieces of a block's turn (list_kernel), by the slots it is launched for: a
+// thread's pieces follow one another (20,011 segments: 256 a turn 5.8 us, 512
+// 7.8, 1,024 13), a large scene's turns share their searches (1M segments:
+// 48, 42 and 44 us)
+constexpr uint32_t kListPieces = 512, kListPiecesSmall = 256;
+constexpr uint32_t kListSmallSlots = 1u << 20;
+constexpr uint32_t kListSpan = 1024;        // tags of a turn whose bases are staged in LDS
+constexpr uint32_t kSmallTags = 4096;       // scenes whose blocks scan all counts themselves
+constexpr uint32_t kSmallBlocks = 768;      // their grid cap
 
 __device__ __forceinline__ uint32_t code_start(uint32_t code) {
     return code_t0u(code) << ((uint32_t)kMaxDepth - code_depth(code));
 }
 // Piece q of the np pieces of tag i, whose first piece has ordinal `first`.
+// Ahead: turns of the row loop unrolled (long rows: four loads in flight; 10,007
+// stress cubics: 40 -> 24.5 us; 1M map segments, of five pieces a curve, 42 us
+// without, 45 with).
+template <int Ahead>
 __device__ __forceinline__ void list_piece(const SceneView& sv, const Cfg& cfg, uint32_t keep,
                                            const uint32_t* __restrict__ codes, bool line, uint32_t i, uint32_t q,
                                            uint32_t np, uint64_t first, Slot* __restrict__ pcs, uint64_t slot_cap) {
@@ -589,6 +612,7 @@ __device__ __forceinline__ void list_piece(const SceneView& sv, const Cfg& cfg, 
         const uint32_t* row = codes + (size_t)i * keep;
         code = row[q];
         const uint32_t start = code_start(code);
+#pragma unroll Ahead
         for (uint32_t r = 0; r < np; r += 4u) {
             const uint4 v = *reinterpret_cast<const uint4*>(row + r);
             rank += (code_start(v.x) < start ? 1u : 0u) + (r + 1u < np && code_start(v.y) < start ? 1u : 0u) +
@@ -599,19 +623,20 @@ __device__ __forceinline__ void list_piece(const SceneView& sv, const Cfg& cfg, 
     if (first + rank < slot_cap) pcs[first + rank] = Slot{i, code};
 }
 
-// From the scanned slot bases; a block takes kListPieces pieces at a time.
+// From the scanned slot bases; a block takes `turn` pieces at a time.
+template <int Ahead>
 __global__ __launch_bounds__(kListBlock) void list_kernel(SceneView sv, Cfg cfg, uint32_t keep,
                                                           const uint32_t* __restrict__ nslots,
                                                           const uint32_t* __restrict__ codes,
                                                           const uint64_t* __restrict__ base, Slot* __restrict__ pcs,
-                                                          uint64_t slot_cap) {
+                                                          uint64_t slot_cap, uint32_t turn) {
     __shared__ uint32_t s_tag[2];
     __shared__ uint32_t s_off[kListSpan];  // pieces of the turn before each of its tags
     const uint32_t n = sv.n_tags, t = threadIdx.x, lane = t & 63u, wv = t >> 6;
     const uint64_t n_pieces = base[n] - n;
     // (piece ordinal of tag i: base[i] - i)
-    for (uint64_t p0 = (uint64_t)blockIdx.x * kListPieces; p0 < n_pieces; p0 += (uint64_t)gridDim.x * kListPieces) {
-        const uint64_t p1 = min(p0 + kListPieces, n_pieces);
+    for (uint64_t p0 = (uint64_t)blockIdx.x * turn; p0 < n_pieces; p0 += (uint64_t)gridDim.x * turn) {
+        const uint64_t p1 = min(p0 + turn, n_pieces);
         // the tags of the turn's first and last piece: the last tag whose
         // pieces start at or before it, 64 probes at a time
         if (wv < 2u) {
@@ -646,7 +671,7 @@ __global__ __launch_bounds__(kListBlock) void list_kernel(SceneView sv, Cfg cfg,
             }
             const uint32_t i = tag0 + lo, w = nslots[i];
             const uint64_t first = staged ? f0 + s_off[lo] : base[i] - i;
-            list_piece(sv, cfg, keep, codes, (w & kCountLine) != 0u, i, (uint32_t)(p - first), (w & ~kCountLine) - 1u,
+            list_piece<Ahead>(sv, cfg, keep, codes, (w & kCountLine) != 0u, i, (uint32_t)(p - first), (w & ~kCountLine) - 1u,
                        first, pcs, slot_cap);
         }
         __syncthreads();  // s_tag and s_off are reused
@@ -654,7 +679,9 @@ __global__ __launch_bounds__(kListBlock) void list_kernel(SceneView sv, Cfg cfg,
 }
 
 // Small scenes: every block scans all slot counts into LDS (n_tags words), so
-// bases and list take one launch without a wait between blocks.
+// bases and list take one launch without a wait between blocks (1,000 cubics:
+// 7.3 us, 11.9 with a scan launch; at 11,000 tags the scan launch and list
+// take 30 us, this 35).
 __global__ __launch_bounds__(kListBlock) void list_small_kernel(SceneView sv, Cfg cfg, uint32_t keep,
                                                                 const uint32_t* __restrict__ nslots,
                                                                 const uint32_t* __restrict__ codes,
@@ -706,7 +733,7 @@ __global__ __launch_bounds__(kListBlock) void list_small_kernel(SceneView sv, Cf
             cnt = le ? cnt - half : half;
         }
         const uint32_t first = i ? s_end[i - 1u] & ~kCountLine : 0u, e = s_end[i];
-        list_piece(sv, cfg, keep, codes, (e & kCountLine) != 0u, i, p - first, (e & ~kCountLine) - first, first, pcs,
+        list_piece<4>(sv, cfg, keep, codes, (e & kCountLine) != 0u, i, p - first, (e & ~kCountLine) - first, first, pcs,
                    slot_cap);
     }
 }
@@ -1288,7 +1315,12 @@ uint32_t slot_block() { return kSlotBlock; }
 hipError_t launch_scan_tags(const uint8_t* tags, uint32_t n, uint32_t* mon, void* ctl, void* st, WsCtl* ws_reset,
                             hipStream_t s) {
     if (n == 0) return hipSuccess;
-    scan_tags_kernel<<<scan_tiles(n), kScanBlock, 0, s>>>(tags, n, mon, (ScanCtl*)ctl, (TileStatus*)st, ws_reset);
+    if (n <= kTagSmall)
+        scan_tags_kernel<kTagItemsSmall><<<count_scan_tiles(n, kTagItemsSmall), kScanBlock, 0, s>>>(
+            tags, n, mon, (ScanCtl*)ctl, (TileStatus*)st, ws_reset);
+    else
+        scan_tags_kernel<kTagItems><<<scan_tiles(n), kScanBlock, 0, s>>>(tags, n, mon, (ScanCtl*)ctl, (TileStatus*)st,
+                                                                         ws_reset);
     return hipGetLastError();
 }
 hipError_t launch_scan_counts(const uint32_t* in, uint32_t n, uint64_t* out, void* ctl, void* st, hipStream_t s) {
@@ -1298,7 +1330,12 @@ hipError_t launch_scan_counts(const uint32_t* in, uint32_t n, uint64_t* out, voi
 }
 hipError_t launch_scan_slots(const uint32_t* nslots, uint32_t n, uint64_t* base, void* ctl, void* st, hipStream_t s) {
     if (n == 0) return hipSuccess;
-    scan_slots_kernel<<<count_scan_tiles(n), kScanBlock, 0, s>>>(nslots, n, base, (ScanCtl*)ctl, (TileStatus*)st);
+    if (n <= kCountSmall)
+        scan_slots_kernel<kCountItemsSmall><<<count_scan_tiles(n, kCountItemsSmall), kScanBlock, 0, s>>>(
+            nslots, n, base, (ScanCtl*)ctl, (TileStatus*)st);
+    else
+        scan_slots_kernel<kCountItems><<<count_scan_tiles(n), kScanBlock, 0, s>>>(nslots, n, base, (ScanCtl*)ctl,
+                                                                                  (TileStatus*)st);
     return hipGetLastError();
 }
 __global__ void zero_u64_kernel(uint64_t* out) {
@@ -1316,12 +1353,23 @@ hipError_t launch_scan_counts_dev(const uint32_t* in, const uint64_t* n_dev, uin
     if (cap <= kRecSmallSlots)
         scan_counts_dev_kernel<kRecCountSmall><<<count_scan_tiles(cap > 0 ? cap : 1, kRecCountSmall), kScanBlock, 0, s>>>(
             in, n_dev, cap, out, (ScanCtl*)ctl, (TileStatus*)st);
+    else if (cap <= kRecMidSlots)
+        scan_counts_dev_kernel<kRecCountMid><<<count_scan_tiles(cap, kRecCountMid), kScanBlock, 0, s>>>(
+            in, n_dev, cap, out, (ScanCtl*)ctl, (TileStatus*)st);
     else
         scan_counts_dev_kernel<kRecCountItems><<<count_scan_tiles(cap, kRecCountItems), kScanBlock, 0, s>>>(
             in, n_dev, cap, out, (ScanCtl*)ctl, (TileStatus*)st);
     return hipGetLastError();
 }
 
+// Longest range of a scene of n tags: a small one is spread over kFillWaves
+// waves (more of them cost their dispatch, about 4 ns each: 20,011 segments
+// 25 us on 4,096 waves, 17 us on 2,048) until a wave has kFillRange tags,
+// a large one over 8,192 (1M segments: 119 us on 4,096 waves, 97 us on 8,192).
+constexpr uint32_t kFillWaves = 2048, kFillRange = 64;
+static uint32_t bisect_fill(uint32_t n) {
+    return std::max((n + 8191u) / 8192u, std::min((n + kFillWaves - 1u) / kFillWaves, kFillRange));
+}
 template <bool Stats>
 static void bisect_launch(uint32_t g, hipStream_t s, int waves, const SceneView& sv, const Cfg& cfg, uint32_t range,
                           uint32_t keep, uint32_t* nslots, uint32_t* codes, unsigned long long* stats) {
@@ -1335,11 +1383,9 @@ static void bisect_launch(uint32_t g, hipStream_t s, int waves, const SceneView&
 hipError_t launch_bisect(const SceneView& sv, const Cfg& cfg, uint32_t range, uint32_t keep, int waves,
                          uint32_t* nslots, uint32_t* codes, unsigned long long* stats, hipStream_t s) {
     if (sv.n_tags == 0) return hipSuccess;
-    if (range == 0 || range % 64u || range > kBisectMaxRange || keep < (uint32_t)kKeepCodes || keep % 4u)
+    if (range == 0 || range % 64u || range > kBisectMaxRange || keep < (uint32_t)kKeepCodes || keep % 16u)
         return hipErrorInvalidValue;
-    // a scene too small to give every SIMD its waves at this range takes
-    // shorter ranges, down to one tag per wave
-    const uint32_t fill = (sv.n_tags + 4095u) / 4096u;
+    const uint32_t fill = bisect_fill(sv.n_tags);
     if (fill < range) range = fill;
     const uint32_t g = (sv.n_tags + range - 1) / range;
     if (stats)
@@ -1357,8 +1403,13 @@ hipError_t launch_list(const SceneView& sv, const Cfg& cfg, uint32_t keep, const
         list_small_kernel<<<g, kListBlock, sv.n_tags * sizeof(uint32_t), s>>>(sv, cfg, keep, nslots, codes, base, pcs,
                                                                              slot_cap);
     } else {
-        const uint32_t g = (uint32_t)std::min<uint64_t>(4096, (slot_cap + kListPieces - 1) / kListPieces);
-        list_kernel<<<g, kListBlock, 0, s>>>(sv, cfg, keep, nslots, codes, base, pcs, slot_cap);
+        const uint32_t turn = slot_cap <= kListSmallSlots ? kListPiecesSmall : kListPieces;
+        const uint32_t g = (uint32_t)std::min<uint64_t>(8192, (slot_cap + turn - 1) / turn);
+        // (many pieces per tag: long rows)
+        if (slot_cap > 8ull * sv.n_tags)
+            list_kernel<4><<<g, kListBlock, 0, s>>>(sv, cfg, keep, nslots, codes, base, pcs, slot_cap, turn);
+        else
+            list_kernel<1><<<g, kListBlock, 0, s>>>(sv, cfg, keep, nslots, codes, base, pcs, slot_cap, turn);
     }
     return hipGetLastError();
 }
@@ -1453,7 +1504,12 @@ hipError_t launch_tag_records(const uint64_t* base, const uint64_t* roff, uint64
     tag_records_kernel<<<(n_tags + 1 + 255) / 256, 256, 0, s>>>(base, roff, slot_cap, n_tags, counts, offs);
     return hipGetLastError();
 }
-size_t scan_status_bytes(uint32_t n) { return (size_t)scan_tiles(n > 0 ? n : 1) * sizeof(TileStatus); }
+// (enough for every scan of at most n items: short tiles for few of them)
+size_t scan_status_bytes(uint32_t n) {
+    const uint32_t few = std::min(std::max(n, 1u), kTagSmall), some = std::min(std::max(n, 1u), kCountSmall);
+    return sizeof(TileStatus) * (size_t)std::max({scan_tiles(std::max(n, 1u)), count_scan_tiles(few, kTagItemsSmall),
+                                                  count_scan_tiles(some, kCountItemsSmall)});
+}
 size_t scan_ctl_bytes() { return sizeof(ScanCtl); }
 
 

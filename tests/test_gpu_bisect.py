@@ -1,7 +1,8 @@
 """The bisection, the piece list and the record launch at the edges of their
 dispatch (GPU, through the C ABI): scenes at the tag counts where the list
-kernel, the record chunks (2^17 slots, four per tag at first) and the record
-scan (2^20 slots) change, tags with more pieces than the bisection keeps codes for, and runs of tags without
+kernel, the record chunks (2^17 slots, four per tag at first), the scans (2^16
+and 2^18 tags, 2^17 and 2^20 slots) and the list's turns change, tags with
+more pieces than the bisection keeps codes for, and runs of tags without
 pieces longer than the list kernel stages.  Against the FP64 oracle at the
 parity bars (or bit for bit against the same paths expanded without the empty
 ones)."""
@@ -14,7 +15,7 @@ from paper_2405_00127_amd import scenes as S
 
 pytestmark = pytest.mark.gpu
 
-SMALL_TAGS = 16384  # kSmallTags of the list kernels
+SMALL_TAGS = 4096  # kSmallTags of the list kernels
 
 
 @pytest.fixture(scope="module")
@@ -60,7 +61,7 @@ def _check(ctx, sc):
     scene.release()
 
 
-@pytest.mark.parametrize("n_tags", [12, 255, 257, 4095, 4097, SMALL_TAGS, SMALL_TAGS + 1, 32768, 32769, 262145])
+@pytest.mark.parametrize("n_tags", [12, 255, 257, SMALL_TAGS, SMALL_TAGS + 1, 16385, 32768, 32769, 65537, 262145])
 def test_tag_counts_at_the_edges(ctx, n_tags):
     _check(ctx, _with_tags(n_tags))
 
