@@ -165,7 +165,7 @@ struct sx_scene {
     void* d_status_rc = nullptr;
     // item workspace of the slot / record kernels
     sx::Unit* d_items = nullptr;
-    float* d_es = nullptr;  // per-slot spiral records
+    uint4* d_es = nullptr;  // per-slot spiral records (their two halves, an array each)
     uint32_t* d_tile_n = nullptr;
     sx::WsCtl* d_ws_ctl = nullptr;
     uint32_t region_per_piece = 0;  // item units per piece in the per-tile regions
@@ -300,8 +300,9 @@ sx::SceneView view(const sx_scene* s) {
 
 sx::ItemWs workspace(const sx_scene* s) {
     sx::ItemWs w;
-    w.units = s->d_items;
-    w.es_tab = s->d_es;
+    w.units = reinterpret_cast<uint4*>(s->d_items);
+    w.es_lo = s->d_es;
+    w.es_hi = s->d_es + s->slot_cap;
     w.tile_n = s->d_tile_n;
     w.ctl = s->d_ws_ctl;
     w.tile = sx::slot_block();
@@ -338,7 +339,7 @@ hipError_t size_slots(sx_scene* s, uint64_t slot_cap, uint32_t region_per_piece,
         dfree(s->d_tile_n);
         dfree(s->d_es);
         A(dalloc(&s->d_slots, slot_cap * sizeof(sx::Slot)));
-        A(dalloc(&s->d_es, slot_cap * 8 * sizeof(float)));
+        A(dalloc(&s->d_es, slot_cap * 2 * sizeof(uint4)));
         A(dalloc(&s->d_rc, (slot_cap + 16) * sizeof(uint32_t)));
         A(dalloc(&s->d_roff, (slot_cap + 1) * sizeof(uint64_t)));
         A(dalloc(&s->d_status_rc, sx::scan_status_bytes((uint32_t)slot_cap)));

@@ -754,6 +754,37 @@ SX_HD void write_item(Unit* units, uint64_t base, uint32_t hdr, uint32_t path, u
     }
 }
 
+// The same into units laid out by their 16-byte quarters: quarter v of unit u
+// of a region of `stride` units at p[v * stride + u], so that neighbouring
+// lanes, which hold neighbouring units, read and write consecutive addresses
+// (64-byte units one after another took a cache line per lane and quarter).
+// Quarters past the payload are left as they are.
+struct UnitAt {
+    uint4* p;         // quarter 0 of the first unit
+    uint64_t stride;
+};
+template <class P>
+SX_FN void write_item_q(const UnitAt& at, uint32_t hdr, uint32_t path, uint32_t slot, uint32_t n0, uint32_t nrec,
+                        uint32_t K, const P& p) {
+    constexpr uint32_t U = Units<P>::n, W = kHdrWords + (uint32_t)(sizeof(P) / 4), Q = (W + 3u) / 4u;
+    uint32_t w[4 * Q];
+    w[4 * Q - 1] = w[4 * Q - 2] = w[4 * Q - 3] = 0u;
+    memcpy(w + kHdrWords, &p, sizeof(P));
+    const uint32_t nc = chunks(nrec, K);
+    for (uint32_t c = 0; c < nc; c++) {
+        const uint32_t nchunk = (c + 1 < nc) ? K : nrec - c * K;
+        w[0] = hdr | (nchunk << 24);
+        w[1] = path;
+        w[2] = slot;
+        w[3] = n0 + c * K;
+        w[4] = c * K;
+        w[5] = nrec;
+#pragma unroll
+        for (uint32_t q = 0; q < Q; q++)
+            at.p[(q & 3u) * at.stride + c * U + (q >> 2)] = make_uint4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
+    }
+}
+
 template <class Alloc, bool Stats = false>
 struct ItemSink {
     Unit* units;
@@ -1672,11 +1703,8 @@ SX_HD inline bool bisect_step(Bisect& b, const Seg&, const Cfg& cfg, bool line, 
 // The accepted piece [t0, t0 + 2^-depth] of the segment (accepted by the
 // fit, or only at the depth cap: a pivot): the same chord and end angles as
 // in the bisection and its Euler spiral (Appendix A; a pivot for reading
-// G28), whose FP32 record goes to the slot's row of the spiral table;
-// emit_piece adds both parallel-curve sides.
-template <class Sink>
-SX_HD void piece_es(Sink& k, const Cfg& cfg, const Seg& s, bool line, uint32_t t0_u, uint32_t depth, bool pivot,
-                    ES& es) {
+// G28); emit_piece adds both parallel-curve sides.
+SX_HD inline void piece_es(const Seg& s, bool line, uint32_t t0_u, uint32_t depth, bool pivot, ES& es) {
     const double dt = depth_dt(depth);
     const double t0 = (double)t0_u * dt;
     const double t1 = t0 + dt;
@@ -1685,7 +1713,6 @@ SX_HD void piece_es(Sink& k, const Cfg& cfg, const Seg& s, bool line, uint32_t t
     const D2 u1 = line ? u0 : unit_tan(s, t1, cubic_q(s.D1, s.A2, s.C3, t1));
     const D2 chord = line ? s.D3 : cubic_chord(s.A2, s.C3, t0, dt, q0);
     const double cc = dot(chord, chord), rcl = cc > 0.0 ? rsqrt_d(cc) : 0.0, cl = cc * rcl;
-    if constexpr (Sink::kStats) k.st[kStPieces]++;
     es.pivot = pivot;
     es.p0 = cubic_world(s, t0);
     es.p1 = cubic_world(s, t1);
@@ -1732,12 +1759,13 @@ SX_HD void piece_es(Sink& k, const Cfg& cfg, const Seg& s, bool line, uint32_t t
     es.fL = (float)es.L;
     es.fbase = (float)base;
     es_ends(es, s.w);
-    set_es_f(es, k.es_tab + 8 * (size_t)k.slot);
 }
 template <class Sink>
 SX_HD void emit_piece(Sink& k, const Cfg& cfg, const Seg& s, bool line, uint32_t t0_u, uint32_t depth, bool pivot) {
     ES es;
-    piece_es(k, cfg, s, line, t0_u, depth, pivot, es);
+    piece_es(s, line, t0_u, depth, pivot, es);
+    if constexpr (Sink::kStats) k.st[kStPieces]++;
+    set_es_f(es, k.es_tab + 8 * (size_t)k.slot);
     emit_sides(k, cfg, es, s.w, s.fill);
 }
 

@@ -11,8 +11,9 @@ namespace sx {
 
 // Item workspace of the slot / record kernels: one region of region_cap
 // 64-byte units per piece tile (the slots from its first piece to the next
-// tile's), then ovf_cap shared overflow units at ovf_base; and the per-slot
-// spiral records (8 floats per slot).
+// tile's), then ovf_cap shared overflow units at ovf_base, every area laid
+// out by quarters (UnitAt); and the per-slot spiral records (two 16-byte
+// halves, each an array over the slots).
 struct WsCtl {
     unsigned long long ovf_n;        // overflow units requested
     unsigned long long items_total;  // units requested by all tiles
@@ -20,8 +21,8 @@ struct WsCtl {
     unsigned long long result[2];    // records and status, for synchronous readback
 };
 struct ItemWs {
-    Unit* units;
-    float* es_tab;
+    uint4* units;
+    uint4 *es_lo, *es_hi;
     uint32_t* tile_n;  // per slot tile: units requested (clamp to region_cap)
     WsCtl* ctl;
     uint32_t tile;        // pieces per tile

@@ -752,31 +752,50 @@ constexpr uint32_t kRecSplitGrid = 1024;  // record-kernel blocks that a small s
 constexpr uint32_t kOvfBlocks = 512;  // most record-kernel blocks striding over the overflow units
 
 // Unit allocation of the piece launch.  A piece's items are first counted
-// by a dry run of its puts (CountAlloc: nothing is written); the lane then
+// by a dry run of its puts (CountSink: nothing is written); the lane then
 // reserves them with one LDS atomic on its tile's counter (the address
 // differs between lanes, so this is a plain per-lane atomic, not a scalar
-// loop over the lanes) and hands its reservation out in order (LaneAlloc).
+// loop over the lanes) and hands its reservation out in order (UnitSink).
 // A reservation that does not fit in the tile's region moves as a whole to
 // the shared overflow area (the part inside the region is left empty).
-struct CountAlloc {
-    uint32_t n;
-    __device__ uint64_t alloc(uint32_t nc) {
-        n += nc;
-        return ~0ull;
+struct CountSink {
+    static constexpr bool kStats = false;
+    uint32_t units;
+    template <class P>
+    __device__ void put(uint32_t, uint32_t nrec, uint32_t K, const P&) {
+        units += chunks(nrec, K) * Units<P>::n;
     }
 };
+template <bool Stats>
+struct UnitSink {
+    static constexpr bool kStats = Stats;
+    UnitAt at;            // the next unit of the reservation (null: dropped)
+    uint32_t path, slot;  // output path id, slot index
+    uint32_t n;           // records of the slot so far
+    uint32_t st[Stats ? kStN : 1];
+    template <class P>
+    __device__ void put(uint32_t hdr, uint32_t nrec, uint32_t K, const P& p) {
+        if constexpr (Stats) st[(hdr & 15u) == kItemOffset ? kStRanges : kStEvolutes]++;
+        if (at.p) {
+            write_item_q(at, hdr, path, slot, n, nrec, K, p);
+            at.p += chunks(nrec, K) * Units<P>::n;
+        }
+        n += nrec;
+    }
+};
+// `need` units from unit `at` of tile `tile`'s region on, or, when they do
+// not fit there, of the overflow area (null: full); the part inside the
+// region is then left empty.
+__device__ __forceinline__ UnitAt place_units(const ItemWs& ws, uint64_t tile, uint32_t at, uint32_t need) {
+    uint4* region = ws.units + tile * ws.region_cap * 4u;
+    if (at + need <= ws.region_cap) return UnitAt{region + at, ws.region_cap};
+    for (uint32_t u = at; u < ws.region_cap; u++) region[u].x = 0u;
+    const unsigned long long o = atomicAdd(&ws.ctl->ovf_n, (unsigned long long)need);
+    return UnitAt{o + need <= ws.ovf_cap ? ws.units + ws.ovf_base * 4u + o : nullptr, ws.ovf_cap};
+}
 constexpr uint32_t kPieceGroup = 4;     // piece tiles a piece-launch workgroup orders together
 constexpr uint32_t kSingleTiles = 1024;  // the last piece tiles, taken one per workgroup
 constexpr uint32_t kGroupTiles = 4096;   // tiles from which groups are taken at all
-struct LaneAlloc {
-    uint64_t next;  // next unit of the reservation, or ~0ull (dropped)
-    __device__ uint64_t alloc(uint32_t nc) {
-        const uint64_t u = next;
-        if (u != ~0ull) next = u + nc;
-        return u;
-    }
-};
-
 // Piece tiles: tile T holds the pieces of ordinals [T, T + 1) x kSlotBlock
 // and owns the slots from the first of them up to the first slot of tile
 // T + 1 (so also the tails of the tags whose last piece it holds; tile 0
@@ -896,10 +915,8 @@ __global__ __launch_bounds__(kSlotBlock, MinWaves) void slot_kernel(SceneView sv
                 sl = pcs[gfirst + o];
                 j = gfirst + o + sl.tag;
             }
-            ItemSink<LaneAlloc, Stats> k;
-            k.units = ws.units;
-            k.es_tab = ws.es_tab;
-            k.al.next = ~0ull;
+            UnitSink<Stats> k;
+            k.at = UnitAt{nullptr, 0u};
             k.path = 0xffffffffu;
             k.slot = (uint32_t)j;
             k.n = 0;
@@ -917,7 +934,11 @@ __global__ __launch_bounds__(kSlotBlock, MinWaves) void slot_kernel(SceneView sv
                 fetch_tag(sv, sl.tag, ti, sg);
                 if (ti.kind == kTagSegment) {
                     have = true;
-                    piece_es(k, cfg, sg, ti.line, code_t0u(sl.code), code_depth(sl.code), code_pivot(sl.code), es);
+                    piece_es(sg, ti.line, code_t0u(sl.code), code_depth(sl.code), code_pivot(sl.code), es);
+                    if constexpr (Stats) k.st[kStPieces]++;
+                    const V2 er = es.pivot ? es.fd : es.frot;
+                    ws.es_lo[j] = make_uint4(f_bits(es.fp0.x), f_bits(es.fp0.y), f_bits(er.x), f_bits(er.y));
+                    ws.es_hi[j] = make_uint4(f_bits(es.fk0), f_bits(es.fk1), f_bits(es.fL), f_bits(es.fbase));
                     side1 = !sg.fill;
                     g0 = side_geo(es, sg.w, 0);
                     g1 = side_geo(es, sg.w, 1);
@@ -974,29 +995,13 @@ __global__ __launch_bounds__(kSlotBlock, MinWaves) void slot_kernel(SceneView sv
             };
             uint32_t need = 0;
             if (have) {
-                ItemSink<CountAlloc, false> dry;
-                dry.units = ws.units;
-                dry.es_tab = ws.es_tab;
-                dry.al.n = 0;
-                dry.path = 0;
-                dry.slot = 0;
-                dry.n = 0;
+                CountSink dry{0u};
                 put_all(dry);
-                need = dry.al.n;
+                need = dry.units;
             }
-            if (need) {
-                // one LDS atomic per lane on its tile's counter (lanes of a wave
-                // can belong to different tiles of the group)
-                const uint32_t at = atomicAdd(&s_n[kt], need);
-                const uint64_t region = ((uint64_t)tile0 + kt) * ws.region_cap;
-                if (at + need <= ws.region_cap) {
-                    k.al.next = region + at;
-                } else {
-                    for (uint32_t u = at; u < ws.region_cap; u++) ws.units[region + u].w[0] = 0u;
-                    const unsigned long long o = atomicAdd(&ws.ctl->ovf_n, (unsigned long long)need);
-                    k.al.next = (o + need <= ws.ovf_cap) ? ws.ovf_base + o : ~0ull;
-                }
-            }
+            // one LDS atomic per lane on its tile's counter (lanes of a wave
+            // can belong to different tiles of the group)
+            if (need) k.at = place_units(ws, tile0 + kt, atomicAdd(&s_n[kt], need), need);
             if (have) put_all(k);
             if (act) {
                 rc[j] = k.n;
@@ -1083,14 +1088,8 @@ __global__ __launch_bounds__(kTailBlock, 3) void tail_kernel(SceneView sv, Cfg c
         if (i < n) {
             if (need) {
                 const uint32_t at = win ? s_at[tile - tile_lo] + local : atomicAdd(&ws.tile_n[tile], need);
-                uint64_t u = tile * ws.region_cap + at;
-                if (at + need > ws.region_cap) {
-                    // the part inside the region is left empty; the item goes to the overflow area
-                    for (uint32_t j = at; j < ws.region_cap; j++) ws.units[tile * ws.region_cap + j].w[0] = 0u;
-                    const unsigned long long o = atomicAdd(&ws.ctl->ovf_n, (unsigned long long)need);
-                    u = (o + need <= ws.ovf_cap) ? ws.ovf_base + o : ~0ull;
-                }
-                if (u != ~0ull) write_item(ws.units, u, k.hdr, path_of(sv, i), (uint32_t)slot, 0u, k.nrec, cfg.K, k.p);
+                const UnitAt u = place_units(ws, tile, at, need);
+                if (u.p) write_item_q(u, k.hdr, path_of(sv, i), (uint32_t)slot, 0u, k.nrec, cfg.K, k.p);
             }
             rc[slot] = k.n;
             asked += need;
@@ -1104,29 +1103,35 @@ __global__ __launch_bounds__(kTailBlock, 3) void tail_kernel(SceneView sv, Cfg c
     if (Stats && joins) atomicAdd(&stats[kStJoins], (unsigned long long)joins);
 }
 
-// One item chunk starting at unit u: loads its one or two units and writes
-// its records.
+// One item chunk starting at a unit: loads its one or two units (the quarters
+// its kind fills) and writes its records.
 template <bool Newton>
-__device__ __forceinline__ void record_item(const SceneView& sv, const ItemWs& ws, const Unit* u,
+__device__ __forceinline__ void record_item(const SceneView& sv, const ItemWs& ws, const UnitAt& u,
                                             const uint64_t* roff, uint64_t n_slots, float* out, uint64_t cap,
                                             int arcs, const XIncF& xi, float* stage = nullptr, uint64_t lo = 0,
                                             uint64_t hi = 0) {
     uint32_t w[2 * kUnitWords];
-    const uint4* src = reinterpret_cast<const uint4*>(u);
 #pragma unroll
-    for (int j = 0; j < 4; j++) reinterpret_cast<uint4*>(w)[j] = src[j];
+    for (int q = 0; q < 4; q++) reinterpret_cast<uint4*>(w)[q] = u.p[q * u.stride];
     const uint32_t kind = w[0] & 15u;
     if (kind == 0u) return;
     if (kind != kItemOffset) {
 #pragma unroll
-        for (int j = 4; j < 8; j++) reinterpret_cast<uint4*>(w)[j] = src[j];
+        for (int q = 0; q < 3; q++) reinterpret_cast<uint4*>(w)[4 + q] = u.p[q * u.stride + 1u];
     }
     const uint32_t path = w[1], slot = w[2];
     if (slot >= n_slots) return;
     const uint64_t end = roff[slot + 1] < cap ? roff[slot + 1] : cap;
     RecOut o{out, roff[slot] + w[3], end, path, arcs, stage, lo, hi};
-    emit_item<Newton>(w, ws.es_tab + 8 * (size_t)slot, xi, o);
+    __align__(16) float es[8];
+    if (kind != kItemJoin) {
+        *reinterpret_cast<uint4*>(es) = ws.es_lo[slot];
+        *reinterpret_cast<uint4*>(es + 4) = ws.es_hi[slot];
+    }
+    emit_item<Newton>(w, es, xi, o);
 }
+static_assert(kHdrWords + sizeof(JoinP) / 4 <= kUnitWords + 12 && kHdrWords + sizeof(EvoluteP) / 4 <= kUnitWords + 12,
+              "record_item loads three quarters of a second unit");
 
 // Per item chunk, the FP32 per-point work: records at
 // roff[slot] + the chunk's position within its slot.  A tile is one block's
@@ -1169,7 +1174,7 @@ __global__ __launch_bounds__(kRecBlock, Newton ? 3 : 6) void record_kernel(Scene
         for (uint32_t turn = b; turn < n_tiles * split; turn += n_main) {
             const uint32_t tile = turn / split, part = turn % split;
             const uint32_t cnt = ws.tile_n[tile] < ws.region_cap ? ws.tile_n[tile] : ws.region_cap;
-            const Unit* base = ws.units + (uint64_t)tile * ws.region_cap;
+            uint4* base = ws.units + (uint64_t)tile * ws.region_cap * 4u;
             const uint64_t s_lo = tile_first_slot(pcs, tile, n_tiles, n_slots);
             const uint64_t s_hi = tile_first_slot(pcs, tile + 1u, n_tiles, n_slots);
             const uint64_t lo = roff[s_lo];
@@ -1179,7 +1184,7 @@ __global__ __launch_bounds__(kRecBlock, Newton ? 3 : 6) void record_kernel(Scene
             const uint64_t n_st = ws.tile_n[tile] > ws.region_cap || split > 1u ? 0u
                                   : (n_rec < kStageWords / words ? n_rec : kStageWords / words);
             for (uint32_t s2 = part * kRecBlock + threadIdx.x; s2 < cnt; s2 += split * kRecBlock)
-                record_item<Newton>(sv, ws, base + s2, roff, n_slots, out, cap_records, arcs, xi, s_stage, lo,
+                record_item<Newton>(sv, ws, UnitAt{base + s2, ws.region_cap}, roff, n_slots, out, cap_records, arcs, xi, s_stage, lo,
                                     lo + n_st);
             if (split > 1u) continue;
             __syncthreads();
@@ -1190,10 +1195,10 @@ __global__ __launch_bounds__(kRecBlock, Newton ? 3 : 6) void record_kernel(Scene
         }
     } else {
         const uint64_t cnt = ws.ctl->ovf_n;
-        const Unit* base = ws.units + ws.ovf_base;
+        uint4* base = ws.units + ws.ovf_base * 4u;
         for (uint64_t s = (uint64_t)(b - n_main) * kRecBlock + threadIdx.x; s < cnt;
              s += (uint64_t)ovf_blocks * kRecBlock)
-            record_item<Newton>(sv, ws, base + s, roff, n_slots, out, cap_records, arcs, xi);
+            record_item<Newton>(sv, ws, UnitAt{base + s, ws.ovf_cap}, roff, n_slots, out, cap_records, arcs, xi);
     }
 }
 
