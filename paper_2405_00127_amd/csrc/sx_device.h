@@ -653,6 +653,7 @@ constexpr uint32_t kIfDneg = 1u << 11;      // evolute: side traversed backwards
 constexpr uint32_t kIfInnerFirst = 1u << 12;  // join: inner part before the outer part
 constexpr uint32_t kIfKSame = 1u << 13;       // offset, h == 0: curvature keeps its sign over the range
 constexpr uint32_t kIfNewton = 1u << 14;      // offset: place points by the Newton-refined exact inverse
+constexpr uint32_t kIfShort = 1u << 15;       // evolute, join: an item of one chunk in one unit (short_unit)
 constexpr uint32_t kXBitsShift = 16;          // offset: the split at the branch breaks (bits 16-22)
 // join outer part kind (bits 16..19), inner part kind (bits 20..21)
 enum { kOutLine1 = 0, kOutLine2 = 1, kOutLine3 = 2, kOutRound = 3 };
@@ -717,6 +718,7 @@ static_assert(Units<OffsetP>::n == 1 && Units<EvoluteP>::n == 2 && Units<JoinP>:
 static_assert(offsetof(EvoluteP, zero) == (kUnitWords - kHdrWords) * 4 && offsetof(JoinP, zero) == (kUnitWords - kHdrWords) * 4,
               "second unit starts with a zero word");
 
+SX_FN uint32_t inner_count(uint32_t inner) { return inner == kInPivot ? 2u : (inner == kInSmooth ? 1u : 0u); }
 SX_FN uint32_t chunks(uint32_t n, uint32_t K) { return (n + K - 1) / K; }
 
 struct Cfg {
@@ -758,19 +760,82 @@ SX_HD void write_item(Unit* units, uint64_t base, uint32_t hdr, uint32_t path, u
 // of a region of `stride` units at p[v * stride + u], so that neighbouring
 // lanes, which hold neighbouring units, read and write consecutive addresses
 // (64-byte units one after another took a cache line per lane and quarter).
-// Quarters past the payload are left as they are.
+// Quarters past the payload are left as they are.  An item of one chunk takes
+// one unit whatever its kind: evolutes and joins leave out the words that say
+// which chunk they are and those that their kind does not use.
 struct UnitAt {
     uint4* p;         // quarter 0 of the first unit
     uint64_t stride;
 };
 template <class P>
+SX_FN uint32_t item_units(uint32_t nrec, uint32_t K) {
+    const uint32_t nc = chunks(nrec, K);
+    return nc > 1u ? nc * Units<P>::n : nc;
+}
+constexpr uint32_t kEvoSplit = kUnitWords - kHdrWords;  // payload words before the zero word (joins too)
+SX_FN void short_unit(uint32_t* s, uint32_t n0, const EvoluteP& p) {
+    uint32_t v[sizeof(EvoluteP) / 4];
+    memcpy(v, &p, sizeof(p));
+    s[3] = n0;
+    for (uint32_t q = 0; q < kEvoSplit; q++) s[4 + q] = v[q];
+    s[14] = v[kEvoSplit + 1];
+    s[15] = v[kEvoSplit + 2];
+}
+// (a join or cap is its slot's only item: n0 = 0)
+SX_FN void short_unit(uint32_t* s, uint32_t, const JoinP& p) {
+    const uint32_t outer = (s[0] >> 16) & 15u;
+    uint32_t v[sizeof(JoinP) / 4];
+    memcpy(v, &p, sizeof(p));
+    for (uint32_t q = 0; q < kEvoSplit; q++) s[3 + q] = v[q];
+    s[13] = f_bits(outer == kOutRound ? p.a0 : p.ax);
+    s[14] = f_bits(outer == kOutRound ? p.sweep : p.ay);
+    s[15] = f_bits(p.w);
+    if (outer == kOutLine3) {  // (a square cap: no inner part)
+        s[7] = f_bits(p.bx);
+        s[8] = f_bits(p.by);
+    }
+}
+// The 28 words of the two-unit form of a short unit.
+SX_FN void long_item(const uint32_t* s, uint32_t* w) {
+    const uint32_t hdr = s[0], nrec = item_n(hdr);
+    const bool evo = (hdr & 15u) == kItemEvolute;
+    w[0] = hdr;
+    w[1] = s[1];
+    w[2] = s[2];
+    w[3] = evo ? s[3] : 0u;
+    w[4] = 0u;
+    w[5] = nrec;
+    for (uint32_t q = 0; q < kEvoSplit; q++) w[kHdrWords + q] = evo ? s[4 + q] : s[3 + q];
+    w[16] = 0u;
+    w[17] = evo ? s[14] : s[13];  // E1 or the round part's a0, sweep and w
+    w[18] = evo ? s[15] : s[14];
+    w[19] = s[15];
+    w[20] = s[13];  // the miter point or the square corners
+    w[21] = s[14];
+    w[22] = s[7];
+    w[23] = s[8];
+    w[24] = nrec - inner_count((hdr >> 20) & 3u);
+}
+template <class P>
 SX_FN void write_item_q(const UnitAt& at, uint32_t hdr, uint32_t path, uint32_t slot, uint32_t n0, uint32_t nrec,
                         uint32_t K, const P& p) {
     constexpr uint32_t U = Units<P>::n, W = kHdrWords + (uint32_t)(sizeof(P) / 4), Q = (W + 3u) / 4u;
     uint32_t w[4 * Q];
+    const uint32_t nc = chunks(nrec, K);
+    if constexpr (U == 2u) {
+        if (nc == 1u) {
+            w[0] = hdr | kIfShort | (nrec << 24);
+            w[1] = path;
+            w[2] = slot;
+            short_unit(w, n0, p);
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; q++)
+                at.p[q * at.stride] = make_uint4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
+            return;
+        }
+    }
     w[4 * Q - 1] = w[4 * Q - 2] = w[4 * Q - 3] = 0u;
     memcpy(w + kHdrWords, &p, sizeof(P));
-    const uint32_t nc = chunks(nrec, K);
     for (uint32_t c = 0; c < nc; c++) {
         const uint32_t nchunk = (c + 1 < nc) ? K : nrec - c * K;
         w[0] = hdr | (nchunk << 24);
@@ -988,7 +1053,6 @@ SX_FN double round_step(double w, double tau_flat) {
 SX_FN uint32_t round_count(const Cfg& cfg, double w, double sweep) {
     return cfg.arcs ? ceil_count(fabs(sweep) * (1.0 / kHalfPi)) : ceil_count(fabs(sweep) * rcp_d(round_step(w, cfg.tau_flat)));
 }
-SX_FN uint32_t inner_count(uint32_t inner) { return inner == kInPivot ? 2u : (inner == kInSmooth ? 1u : 0u); }
 SX_FN uint32_t outer_count(uint32_t outer, uint32_t n_round) {
     return outer == kOutLine1 ? 1u : (outer == kOutLine2 ? 2u : (outer == kOutLine3 ? 3u : n_round));
 }

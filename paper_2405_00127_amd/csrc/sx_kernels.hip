@@ -763,7 +763,7 @@ struct CountSink {
     uint32_t units;
     template <class P>
     __device__ void put(uint32_t, uint32_t nrec, uint32_t K, const P&) {
-        units += chunks(nrec, K) * Units<P>::n;
+        units += item_units<P>(nrec, K);
     }
 };
 template <bool Stats>
@@ -778,7 +778,7 @@ struct UnitSink {
         if constexpr (Stats) st[(hdr & 15u) == kItemOffset ? kStRanges : kStEvolutes]++;
         if (at.p) {
             write_item_q(at, hdr, path, slot, n, nrec, K, p);
-            at.p += chunks(nrec, K) * Units<P>::n;
+            at.p += item_units<P>(nrec, K);
         }
         n += nrec;
     }
@@ -1079,7 +1079,7 @@ __global__ __launch_bounds__(kTailBlock, 3) void tail_kernel(SceneView sv, Cfg c
             Seg sg;
             fetch_tag(sv, i, ti, sg);
             emit_tail(k, cfg, sv, i, ti, sg);
-            need = k.nrec ? chunks(k.nrec, cfg.K) * Units<JoinP>::n : 0u;
+            need = item_units<JoinP>(k.nrec, cfg.K);
             if (win && need) local = atomicAdd(&s_cnt[tile - tile_lo], need);
         }
         __syncthreads();
@@ -1115,7 +1115,12 @@ __device__ __forceinline__ void record_item(const SceneView& sv, const ItemWs& w
     for (int q = 0; q < 4; q++) reinterpret_cast<uint4*>(w)[q] = u.p[q * u.stride];
     const uint32_t kind = w[0] & 15u;
     if (kind == 0u) return;
-    if (kind != kItemOffset) {
+    if (w[0] & kIfShort) {
+        uint32_t s[kUnitWords];
+#pragma unroll
+        for (uint32_t q = 0; q < kUnitWords; q++) s[q] = w[q];
+        long_item(s, w);
+    } else if (kind != kItemOffset) {
 #pragma unroll
         for (int q = 0; q < 3; q++) reinterpret_cast<uint4*>(w)[4 + q] = u.p[q * u.stride + 1u];
     }
