@@ -653,7 +653,7 @@ constexpr uint32_t kIfDneg = 1u << 11;      // evolute: side traversed backwards
 constexpr uint32_t kIfInnerFirst = 1u << 12;  // join: inner part before the outer part
 constexpr uint32_t kIfKSame = 1u << 13;       // offset, h == 0: curvature keeps its sign over the range
 constexpr uint32_t kIfNewton = 1u << 14;      // offset: place points by the Newton-refined exact inverse
-constexpr uint32_t kIfShort = 1u << 15;       // evolute, join: an item of one chunk in one unit (short_unit)
+constexpr uint32_t kIfShort = 1u << 15;       // evolute, join: one chunk, in one unit (short_unit); offset: no second quarter
 constexpr uint32_t kXBitsShift = 16;          // offset: the split at the branch breaks (bits 16-22)
 // join outer part kind (bits 16..19), inner part kind (bits 20..21)
 enum { kOutLine1 = 0, kOutLine2 = 1, kOutLine3 = 2, kOutRound = 3 };
@@ -678,13 +678,15 @@ struct ItemHdr {
 constexpr uint32_t kHdrWords = 6;
 SX_FN uint32_t item_n(uint32_t hdr) { return hdr >> 24; }
 
-// offset-item payload: the range [ua, ub] of side h, its exact end points,
+// offset-item payload (each line here a quarter of the unit, with the header's
+// last two words before ua): the range [ua, ub] of side h, its exact end points,
 // and for density placement the F increment over the range and the FP32 sum
 // of its branch pieces' x lengths (from the FP64 count)
 struct OffsetP {
-    float ua, du, len0, fh;  // u range, x length of its first branch piece, side h
+    float ua, du;  // u range
     float Pax, Pay, Pbx, Pby;
-    float dF, dF0;  // F increment of the range and of its first branch piece
+    float len0, fh;  // x length of the range's first branch piece, side h
+    float dF, dF0;   // F increment of the range and of its first branch piece
     // (with kIfNewton: len0 and dF0 hold the low and high words of the FP64
     // density coordinate x at ua, dF the x length of the range)
 };
@@ -847,6 +849,23 @@ SX_FN void write_item_q(const UnitAt& at, uint32_t hdr, uint32_t path, uint32_t 
 #pragma unroll
         for (uint32_t q = 0; q < Q; q++)
             at.p[(q & 3u) * at.stride + c * U + (q >> 2)] = make_uint4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
+    }
+}
+
+// An offset item leaves out the second quarter (its chunk and u range) when it
+// is one chunk of the whole range [0, 1], and then the fourth one (the
+// placement) too when it is a single record.
+SX_FN void write_item_q(const UnitAt& at, uint32_t hdr, uint32_t path, uint32_t slot, uint32_t n0, uint32_t nrec,
+                        uint32_t K, const OffsetP& p) {
+    const uint32_t nc = chunks(nrec, K);
+    const bool brief = nc == 1u && p.ua == 0.0f && p.du == 1.0f;
+    for (uint32_t c = 0; c < nc; c++) {
+        const uint32_t nchunk = (c + 1 < nc) ? K : nrec - c * K;
+        at.p[c] = make_uint4(hdr | (brief ? kIfShort : 0u) | (nchunk << 24), path, slot, n0 + c * K);
+        if (!brief) at.p[at.stride + c] = make_uint4(c * K, nrec, f_bits(p.ua), f_bits(p.du));
+        at.p[2u * at.stride + c] = make_uint4(f_bits(p.Pax), f_bits(p.Pay), f_bits(p.Pbx), f_bits(p.Pby));
+        if (!brief || nrec > 1u)
+            at.p[3u * at.stride + c] = make_uint4(f_bits(p.len0), f_bits(p.fh), f_bits(p.dF), f_bits(p.dF0));
     }
 }
 
@@ -1356,9 +1375,9 @@ SX_HD inline void emit_item(const uint32_t* it, const float* es_rec, const XIncF
         Place pl;
         PlaceN pn;
         const bool newton = Newton && (hdr & kIfNewton) != 0;
+        const uint32_t n = h.ntot;
         if (newton) place_newton_init(pn, p);
         else place_init(pl, es, p, hdr, xi);
-        const uint32_t n = h.ntot;
         pl.inv_n = 1.0f / (float)n;
         const bool neg = (hdr & kIfDirNeg) != 0;
         // point k0 of the chunk

@@ -1110,17 +1110,26 @@ __device__ __forceinline__ void record_item(const SceneView& sv, const ItemWs& w
                                             const uint64_t* roff, uint64_t n_slots, float* out, uint64_t cap,
                                             int arcs, const XIncF& xi, float* stage = nullptr, uint64_t lo = 0,
                                             uint64_t hi = 0) {
-    uint32_t w[2 * kUnitWords];
-#pragma unroll
-    for (int q = 0; q < 4; q++) reinterpret_cast<uint4*>(w)[q] = u.p[q * u.stride];
+    uint32_t w[2 * kUnitWords] = {};
+    *reinterpret_cast<uint4*>(w) = u.p[0];
+    *reinterpret_cast<uint4*>(w + 8) = u.p[2u * u.stride];
     const uint32_t kind = w[0] & 15u;
     if (kind == 0u) return;
-    if (w[0] & kIfShort) {
+    // the quarters that the item has (write_item_q), beside the slot's record
+    // offset and spiral (all four at once, in small scenes: 1 us slower)
+    const bool off = kind == kItemOffset, brief = (w[0] & kIfShort) != 0u;
+    const bool single = off && brief && item_n(w[0]) == 1u;
+    if (!off || !brief) *reinterpret_cast<uint4*>(w + 4) = u.p[u.stride];
+    if (!single) *reinterpret_cast<uint4*>(w + 12) = u.p[3u * u.stride];
+    if (off) {
+        w[5] = brief ? item_n(w[0]) : w[5];
+        w[7] = brief ? f_bits(1.0f) : w[7];
+    } else if (brief) {
         uint32_t s[kUnitWords];
 #pragma unroll
         for (uint32_t q = 0; q < kUnitWords; q++) s[q] = w[q];
         long_item(s, w);
-    } else if (kind != kItemOffset) {
+    } else {
 #pragma unroll
         for (int q = 0; q < 3; q++) reinterpret_cast<uint4*>(w)[4 + q] = u.p[q * u.stride + 1u];
     }
@@ -1129,7 +1138,7 @@ __device__ __forceinline__ void record_item(const SceneView& sv, const ItemWs& w
     const uint64_t end = roff[slot + 1] < cap ? roff[slot + 1] : cap;
     RecOut o{out, roff[slot] + w[3], end, path, arcs, stage, lo, hi};
     __align__(16) float es[8];
-    if (kind != kItemJoin) {
+    if (kind == kItemEvolute || (off && (arcs || !single))) {  // (a single line needs no spiral)
         *reinterpret_cast<uint4*>(es) = ws.es_lo[slot];
         *reinterpret_cast<uint4*>(es + 4) = ws.es_hi[slot];
     }
