@@ -16,7 +16,7 @@ namespace sx {
 // halves, each an array over the slots).
 struct WsCtl {
     unsigned long long ovf_n;        // overflow units requested
-    unsigned long long items_total;  // units requested by all tiles
+    unsigned long long items_total;  // units requested by all tiles (of a run that dropped some)
     unsigned long long slots_total;  // slots of the last expansion
     unsigned long long result[2];    // records and status, for synchronous readback
 };

@@ -1010,10 +1010,7 @@ __global__ __launch_bounds__(kSlotBlock, MinWaves) void slot_kernel(SceneView sv
             }
         }
         __syncthreads();
-        if (t < n_gt) {
-            ws.tile_n[tile0 + t] = s_n[t];
-            atomicAdd(&ws.ctl->items_total, (unsigned long long)s_n[t]);
-        }
+        if (t < n_gt) ws.tile_n[tile0 + t] = s_n[t];
     }
     if (Stats) {
         for (int q = kStPieces; q <= kStEvolutes; q++)
@@ -1052,12 +1049,10 @@ __global__ __launch_bounds__(kTailBlock, 3) void tail_kernel(SceneView sv, Cfg c
                                                             unsigned long long* __restrict__ stats) {
     __shared__ uint32_t s_cnt[kTailWin];
     __shared__ uint32_t s_at[kTailWin];
-    __shared__ uint32_t s_asked;
     const uint32_t n = sv.n_tags;
     if (base[n] > slot_cap) return;  // reported by the record kernel
     const uint32_t t = threadIdx.x;
-    if (t == 0) s_asked = 0u;
-    uint32_t asked = 0, joins = 0;
+    uint32_t joins = 0;
     for (uint32_t i0 = blockIdx.x * kTailBlock; i0 < n; i0 += gridDim.x * kTailBlock) {
         const uint32_t i = i0 + t;
         const uint32_t ilast = min(n, i0 + kTailBlock) - 1u;
@@ -1092,14 +1087,10 @@ __global__ __launch_bounds__(kTailBlock, 3) void tail_kernel(SceneView sv, Cfg c
                 if (u.p) write_item_q(u, k.hdr, path_of(sv, i), (uint32_t)slot, 0u, k.nrec, cfg.K, k.p);
             }
             rc[slot] = k.n;
-            asked += need;
             if (Stats) joins += k.st[kStJoins];
         }
         __syncthreads();  // s_cnt and s_at are reused
     }
-    atomicAdd(&s_asked, asked);
-    __syncthreads();
-    if (t == 0 && s_asked) atomicAdd(&ws.ctl->items_total, (unsigned long long)s_asked);
     if (Stats && joins) atomicAdd(&stats[kStJoins], (unsigned long long)joins);
 }
 
@@ -1170,6 +1161,14 @@ __global__ __launch_bounds__(kRecBlock, Newton ? 3 : 6) void record_kernel(Scene
         dst[0] = n_slots <= slot_cap ? roff[n_slots] : 0ull;
         dst[1] = fit ? 0ull : 1ull;
         ws.ctl->slots_total = n_slots;
+    }
+    if (!fit && n_slots <= slot_cap && blockIdx.x == 0u) {
+        // the units to make room for (counting them as they were taken, one
+        // atomic per block on one address, 13 ns each, set the tail launch's
+        // length: 69 us of the 1M-segment map scene, 43 without)
+        unsigned long long asked = 0;
+        for (uint32_t i = threadIdx.x; i < piece_tile_count(n_slots - sv.n_tags); i += kRecBlock) asked += ws.tile_n[i];
+        if (asked) atomicAdd(&ws.ctl->items_total, asked);
     }
     // nothing is written when the records exceed the capacity, or slots or items were dropped
     if (!fit || roff[n_slots] > cap_records) return;
