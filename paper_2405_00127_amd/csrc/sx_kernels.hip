@@ -29,6 +29,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "sx_device.h"
 #include "sx_kernels.h"
@@ -749,6 +750,12 @@ constexpr uint32_t kRecGrid = 8192;  // grid cap of the record kernel (tiles str
 constexpr uint32_t kStageWords = 6400;  // LDS words staging a tile's records (25 KB)
 constexpr uint32_t kRecSplit = 8;     // most blocks of a tile (scenes of few tiles)
 constexpr uint32_t kRecSplitGrid = 1024;  // record-kernel blocks that a small scene spreads over
+// Slots from which the items, about 100 bytes a slot, are more than the 256 MB
+// cache holds until they are read: they are then loaded past the caches (1M
+// map segments, 3.7M slots: records 223 -> 210 us; 0.9M slots of stress cubics
+// the other way, 56 -> 62 us).  Stored past them, the piece launch's lines,
+// which fill up bit by bit, took 415 us instead of 243; the tails' nothing.
+constexpr uint64_t kStreamSlots = 1u << 21;
 constexpr uint32_t kOvfBlocks = 512;  // most record-kernel blocks striding over the overflow units
 
 // Unit allocation of the piece launch.  A piece's items are first counted
@@ -830,10 +837,12 @@ __device__ __forceinline__ uint64_t tail_tile(const uint64_t* base, uint32_t i) 
 // (the piece's k0, k1, L, width and cusp go through the wave's part of LDS,
 // so no block barrier is needed), and then each thread writes its piece's
 // items in canonical order.
-// Bound by FP64 issue (about 155 us of the map scene's 279, 1M segments) and by
-// the items' 0.5 GB written after it.  With the library's divisions, square
-// roots and arctangents, separate multiplies and adds in the polynomials, and
-// all six branch breaks walked per range: 362 us.
+// Bound by instruction issue (107M wave instructions, mostly FP64, are 175 us of
+// the map scene's 245, 1M segments, with 45% of the lanes active) and by the
+// items written after it.  With the library's divisions, square roots and
+// arctangents, separate multiplies and adds in the polynomials, and all six
+// branch breaks walked per range: 362 us; with whole items of one or two
+// units: 279 us.
 template <int MinWaves, bool Stats, bool Newton>
 __global__ __launch_bounds__(kSlotBlock, MinWaves) void slot_kernel(SceneView sv, Cfg cfg, ItemWs ws,
                                                                     const Slot* __restrict__ pcs,
@@ -1041,7 +1050,10 @@ struct TailSink {
 // after the piece launch's items: a block's consecutive tags have increasing
 // tail tiles spanning a few tiles, so it counts its units per tile in LDS and
 // takes them from each tile's counter with one global atomic (per lane only
-// when the block spans more than kTailWin tiles).
+// when the block spans more than kTailWin tiles).  Bound by a block's chain of
+// dependent loads, its tiles' atomics and the write: 43 us for 1M tags with
+// blocks of 128 or 256, 50 us with 1,024, whose few blocks also leave a small
+// scene on few CUs (1,000 cubics: 6.9, 7.7, 12 and 18 us with 128 to 1,024).
 template <bool Stats>
 __global__ __launch_bounds__(kTailBlock, 3) void tail_kernel(SceneView sv, Cfg cfg, ItemWs ws,
                                                             const uint64_t* __restrict__ base, uint64_t slot_cap,
@@ -1094,24 +1106,33 @@ __global__ __launch_bounds__(kTailBlock, 3) void tail_kernel(SceneView sv, Cfg c
     if (Stats && joins) atomicAdd(&stats[kStJoins], (unsigned long long)joins);
 }
 
+// Stream: an item is read once, past the caches (kStreamSlots).
+template <bool Stream>
+__device__ __forceinline__ uint4 load_quarter(const uint4* p) {
+    typedef uint32_t V __attribute__((ext_vector_type(4)));
+    if (!Stream) return *p;
+    const V v = __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 // One item chunk starting at a unit: loads its one or two units (the quarters
 // its kind fills) and writes its records.
-template <bool Newton>
+template <bool Newton, bool Stream>
 __device__ __forceinline__ void record_item(const SceneView& sv, const ItemWs& ws, const UnitAt& u,
                                             const uint64_t* roff, uint64_t n_slots, float* out, uint64_t cap,
                                             int arcs, const XIncF& xi, float* stage = nullptr, uint64_t lo = 0,
                                             uint64_t hi = 0) {
     uint32_t w[2 * kUnitWords] = {};
-    *reinterpret_cast<uint4*>(w) = u.p[0];
-    *reinterpret_cast<uint4*>(w + 8) = u.p[2u * u.stride];
+    *reinterpret_cast<uint4*>(w) = load_quarter<Stream>(u.p);
+    *reinterpret_cast<uint4*>(w + 8) = load_quarter<Stream>(u.p + 2u * u.stride);
     const uint32_t kind = w[0] & 15u;
     if (kind == 0u) return;
     // the quarters that the item has (write_item_q), beside the slot's record
     // offset and spiral (all four at once, in small scenes: 1 us slower)
     const bool off = kind == kItemOffset, brief = (w[0] & kIfShort) != 0u;
     const bool single = off && brief && item_n(w[0]) == 1u;
-    if (!off || !brief) *reinterpret_cast<uint4*>(w + 4) = u.p[u.stride];
-    if (!single) *reinterpret_cast<uint4*>(w + 12) = u.p[3u * u.stride];
+    if (!off || !brief) *reinterpret_cast<uint4*>(w + 4) = load_quarter<Stream>(u.p + u.stride);
+    if (!single) *reinterpret_cast<uint4*>(w + 12) = load_quarter<Stream>(u.p + 3u * u.stride);
     if (off) {
         w[5] = brief ? item_n(w[0]) : w[5];
         w[7] = brief ? f_bits(1.0f) : w[7];
@@ -1147,7 +1168,9 @@ static_assert(kHdrWords + sizeof(JoinP) / 4 <= kUnitWords + 12 && kHdrWords + si
 // chunks of 4.  The first block also publishes dst[0] = records and dst[1] =
 // 0 when everything fit, else 1 (slots or items were dropped: the workspace
 // must grow; the counters stay in ws.ctl), for which a launch of its own
-// took 4.6 us.
+// took 4.6 us.  Bound by its bytes and by waiting for them, not by the points:
+// 1M map segments, 210 us; of 243 us before the items shrank, 237 were left
+// with every point's computation taken out, 222 without the copy out.
 template <bool Newton>
 __global__ __launch_bounds__(kRecBlock, Newton ? 3 : 6) void record_kernel(SceneView sv, ItemWs ws, int arcs,
                                                            const uint64_t* __restrict__ roff,
@@ -1196,14 +1219,20 @@ __global__ __launch_bounds__(kRecBlock, Newton ? 3 : 6) void record_kernel(Scene
             // staged: those records are written by the overflow blocks)
             const uint64_t n_st = ws.tile_n[tile] > ws.region_cap || split > 1u ? 0u
                                   : (n_rec < kStageWords / words ? n_rec : kStageWords / words);
-            for (uint32_t s2 = part * kRecBlock + threadIdx.x; s2 < cnt; s2 += split * kRecBlock)
-                record_item<Newton>(sv, ws, UnitAt{base + s2, ws.region_cap}, roff, n_slots, out, cap_records, arcs, xi, s_stage, lo,
-                                    lo + n_st);
+            auto items = [&](auto st) {
+                for (uint32_t s2 = part * kRecBlock + threadIdx.x; s2 < cnt; s2 += split * kRecBlock)
+                    record_item<Newton, decltype(st)::value>(sv, ws, UnitAt{base + s2, ws.region_cap}, roff, n_slots,
+                                                             out, cap_records, arcs, xi, s_stage, lo, lo + n_st);
+            };
+            if (n_slots > kStreamSlots) items(std::true_type{});
+            else items(std::false_type{});
             if (split > 1u) continue;
             __syncthreads();
             uint32_t* dst32 = reinterpret_cast<uint32_t*>(out) + lo * words;
             const uint32_t* src = reinterpret_cast<const uint32_t*>(s_stage);
-            for (uint32_t d = threadIdx.x; d < (uint32_t)n_st * words; d += kRecBlock) dst32[d] = src[d];
+            // (written once: past the caches)
+            for (uint32_t d = threadIdx.x; d < (uint32_t)n_st * words; d += kRecBlock)
+                __builtin_nontemporal_store(src[d], dst32 + d);
             __syncthreads();
         }
     } else {
@@ -1211,7 +1240,7 @@ __global__ __launch_bounds__(kRecBlock, Newton ? 3 : 6) void record_kernel(Scene
         uint4* base = ws.units + ws.ovf_base * 4u;
         for (uint64_t s = (uint64_t)(b - n_main) * kRecBlock + threadIdx.x; s < cnt;
              s += (uint64_t)ovf_blocks * kRecBlock)
-            record_item<Newton>(sv, ws, UnitAt{base + s, ws.ovf_cap}, roff, n_slots, out, cap_records, arcs, xi);
+            record_item<Newton, false>(sv, ws, UnitAt{base + s, ws.ovf_cap}, roff, n_slots, out, cap_records, arcs, xi);
     }
 }
 
