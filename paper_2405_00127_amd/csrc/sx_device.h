@@ -1118,7 +1118,10 @@ SX_HD void emit_cap(Sink& k, const Cfg& cfg, int cap, D2 p, D2 u, double w, bool
 
 template <class Sink>
 SX_HD void emit_join(Sink& k, const Cfg& cfg, int join, double miter_limit, D2 p, D2 ta, D2 tb, double w) {
-    D2 ua = unit(ta), ub = unit(tb);
+    // (correctly rounded: a right angle's turn is pi / 2 and a reversal's cross
+    // product 0 exactly, as the oracle has them)
+    const double ra = 1.0 / sqrt(ta.x * ta.x + ta.y * ta.y), rb = 1.0 / sqrt(tb.x * tb.x + tb.y * tb.y);
+    D2 ua = d2(ta.x * ra, ta.y * ra), ub = d2(tb.x * rb, tb.y * rb);
     double cr = cross(ua, ub), dp = dot(ua, ub);
     D2 Na = rnormal(ua), Nb = rnormal(ub);
     JoinP jp = {};
@@ -1141,7 +1144,7 @@ SX_HD void emit_join(Sink& k, const Cfg& cfg, int join, double miter_limit, D2 p
     jp.fx = fi.x; jp.fy = fi.y; jp.px = fp.x; jp.py = fp.y; jp.tx = ti.x; jp.ty = ti.y;
     uint32_t outer = kOutLine1;
     if (join == kJoinRound) {
-        double dphi = unit_angle(cr, dp, rcp_d(1.0 + fabs(dp)));  // FP64: it decides the count
+        double dphi = atan2(cr, dp);  // FP64: it decides the count
         jp.a0 = atan2f((float)(from.y - p.y), (float)(from.x - p.x));
         jp.sweep = (float)fabs(dphi); jp.w = (float)w;
         jp.n_outer = round_count(cfg, w, fabs(dphi));
@@ -1525,36 +1528,37 @@ SX_FN D2 cubic_chord(D2 A2, D2 C3, double t0, double dt, D2 q0) {
 }
 // length of the control polygon
 SX_FN double poly_len(const Seg& s) { return len(s.D1) + len(s.D2_ - s.D1) + len(s.D3 - s.D2_); }
-// The unit tangent at t (Section 7.3: a near-zero q at an interior t is
-// replaced by a sample beside it; the polygon's length, three square roots,
-// is needed only below its bound by coordinate sums).
-SX_FN D2 unit_tan(const Seg& s, double t, D2 q) {
-    if (t == 0.0) return unit(s.ts);
-    if (t == 1.0) return unit(s.te);
+
+// What decides ties is computed in the oracle's order of operations, so that
+// symmetric curves give the same bits on both sides (a quarter circle's end
+// angles are equal and sum to pi / 2; in the power form above they came out
+// an ulp apart, and its side then took the counts of a spiral, or two arcs):
+// q = B'/3 in Bernstein form, and B(t0 + dt) - B(t0) by the terminating
+// Taylor expansion, q0 = q(t0).
+SX_FN D2 bern_q(const Seg& s, double t) {
+    const double mt = 1.0 - t, wa = mt * mt, wb = 2.0 * t * mt, wc = t * t;
+    const D2 a = s.D1, b = s.D2_ - s.D1, c = s.D3 - s.D2_;
+    return d2(wa * a.x + wb * b.x + wc * c.x, wa * a.y + wb * b.y + wc * c.y);
+}
+SX_FN D2 taylor_chord(const Seg& s, double t0, double dt, D2 q0) {
+    const double mt = 1.0 - t0, e1 = 3.0 * dt, e2 = 3.0 * dt * dt, e3 = dt * dt * dt;
+    const D2 B2 = s.D3 - s.D2_ * 2.0 + s.D1;
+    const D2 b2 = d2(mt * s.A2.x + t0 * B2.x, mt * s.A2.y + t0 * B2.y);
+    return d2(e1 * q0.x + e2 * b2.x + e3 * s.C3.x, e1 * q0.y + e2 * b2.y + e3 * s.C3.y);
+}
+// The tangent direction at t, q = q(t) (Section 7.3: a near-zero q at an
+// interior t is replaced by a sample beside it; the polygon's length, three
+// square roots, is needed only below its bound by coordinate sums).
+SX_FN D2 tangent(const Seg& s, double t, D2 q) {
+    if (t == 0.0) return s.ts;
+    if (t == 1.0) return s.te;
     const D2 e = s.D2_ - s.D1, f = s.D3 - s.D2_;
     const double sum = fabs(s.D1.x) + fabs(s.D1.y) + fabs(e.x) + fabs(e.y) + fabs(f.x) + fabs(f.y);
     const double ss = dot(q, q), most = kEpsQ * sum;
     if (!(ss >= most * most)) {
         const double eps = kEpsQ * poly_len(s);
-        if (!(ss >= eps * eps)) q = cubic_q(s.D1, s.A2, s.C3, (t + kDeltaT < 1.0) ? t + kDeltaT : t - kDeltaT);
+        if (!(ss >= eps * eps)) q = bern_q(s, (t + kDeltaT < 1.0) ? t + kDeltaT : t - kDeltaT);
     }
-    return unit(q);
-}
-
-// q at t in Bernstein form, with Section 7.3's replacement: the tangents that
-// a pivot turns between.  At an exact reversal the turn is pi either way and
-// its sign is that of a cross product of two opposite vectors, rounding
-// alone; this is the form whose rounding the oracle shares.
-SX_FN D2 pivot_tan(const Seg& s, double t) {
-    if (t == 0.0) return s.ts;
-    if (t == 1.0) return s.te;
-    const D2 a = s.D1, b = s.D2_ - s.D1, c = s.D3 - s.D2_;
-    auto at = [&](double x) {
-        const double mt = 1.0 - x, wa = mt * mt, wb = 2.0 * x * mt, wc = x * x;
-        return d2(wa * a.x + wb * b.x + wc * c.x, wa * a.y + wb * b.y + wc * c.y);
-    };
-    D2 q = at(t);
-    if (len(q) < kEpsQ * poly_len(s)) q = at((t + kDeltaT < 1.0) ? t + kDeltaT : t - kDeltaT);
     return q;
 }
 
@@ -1797,10 +1801,11 @@ SX_HD inline void piece_es(const Seg& s, bool line, uint32_t t0_u, uint32_t dept
     const double dt = depth_dt(depth);
     const double t0 = (double)t0_u * dt;
     const double t1 = t0 + dt;
-    const D2 q0 = line ? s.D1 : cubic_q(s.D1, s.A2, s.C3, t0);
-    const D2 u0 = unit_tan(s, t0, q0);
-    const D2 u1 = line ? u0 : unit_tan(s, t1, cubic_q(s.D1, s.A2, s.C3, t1));
-    const D2 chord = line ? s.D3 : cubic_chord(s.A2, s.C3, t0, dt, q0);
+    const D2 q0 = t0 == 0.0 ? s.D1 : bern_q(s, t0);
+    const D2 ta = tangent(s, t0, q0);
+    const D2 tb = line ? ta : tangent(s, t1, bern_q(s, t1));
+    const D2 u0 = unit(ta), u1 = line ? u0 : unit(tb);
+    const D2 chord = line ? s.D3 : taylor_chord(s, t0, dt, q0);
     const double cc = dot(chord, chord), rcl = cc > 0.0 ? rsqrt_d(cc) : 0.0, cl = cc * rcl;
     es.pivot = pivot;
     es.p0 = cubic_world(s, t0);
@@ -1816,17 +1821,13 @@ SX_HD inline void piece_es(const Seg& s, bool line, uint32_t t0_u, uint32_t dept
         rot = chord;
         base = atan2(rot.y, rot.x);
     } else if (pivot) {
-        const D2 a = pivot_tan(s, t0), b = pivot_tan(s, t1);
-        es.k0 = atan2(cross(a, b), dot(a, b));
+        es.k0 = atan2(cross(ta, tb), dot(ta, tb));
         es.k1 = 0.0;
         c = es_chord(0.5 * es.k0, 0.5 * es.k0);
-        base = atan2(a.y, a.x) + 0.5 * es.k0;
+        base = atan2(ta.y, ta.x) + 0.5 * es.k0;
     } else {
         // the end angles between the tangents and the chord
-        const double sn0 = cross(u0, chord) * rcl, sn1 = cross(chord, u1) * rcl;
-        const double c0 = dot(u0, chord) * rcl, c1 = dot(chord, u1) * rcl;
-        const double e0 = 1.0 + fabs(c0), e1 = 1.0 + fabs(c1), r = rcp_d(e0 * e1);
-        const double th0 = unit_angle(sn0, c0, r * e1), th1 = unit_angle(sn1, c1, r * e0);
+        const double th0 = atan2(cross(ta, chord), dot(ta, chord)), th1 = atan2(cross(chord, tb), dot(chord, tb));
         es.k0 = th0 + th1;
         es.k1 = es_k1(th0, th1);
         c = es_chord(th0, th1);

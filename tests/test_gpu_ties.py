@@ -1,0 +1,42 @@
+"""Counts of drawings whose decisions are ties (shapes.py) on the GPU, through
+the C ABI: those of the oracle, with no margin for the tags whose decisions
+are close; the records at the parity bars."""
+import numpy as np
+import pytest
+
+import oracle as O
+import parity as P
+import shapes
+from paper_2405_00127_amd import scenes as S
+
+pytestmark = pytest.mark.gpu
+
+
+def _same_as_the_oracle(sc, newton=False):
+    import torch
+
+    from paper_2405_00127_amd import binding as B
+
+    torch.cuda.set_device(0)
+    ctx = B.Context(0, density=B.DENSITY_NEWTON if newton else B.DENSITY_APPROX)
+    try:
+        scene = ctx.encode(sc)
+        recs, _, _ = ctx.expand(scene, sc.tolerance, sc.output_mode)
+        counts = ctx.counts(scene, sc.tolerance, sc.output_mode).cpu().numpy().astype(np.uint32)
+        ref = O.expand(sc, fit_mode=O.DENSITY_NEWTON) if newton else O.expand(sc)
+        assert np.array_equal(counts, ref.counts), int((counts != ref.counts).sum())
+        rep = P.compare(counts, B.records_to_numpy(recs, sc.output_mode), ref, sc.output_mode)
+        assert rep.ok(), rep
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("name,mode,newton", [(n, m, f) for n in shapes.SYMMETRIC for m, f in
+                                              ((S.OUT_LINES, False), (S.OUT_ARCS, False), (S.OUT_LINES, True))
+                                              if m == S.OUT_LINES or n not in shapes.LINES_ONLY])
+def test_symmetric_shapes_have_the_oracles_counts(name, mode, newton):
+    for s in (1.0, 2.0, 1.0 / 3.0):
+        sc = shapes.SYMMETRIC[name](shapes.scale(s))
+        sc.output_mode = mode
+        print("ties", name, mode, newton, s, flush=True)
+        _same_as_the_oracle(sc, newton)
