@@ -145,6 +145,12 @@ SX_FN D2 unit(D2 a) {
     const double r = rsqrt_d(a.x * a.x + a.y * a.y);
     return d2(a.x * r, a.y * r);
 }
+// the same correctly rounded, in the oracle's operations: for tests that can
+// be a tie
+SX_FN D2 unit_r(D2 a) {
+    const double l = sqrt(a.x * a.x + a.y * a.y);
+    return d2(a.x / l, a.y / l);
+}
 // right normal N = (T_y, -T_x); N' = kappa T
 SX_FN D2 rnormal(D2 t) { return d2(t.y, -t.x); }
 SX_FN V2 f32(D2 a) { return v2((float)a.x, (float)a.y); }
@@ -1118,10 +1124,8 @@ SX_HD void emit_cap(Sink& k, const Cfg& cfg, int cap, D2 p, D2 u, double w, bool
 
 template <class Sink>
 SX_HD void emit_join(Sink& k, const Cfg& cfg, int join, double miter_limit, D2 p, D2 ta, D2 tb, double w) {
-    // (correctly rounded: a right angle's turn is pi / 2 and a reversal's cross
-    // product 0 exactly, as the oracle has them)
-    const double ra = 1.0 / sqrt(ta.x * ta.x + ta.y * ta.y), rb = 1.0 / sqrt(tb.x * tb.x + tb.y * tb.y);
-    D2 ua = d2(ta.x * ra, ta.y * ra), ub = d2(tb.x * rb, tb.y * rb);
+    // (a right angle's turn is pi / 2 and a reversal's cross product 0, exactly)
+    D2 ua = unit_r(ta), ub = unit_r(tb);
     double cr = cross(ua, ub), dp = dot(ua, ub);
     D2 Na = rnormal(ua), Nb = rnormal(ub);
     JoinP jp = {};
@@ -1718,8 +1722,11 @@ SX_FN double node_tan(const NodeSeg& n, double t, D2 q, D2& u) {
     return ss * r;
 }
 // Whether a node is accepted: the Section 7.1 estimate with reading G2 and
-// the hodograph test of reading G29.
-SX_HD inline bool node_accepted(const NodeSeg& n, const Cfg& cfg, uint32_t t0_u, uint32_t depth) {
+// the hodograph test of reading G29.  tie: accepted by the estimate, and the
+// hodograph's sum is zero up to rounding (S and U curves whose middle vector
+// is perpendicular to both ends): hodo_turns then decides.
+SX_HD inline bool node_accepted(const NodeSeg& n, const Cfg& cfg, uint32_t t0_u, uint32_t depth, bool& tie) {
+    tie = false;
     const double dt = depth_dt(depth);
     const double t0 = (double)t0_u * dt;
     const double t1 = t0 + dt;
@@ -1748,14 +1755,25 @@ SX_HD inline bool node_accepted(const NodeSeg& n, const Cfg& cfg, uint32_t t0_u,
     const double ma = m0 * dt, mc = m1 * dt;
     const double est = fit_estimate_sc(th0, th1, sn0, c0, sn1, c1, v0, v1, ma * rcl, mc * rcl);
     const double err = cfg.paper_fit ? est * cl : est * (cl + kFitK * n.w) * kFitS;
-    bool hodo_ok = true;
-    {
-        const D2 a = u0 * ma, c = u1 * mc, b = chord - a - c;
-        // a middle vector that is zero up to rounding leaves only the turn from a to c (< pi)
-        const double lim = 1e-9 * (ma + mc);
-        if (ma > 0.0 && mc > 0.0 && dot(b, b) > lim * lim) hodo_ok = (dot(a, b) * mc + dot(b, c) * ma) > 0.0;
-    }
-    return hodo_ok && (err <= cfg.tau_fit);
+    if (!(err <= cfg.tau_fit)) return false;
+    const D2 a = u0 * ma, c = u1 * mc, b = chord - a - c;
+    // a middle vector that is zero up to rounding leaves only the turn from a to c (< pi)
+    const double lim = 1e-9 * (ma + mc);
+    if (!(ma > 0.0 && mc > 0.0 && dot(b, b) > lim * lim)) return true;
+    // (b's rounding, and that of q in its power form, is below 1e-10 of ma + mc)
+    const double hv = dot(a, b) * mc + dot(b, c) * ma;
+    tie = fabs(hv) <= 1e-10 * (ma + mc) * ma * mc;
+    return hv > 0.0;
+}
+// The hodograph test of a node in the oracle's order of operations.
+SX_HD inline bool hodo_turns(const Seg& s, uint32_t t0_u, uint32_t depth) {
+    const double dt = depth_dt(depth), t0 = (double)t0_u * dt, t1 = t0 + dt;
+    const D2 q0 = t0 == 0.0 ? s.D1 : bern_q(s, t0), q1 = t1 == 1.0 ? s.D3 - s.D2_ : bern_q(s, t1);
+    const D2 ta = tangent(s, t0, q0), tb = tangent(s, t1, q1);
+    const D2 va = t0 == 0.0 ? q0 : ta, vb = t1 == 1.0 ? q1 : tb;
+    const double ma = sqrt(dot(va, va)) * dt, mc = sqrt(dot(vb, vb)) * dt;
+    const D2 a = unit_r(ta) * ma, c = unit_r(tb) * mc, b = taylor_chord(s, t0, dt, q0) - a - c;
+    return dot(a, b) * mc + dot(b, c) * ma > 0.0;
 }
 
 // The tree of one segment in parameter order: the two-word stack (t0_u,
@@ -1772,9 +1790,10 @@ SX_FN void bisect_init(Bisect& b, const Seg& s) {
 // One trial.  Returns true when [t0, t0 + dt] is accepted (its t0_u and depth
 // are reported before the stack pops; a line is its own piece); *done is set
 // when the segment is fully covered.
-SX_HD inline bool bisect_step(Bisect& b, const Seg&, const Cfg& cfg, bool line, uint32_t& acc_t0u,
+SX_HD inline bool bisect_step(Bisect& b, const Seg& s, const Cfg& cfg, bool line, uint32_t& acc_t0u,
                               uint32_t& acc_depth, bool& acc_pivot, bool& done) {
-    const bool ok = line || node_accepted(b.n, cfg, b.t0_u, b.depth);
+    bool tie = false, ok = line || node_accepted(b.n, cfg, b.t0_u, b.depth, tie);
+    if (tie) ok = hodo_turns(s, b.t0_u, b.depth);
     done = false;
     if (ok || b.depth >= (uint32_t)kMaxDepth) {
         acc_t0u = b.t0_u;

@@ -527,7 +527,13 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
             const NodeSeg e{d2(s_seg[0][sg], s_seg[1][sg]), d2(s_seg[2][sg], s_seg[3][sg]),
                             d2(s_seg[4][sg], s_seg[5][sg]), d2(s_seg[6][sg], s_seg[7][sg]),
                             d2(s_seg[8][sg], s_seg[9][sg]), s_seg[10][sg], s_seg[11][sg], s_seg[12][sg]};
-            const bool ok = node_accepted(e, cfg, t0u, depth);
+            bool tie, ok = node_accepted(e, cfg, t0u, depth, tie);
+            if (tie) {
+                TagInfo ti;
+                Seg s;
+                fetch_tag(sv, s_tag[sg], ti, s);
+                ok = hodo_turns(s, t0u, depth);
+            }
             if (Stats) n_trials++;
             split = !ok && depth < (uint32_t)kMaxDepth;
             if (!split) {

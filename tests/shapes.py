@@ -91,7 +91,3 @@ SYMMETRIC = {
     "reversals_round": lambda x: reversals(S.JOIN_ROUND, xform=x),
     "reversals_bevel": lambda x: reversals(S.JOIN_BEVEL, xform=x),
 }
-# Sides of unequal lengths at right angles: the oracle divides by a length
-# where the kernels multiply by its reciprocal, so an arc's count (1 at pi / 2,
-# 2 above) is a matter of that rounding.
-LINES_ONLY = {"reversals_round", "reversals_bevel"}

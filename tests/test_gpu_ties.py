@@ -31,12 +31,22 @@ def _same_as_the_oracle(sc, newton=False):
         ctx.close()
 
 
-@pytest.mark.parametrize("name,mode,newton", [(n, m, f) for n in shapes.SYMMETRIC for m, f in
-                                              ((S.OUT_LINES, False), (S.OUT_ARCS, False), (S.OUT_LINES, True))
-                                              if m == S.OUT_LINES or n not in shapes.LINES_ONLY])
+@pytest.mark.parametrize("mode,newton", [(S.OUT_LINES, False), (S.OUT_ARCS, False), (S.OUT_LINES, True)])
+@pytest.mark.parametrize("name", shapes.SYMMETRIC)
 def test_symmetric_shapes_have_the_oracles_counts(name, mode, newton):
     for s in (1.0, 2.0, 1.0 / 3.0):
         sc = shapes.SYMMETRIC[name](shapes.scale(s))
         sc.output_mode = mode
         print("ties", name, mode, newton, s, flush=True)
         _same_as_the_oracle(sc, newton)
+
+
+@pytest.mark.parametrize("mode", [S.OUT_LINES, S.OUT_ARCS])
+@pytest.mark.parametrize("size,w", [(0.25, 1.0), (1.0, 1.0), (0.25, 10.0)])
+def test_perpendicular_hodographs_have_the_oracles_counts(size, w, mode):
+    """The hodograph test's sum is 0 or rounding alone: the oracle's rounding."""
+    for s in (1.0, 1.0 / 3.0, 0.7, np.sqrt(0.5)):
+        sc = shapes.connectors(size, w, shapes.scale(s))
+        sc.tolerance, sc.output_mode = 1.0, mode
+        print("hodographs", size, w, mode, s, flush=True)
+        _same_as_the_oracle(sc)
