@@ -153,7 +153,8 @@ struct sx_scene {
     // per tag: monoids, slot counts and their exclusive scan (slot bases)
     uint32_t* d_mon = nullptr;
     uint32_t* d_nslots = nullptr;
-    uint32_t* d_codes = nullptr;  // the first piece codes of each tag (count pass)
+    uint32_t* d_codes = nullptr;  // the first piece codes of each tag
+    uint32_t* d_ordered = nullptr;  // all piece codes of tags with more (slot_cap words)
     uint64_t* d_base = nullptr;
     // per slot: the slot, its record count and record offset
     sx::Slot* d_slots = nullptr;
@@ -250,6 +251,7 @@ void free_scene(sx_scene* s) {
     dfree(s->d_mon);
     dfree(s->d_nslots);
     dfree(s->d_codes);
+    dfree(s->d_ordered);
     dfree(s->d_base);
     dfree(s->d_slots);
     dfree(s->d_rc);
@@ -338,7 +340,9 @@ hipError_t size_slots(sx_scene* s, uint64_t slot_cap, uint32_t region_per_piece,
         dfree(s->d_status_rc);
         dfree(s->d_tile_n);
         dfree(s->d_es);
+        dfree(s->d_ordered);
         A(dalloc(&s->d_slots, slot_cap * sizeof(sx::Slot)));
+        A(dalloc(&s->d_ordered, slot_cap * sizeof(uint32_t)));
         A(dalloc(&s->d_es, slot_cap * 2 * sizeof(uint4)));
         A(dalloc(&s->d_rc, (slot_cap + 16) * sizeof(uint32_t)));
         A(dalloc(&s->d_roff, (slot_cap + 1) * sizeof(uint64_t)));
@@ -471,14 +475,14 @@ hipError_t run_one(const sx_ctx* ctx, const sx_scene* s, const sx::Cfg& conf, in
                                         st);
         case kPhBisectCount:
             return sx::launch_bisect(view(s), cfg, t.bisect_range, sx::keep_codes_of(s->n_tags), (int)t.bisect_waves,
-                                     s->d_nslots, s->d_codes, stats, st);
+                                     s->d_nslots, s->d_codes, s->d_ordered, s->slot_cap, s->d_ws_ctl, stats, st);
         case kPhScanSlots:
             // (a small scene's bases are part of the next phase)
             if (sx::list_is_small(s->n_tags)) return hipSuccess;
             return sx::launch_scan_slots(s->d_nslots, s->n_tags, s->d_base, ctl_block(s, 1), s->d_status_nslots, st);
         case kPhBisectWrite:
-            return sx::launch_list(view(s), cfg, sx::keep_codes_of(s->n_tags), s->d_nslots, s->d_codes, s->d_base,
-                                   s->d_slots, s->slot_cap, st);
+            return sx::launch_list(s->n_tags, sx::keep_codes_of(s->n_tags), s->d_nslots, s->d_codes, s->d_ordered,
+                                   s->slot_cap, s->d_base, s->d_slots, s->slot_cap, st);
         case kPhPieces:
             return sx::launch_slots(view(s), cfg, workspace(s), s->d_slots, n_slots_dev(s), s->slot_cap, s->d_rc,
                                     (int)t.piece_waves, stats, st);
@@ -1031,7 +1035,10 @@ int sx_run_phase(sx_ctx* ctx, const sx_scene* s, int phase, float tolerance, int
     hipStream_t st = (hipStream_t)stream;
     const_cast<sx_scene*>(s)->last_stream = st;
     const uint64_t rec = output_mode == SX_OUT_ARCS ? sizeof(sx_arc) : sizeof(sx_line);
-    hipError_t e = run_one(ctx, s, cfg, phase, out_dev, out_capacity_bytes / rec, nullptr, st);
+    hipError_t e = hipSuccess;
+    // (the bisection alone, again and again: its codes go to the same place)
+    if (phase == kPhBisectCount) e = sx::launch_zero({{&s->d_ws_ctl->ordered_n, sizeof(s->d_ws_ctl->ordered_n)}}, st);
+    if (e == hipSuccess) e = run_one(ctx, s, cfg, phase, out_dev, out_capacity_bytes / rec, nullptr, st);
     return e == hipSuccess ? SX_OK : hip_fail(ctx, e, "phase launch");
 }
 

@@ -18,6 +18,7 @@ struct WsCtl {
     unsigned long long ovf_n;        // overflow units requested
     unsigned long long items_total;  // units requested by all tiles (of a run that dropped some)
     unsigned long long slots_total;  // slots of the last expansion
+    unsigned long long ordered_n;    // piece codes of tags with more than are kept
     unsigned long long result[2];    // records and status, for synchronous readback
 };
 struct ItemWs {
@@ -76,24 +77,28 @@ hipError_t launch_scan_counts_dev(const uint32_t* in, const uint64_t* n_dev, uin
 constexpr int kKeepCodes = 32;  // fewest piece codes kept per tag by the bisection
 // Piece codes the bisection keeps per tag for n tags: a budget of 2^25 words
 // shared by the tags, at least kKeepCodes and at most 1024 per tag (a tag with
-// more pieces runs its bisection a second time, in the list kernel), a
-// multiple of 16 (rows are read as four uint4).
+// more pieces runs its bisection a second time), a multiple of 16 (rows are
+// read as four uint4).
 inline uint32_t keep_codes_of(uint32_t n) {
     const uint64_t k = ((1ull << 25) / ((uint64_t)n + 1u)) & ~15ull;
     return (uint32_t)(k < (uint64_t)kKeepCodes ? kKeepCodes : (k > 1024u ? 1024u : k));
 }
 // Slots per tag (pieces + 1; bit 31 marks a line) and, in no defined order,
-// the codes of its first pieces found.
+// the codes of its pieces; a tag with more than `keep` has them in order in
+// `ordered` from the index that its row starts with (ctl->ordered_n of
+// ordered_cap words are taken).
 hipError_t launch_bisect(const SceneView& sv, const Cfg& cfg, uint32_t range, uint32_t keep, int waves,
-                         uint32_t* nslots, uint32_t* codes, unsigned long long* stats, hipStream_t s);
+                         uint32_t* nslots, uint32_t* codes, uint32_t* ordered, uint64_t ordered_cap, WsCtl* ctl,
+                         unsigned long long* stats, hipStream_t s);
 // Slot bases: exclusive scan of the slot counts (base[n] the total).
 hipError_t launch_scan_slots(const uint32_t* nslots, uint32_t n, uint64_t* base, void* ctl, void* st, hipStream_t s);
 // The piece list pcs: piece p of the scene (canonical order) as {tag, code},
 // its slot being p + tag.  Small scenes (list_is_small): computes the slot
 // bases too.
 bool list_is_small(uint32_t n_tags);
-hipError_t launch_list(const SceneView& sv, const Cfg& cfg, uint32_t keep, const uint32_t* nslots,
-                       const uint32_t* codes, uint64_t* base, Slot* pcs, uint64_t slot_cap, hipStream_t s);
+hipError_t launch_list(uint32_t n_tags, uint32_t keep, const uint32_t* nslots, const uint32_t* codes,
+                       const uint32_t* ordered, uint64_t ordered_cap, uint64_t* base, Slot* pcs, uint64_t slot_cap,
+                       hipStream_t s);
 // pieces (one thread per piece, tiles of slot_block() pieces)
 hipError_t launch_slots(const SceneView& sv, const Cfg& cfg, const ItemWs& ws, const Slot* pcs,
                         const uint64_t* n_slots_dev, uint64_t slot_cap, uint32_t* rc, int waves,

@@ -6,7 +6,8 @@
 //  bisect_kernel          Algorithm 2 in FP64 over the bisection trees' open
 //                         nodes (a wave owns a range of tags and tries 64
 //                         nodes at a time): slots per tag (pieces + 1 tail)
-//                         and the codes of the pieces found.
+//                         and the codes of the pieces found; those of a tag
+//                         with more than are kept, in order, by a second run.
 //  list_kernel            every piece {tag, code} at its canonical position
 //  list_small_kernel      in the piece list (small scenes: with the scan of
 //                         the slot counts).
@@ -282,6 +283,7 @@ __global__ __launch_bounds__(kScanBlock) void scan_tags_kernel(const uint8_t* __
     if (ws_reset && blockIdx.x == 0 && threadIdx.x == 0) {
         ws_reset->ovf_n = 0;
         ws_reset->items_total = 0;
+        ws_reset->ordered_n = 0;
     }
     auto load = [&](uint64_t base, Pair* item) {
         if (base + Items <= n) {
@@ -433,18 +435,150 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// A tag with more pieces than codes kept runs its bisection once more, at the
+// end of its wave's range, by the whole wave, and its codes go to `ordered` in
+// parameter order.  Their starts are marked in a bitmap of the 2^kMaxDepth
+// parameters (over the LDS of the first part), so that their order is that of
+// the bits and a piece's depth follows from the next one's start.  The first
+// round tries every node above depth 6, of which the ones below an accepted
+// node are then dropped.  (With one lane per tag and the trials in order, in
+// the list launch, 400,000 stress cubics with 80 codes kept took 24.5 ms there,
+// 2.9 ms this way; 1M map segments, 32 kept, 68 us and 20 us; without that code
+// the list kernel needs 24 VGPRs instead of 93.)
+constexpr uint32_t kMarkWords = 1u << (kMaxDepth - 5);
+struct BisectLds {
+    double seg[13][kNodeSegs];      // NodeSeg
+    uint32_t tag[kNodeSegs];        // tag of a segment
+    uint32_t open[kNodeSegs];       // its open nodes
+    uint32_t found[kNodeSegs];      // its pieces so far
+    uint32_t free_[kNodeSegs];      // unused segments
+    uint32_t curve[128];            // ring of curves not yet taken
+    uint32_t node[kNodeStack];      // segment << 21 | depth << 16 | t0
+    uint32_t rich[kBisectMaxRange / 32];  // tags with more pieces than codes kept
+};
+static_assert(offsetof(BisectLds, node) >= kMarkWords * 4, "the bitmap ends before the node stack");
+static_assert(kMarkWords == 32u * kBisectBlock, "32 words per lane");
+
+__device__ __forceinline__ bool try_node(const SceneView& sv, const Cfg& cfg, const NodeSeg& e, uint32_t tag,
+                                         uint32_t t0u, uint32_t depth) {
+    bool tie, ok = node_accepted(e, cfg, t0u, depth, tie);
+    if (tie) {
+        TagInfo ti;
+        Seg s;
+        fetch_tag(sv, tag, ti, s);
+        ok = hodo_turns(s, t0u, depth);
+    }
+    return ok;
+}
+
+// The pieces of tag i in order (a wave), room for `room` of them; returns
+// their number.
+__device__ __forceinline__ uint32_t order_codes(const SceneView& sv, const Cfg& cfg, uint32_t i, uint32_t* mark,
+                                                uint32_t* node, uint32_t* __restrict__ out, uint64_t room) {
+    const uint32_t lane = threadIdx.x;
+    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    constexpr uint32_t D = (uint32_t)kMaxDepth;
+    NodeSeg e;
+    {
+        TagInfo ti;
+        Seg s;
+        fetch_tag(sv, i, ti, s);
+        e = node_seg(s);
+    }
+    // (word w of the bitmap at [w % 32][w / 32]: lane l owns words 32 l to 32 l + 31)
+    for (uint32_t w = 0; w < 32u; w++) mark[w * 64u + lane] = 0u;
+    uint32_t n_node = 0;
+    for (bool first = true;; first = false) {
+        const uint32_t n_pop = min(n_node, 64u);
+        if (!first && n_pop == 0u) break;
+        uint32_t depth = 31u - (uint32_t)__builtin_clz(lane + 1u), t0u = lane + 1u - (1u << depth);
+        bool act = lane < (first ? 63u : n_pop);
+        if (!first && act) {
+            const uint32_t w = node[n_node - 1u - lane];
+            depth = w >> 16;
+            t0u = w & 0xffffu;
+        }
+        n_node -= n_pop;
+        wave_lds_sync();
+        const bool ok = act && try_node(sv, cfg, e, i, t0u, depth);
+        if (first) {
+            const uint64_t m = __ballot(ok);
+            for (uint32_t p = (lane + 1u) >> 1; p != 0u; p >>= 1) act = act && ((m >> (p - 1u)) & 1ull) == 0ull;
+        }
+        const bool split = act && !ok && depth < D && (!first || depth == 5u);
+        if (act && (ok || depth == D)) {
+            const uint32_t at = t0u << (D - depth);
+            atomicOr(&mark[((at >> 5) & 31u) * 64u + (at >> 10)], 1u << (at & 31u));
+        }
+        const uint64_t m_split = __ballot(split);
+        const uint32_t n_split = (uint32_t)__popcll(m_split);
+        if (split) {
+            const uint32_t to = n_node + 2u * (n_split - 1u - (uint32_t)__popcll(m_split & below));
+            const uint32_t w = ((depth + 1u) << 16) | (2u * t0u);
+            if (to + 1u < kNodeStack) {
+                node[to] = w;
+                node[to + 1u] = w + 1u;
+            }
+        }
+        n_node += 2u * n_split;
+        wave_lds_sync();
+    }
+    // this lane's pieces: their number, its first start, the next lane's
+    uint32_t cnt = 0, head = 1u << D;
+    for (uint32_t w = 0; w < 32u; w++) {
+        const uint32_t bits = mark[w * 64u + lane];
+        if (cnt == 0u && bits) head = lane * 1024u + w * 32u + (uint32_t)__builtin_ctz(bits);
+        cnt += (uint32_t)__popc(bits);
+    }
+    uint32_t q = cnt;
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t u = __shfl_up(q, d, 64);
+        if ((int)lane >= d) q += u;
+    }
+    const uint32_t total = __shfl(q, 63, 64);
+    q -= cnt;
+    const uint64_t later = __ballot(cnt != 0u) & ~(below | (1ull << lane));
+    const uint32_t after = __shfl(head, later ? (int)__builtin_ctzll(later) : (int)lane, 64);
+    const uint32_t tail = later ? after : 1u << D;
+    auto put = [&](uint32_t n, uint32_t start, uint32_t depth) {
+        const bool pivot = depth == D && !try_node(sv, cfg, e, i, start, D);
+        if (n < room) out[n] = slot_code(start >> (D - depth), depth, pivot);
+    };
+    uint32_t at = head;  // the piece to write: it ends where the next one starts
+    for (uint32_t w = 0; w < 32u && cnt; w++) {
+        uint32_t bits = mark[w * 64u + lane];
+        while (bits) {
+            const uint32_t next = lane * 1024u + w * 32u + (uint32_t)__builtin_ctz(bits);
+            bits &= bits - 1u;
+            if (next == at) continue;  // (its own start)
+            const uint32_t depth = D - (uint32_t)__builtin_ctz(next - at);
+            put(q++, at, depth);
+            at = next;
+        }
+    }
+    if (cnt) {
+        const uint32_t depth = D - (uint32_t)__builtin_ctz(tail - at);
+        put(q, at, depth);
+    }
+    wave_lds_sync();
+    return total;
+}
+
 template <bool Stats, int MinWaves>
 __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneView sv, Cfg cfg, uint32_t range,
                                                                         uint32_t keep, uint32_t* __restrict__ nslots,
                                                                         uint32_t* __restrict__ codes,
+                                                                        uint32_t* __restrict__ ordered,
+                                                                        uint64_t ordered_cap, WsCtl* ctl,
                                                                         unsigned long long* __restrict__ stats) {
-    __shared__ double s_seg[13][kNodeSegs];      // NodeSeg
-    __shared__ uint32_t s_node[kNodeStack];      // segment << 21 | depth << 16 | t0
-    __shared__ uint32_t s_tag[kNodeSegs];        // tag of a segment
-    __shared__ uint32_t s_open[kNodeSegs];       // its open nodes
-    __shared__ uint32_t s_found[kNodeSegs];      // its pieces so far
-    __shared__ uint32_t s_free[kNodeSegs];       // unused segments
-    __shared__ uint32_t s_curve[128];            // ring of curves not yet taken
+    __shared__ BisectLds lds;
+    auto& s_seg = lds.seg;
+    auto& s_node = lds.node;
+    auto& s_tag = lds.tag;
+    auto& s_open = lds.open;
+    auto& s_found = lds.found;
+    auto& s_free = lds.free_;
+    auto& s_curve = lds.curve;
     const uint32_t lane = threadIdx.x;
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const uint32_t a = blockIdx.x * range;
@@ -454,6 +588,8 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
     uint32_t c_lo = 0, c_hi = 0;           // the ring's entries
     uint32_t n_free = kNodeSegs, n_node = 0;
     s_free[lane] = lane;
+    if (lane < kBisectMaxRange / 32u) lds.rich[lane] = 0u;
+    uint32_t more = 0;  // pieces of this lane's tags with more than are kept
     wave_lds_sync();
     for (;;) {
         // this turn's nodes: the top of the stack on the first lanes
@@ -527,13 +663,7 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
             const NodeSeg e{d2(s_seg[0][sg], s_seg[1][sg]), d2(s_seg[2][sg], s_seg[3][sg]),
                             d2(s_seg[4][sg], s_seg[5][sg]), d2(s_seg[6][sg], s_seg[7][sg]),
                             d2(s_seg[8][sg], s_seg[9][sg]), s_seg[10][sg], s_seg[11][sg], s_seg[12][sg]};
-            bool tie, ok = node_accepted(e, cfg, t0u, depth, tie);
-            if (tie) {
-                TagInfo ti;
-                Seg s;
-                fetch_tag(sv, s_tag[sg], ti, s);
-                ok = hodo_turns(s, t0u, depth);
-            }
+            const bool ok = try_node(sv, cfg, e, s_tag[sg], t0u, depth);
             if (Stats) n_trials++;
             split = !ok && depth < (uint32_t)kMaxDepth;
             if (!split) {
@@ -542,7 +672,14 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
             }
             // the lane that closes a segment's last open node finishes its tag
             done = atomicAdd(&s_open[sg], split ? 1u : ~0u) == 1u && !split;
-            if (done) nslots[s_tag[sg]] = s_found[sg] + 1u;
+            if (done) {
+                const uint32_t np = s_found[sg], k = s_tag[sg] - a;
+                nslots[a + k] = np + 1u;
+                if (np > keep) {
+                    more += np;
+                    atomicOr(&lds.rich[k >> 5], 1u << (k & 31u));
+                }
+            }
         }
         // the halves of this turn's nodes, the deepest (lane 0's) on top
         const uint64_t m_split = __ballot(split), m_done = __ballot(done);
@@ -560,6 +697,25 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
         n_free += (uint32_t)__popcll(m_done);
         wave_lds_sync();
     }
+    if (__ballot(more != 0u)) {
+        for (int d = 32; d >= 1; d >>= 1) more += __shfl_xor(more, d, 64);
+        unsigned long long at = 0;
+        if (lane == 0u) at = atomicAdd(&ctl->ordered_n, (unsigned long long)more);
+        at = __shfl(at, 0, 64);
+        // (none when full: the scene then has more slots than the buffers hold)
+        const bool fits = at + more <= ordered_cap;
+        uint32_t off = fits ? (uint32_t)at : ~0u;
+        for (uint32_t w = 0; w < (b - a + 31u) / 32u; w++) {
+            uint32_t bits = lds.rich[w];
+            while (bits) {
+                const uint32_t i = a + w * 32u + (uint32_t)__builtin_ctz(bits);
+                bits &= bits - 1u;
+                if (lane == 0u) codes[(size_t)i * keep] = off;
+                if (fits) off += order_codes(sv, cfg, i, reinterpret_cast<uint32_t*>(&lds), s_node, ordered + off,
+                                              ordered_cap - off);
+            }
+        }
+    }
     if (Stats) {
         atomicAdd(&stats[kStTrials], (unsigned long long)n_trials);
         atomicAdd(&stats[kStLines], (unsigned long long)n_lines);
@@ -573,8 +729,8 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
 // hundreds, a line one), so blocks of tags would wait for their richest tag.
 // The thread finds its tag from the slot bases and takes its place among the
 // tag's kept codes by counting the ones that start before it (the lanes of a
-// tag read its row together).  A tag with more pieces than codes kept runs
-// its bisection again, in order, on the thread of its first piece.
+// tag read its row together).  A tag with more pieces than codes kept has
+// them in order elsewhere.
 constexpr int kListBlock = 256;
 // pieces of a block's turn (list_kernel), by the slots it is launched for: a
 // thread's pieces follow one another (20,011 segments: 256 a turn 5.8 us, 512
@@ -594,24 +750,13 @@ __device__ __forceinline__ uint32_t code_start(uint32_t code) {
 // stress cubics: 40 -> 24.5 us; 1M map segments, of five pieces a curve, 42 us
 // without, 45 with).
 template <int Ahead>
-__device__ __forceinline__ void list_piece(const SceneView& sv, const Cfg& cfg, uint32_t keep,
-                                           const uint32_t* __restrict__ codes, bool line, uint32_t i, uint32_t q,
-                                           uint32_t np, uint64_t first, Slot* __restrict__ pcs, uint64_t slot_cap) {
+__device__ __forceinline__ void list_piece(uint32_t keep, const uint32_t* __restrict__ codes,
+                                           const uint32_t* __restrict__ ordered, uint64_t ordered_cap, bool line,
+                                           uint32_t i, uint32_t q, uint32_t np, uint64_t first,
+                                           Slot* __restrict__ pcs, uint64_t slot_cap) {
     if (np > keep) {
-        if (q != 0u) return;
-        TagInfo ti;
-        Seg s;
-        fetch_tag(sv, i, ti, s);
-        Bisect bs;
-        bisect_init(bs, s);
-        for (bool done = false; !done;) {
-            uint32_t t0u = 0, depth = 0;
-            bool pivot = false;
-            if (bisect_step(bs, s, cfg, false, t0u, depth, pivot, done)) {
-                if (first < slot_cap) pcs[first] = Slot{i, slot_code(t0u, depth, pivot)};
-                first++;
-            }
-        }
+        const uint64_t at = (uint64_t)codes[(size_t)i * keep] + q;
+        if (first + q < slot_cap) pcs[first + q] = Slot{i, at < ordered_cap ? ordered[at] : slot_code(0u, 0u, false)};
         return;
     }
     uint32_t code = slot_code(0u, 0u, false) | kCodeLine, rank = 0;
@@ -632,14 +777,15 @@ __device__ __forceinline__ void list_piece(const SceneView& sv, const Cfg& cfg, 
 
 // From the scanned slot bases; a block takes `turn` pieces at a time.
 template <int Ahead>
-__global__ __launch_bounds__(kListBlock) void list_kernel(SceneView sv, Cfg cfg, uint32_t keep,
+__global__ __launch_bounds__(kListBlock) void list_kernel(uint32_t n, uint32_t keep,
                                                           const uint32_t* __restrict__ nslots,
                                                           const uint32_t* __restrict__ codes,
+                                                          const uint32_t* __restrict__ ordered, uint64_t ordered_cap,
                                                           const uint64_t* __restrict__ base, Slot* __restrict__ pcs,
                                                           uint64_t slot_cap, uint32_t turn) {
     __shared__ uint32_t s_tag[2];
     __shared__ uint32_t s_off[kListSpan];  // pieces of the turn before each of its tags
-    const uint32_t n = sv.n_tags, t = threadIdx.x, lane = t & 63u, wv = t >> 6;
+    const uint32_t t = threadIdx.x, lane = t & 63u, wv = t >> 6;
     const uint64_t n_pieces = base[n] - n;
     // (piece ordinal of tag i: base[i] - i)
     for (uint64_t p0 = (uint64_t)blockIdx.x * turn; p0 < n_pieces; p0 += (uint64_t)gridDim.x * turn) {
@@ -678,8 +824,8 @@ __global__ __launch_bounds__(kListBlock) void list_kernel(SceneView sv, Cfg cfg,
             }
             const uint32_t i = tag0 + lo, w = nslots[i];
             const uint64_t first = staged ? f0 + s_off[lo] : base[i] - i;
-            list_piece<Ahead>(sv, cfg, keep, codes, (w & kCountLine) != 0u, i, (uint32_t)(p - first), (w & ~kCountLine) - 1u,
-                       first, pcs, slot_cap);
+            list_piece<Ahead>(keep, codes, ordered, ordered_cap, (w & kCountLine) != 0u, i, (uint32_t)(p - first),
+                              (w & ~kCountLine) - 1u, first, pcs, slot_cap);
         }
         __syncthreads();  // s_tag and s_off are reused
     }
@@ -689,14 +835,15 @@ __global__ __launch_bounds__(kListBlock) void list_kernel(SceneView sv, Cfg cfg,
 // bases and list take one launch without a wait between blocks (1,000 cubics:
 // 7.3 us, 11.9 with a scan launch; at 11,000 tags the scan launch and list
 // take 30 us, this 35).
-__global__ __launch_bounds__(kListBlock) void list_small_kernel(SceneView sv, Cfg cfg, uint32_t keep,
+__global__ __launch_bounds__(kListBlock) void list_small_kernel(uint32_t n, uint32_t keep,
                                                                 const uint32_t* __restrict__ nslots,
                                                                 const uint32_t* __restrict__ codes,
-                                                                uint64_t* __restrict__ base, Slot* __restrict__ pcs,
+                                                                const uint32_t* __restrict__ ordered,
+                                                                uint64_t ordered_cap, uint64_t* __restrict__ base, Slot* __restrict__ pcs,
                                                                 uint64_t slot_cap) {
     extern __shared__ uint32_t s_end[];  // pieces of tags 0..i; bit 31: a line
     __shared__ uint32_t s_wave[kListBlock / 64];
-    const uint32_t n = sv.n_tags, t = threadIdx.x, lane = t & 63u, wv = t >> 6;
+    const uint32_t t = threadIdx.x, lane = t & 63u, wv = t >> 6;
     // each thread's consecutive tags (a multiple of 4 of them), 16 bytes at a time
     const uint32_t per = ((n + kListBlock - 1u) / kListBlock + 3u) & ~3u;
     const uint32_t i0 = min(t * per, n), i1 = min(i0 + per, n);
@@ -740,8 +887,8 @@ __global__ __launch_bounds__(kListBlock) void list_small_kernel(SceneView sv, Cf
             cnt = le ? cnt - half : half;
         }
         const uint32_t first = i ? s_end[i - 1u] & ~kCountLine : 0u, e = s_end[i];
-        list_piece<4>(sv, cfg, keep, codes, (e & kCountLine) != 0u, i, p - first, (e & ~kCountLine) - first, first, pcs,
-                   slot_cap);
+        list_piece<4>(keep, codes, ordered, ordered_cap, (e & kCountLine) != 0u, i, p - first,
+                      (e & ~kCountLine) - first, first, pcs, slot_cap);
     }
 }
 
@@ -1428,16 +1575,14 @@ static uint32_t bisect_fill(uint32_t n) {
 }
 template <bool Stats>
 static void bisect_launch(uint32_t g, hipStream_t s, int waves, const SceneView& sv, const Cfg& cfg, uint32_t range,
-                          uint32_t keep, uint32_t* nslots, uint32_t* codes, unsigned long long* stats) {
-    if (waves <= 2)
-        bisect_kernel<Stats, 2><<<g, kBisectBlock, 0, s>>>(sv, cfg, range, keep, nslots, codes, stats);
-    else if (waves == 3)
-        bisect_kernel<Stats, 3><<<g, kBisectBlock, 0, s>>>(sv, cfg, range, keep, nslots, codes, stats);
-    else
-        bisect_kernel<Stats, 4><<<g, kBisectBlock, 0, s>>>(sv, cfg, range, keep, nslots, codes, stats);
+                          uint32_t keep, uint32_t* nslots, uint32_t* codes, uint32_t* ordered, uint64_t ordered_cap,
+                          WsCtl* ctl, unsigned long long* stats) {
+    auto* k = waves <= 2 ? bisect_kernel<Stats, 2> : (waves == 3 ? bisect_kernel<Stats, 3> : bisect_kernel<Stats, 4>);
+    k<<<g, kBisectBlock, 0, s>>>(sv, cfg, range, keep, nslots, codes, ordered, ordered_cap, ctl, stats);
 }
 hipError_t launch_bisect(const SceneView& sv, const Cfg& cfg, uint32_t range, uint32_t keep, int waves,
-                         uint32_t* nslots, uint32_t* codes, unsigned long long* stats, hipStream_t s) {
+                         uint32_t* nslots, uint32_t* codes, uint32_t* ordered, uint64_t ordered_cap, WsCtl* ctl,
+                         unsigned long long* stats, hipStream_t s) {
     if (sv.n_tags == 0) return hipSuccess;
     if (range == 0 || range % 64u || range > kBisectMaxRange || keep < (uint32_t)kKeepCodes || keep % 16u)
         return hipErrorInvalidValue;
@@ -1445,27 +1590,26 @@ hipError_t launch_bisect(const SceneView& sv, const Cfg& cfg, uint32_t range, ui
     if (fill < range) range = fill;
     const uint32_t g = (sv.n_tags + range - 1) / range;
     if (stats)
-        bisect_launch<true>(g, s, waves, sv, cfg, range, keep, nslots, codes, stats);
+        bisect_launch<true>(g, s, waves, sv, cfg, range, keep, nslots, codes, ordered, ordered_cap, ctl, stats);
     else
-        bisect_launch<false>(g, s, waves, sv, cfg, range, keep, nslots, codes, stats);
+        bisect_launch<false>(g, s, waves, sv, cfg, range, keep, nslots, codes, ordered, ordered_cap, ctl, stats);
     return hipGetLastError();
 }
 bool list_is_small(uint32_t n_tags) { return n_tags <= kSmallTags; }
-hipError_t launch_list(const SceneView& sv, const Cfg& cfg, uint32_t keep, const uint32_t* nslots,
-                       const uint32_t* codes, uint64_t* base, Slot* pcs, uint64_t slot_cap, hipStream_t s) {
-    if (sv.n_tags == 0) return hipSuccess;
-    if (list_is_small(sv.n_tags)) {
+hipError_t launch_list(uint32_t n_tags, uint32_t keep, const uint32_t* nslots, const uint32_t* codes,
+                       const uint32_t* ordered, uint64_t ordered_cap, uint64_t* base, Slot* pcs, uint64_t slot_cap,
+                       hipStream_t s) {
+    if (n_tags == 0) return hipSuccess;
+    if (list_is_small(n_tags)) {
         const uint32_t g = (uint32_t)std::min<uint64_t>(kSmallBlocks, (slot_cap + kListBlock - 1) / kListBlock);
-        list_small_kernel<<<g, kListBlock, sv.n_tags * sizeof(uint32_t), s>>>(sv, cfg, keep, nslots, codes, base, pcs,
-                                                                             slot_cap);
+        list_small_kernel<<<g, kListBlock, n_tags * sizeof(uint32_t), s>>>(n_tags, keep, nslots, codes, ordered,
+                                                                          ordered_cap, base, pcs, slot_cap);
     } else {
         const uint32_t turn = slot_cap <= kListSmallSlots ? kListPiecesSmall : kListPieces;
         const uint32_t g = (uint32_t)std::min<uint64_t>(8192, (slot_cap + turn - 1) / turn);
         // (many pieces per tag: long rows)
-        if (slot_cap > 8ull * sv.n_tags)
-            list_kernel<4><<<g, kListBlock, 0, s>>>(sv, cfg, keep, nslots, codes, base, pcs, slot_cap, turn);
-        else
-            list_kernel<1><<<g, kListBlock, 0, s>>>(sv, cfg, keep, nslots, codes, base, pcs, slot_cap, turn);
+        auto* k = slot_cap > 8ull * n_tags ? list_kernel<4> : list_kernel<1>;
+        k<<<g, kListBlock, 0, s>>>(n_tags, keep, nslots, codes, ordered, ordered_cap, base, pcs, slot_cap, turn);
     }
     return hipGetLastError();
 }

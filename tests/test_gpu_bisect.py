@@ -69,7 +69,7 @@ def test_tag_counts_at_the_edges(ctx, n_tags):
 @pytest.mark.parametrize("n_cubics,extra", [(6, 0), (6, SMALL_TAGS)])
 def test_more_pieces_than_codes_kept(ctx, n_cubics, extra):
     """About 1,400 pieces per cubic (1,024 codes are kept at most): the
-    tag's bisection runs again in the list kernel, small and general."""
+    tag's bisection runs again, from the list kernels, small and general."""
     sc = S.scene_c1(5, n_paths=2, n_cubics=n_cubics, tolerance=1e-5)
     if extra:
         b = S.SceneBuilder()
@@ -80,6 +80,43 @@ def test_more_pieces_than_codes_kept(ctx, n_cubics, extra):
         sc = b.build(sc.styles, sc.xforms, tolerance=1e-5)
     assert len(O.expand(sc).pieces) > 1024 * n_cubics
     _check(ctx, sc)
+
+
+@pytest.mark.parametrize("mode", [S.OUT_LINES, S.OUT_ARCS])
+@pytest.mark.parametrize("kept,others", [(1008, 31_000), (80, 380_000), (32, 1_050_000)])
+def test_codes_kept_do_not_change_the_outline(ctx, kept, others, mode):
+    """2,000 stress cubics (cusps, loops, degenerate ones; 10 to 400 pieces
+    each), alone, with all their codes kept, and before so many lines that
+    `kept` codes are kept per tag: the same records.  A cubic in a thousand
+    pieces among them."""
+    from paper_2405_00127_amd import binding as B
+
+    few = S.scene_c3(6, n_cubics=2000, output_mode=mode, tolerance=0.02)
+    b = S.SceneBuilder()
+    for k in range(few.n_paths):
+        b.add_path(*few.path(k), int(few.style_ix[k]), 0)
+    b.add_path([S.MOVE, S.CUBIC], [[0, 0], [3e6, 1e6], [-2e6, 1e6], [1e6, 0]], 0, 0)
+    few = b.build(few.styles, few.xforms, tolerance=few.tolerance, output_mode=mode)
+    n = others // 21
+    x = np.arange(21 * n, dtype=np.float32).reshape(n, 21)
+    lines = np.stack([x % 997, (x % 2) * 9 + x % 13], 2)
+    many = b.build(few.styles, few.xforms, tolerance=few.tolerance, output_mode=mode)
+    many.verbs = np.concatenate([many.verbs, np.tile(np.uint8([S.MOVE] + [S.LINE] * 20), n)])
+    many.verb_off = np.concatenate([many.verb_off, many.verb_off[-1] + 21 * np.arange(1, n + 1, dtype=np.uint32)])
+    many.pts = np.concatenate([many.pts, lines.reshape(-1, 2)])
+    many.pt_off = np.concatenate([many.pt_off, many.pt_off[-1] + 21 * np.arange(1, n + 1, dtype=np.uint32)])
+    many.style_ix = np.concatenate([many.style_ix, np.zeros(n, np.uint32)])
+    many.xform_ix = np.concatenate([many.xform_ix, np.zeros(n, np.uint32)])
+    got = []
+    for sc in (few, many):
+        scene = ctx.encode(sc)
+        assert sc is few or max(32, (2**25 // (scene.n_tags + 1)) & ~15) == kept, scene.n_tags
+        recs, _, _ = ctx.expand(scene, sc.tolerance, mode)
+        got.append(B.records_to_numpy(recs, mode).copy())
+        scene.release()
+    assert len(got[0]) > 300_000
+    assert np.array_equal(got[1][: len(got[0])], got[0])
+    assert got[1]["path"][len(got[0])] == few.n_paths
 
 
 def test_long_runs_of_tags_without_pieces(ctx):
