@@ -170,7 +170,7 @@ struct sx_scene {
     uint32_t* d_tile_n = nullptr;
     sx::WsCtl* d_ws_ctl = nullptr;
     uint32_t region_per_piece = 0;  // item units per piece in the per-tile regions
-    uint64_t ovf_cap = 0;          // shared overflow units
+    uint64_t ovf_cap = 0;          // shared overflow units (overflow_units: with a small scene's spill)
     uint64_t slot_cap = 0;         // slots the slot buffers hold
     // allocated capacities (a batch arena is reused for smaller contents)
     uint32_t cap_tags = 0, cap_pts = 0, cap_styles = 0, cap_xforms = 0, cap_paths = 0;
@@ -300,6 +300,25 @@ sx::SceneView view(const sx_scene* s) {
     return v;
 }
 
+// A scene of few pieces cannot fill the chip with threads of chunk_k records
+// each, which then follow one another: it takes chunks of at most
+// kSmallChunk.  (At 2^17 slots and two records per slot, chunks of 4 still
+// make no more threads than the chip holds at two waves per SIMD.)
+constexpr uint64_t kSmallSlots = 1ull << 17;
+constexpr uint32_t kSmallChunk = 4;
+
+// Item units of a scene's tile regions, and of its overflow area.  Items that
+// a region does not hold take chunks of chunk_k records in the overflow area,
+// but a small scene's short chunks can fill a region with items of which
+// chunks of chunk_k would have filled only a part: up to a region more per
+// tile overflows, and has to have room for a call to be served as with them.
+uint64_t region_units(const sx_scene* s) {
+    return (uint64_t)sx::slot_tiles(s->slot_cap) * sx::slot_block() * s->region_per_piece;
+}
+uint64_t overflow_units(const sx_scene* s) {
+    return s->ovf_cap + (s->slot_cap <= kSmallSlots ? region_units(s) : 0u);
+}
+
 sx::ItemWs workspace(const sx_scene* s) {
     sx::ItemWs w;
     w.units = reinterpret_cast<uint4*>(s->d_items);
@@ -309,8 +328,8 @@ sx::ItemWs workspace(const sx_scene* s) {
     w.ctl = s->d_ws_ctl;
     w.tile = sx::slot_block();
     w.region_cap = s->region_per_piece * w.tile;
-    w.ovf_base = (uint64_t)sx::slot_tiles(s->slot_cap) * w.region_cap;
-    w.ovf_cap = s->ovf_cap;
+    w.ovf_base = region_units(s);
+    w.ovf_cap = overflow_units(s);
     return w;
 }
 
@@ -319,7 +338,7 @@ char* ctl_block(const sx_scene* s, int k) { return (char*)s->d_scan_ctl + k * sx
 // (Re)allocate the slot buffers for slot_cap slots and the item workspace
 // (region_per_piece 64-byte units per piece in the tile regions, one region
 // per slot_block() slots of capacity, since pieces never outnumber slots; ovf
-// shared units).
+// shared units, and a small scene's spill).
 // Scan status words are zeroed when allocated.  Ordered on st; allocation is
 // synchronous.
 hipError_t size_slots(sx_scene* s, uint64_t slot_cap, uint32_t region_per_piece, uint64_t ovf, hipStream_t st) {
@@ -356,8 +375,7 @@ hipError_t size_slots(sx_scene* s, uint64_t slot_cap, uint32_t region_per_piece,
     dfree(s->d_items);
     s->region_per_piece = region_per_piece;
     s->ovf_cap = ovf;
-    const uint64_t items = (uint64_t)sx::slot_tiles(slot_cap) * sx::slot_block() * region_per_piece + ovf;
-    return dalloc(&s->d_items, items * sizeof(sx::Unit));
+    return dalloc(&s->d_items, (region_units(s) + overflow_units(s)) * sizeof(sx::Unit));
 }
 
 // Grow the scene's device buffers to hold at least the given sizes (the
@@ -449,13 +467,6 @@ bool make_cfg(const sx_ctx* ctx, float tol, int mode, sx::Cfg& cfg) {
     return true;
 }
 
-// A scene of few pieces cannot fill the chip with threads of chunk_k records
-// each, which then follow one another: it takes chunks of at most
-// kSmallChunk.  (At 2^17 slots and two records per slot, chunks of 4 still
-// make no more threads than the chip holds at two waves per SIMD.)
-constexpr uint64_t kSmallSlots = 1ull << 17;
-constexpr uint32_t kSmallChunk = 4;
-
 const uint64_t* n_slots_dev(const sx_scene* s) { return s->d_base + s->n_tags; }
 
 // Pipeline phases (each one kernel, in this order on one stream).
@@ -468,6 +479,7 @@ hipError_t run_one(const sx_ctx* ctx, const sx_scene* s, const sx::Cfg& conf, in
     const sx_tuning& t = ctx->tune;
     if (s->n_tags == 0) return hipSuccess;
     sx::Cfg cfg = conf;
+    cfg.K_ovf = cfg.K;
     if (s->slot_cap <= kSmallSlots) cfg.K = std::min(cfg.K, kSmallChunk);
     switch (ph) {
         case kPhScanTags:

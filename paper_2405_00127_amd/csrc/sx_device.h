@@ -738,6 +738,7 @@ struct Cfg {
     int paper_fit;                          // fit error: Section 7.1 estimate x chord (else offset-aware)
     int newton;                             // exact density integral, Newton-refined inverse (Section 4.2)
     uint32_t K;                             // records per item chunk
+    uint32_t K_ovf;                         // the same for items past a tile's region (at least K)
     double xinc[5];                         // F increments between the branch breaks
 };
 

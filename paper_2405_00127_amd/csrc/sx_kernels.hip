@@ -917,12 +917,14 @@ constexpr uint32_t kOvfBlocks = 512;  // most record-kernel blocks striding over
 // differs between lanes, so this is a plain per-lane atomic, not a scalar
 // loop over the lanes) and hands its reservation out in order (UnitSink).
 // A reservation that does not fit in the tile's region moves as a whole to
-// the shared overflow area (the part inside the region is left empty).
+// the shared overflow area (the part inside the region is left empty), in
+// chunks of K_ovf records: a small scene's short chunks take up to four times
+// the units, and what its regions do not hold has to fit where longer ones did.
 struct CountSink {
     static constexpr bool kStats = false;
-    uint32_t units;
+    uint32_t K, units;
     template <class P>
-    __device__ void put(uint32_t, uint32_t nrec, uint32_t K, const P&) {
+    __device__ void put(uint32_t, uint32_t nrec, uint32_t, const P&) {
         units += item_units<P>(nrec, K);
     }
 };
@@ -930,11 +932,12 @@ template <bool Stats>
 struct UnitSink {
     static constexpr bool kStats = Stats;
     UnitAt at;            // the next unit of the reservation (null: dropped)
+    uint32_t K;           // records per chunk
     uint32_t path, slot;  // output path id, slot index
     uint32_t n;           // records of the slot so far
     uint32_t st[Stats ? kStN : 1];
     template <class P>
-    __device__ void put(uint32_t hdr, uint32_t nrec, uint32_t K, const P& p) {
+    __device__ void put(uint32_t hdr, uint32_t nrec, uint32_t, const P& p) {
         if constexpr (Stats) st[(hdr & 15u) == kItemOffset ? kStRanges : kStEvolutes]++;
         if (at.p) {
             write_item_q(at, hdr, path, slot, n, nrec, K, p);
@@ -943,12 +946,17 @@ struct UnitSink {
         n += nrec;
     }
 };
-// `need` units from unit `at` of tile `tile`'s region on, or, when they do
-// not fit there, of the overflow area (null: full); the part inside the
-// region is then left empty.
-__device__ __forceinline__ UnitAt place_units(const ItemWs& ws, uint64_t tile, uint32_t at, uint32_t need) {
+// Units `at` to `at` + `need` of a tile's region, when they fit there.
+__device__ __forceinline__ bool units_fit(const ItemWs& ws, uint32_t at, uint32_t need) {
+    return at + need <= ws.region_cap;
+}
+__device__ __forceinline__ UnitAt region_units(const ItemWs& ws, uint64_t tile, uint32_t at) {
+    return UnitAt{ws.units + tile * ws.region_cap * 4u + at, ws.region_cap};
+}
+// `need` units of the overflow area (null: full); the region's units from `at`
+// on, reserved and not used, are left empty.
+__device__ __forceinline__ UnitAt overflow_units(const ItemWs& ws, uint64_t tile, uint32_t at, uint32_t need) {
     uint4* region = ws.units + tile * ws.region_cap * 4u;
-    if (at + need <= ws.region_cap) return UnitAt{region + at, ws.region_cap};
     for (uint32_t u = at; u < ws.region_cap; u++) region[u].x = 0u;
     const unsigned long long o = atomicAdd(&ws.ctl->ovf_n, (unsigned long long)need);
     return UnitAt{o + need <= ws.ovf_cap ? ws.units + ws.ovf_base * 4u + o : nullptr, ws.ovf_cap};
@@ -1079,6 +1087,7 @@ __global__ __launch_bounds__(kSlotBlock, MinWaves) void slot_kernel(SceneView sv
             }
             UnitSink<Stats> k;
             k.at = UnitAt{nullptr, 0u};
+            k.K = cfg.K;
             k.path = 0xffffffffu;
             k.slot = (uint32_t)j;
             k.n = 0;
@@ -1155,15 +1164,25 @@ __global__ __launch_bounds__(kSlotBlock, MinWaves) void slot_kernel(SceneView sv
                         range_put(sink, cfg, es, g1.h, g1.tc, 1.0, g1.rev2, false, true, g1.Pc, g1.P1, w_res[qb]);
                 }
             };
-            uint32_t need = 0;
             if (have) {
-                CountSink dry{0u};
-                put_all(dry);
-                need = dry.units;
+                // one LDS atomic per lane on its tile's counter (lanes of a wave
+                // can belong to different tiles of the group)
+                uint32_t at = 0;
+                for (bool spill = false;; spill = true) {
+                    CountSink dry{k.K, 0u};
+                    put_all(dry);
+                    if (spill) {
+                        k.at = overflow_units(ws, tile0 + kt, at, dry.units);
+                        break;
+                    }
+                    at = atomicAdd(&s_n[kt], dry.units);
+                    if (units_fit(ws, at, dry.units)) {
+                        k.at = region_units(ws, tile0 + kt, at);
+                        break;
+                    }
+                    k.K = cfg.K_ovf;
+                }
             }
-            // one LDS atomic per lane on its tile's counter (lanes of a wave
-            // can belong to different tiles of the group)
-            if (need) k.at = place_units(ws, tile0 + kt, atomicAdd(&s_n[kt], need), need);
             if (have) put_all(k);
             if (act) {
                 rc[j] = k.n;
@@ -1248,8 +1267,11 @@ __global__ __launch_bounds__(kTailBlock, 3) void tail_kernel(SceneView sv, Cfg c
         if (i < n) {
             if (need) {
                 const uint32_t at = win ? s_at[tile - tile_lo] + local : atomicAdd(&ws.tile_n[tile], need);
-                const UnitAt u = place_units(ws, tile, at, need);
-                if (u.p) write_item_q(u, k.hdr, path_of(sv, i), (uint32_t)slot, 0u, k.nrec, cfg.K, k.p);
+                const bool fit = units_fit(ws, at, need);
+                const uint32_t K = fit ? cfg.K : cfg.K_ovf;
+                const UnitAt u = fit ? region_units(ws, tile, at)
+                                     : overflow_units(ws, tile, at, item_units<JoinP>(k.nrec, K));
+                if (u.p) write_item_q(u, k.hdr, path_of(sv, i), (uint32_t)slot, 0u, k.nrec, K, k.p);
             }
             rc[slot] = k.n;
             if (Stats) joins += k.st[kStJoins];

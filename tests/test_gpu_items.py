@@ -60,3 +60,48 @@ def test_chunk_sizes_give_the_same_bytes(copies, chunks, mode, newton):
             assert rep.ok(), rep
     finally:
         ctx.close()
+
+
+def _right_angles(n, join=S.JOIN_ROUND):
+    """Polylines of right angles with wide joins (18 records each at tolerance
+    0.1): more item units per tag than the tile regions hold."""
+    b = S.SceneBuilder()
+    for k in range(n // 100):
+        steps = np.tile([[30.0, 0.0], [0.0, 30.0]], (50, 1))
+        pts = np.concatenate([[[0.0, 0.0]], np.cumsum(steps, 0)]) + [20.0 * (k % 97), 20.0 * (k // 97)]
+        b.add_path([S.MOVE] + [S.LINE] * 100, pts, 0, 0)
+    return b.build(S.make_styles([50.0], join, S.CAP_ROUND), tolerance=0.1)
+
+
+@pytest.mark.parametrize("n", [8000, 20000, 32000])
+@pytest.mark.parametrize("chunk_k", [16, 255])
+def test_short_chunks_fit_where_long_ones_did(n, chunk_k):
+    """A small scene's chunks of four records take more units than those of
+    chunk_k: a fresh scene's workspace still serves an asynchronous expansion
+    that it served with them (6 and 4 units a tag of 4 in the regions and 4 in
+    the overflow area), with the bytes of a synchronous one of long chunks."""
+    import torch
+
+    from paper_2405_00127_amd import binding as B
+
+    sc = _right_angles(n)
+    ctx = B.Context(0)
+    try:
+        ctx.set_tuning(chunk_k=chunk_k)
+        scene = ctx.encode(sc)
+        out = torch.zeros(scene.n_tags * 24 * B.RECORD_BYTES[0], dtype=torch.uint8, device="cuda")
+        status = torch.ones(2, dtype=torch.int64, device="cuda")
+        ctx.expand_async(scene, out.data_ptr(), out.numel(), status.data_ptr(), sc.tolerance, S.OUT_LINES)
+        torch.cuda.synchronize()
+        assert int(status[1]) == 0
+        # the same paths among so many that their chunks are chunk_k long
+        b = S.SceneBuilder()
+        for k in range(sc.n_paths):
+            b.add_path(*sc.path(k), 0, 0)
+        for k in range(400):
+            b.add_path([S.MOVE] + [S.LINE] * 100, np.stack([np.arange(101) * 3.0, np.arange(101) % 2], 1), 0, 0)
+        recs, n_rec, buf = ctx.expand(ctx.encode(b.build(sc.styles, tolerance=0.1)), 0.1, S.OUT_LINES)
+        m = int(status[0]) * B.RECORD_BYTES[0]
+        assert torch.equal(out[:m], buf[:m])
+    finally:
+        ctx.close()
