@@ -116,7 +116,9 @@ class DevPool {
 
 static void* pinned_get(size_t bytes) {
     void* p = nullptr;
-    return hipHostMalloc(&p, bytes, hipHostMallocDefault) == hipSuccess ? p : nullptr;
+    if (hipHostMalloc(&p, bytes, hipHostMallocDefault) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
 }
 static void pinned_put(void* p) { (void)hipHostFree(p); }
 // Scenes of up to this many verbs are encoded into the context's pinned
@@ -230,6 +232,7 @@ int fail(sx_ctx* ctx, int code, const std::string& msg) {
     return code;
 }
 int hip_fail(sx_ctx* ctx, hipError_t e, const char* what) {
+    (void)hipGetLastError();  // (reported here, not by the next launch)
     std::string m = std::string(what) + ": " + hipGetErrorString(e);
     return fail(ctx, e == hipErrorOutOfMemory ? SX_ENOMEM : SX_EDEVICE, m);
 }
@@ -575,6 +578,7 @@ int sx_ctx_create(int device, const sx_config* cfg, sx_ctx** out) {
     c->pool = std::make_shared<DevPool>(device);
     if (hipSetDevice(device) != hipSuccess) { delete c; return SX_EDEVICE; }
     if (hipHostMalloc((void**)&c->pinned, sizeof(sx::WsCtl), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
         delete c;
         return SX_ENOMEM;
     }

@@ -1,0 +1,123 @@
+"""The library's host side over a stand-in for the HIP runtime (tests/host/
+api_on_host.hip): every allocation of an entry point made to fail in turn.
+The call reports SX_ENOMEM, no launch is given a null address, nothing leaks,
+and the same call goes through afterwards.  CPU only."""
+import ctypes as C
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2405_00127_amd import binding as B
+from paper_2405_00127_amd import scenes as S
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2405_00127_amd", "csrc")
+HIPCC = "/opt/rocm/bin/hipcc" if os.path.exists("/opt/rocm/bin/hipcc") else shutil.which("hipcc")
+ENOMEM = -2
+
+
+@pytest.fixture(scope="module")
+def api(tmp_path_factory):
+    if not HIPCC:
+        pytest.skip("hipcc not available")
+    out = str(tmp_path_factory.mktemp("apihost") / "libapihost.so")
+    subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-O1", "-g", "-std=c++17", "-fPIC", "-shared",
+                           "-Wl,-Bsymbolic", "-Wno-unused-command-line-argument",
+                           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                           "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-o", out,
+                           os.path.join(os.path.dirname(__file__), "host", "api_on_host.hip"),
+                           os.path.join(CSRC, "sx_encode.cpp")], stderr=subprocess.DEVNULL)
+    L = C.CDLL(out)
+    for f in ("ah_live", "ah_dev_bytes", "ah_pin_most"):
+        getattr(L, f).restype = C.c_uint64
+    L.ah_calls.restype = C.c_long
+    L.ah_fail.argtypes = [C.c_long]
+    L.ah_limit.argtypes = [C.c_uint64]
+    L.ah_result.argtypes = [C.c_uint64] * 3
+    L.sx_expand.argtypes = [C.c_void_p, C.c_void_p, C.c_float, C.c_int, C.c_void_p, C.c_uint64, C.c_void_p, C.c_void_p]
+    L.sx_expand_async.argtypes = L.sx_expand.argtypes
+    L.ah_fail(-1)
+    L.ah_limit(2**63)
+    L.ah_new_fail(-1)
+    return L
+
+
+class Ctx:
+    def __init__(self, L, h=None):
+        self.L, self.h = L, h or C.c_void_p()
+        assert h or L.sx_ctx_create(0, None, C.byref(self.h)) == 0
+
+    def encode(self, sc, dashed=False, paths=None):
+        """Returns (status, scene)."""
+        keep = [np.ascontiguousarray(sc.verbs, np.uint8), np.ascontiguousarray(sc.verb_off, np.uint32),
+                np.ascontiguousarray(sc.pts, np.float32), np.ascontiguousarray(sc.pt_off, np.uint32),
+                np.ascontiguousarray(sc.style_ix, np.uint32), np.ascontiguousarray(sc.xform_ix, np.uint32)]
+        p = B._Paths(*[k.ctypes.data for k in keep], sc.n_paths)
+        st, xf = np.ascontiguousarray(sc.styles), np.ascontiguousarray(sc.xforms, np.float32)
+        out = C.c_void_p()
+        a = (self.h, C.byref(p), C.c_void_p(st.ctypes.data))
+        b = (C.c_uint32(len(st)), C.c_void_p(xf.ctypes.data), C.c_uint32(len(xf)), None, C.byref(out))
+        if dashed:
+            pat = np.array([3.0, 2.0], np.float32)
+            tab = (B._Dash * len(st))(*[B._Dash(pat.ctypes.data, 2, 0.0)] * len(st))
+            return self.L.sx_scene_encode_dashed(*a, tab, *b), out
+        return self.L.sx_scene_encode(*a, *b), out
+
+    def release(self, scene):
+        assert self.L.sx_scene_release(self.h, scene) == 0
+
+    def close(self):
+        assert self.L.sx_ctx_destroy(self.h) == 0
+
+
+def _each_failure(L, call, undo):
+    """call() with its k-th allocation failing, for every k."""
+    L.ah_fail(-1)
+    rc, got = call()
+    assert rc == 0
+    n = L.ah_calls()
+    undo(got)
+    assert n > 5
+    for k in range(n):
+        L.ah_fail(k)
+        rc, got = call()
+        if L.ah_calls() <= k:  # (served by kept memory: fewer allocations than at first)
+            assert rc == 0
+            undo(got)
+            break
+        assert rc == ENOMEM, (k, rc)
+        assert L.ah_bad() == 0, k
+        L.ah_fail(-1)
+        rc, got = call()
+        assert rc == 0 and L.ah_bad() == 0, k
+        undo(got)
+
+
+def _fresh(L, sc, dashed):
+    """(call, undo) encoding sc in a context of its own: nothing kept."""
+    def call():
+        h = C.c_void_p()
+        if L.sx_ctx_create(0, None, C.byref(h)):
+            return ENOMEM, None
+        ctx = Ctx(L, h)
+        rc, scene = ctx.encode(sc, dashed)
+        if rc:
+            ctx.close()
+        return rc, (ctx, scene)
+
+    def undo(got):
+        got[0].release(got[1])
+        got[0].close()
+
+    return call, undo
+
+
+@pytest.mark.parametrize("dashed", [False])
+def test_encoding_out_of_memory(api, dashed):
+    live = api.ah_live()
+    _each_failure(api, *_fresh(api, S.scene_map(1, 400, 4), dashed))
+    assert api.ah_live() == live
+
