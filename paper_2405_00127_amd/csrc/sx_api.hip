@@ -869,13 +869,14 @@ int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* s
         e = hipMemcpyAsync(b.desc, desc.data(), desc.size() * sizeof(sx::DashDesc), hipMemcpyHostToDevice, st);
     if (e == hipSuccess && !pat.empty())
         e = hipMemcpyAsync(b.pat, pat.data(), pat.size() * sizeof(int64_t), hipMemcpyHostToDevice, st);
-    A(sx::launch_zero({{b.ctl0, sx::scan_ctl_bytes()},
-                       {b.ctl1, sx::scan_ctl_bytes()},
-                       {b.ctl2, sx::scan_ctl_bytes()},
-                       {b.st0, sx::scan_status_bytes(n)},
-                       {b.st1, sx::scan_status_bytes(n)},
-                       {b.flag, sizeof(uint32_t)}},
-                      st));
+    if (e == hipSuccess)
+        e = sx::launch_zero({{b.ctl0, sx::scan_ctl_bytes()},
+                             {b.ctl1, sx::scan_ctl_bytes()},
+                             {b.ctl2, sx::scan_ctl_bytes()},
+                             {b.st0, sx::scan_status_bytes(n)},
+                             {b.st1, sx::scan_status_bytes(n)},
+                             {b.flag, sizeof(uint32_t)}},
+                            st);
     if (e == hipSuccess && n)
         e = sx::launch_scan_tags(src->d_tags, n, src->d_mon, ctl_block(src, 0), src->d_status_tags, nullptr, st);
     // phase 0: lengths, positions, subpath starts, chunks per tag and their scan
@@ -896,7 +897,7 @@ int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* s
         A(dalloc(&b.otag, nc * sizeof(uint64_t)));
         A(dalloc(&b.opt, nc * sizeof(uint64_t)));
         A(dalloc(&b.st2, sx::scan_status_bytes(b.n_ch)));
-        A(sx::launch_zero({{b.st2, sx::scan_status_bytes(b.n_ch)}}, st));
+        if (e == hipSuccess) e = sx::launch_zero({{b.st2, sx::scan_status_bytes(b.n_ch)}}, st);
         A(hipEventRecord(ev[2], st));
         if (e == hipSuccess) e = sx::launch_dash(view(src), b, 1, nullptr, nullptr, st);
         A(hipEventRecord(ev[3], st));
@@ -923,15 +924,15 @@ int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* s
         A(hipEventRecord(ev[4], st));
         if (e == hipSuccess && n) e = sx::launch_dash(view(src), b, 2, dst->d_tags, dst->d_pts, st);
         A(hipEventRecord(ev[5], st));
-        if (src->n_styles)
-            A(hipMemcpyAsync(dst->d_styles, src->d_styles, src->n_styles * sizeof(sx::StyleD),
-                             hipMemcpyDeviceToDevice, st));
-        if (src->n_xforms)
-            A(hipMemcpyAsync(dst->d_xforms, src->d_xforms, src->n_xforms * 6 * sizeof(float), hipMemcpyDeviceToDevice,
-                             st));
-        if (src->n_paths)
-            A(hipMemcpyAsync(dst->d_path_map, src->d_path_map, src->n_paths * sizeof(uint32_t),
-                             hipMemcpyDeviceToDevice, st));
+        if (e == hipSuccess && src->n_styles)
+            e = hipMemcpyAsync(dst->d_styles, src->d_styles, src->n_styles * sizeof(sx::StyleD),
+                               hipMemcpyDeviceToDevice, st);
+        if (e == hipSuccess && src->n_xforms)
+            e = hipMemcpyAsync(dst->d_xforms, src->d_xforms, src->n_xforms * 6 * sizeof(float),
+                               hipMemcpyDeviceToDevice, st);
+        if (e == hipSuccess && src->n_paths)
+            e = hipMemcpyAsync(dst->d_path_map, src->d_path_map, src->n_paths * sizeof(uint32_t),
+                               hipMemcpyDeviceToDevice, st);
         A(hipStreamSynchronize(st));
         float ms[3] = {0.0f, 0.0f, 0.0f};
         if (e == hipSuccess && n && hipEventElapsedTime(&ms[0], ev[0], ev[1]) == hipSuccess &&

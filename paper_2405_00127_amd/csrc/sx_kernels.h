@@ -57,6 +57,12 @@ struct ZeroList {
         for (const ZeroPart& x : l)
             if (n < kZeroParts) part[n++] = x;
     }
+    // no part without an address (launch_zero refuses it)
+    bool ok() const {
+        for (const ZeroPart& x : part)
+            if (x.bytes && !x.p) return false;
+        return true;
+    }
 };
 hipError_t launch_zero(const ZeroList& list, hipStream_t s);
 

@@ -1711,6 +1711,7 @@ __global__ __launch_bounds__(256) void zero_kernel(ZeroList l) {
     }
 }
 hipError_t launch_zero(const ZeroList& list, hipStream_t s) {
+    if (!list.ok()) return hipErrorInvalidValue;
     size_t most = 0;
     for (const ZeroPart& x : list.part) most = std::max(most, x.bytes);
     if (most == 0) return hipSuccess;

@@ -116,6 +116,7 @@ hipError_t launch_zero(const ZeroList& l, hipStream_t) {
             need({x.p});
             if (x.p) memset(x.p, 0, std::min<size_t>(x.bytes, (size_t)1 << 22));
         }
+    if (!l.ok()) return hipErrorInvalidValue;
     return launched();
 }
 hipError_t launch_scan_tags(const uint8_t* tags, uint32_t, uint32_t* mon, void* ctl, void* st, WsCtl*, hipStream_t) {
@@ -190,6 +191,7 @@ hipError_t launch_dash(const SceneView& sv, const DashBufs& b, int phase, uint8_
 }  // namespace sx
 
 extern "C" {
+int ah_zero_ok(void* a, size_t na, void* b, size_t nb) { return sx::ZeroList{{a, na}, {b, nb}}.ok(); }
 void ah_fail(long k) { g_calls = 0, g_fail = k; }
 long ah_calls() { return g_calls; }
 void ah_limit(size_t n) { g_limit = n; }

@@ -115,9 +115,14 @@ def _fresh(L, sc, dashed):
     return call, undo
 
 
-@pytest.mark.parametrize("dashed", [False])
+@pytest.mark.parametrize("dashed", [False, True])
 def test_encoding_out_of_memory(api, dashed):
     live = api.ah_live()
     _each_failure(api, *_fresh(api, S.scene_map(1, 400, 4), dashed))
     assert api.ah_live() == live
 
+
+def test_zeroing_needs_an_address(api):
+    api.ah_zero_ok.argtypes = [C.c_void_p, C.c_uint64, C.c_void_p, C.c_uint64]
+    assert api.ah_zero_ok(64, 4, None, 0) and api.ah_zero_ok(64, 4, 128, 8)
+    assert not api.ah_zero_ok(64, 4, None, 8) and not api.ah_zero_ok(None, 4, 128, 8)
