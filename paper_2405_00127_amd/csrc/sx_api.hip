@@ -355,7 +355,8 @@ hipError_t size_slots(sx_scene* s, uint64_t slot_cap, uint32_t region_per_piece,
         p = nullptr;
     };
     auto dalloc = [&](auto** p, size_t bytes) { return s->pool->take((void**)p, bytes); };
-    if (slot_cap != s->slot_cap || !s->d_slots) {
+    if (slot_cap != s->slot_cap) {
+        s->slot_cap = 0;  // (until all of them are there)
         dfree(s->d_slots);
         dfree(s->d_rc);
         dfree(s->d_roff);
@@ -401,6 +402,7 @@ hipError_t reserve_scene(sx_scene* s, uint32_t n_tags, uint32_t n_pts, uint32_t 
     };
     if (first || n_tags > s->cap_tags) {
         const uint32_t c = n_tags;
+        s->cap_tags = 0;  // (until everything is there)
         const size_t ntag_pad = ((size_t)c + 16 + 15) & ~(size_t)15;
         regrow(s->d_tags, ntag_pad);
         regrow(s->d_mon, 4 * (size_t)sx::mon_stride_of(c) * sizeof(uint32_t));
@@ -419,7 +421,6 @@ hipError_t reserve_scene(sx_scene* s, uint32_t n_tags, uint32_t n_pts, uint32_t 
             A(dalloc(&s->d_ws_ctl, sizeof(sx::WsCtl)));
         }
         if (e != hipSuccess) return e;
-        s->cap_tags = c;
         // the tag padding, the scans' status words (epoch 0: not ready) and counters
         A(sx::launch_zero({{s->d_tags, ntag_pad},
                            {s->d_status_tags, sx::scan_status_bytes(c)},
@@ -428,27 +429,28 @@ hipError_t reserve_scene(sx_scene* s, uint32_t n_tags, uint32_t n_pts, uint32_t 
                            {s->d_ws_ctl, first ? sizeof(sx::WsCtl) : 0}},
                           st));
         const uint64_t want = std::max<uint64_t>((uint64_t)c * kSlotsPerTag, kMinSlots);
-        if (!streams_only && want > s->slot_cap) {
+        if (e == hipSuccess && !streams_only && (want > s->slot_cap || !s->d_items)) {
             const uint32_t region = s->region_per_piece ? s->region_per_piece : kRegionPerPiece;
-            A(size_slots(s, std::min<uint64_t>(want, kMaxSlotCap), region,
+            A(size_slots(s, std::min<uint64_t>(std::max(want, s->slot_cap), kMaxSlotCap), region,
                          std::max<uint64_t>(std::max<uint64_t>(want, s->ovf_cap), kMinOverflow), st));
         }
+        if (e == hipSuccess) s->cap_tags = c;
     }
     if (first || n_pts > s->cap_pts) {
         regrow(s->d_pts, (size_t)n_pts * sizeof(float2));
-        s->cap_pts = n_pts;
+        s->cap_pts = e == hipSuccess ? n_pts : 0;
     }
     if (first || n_styles > s->cap_styles) {
         regrow(s->d_styles, (size_t)n_styles * sizeof(sx::StyleD));
-        s->cap_styles = n_styles;
+        s->cap_styles = e == hipSuccess ? n_styles : 0;
     }
     if (first || n_xforms > s->cap_xforms) {
         regrow(s->d_xforms, (size_t)n_xforms * 6 * sizeof(float));
-        s->cap_xforms = n_xforms;
+        s->cap_xforms = e == hipSuccess ? n_xforms : 0;
     }
     if (first || n_paths > s->cap_paths) {
         regrow(s->d_path_map, (size_t)n_paths * sizeof(uint32_t));
-        s->cap_paths = n_paths;
+        s->cap_paths = e == hipSuccess ? n_paths : 0;
     }
     if (e == hipSuccess) s->allocated = true;
     return e;
@@ -513,9 +515,17 @@ hipError_t run_one(const sx_ctx* ctx, const sx_scene* s, const sx::Cfg& conf, in
     return hipErrorInvalidValue;
 }
 
+// Whether everything a launch needs is allocated (a scene or batch whose
+// growth failed keeps what it could not replace at capacity 0).
+bool allocated(const sx_scene* s) {
+    return s->n_tags <= s->cap_tags && s->n_pts <= s->cap_pts && s->n_styles <= s->cap_styles &&
+           s->n_xforms <= s->cap_xforms && s->n_paths <= s->cap_paths && s->slot_cap && s->d_items;
+}
+
 // the whole pipeline; dst (device) receives {records, 0 or 1 = workspace too small}
 int run_all(sx_ctx* ctx, const sx_scene* s, const sx::Cfg& cfg, void* out, uint64_t cap_records, uint64_t* dst,
             hipStream_t st) {
+    if (s->n_tags && !allocated(s)) return fail(ctx, SX_ENOMEM, "workspace");
     hipError_t e = s->n_tags == 0 ? sx::launch_no_records(dst, st) : hipSuccess;
     for (int ph = 0; ph < kPhN && e == hipSuccess; ph++) e = run_one(ctx, s, cfg, ph, out, cap_records, nullptr, st, dst);
     return e == hipSuccess ? SX_OK : hip_fail(ctx, e, "pipeline launch");
@@ -527,6 +537,11 @@ int run_all(sx_ctx* ctx, const sx_scene* s, const sx::Cfg& cfg, void* out, uint6
 // functions of the scene, tolerance and mode, so the grown run fits.
 int run_sized(sx_ctx* ctx, sx_scene* s, const sx::Cfg& cfg, void* out, uint64_t cap_records, uint64_t* n_records,
               hipStream_t st) {
+    if (!s->slot_cap || !s->d_items) {  // a growth that failed
+        const uint64_t cap = s->slot_cap ? s->slot_cap : std::max<uint64_t>((uint64_t)s->cap_tags * kSlotsPerTag, kMinSlots);
+        hipError_t e = size_slots(s, std::min<uint64_t>(cap, kMaxSlotCap), s->region_per_piece, std::max(s->ovf_cap, cap), st);
+        if (e != hipSuccess) return hip_fail(ctx, e, "workspace allocation");
+    }
     for (int attempt = 0; attempt < 3; attempt++) {
         uint64_t* dst = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(s->d_ws_ctl) + offsetof(sx::WsCtl, result));
         int r = run_all(ctx, s, cfg, out, cap_records, dst, st);
@@ -1049,6 +1064,7 @@ int sx_run_phase(sx_ctx* ctx, const sx_scene* s, int phase, float tolerance, int
     if (phase < 0 || phase >= kPhN) return fail(ctx, SX_EINVAL, "bad phase");
     if (phase == kPhRecords && out_capacity_bytes && !out_dev) return fail(ctx, SX_EINVAL, "null output buffer");
     if (s->n_tags == 0) return SX_OK;
+    if (!allocated(s)) return fail(ctx, SX_ENOMEM, "workspace");
     hipStream_t st = (hipStream_t)stream;
     const_cast<sx_scene*>(s)->last_stream = st;
     const uint64_t rec = output_mode == SX_OUT_ARCS ? sizeof(sx_arc) : sizeof(sx_line);
@@ -1230,6 +1246,7 @@ int sx_debug_piece_stats(sx_ctx* ctx, const sx_scene* s, float tolerance, int ou
 
 int sx_debug_monoids(sx_ctx* ctx, const sx_scene* s, uint32_t* out4xn_dev, void* stream) {
     if (!ctx || !s || (!out4xn_dev && s->n_tags)) return SX_EINVAL;
+    if (s->n_tags > s->cap_tags) return fail(ctx, SX_ENOMEM, "workspace");
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = sx::launch_scan_tags(s->d_tags, s->n_tags, s->d_mon, ctl_block(s, 0), s->d_status_tags, nullptr, st);
     const size_t stride = sx::mon_stride_of(s->n_tags);

@@ -12,7 +12,7 @@
 namespace {
 std::map<void*, size_t> g_live;  // allocations, device and pinned
 size_t g_dev_bytes, g_pin_most;  // device bytes held, largest pinned request
-long g_calls, g_fail = -1;       // allocations so far; the one that fails (-2: every pinned one)
+long g_calls, g_fail = -1;       // allocations so far; the first one that fails (-2: every pinned one)
 size_t g_limit = ~(size_t)0;     // device bytes there are
 int g_bad;                       // launches given a null address, frees of what is not live
 int g_syncs;                     // hipDeviceSynchronize calls
@@ -28,6 +28,7 @@ void need(std::initializer_list<const void*> ps) {
     for (const void* p : ps)
         if (!p) g_bad++;
 }
+bool fails() { return g_calls++ >= g_fail && g_fail >= 0; }
 hipError_t launched() {
     const hipError_t e = g_last;  // as hipGetLastError after a launch
     g_last = hipSuccess;
@@ -46,7 +47,7 @@ void operator delete(void* p, size_t) noexcept { free(p); }
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
     *p = nullptr;
-    if (g_calls++ == g_fail || g_dev_bytes + n > g_limit) return out(hipErrorOutOfMemory);
+    if (fails() || g_dev_bytes + n > g_limit) return out(hipErrorOutOfMemory);
     // (only what the host side touches is backed: the tests stay small)
     *p = calloc(1, n < ((size_t)1 << 22) ? n : (size_t)1 << 22);
     g_live[*p] = n;
@@ -67,7 +68,7 @@ hipError_t hipFree(void* p) {
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
     *p = nullptr;
     if (n > g_pin_most) g_pin_most = n;
-    if (g_calls++ == g_fail || g_fail == -2) return out(hipErrorOutOfMemory);
+    if (fails() || g_fail == -2) return out(hipErrorOutOfMemory);
     *p = malloc(n);
     g_live[*p] = 0;
     return hipSuccess;

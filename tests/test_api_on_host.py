@@ -1,5 +1,5 @@
 """The library's host side over a stand-in for the HIP runtime (tests/host/
-api_on_host.hip): every allocation of an entry point made to fail in turn.
+api_on_host.hip): the allocations of an entry point made to fail from each one on.
 The call reports SX_ENOMEM, no launch is given a null address, nothing leaks,
 and the same call goes through afterwards.  CPU only."""
 import ctypes as C
@@ -74,7 +74,7 @@ class Ctx:
 
 
 def _each_failure(L, call, undo):
-    """call() with its k-th allocation failing, for every k."""
+    """call() with no allocation after its first k, for every k."""
     L.ah_fail(-1)
     rc, got = call()
     assert rc == 0
@@ -126,3 +126,74 @@ def test_zeroing_needs_an_address(api):
     api.ah_zero_ok.argtypes = [C.c_void_p, C.c_uint64, C.c_void_p, C.c_uint64]
     assert api.ah_zero_ok(64, 4, None, 0) and api.ah_zero_ok(64, 4, 128, 8)
     assert not api.ah_zero_ok(64, 4, None, 8) and not api.ah_zero_ok(None, 4, 128, 8)
+
+
+def test_growing_a_workspace_out_of_memory(api):
+    """A synchronous expansion that has to grow its slots or items: after a
+    failed growth nothing is launched on what is missing, an asynchronous call
+    reports it, and a synchronous one makes up for it."""
+    live = api.ah_live()
+    ctx = Ctx(api)
+    n = C.c_uint64()
+    words = (C.c_uint64 * 2)()
+    for slots, items, ovf in ((200_000, 10_000, 0), (3_000, 900_000, 800_000)):
+        for k in range(100):
+            rc, scene = ctx.encode(S.scene_map(1, 400, 4))
+            assert rc == 0
+            api.ah_result(slots, items, ovf)
+            api.ah_fail(k)
+            rc = api.sx_expand(ctx.h, scene, 0.25, 0, None, 0, C.byref(n), None)
+            over = api.ah_calls() <= k
+            assert rc == (0 if over else ENOMEM)
+            api.ah_fail(-1)
+            assert api.sx_expand_async(ctx.h, scene, 0.25, 0, None, 0, words, None) in (0, ENOMEM)
+            assert api.ah_bad() == 0, (slots, k)
+            assert api.sx_expand(ctx.h, scene, 0.25, 0, None, 0, C.byref(n), None) == 0
+            assert api.sx_expand_async(ctx.h, scene, 0.25, 0, None, 0, words, None) == 0 and words[1] == 0
+            assert api.ah_bad() == 0, (slots, k)
+            ctx.release(scene)
+            ctx.close()  # (nothing kept for the next one)
+            ctx = Ctx(api)
+            if over:
+                break
+        assert over and k > 0
+    ctx.close()
+    assert api.ah_live() == live
+
+
+def test_growing_a_batch_out_of_memory(api):
+    """After a failed growth the batch expands nothing until it is set again,
+    to less or to as much."""
+    live = api.ah_live()
+    api.ah_result(100, 100, 0)
+    words = (C.c_uint64 * 8)()
+    f32, i32, u64 = C.c_float, C.c_int, C.c_uint64
+    for k in range(100):
+        ctx = Ctx(api)
+        (r0, small), (r1, large) = ctx.encode(S.scene_map(1, 40, 1)), ctx.encode(S.scene_map(2, 60_000, 600))
+        batch = C.c_void_p()
+        assert r0 == r1 == 0 and api.sx_batch_create(ctx.h, C.byref(batch)) == 0
+
+        def put(scene):
+            return api.sx_batch_set(ctx.h, batch, (C.c_void_p * 1)(scene), C.c_uint32(1), None)
+
+        def expand():
+            return api.sx_batch_expand(ctx.h, batch, f32(0.25), i32(0), None, u64(0), words, words, None)
+
+        assert put(small) == 0 and expand() == 0
+        api.ah_fail(k)
+        rc = put(large)
+        over = api.ah_calls() <= k
+        assert rc == (0 if over else ENOMEM)
+        api.ah_fail(-1)
+        assert expand() in (0, ENOMEM) and api.ah_bad() == 0, k
+        assert put(small) == 0 and expand() == 0 and api.ah_bad() == 0, k
+        assert put(large) == 0 and expand() == 0 and api.ah_bad() == 0, k
+        assert api.sx_batch_destroy(ctx.h, batch) == 0
+        ctx.release(small)
+        ctx.release(large)
+        ctx.close()
+        if over:
+            break
+    assert over and k > 5
+    assert api.ah_live() == live
