@@ -121,8 +121,9 @@ static void* pinned_get(size_t bytes) {
     return nullptr;
 }
 static void pinned_put(void* p) { (void)hipHostFree(p); }
-// Scenes of up to this many verbs are encoded into the context's pinned
-// buffers (a few MB, kept); larger ones into pageable memory of their own.
+// Scenes of up to this many verbs and paths are encoded into the context's
+// pinned buffers (at most about 15 MB, kept); larger ones, or when those
+// cannot be had, into pageable memory of their own.
 constexpr uint32_t kPinnedVerbs = 1u << 18;
 
 struct sx_ctx {
@@ -705,13 +706,21 @@ static int encode_impl(sx_ctx* ctx, const sx_paths* paths, const sx_style* style
     if ((n_styles && !styles) || (n_xforms && !xforms)) return fail(ctx, SX_EINVAL, "null style/transform table");
     if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, SX_EDEVICE, "hipSetDevice");
     sx::HostEncoding own;
-    sx::HostEncoding& enc = paths->n_paths && paths->verb_off[paths->n_paths] > kPinnedVerbs ? own : ctx->enc;
+    const bool large = paths->n_paths && std::max(paths->verb_off[paths->n_paths], paths->n_paths) > kPinnedVerbs;
+    sx::HostEncoding* to = large ? &own : &ctx->enc;
     std::string err;
-    try {
-        if (!sx::encode_paths(*paths, styles, n_styles, n_xforms, enc, err)) return fail(ctx, SX_EINVAL, err);
-    } catch (const std::bad_alloc&) {
-        return fail(ctx, SX_ENOMEM, "host encoding");
+    for (bool done = false; !done;) {
+        try {
+            if (!sx::encode_paths(*paths, styles, n_styles, n_xforms, *to, err)) return fail(ctx, SX_EINVAL, err);
+            done = true;
+        } catch (const std::bad_alloc&) {
+            if (to == &own) return fail(ctx, SX_ENOMEM, "host encoding");
+            ctx->enc.tags.reset();
+            ctx->enc.data.reset();
+            to = &own;
+        }
     }
+    const sx::HostEncoding& enc = *to;
     // validate the styles and transforms that are actually used
     std::vector<sx::StyleD> sd(enc.style_stream.size());
     for (size_t i = 0; i < enc.style_stream.size(); i++) {

@@ -9,6 +9,7 @@
 // point is added where a subpath ends elsewhere without a closepath.
 #include "sx_encode.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 
@@ -41,9 +42,11 @@ bool encode_paths(const sx_paths& in, const sx_style* styles, uint32_t n_styles,
     out.clear();
     if (in.n_paths) {
         // about what comes out: a marker and three points per path besides
-        // the input's (room() below covers whatever there is)
-        out.tags.room((size_t)in.verb_off[in.n_paths] + 2 * (size_t)in.n_paths);
-        out.data.room(2 * ((size_t)in.pt_off[in.n_paths] + 4 * (size_t)in.n_paths));
+        // the input's (room() below covers whatever there is; the offsets are
+        // not checked yet: no more points than the verbs can have)
+        const size_t verbs = in.verb_off[in.n_paths], pts = in.pt_off[in.n_paths];
+        out.tags.room(verbs + 2 * (size_t)in.n_paths);
+        out.data.room(2 * (std::min(pts, 3 * verbs) + 4 * (size_t)in.n_paths));
     }
     int64_t prev_style = -1, prev_xf = -1;
     auto put_pt = [&](float x, float y) {
@@ -61,6 +64,13 @@ bool encode_paths(const sx_paths& in, const sx_style* styles, uint32_t n_styles,
         const bool fill = (styles[in.style_ix[k]].flags & SX_STYLE_FILL) != 0;
         const float* P = in.pts + 2 * (size_t)in.pt_off[k];
         const uint32_t np = in.pt_off[k + 1] - in.pt_off[k];
+        // (points that the verbs have: with other offsets nothing is read ahead)
+        uint32_t has = 0;
+        for (uint32_t vi = in.verb_off[k]; vi < in.verb_off[k + 1]; vi++) {
+            const uint32_t v = in.verbs[vi];
+            has += v > 3u ? 0u : (v ? v : 1u);
+        }
+        const bool ahead = has == np;
         uint32_t pi = 0;
         SubpathState sp;
         auto close_line = [&]() {
@@ -88,7 +98,7 @@ bool encode_paths(const sx_paths& in, const sx_style* styles, uint32_t n_styles,
             // a verb adds at most a closing line and a marker, or its own points and a start
             out.tags.room(4);
             out.data.room(16);
-            if (v - 1u < 3u && pi + 3 <= np && sp.has_dir) {
+            if (v - 1u < 3u && ahead && pi + 3 <= np && sp.has_dir) {
                 const uint32_t c = v;
                 // inside a path every segment reads three points and
                 // advances by its own, with no branch on its degree (the

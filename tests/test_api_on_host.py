@@ -197,3 +197,28 @@ def test_growing_a_batch_out_of_memory(api):
             break
     assert over and k > 5
     assert api.ah_live() == live
+
+
+def test_malformed_offsets_reserve_no_memory(api):
+    """Offsets are read before they are checked: a point offset far past the
+    points is refused without memory for the points that it names."""
+    ctx = Ctx(api)
+    sc = S.single_path_scene([S.MOVE, S.LINE, S.LINE], [[0, 0], [9, 0], [9, 9]], 1.0)
+    sc.pt_off = np.array([0, 0xFFFFFFF0], np.uint32)
+    api.ah_pin_most()
+    assert ctx.encode(sc)[0] == -1
+    assert api.ah_pin_most() < 4096
+    ctx.close()
+
+
+def test_encoding_without_pinned_memory(api):
+    live = api.ah_live()
+    ctx = Ctx(api)
+    for sc in (S.scene_map(1, 400, 4), S.scene_map(2, 4000, 40)):
+        api.ah_fail(-2)
+        rc, scene = ctx.encode(sc)
+        api.ah_fail(-1)
+        assert rc == 0 and api.ah_last() == 0
+        ctx.release(scene)
+    ctx.close()
+    assert api.ah_live() == live

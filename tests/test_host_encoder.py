@@ -103,3 +103,27 @@ def test_host_encoder_rejects_what_the_oracle_rejects(shim, bad):
     rc, _ = _encode(shim, sc)
     assert rc == -1
     assert O.encode(sc).status == -1
+
+
+def test_offsets_past_the_points_are_refused_without_reading_them(shim):
+    """The point offsets say more points than there are: the verbs' own points
+    are all that is read (the array ends at a page that cannot be)."""
+    import mmap
+
+    libc = C.CDLL(None, use_errno=True)
+    page = mmap.PAGESIZE
+    libc.mmap.restype = C.c_void_p
+    libc.mmap.argtypes = [C.c_void_p, C.c_size_t, C.c_int, C.c_int, C.c_int, C.c_long]
+    libc.mprotect.argtypes = [C.c_void_p, C.c_size_t, C.c_int]
+    at = libc.mmap(None, 2 * page, 3, mmap.MAP_PRIVATE | mmap.MAP_ANONYMOUS, -1, 0)
+    assert libc.mprotect(at + page, page, 0) == 0
+    verbs = np.array([S.MOVE, S.LINE, S.LINE, S.LINE], np.uint8)
+    pts = np.array([[0, 0], [9, 0], [9, 9], [0, 9]], np.float32)
+    where = at + page - pts.nbytes
+    C.memmove(where, pts.ctypes.data, pts.nbytes)
+    off, ix = np.array([0, 4], np.uint32), np.zeros(1, np.uint32)
+    st = S.make_styles([1.0], S.JOIN_ROUND, S.CAP_BUTT)
+    for n, want in ((4, 0), (7, -1), (1 << 20, -1)):
+        pt_off = np.array([0, n], np.uint32)
+        p = _Paths(verbs.ctypes.data, off.ctypes.data, where, pt_off.ctypes.data, ix.ctypes.data, ix.ctypes.data, 1)
+        assert shim.shim_encode(C.byref(p), st.ctypes.data, 1, 1) == want, n
