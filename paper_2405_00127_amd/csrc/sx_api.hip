@@ -32,12 +32,15 @@ class DevPool {
     DevPool(const DevPool&) = delete;
     DevPool& operator=(const DevPool&) = delete;
     ~DevPool() { close(); }
-    // Waits for the device; false when that failed (a stream being captured).
+    // Waits for the device; false when that failed.  By freeing a small block:
+    // hipFree waits for every stream, and a stream captured in the relaxed mode
+    // goes on, where hipDeviceSynchronize would end its capture.
     bool idle() {
         int cur = device_;
         (void)hipGetDevice(&cur);
         if (cur != device_ && hipSetDevice(device_) != hipSuccess) return false;
-        const bool ok = hipDeviceSynchronize() == hipSuccess;
+        void* p = nullptr;
+        const bool ok = hipMalloc(&p, 16) == hipSuccess && hipFree(p) == hipSuccess;
         if (!ok) (void)hipGetLastError();
         if (cur != device_) (void)hipSetDevice(cur);
         return ok;

@@ -15,7 +15,7 @@ size_t g_dev_bytes, g_pin_most;  // device bytes held, largest pinned request
 long g_calls, g_fail = -1;       // allocations so far; the first one that fails (-2: every pinned one)
 size_t g_limit = ~(size_t)0;     // device bytes there are
 int g_bad;                       // launches given a null address, frees of what is not live
-int g_syncs;                     // hipDeviceSynchronize calls
+int g_capture;                   // 1: a stream is being captured, relaxed; 2: its capture was ended by a wait
 hipError_t g_last = hipSuccess;
 int g_new_fail = -1;             // C++ allocations until one fails
 sx::WsCtl g_result;              // what the next expansion leaves
@@ -47,7 +47,8 @@ void operator delete(void* p, size_t) noexcept { free(p); }
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
     *p = nullptr;
-    if (fails() || g_dev_bytes + n > g_limit) return out(hipErrorOutOfMemory);
+    // (16 bytes: the pool's wait for the device, which no call depends on)
+    if ((n > 16 && fails()) || g_dev_bytes + n > g_limit) return out(hipErrorOutOfMemory);
     // (only what the host side touches is backed: the tests stay small)
     *p = calloc(1, n < ((size_t)1 << 22) ? n : (size_t)1 << 22);
     g_live[*p] = n;
@@ -86,8 +87,9 @@ hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) {
     return hipSuccess;
 }
 hipError_t hipDeviceSynchronize() {
-    g_syncs++;
-    return hipSuccess;
+    if (!g_capture) return hipSuccess;
+    g_capture = 2;
+    return out(hipErrorStreamCaptureUnsupported);
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
@@ -199,7 +201,11 @@ void ah_limit(size_t n) { g_limit = n; }
 void ah_new_fail(int k) { g_new_fail = k; }
 int ah_new_left() { return g_new_fail; }
 int ah_bad() { return g_bad; }
-int ah_syncs() { return g_syncs; }
+int ah_capture(int on) {
+    const int was = g_capture;
+    g_capture = on;
+    return was;
+}
 int ah_last() { return (int)launched(); }
 uint64_t ah_live() { return g_live.size(); }
 uint64_t ah_dev_bytes() { return g_dev_bytes; }

@@ -222,3 +222,14 @@ def test_encoding_without_pinned_memory(api):
         ctx.release(scene)
     ctx.close()
     assert api.ah_live() == live
+
+
+def test_release_leaves_a_capture_alone(api):
+    """A scene released while another stream is captured (relaxed mode)."""
+    ctx = Ctx(api)
+    rc, scene = ctx.encode(S.scene_map(1, 400, 4))
+    assert rc == 0
+    api.ah_capture(1)
+    ctx.release(scene)
+    assert api.ah_capture(0) == 1
+    ctx.close()

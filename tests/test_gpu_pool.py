@@ -79,3 +79,60 @@ def test_batch_outlives_its_context():
     batch.prepare(0.25, 0)
     ctx.close()
     batch.destroy()
+
+
+def test_release_while_another_scene_is_captured():
+    """A relaxed capture goes on when a scene is released; its graph replays."""
+    import torch
+
+    from paper_2405_00127_amd import binding as B
+
+    torch.cuda.set_device(0)
+    ctx = B.Context(0)
+    sc = S.scene_map(1, 3000, 30)
+    scene, want = _records(ctx, sc)
+    other, _ = _records(ctx, S.scene_map(2, 3000, 30))
+    out = torch.zeros(want.nbytes, dtype=torch.uint8, device="cuda")
+    status = torch.zeros(2, dtype=torch.int64, device="cuda")
+    torch.cuda.synchronize()
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        graph.capture_begin(capture_error_mode="relaxed")
+        ctx.expand_async(scene, out.data_ptr(), out.numel(), status.data_ptr(), sc.tolerance, 0, stream=stream)
+        other.release()
+        graph.capture_end()
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), want.reshape(-1).view(np.uint32))
+    scene.release()
+    ctx.close()
+
+
+def test_release_waits_for_every_stream():
+    """Work of a scene that is still queued on a stream other than its last."""
+    import torch
+
+    from paper_2405_00127_amd import binding as B
+
+    torch.cuda.set_device(0)
+    ctx = B.Context(0)
+    scene, want = _records(ctx, S.scene_map(7, 40000, 400))
+    busy, last = torch.cuda.Stream(), torch.cuda.Stream()
+    out = torch.empty(want.nbytes, dtype=torch.uint8, device="cuda")
+    status = torch.zeros(2, dtype=torch.int64, device="cuda")
+    work = torch.ones(1 << 28, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(busy):
+        for _ in range(40):
+            work.mul_(1.0)
+    ctx.expand_async(scene, out.data_ptr(), out.numel(), status.data_ptr(), 0.25, 0, stream=busy)
+    done = busy.record_event()
+    # (the scene's last stream, with no work queued on it)
+    ctx.run_phase(scene, 2, 0.25, 0, stream=last)
+    assert not done.query()
+    scene.release()
+    assert done.query()
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), want.reshape(-1).view(np.uint32))
+    ctx.close()
