@@ -160,7 +160,13 @@ const char *sx_version(void);
  * reserved style flags, for strokes half_width < 0, miter_limit < 1, bad
  * join or cap, or a transform that is not a similarity; for fills a
  * transform that is not an invertible finite affine map),
- * SX_ENOMEM, SX_EDEVICE.  The scene is owned by ctx. */
+ * SX_ENOMEM, SX_EDEVICE.  The scene is owned by ctx.
+ * Of the device memory of scenes that are released, their context keeps
+ * blocks of 256 KB and more, up to 384 MB in all, for the scenes that it
+ * encodes next (a block serves requests of at least half its size).
+ * sx_ctx_destroy gives them back, and so does, in every context of the
+ * process, an allocation of this library that fails; other users of the
+ * device's memory cannot reclaim them. */
 int sx_scene_encode(sx_ctx *ctx, const sx_paths *paths, const sx_style *styles, uint32_t n_styles,
                     const sx_affine *xforms, uint32_t n_xforms, void *stream, sx_scene **out);
 /* Dash pattern of a stroke style (SVG stroke-dasharray / stroke-dashoffset,

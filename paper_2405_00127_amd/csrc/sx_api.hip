@@ -26,12 +26,23 @@
 // idle, as hipFree would wait for it, so it has no user on any stream.
 // Shared by the context and its scenes (a scene may be released after its
 // context; nothing is kept then).
+// A device allocation that fails makes every context of the process give its
+// kept blocks back.
 class DevPool {
    public:
-    explicit DevPool(int device) : device_(device) {}
+    explicit DevPool(int device) : device_(device) {
+        std::lock_guard<std::mutex> lk(all_mu());
+        all().push_back(this);
+    }
     DevPool(const DevPool&) = delete;
     DevPool& operator=(const DevPool&) = delete;
-    ~DevPool() { close(); }
+    ~DevPool() {
+        {
+            std::lock_guard<std::mutex> lk(all_mu());
+            all().erase(std::find(all().begin(), all().end(), this));
+        }
+        close();
+    }
     // Waits for the device; false when that failed.  By freeing a small block:
     // hipFree waits for every stream, and a stream captured in the relaxed mode
     // goes on, where hipDeviceSynchronize would end its capture.
@@ -46,10 +57,10 @@ class DevPool {
         return ok;
     }
     hipError_t take(void** p, size_t bytes) {
-        std::lock_guard<std::mutex> lk(mu_);
         *p = nullptr;
         bytes = (std::max<size_t>(bytes, 16) + 255) & ~(size_t)255;
         if (bytes >= kPoolMin) {
+            std::lock_guard<std::mutex> lk(mu_);
             // the smallest block that holds it, at most twice its size
             size_t best = held_.size();
             for (size_t i = 0; i < held_.size(); i++)
@@ -60,18 +71,20 @@ class DevPool {
                 const Blk b = held_[best];
                 held_.erase(held_.begin() + (ptrdiff_t)best);
                 total_ -= b.bytes;
-                out_[b.p] = b.bytes;
+                note(b.p, b.bytes);
                 *p = b.p;
                 return hipSuccess;
             }
         }
         hipError_t e = hipMalloc(p, bytes);
-        if (e == hipErrorOutOfMemory && !held_.empty()) {
+        if (e == hipErrorOutOfMemory && trim_all()) {
             (void)hipGetLastError();
-            trim(0);
             e = hipMalloc(p, bytes);
         }
-        if (e == hipSuccess && bytes >= kPoolMin) out_[*p] = bytes;
+        if (e == hipSuccess && bytes >= kPoolMin) {
+            std::lock_guard<std::mutex> lk(mu_);
+            note(*p, bytes);
+        }
         return e;
     }
     // Gives a block back; is_idle: idle() was called and held.
@@ -82,12 +95,15 @@ class DevPool {
         const size_t bytes = it == out_.end() ? 0 : it->second;
         if (bytes) out_.erase(it);
         if (bytes && bytes <= kPoolBytes && is_idle && !closed_) {
-            held_.push_back(Blk{p, bytes});
-            total_ += bytes;
-            trim(kPoolBytes);
-        } else {
-            (void)hipFree(p);
+            try {
+                held_.push_back(Blk{p, bytes});
+                total_ += bytes;
+                trim(kPoolBytes);
+                return;
+            } catch (const std::bad_alloc&) {
+            }
         }
+        (void)hipFree(p);
     }
     void close() {
         std::lock_guard<std::mutex> lk(mu_);
@@ -101,6 +117,33 @@ class DevPool {
         void* p;
         size_t bytes;
     };
+    // (never destroyed: a context may outlive the library's static objects)
+    static std::mutex& all_mu() {
+        static std::mutex* m = new std::mutex;
+        return *m;
+    }
+    static std::vector<DevPool*>& all() {
+        static std::vector<DevPool*>* v = new std::vector<DevPool*>;
+        return *v;
+    }
+    // frees what every pool holds; false when that was nothing
+    static bool trim_all() {
+        std::lock_guard<std::mutex> lk(all_mu());
+        bool any = false;
+        for (DevPool* q : all()) {
+            std::lock_guard<std::mutex> lq(q->mu_);
+            any = any || !q->held_.empty();
+            q->trim(0);
+        }
+        return any;
+    }
+    // the size of a block in use (one that is not noted is freed, not kept)
+    void note(void* p, size_t bytes) {
+        try {
+            out_[p] = bytes;
+        } catch (const std::bad_alloc&) {
+        }
+    }
     // frees the oldest blocks until at most `most` bytes are held
     void trim(size_t most) {
         while (!held_.empty() && (total_ > most || held_.size() > kPoolBlocks)) {

@@ -233,3 +233,23 @@ def test_release_leaves_a_capture_alone(api):
     ctx.release(scene)
     assert api.ah_capture(0) == 1
     ctx.close()
+
+
+def test_kept_blocks_are_given_back_to_another_context(api):
+    """Blocks that a context keeps for its next scene do not take the device's
+    last memory from another context."""
+    live = api.ah_live()
+    one, two = Ctx(api), Ctx(api)
+    rc, scene = one.encode(S.scene_map(1, 400, 4))
+    assert rc == 0
+    need = api.ah_dev_bytes()
+    one.release(scene)
+    assert api.ah_dev_bytes() > need // 2  # kept
+    api.ah_limit(need + need // 8)
+    rc, scene = two.encode(S.scene_map(1, 400, 4))
+    assert rc == 0
+    api.ah_limit(2**63)
+    two.release(scene)
+    one.close()
+    two.close()
+    assert api.ah_live() == live
