@@ -101,6 +101,7 @@ class DevPool {
                 trim(kPoolBytes);
                 return;
             } catch (const std::bad_alloc&) {
+                // (freed, not kept)
             }
         }
         (void)hipFree(p);
@@ -274,14 +275,31 @@ constexpr uint64_t kMinSlots = 4096;
 constexpr uint64_t kMinOverflow = 65536;    // initial shared overflow units (minimum)
 constexpr uint32_t kMaxSlotCap = 0xfffff000u;  // slots are indexed by u32
 
-int fail(sx_ctx* ctx, int code, const std::string& msg) {
-    if (ctx) ctx->err = msg;
+int fail(sx_ctx* ctx, int code, const char* msg) noexcept {
+    try {
+        if (ctx) ctx->err = msg;
+    } catch (const std::bad_alloc&) {
+        ctx->err.clear();
+    }
     return code;
 }
-int hip_fail(sx_ctx* ctx, hipError_t e, const char* what) {
+
+int hip_fail(sx_ctx* ctx, hipError_t e, const char* what) noexcept {
     (void)hipGetLastError();  // (reported here, not by the next launch)
-    std::string m = std::string(what) + ": " + hipGetErrorString(e);
-    return fail(ctx, e == hipErrorOutOfMemory ? SX_ENOMEM : SX_EDEVICE, m);
+    char msg[256];
+    snprintf(msg, sizeof(msg), "%s: %s", what, hipGetErrorString(e));
+    return fail(ctx, e == hipErrorOutOfMemory ? SX_ENOMEM : SX_EDEVICE, msg);
+}
+
+// What an entry point does, with host memory that runs out reported
+// (no C++ exception leaves the library).
+template <class F>
+int guarded(sx_ctx* ctx, F f) noexcept {
+    try {
+        return f();
+    } catch (const std::bad_alloc&) {
+        return fail(ctx, SX_ENOMEM, "host memory");
+    }
 }
 
 // The scene's large blocks go back to its context's pool: the device is idle
@@ -637,7 +655,10 @@ int sx_ctx_create(int device, const sx_config* cfg, sx_ctx** out) {
     if (!c) return SX_ENOMEM;
     c->device = device;
     c->cfg = conf;
-    c->pool = std::make_shared<DevPool>(device);
+    if (guarded(nullptr, [&] { return c->pool = std::make_shared<DevPool>(device), SX_OK; }) != SX_OK) {
+        delete c;
+        return SX_ENOMEM;
+    }
     if (hipSetDevice(device) != hipSuccess) { delete c; return SX_EDEVICE; }
     if (hipHostMalloc((void**)&c->pinned, sizeof(sx::WsCtl), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
@@ -741,6 +762,17 @@ static void soup_terms(const sx::HostEncoding& enc, const sx_style* styles, cons
     }
 }
 
+// A scene until it is handed out.
+struct SceneOwner {
+    sx_scene* s = nullptr;
+    ~SceneOwner() { free_scene(s); }
+    sx_scene* give() {
+        sx_scene* r = s;
+        s = nullptr;
+        return r;
+    }
+};
+
 static int encode_impl(sx_ctx* ctx, const sx_paths* paths, const sx_style* styles, uint32_t n_styles,
                        const sx_affine* xforms, uint32_t n_xforms, void* stream, sx_scene** out,
                        std::vector<uint32_t>* style_stream, bool streams_only = false) {
@@ -757,7 +789,7 @@ static int encode_impl(sx_ctx* ctx, const sx_paths* paths, const sx_style* style
     std::string err;
     for (bool done = false; !done;) {
         try {
-            if (!sx::encode_paths(*paths, styles, n_styles, n_xforms, *to, err)) return fail(ctx, SX_EINVAL, err);
+            if (!sx::encode_paths(*paths, styles, n_styles, n_xforms, *to, err)) return fail(ctx, SX_EINVAL, err.c_str());
             done = true;
         } catch (const std::bad_alloc&) {
             if (to == &own) return fail(ctx, SX_ENOMEM, "host encoding");
@@ -800,7 +832,8 @@ static int encode_impl(sx_ctx* ctx, const sx_paths* paths, const sx_style* style
         const float v[6] = {X.a, X.b, X.c, X.d, X.e, X.f};
         memcpy(&xd[6 * i], v, sizeof(v));
     }
-    sx_scene* s = new (std::nothrow) sx_scene();
+    SceneOwner own_s;
+    sx_scene* s = own_s.s = new (std::nothrow) sx_scene();
     if (!s) return fail(ctx, SX_ENOMEM, "scene alloc");
     s->ctx = ctx;
     s->pool = ctx->pool;
@@ -811,10 +844,7 @@ static int encode_impl(sx_ctx* ctx, const sx_paths* paths, const sx_style* style
     s->n_xforms = (uint32_t)enc.xform_stream.size();
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = reserve_scene(s, s->n_tags, s->n_pts, s->n_styles, s->n_xforms, s->n_paths, st, streams_only);
-    if (e != hipSuccess) {
-        free_scene(s);
-        return hip_fail(ctx, e, "scene allocation");
-    }
+    if (e != hipSuccess) return hip_fail(ctx, e, "scene allocation");
     auto A = [&](hipError_t r) {
         if (e == hipSuccess) e = r;
     };
@@ -828,25 +858,24 @@ static int encode_impl(sx_ctx* ctx, const sx_paths* paths, const sx_style* style
                          hipMemcpyHostToDevice, st));
     // host vectors die with this call: finish the uploads before returning
     A(hipStreamSynchronize(st));
-    if (e != hipSuccess) {
-        free_scene(s);
-        return hip_fail(ctx, e, "scene upload");
-    }
+    if (e != hipSuccess) return hip_fail(ctx, e, "scene upload");
     if (!streams_only) soup_terms(enc, styles, xforms, s->est);
     if (style_stream) *style_stream = enc.style_stream;
     s->last_stream = st;
-    *out = s;
+    *out = own_s.give();
     return SX_OK;
 }
 
 int sx_scene_encode(sx_ctx* ctx, const sx_paths* paths, const sx_style* styles, uint32_t n_styles,
                     const sx_affine* xforms, uint32_t n_xforms, void* stream, sx_scene** out) {
-    return encode_impl(ctx, paths, styles, n_styles, xforms, n_xforms, stream, out, nullptr);
+    return guarded(ctx, [&] {
+        return encode_impl(ctx, paths, styles, n_styles, xforms, n_xforms, stream, out, nullptr);
+    });
 }
 
-int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* styles, const sx_dash* dashes,
-                           uint32_t n_styles, const sx_affine* xforms, uint32_t n_xforms, void* stream,
-                           sx_scene** out) {
+static int encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* styles, const sx_dash* dashes,
+                         uint32_t n_styles, const sx_affine* xforms, uint32_t n_xforms, void* stream,
+                         sx_scene** out) {
     if (!ctx || !out) return SX_EINVAL;
     *out = nullptr;
     if (n_styles && !dashes) return fail(ctx, SX_EINVAL, "null dash table");
@@ -879,7 +908,9 @@ int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* s
     }
     hipStream_t st = (hipStream_t)stream;
     std::vector<uint32_t> sstream;
-    sx_scene* src = nullptr;
+    SceneOwner own_src, own_dst;
+    sx_scene*& src = own_src.s;
+    sx_scene*& dst = own_dst.s;
     int r = encode_impl(ctx, paths, styles, n_styles, xforms, n_xforms, stream, &src, &sstream, true);
     if (r != SX_OK) return r;
     const uint32_t n = src->n_tags;
@@ -896,10 +927,8 @@ int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* s
     {
         const uint32_t np = paths->n_paths ? paths->pt_off[paths->n_paths] : 0u;
         for (uint32_t j = 0; j < 2u * np; j++)
-            if (!(std::fabs(paths->pts[j]) <= 16777216.0f)) {
-                free_scene(src);
+            if (!(std::fabs(paths->pts[j]) <= 16777216.0f))
                 return fail(ctx, SX_EINVAL, "dashed paths need coordinates within 2^24 units");
-            }
     }
     hipError_t e = hipSuccess;
     auto A = [&](hipError_t x) {
@@ -912,7 +941,7 @@ int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* s
         ctx->pool->give((void*)p, idle);
         p = nullptr;
     };
-    sx_scene* dst = nullptr;
+    // (nothing throws from here on)
     // device time of the three dashing phases (the host reads the sizes and
     // allocates between them)
     hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -1033,14 +1062,18 @@ int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* s
     dfree(b.st2);
     for (auto& x : ev)
         if (x) (void)hipEventDestroy(x);
-    free_scene(src);
-    if (e != hipSuccess || r != SX_OK) {
-        free_scene(dst);
-        return r != SX_OK ? r : hip_fail(ctx, e, "dashed encoding");
-    }
+    if (e != hipSuccess || r != SX_OK) return r != SX_OK ? r : hip_fail(ctx, e, "dashed encoding");
     dst->last_stream = st;
-    *out = dst;
+    *out = own_dst.give();
     return SX_OK;
+}
+
+int sx_scene_encode_dashed(sx_ctx* ctx, const sx_paths* paths, const sx_style* styles, const sx_dash* dashes,
+                           uint32_t n_styles, const sx_affine* xforms, uint32_t n_xforms, void* stream,
+                           sx_scene** out) {
+    return guarded(ctx, [&] {
+        return encode_dashed(ctx, paths, styles, dashes, n_styles, xforms, n_xforms, stream, out);
+    });
 }
 
 int sx_scene_dash_ms(const sx_scene* s, float* ms) {

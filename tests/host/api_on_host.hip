@@ -24,6 +24,11 @@ hipError_t out(hipError_t e) {
     if (e != hipSuccess) g_last = e;
     return e;
 }
+struct Quiet {  // the stand-in's own C++ allocations do not fail
+    int k = g_new_fail;
+    Quiet() { g_new_fail = -1; }
+    ~Quiet() { g_new_fail = k; }
+};
 void need(std::initializer_list<const void*> ps) {
     for (const void* p : ps)
         if (!p) g_bad++;
@@ -46,6 +51,7 @@ void operator delete(void* p, size_t) noexcept { free(p); }
 
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
+    Quiet q;
     *p = nullptr;
     // (16 bytes: the pool's wait for the device, which no call depends on)
     if ((n > 16 && fails()) || g_dev_bytes + n > g_limit) return out(hipErrorOutOfMemory);
@@ -67,6 +73,7 @@ hipError_t hipFree(void* p) {
     return hipSuccess;
 }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+    Quiet q;
     *p = nullptr;
     if (n > g_pin_most) g_pin_most = n;
     if (fails() || g_fail == -2) return out(hipErrorOutOfMemory);

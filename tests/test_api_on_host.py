@@ -253,3 +253,22 @@ def test_kept_blocks_are_given_back_to_another_context(api):
     one.close()
     two.close()
     assert api.ah_live() == live
+
+
+@pytest.mark.parametrize("dashed", [False, True])
+def test_host_allocations_that_fail(api, dashed):
+    """No C++ exception leaves an entry point."""
+    live = api.ah_live()
+    call, undo = _fresh(api, S.scene_map(1, 400, 4), dashed)
+    for k in range(1000):
+        api.ah_new_fail(k)
+        rc, got = call()
+        left = api.ah_new_left()
+        api.ah_new_fail(-1)
+        assert rc in (0, ENOMEM) and api.ah_bad() == 0, k
+        if rc == 0:
+            undo(got)
+        if left >= 0:
+            break
+    assert left >= 0 and k > 10
+    assert api.ah_live() == live
