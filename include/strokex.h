@@ -374,10 +374,12 @@ int sx_batch_expand(sx_ctx *ctx, sx_batch *batch, float tolerance, int output_mo
  *   chunk_k       1..255: records per emission item chunk (work per thread
  *                 of the record kernel; scenes of few pieces take at most 4);
  *   bisect_range  tags per bisection wave, a multiple of 64 up to 1024
- *                 (0 = 256): longer ranges keep lanes refilled longer (small
- *                 scenes take shorter ones, one wave per SIMD slot);
+ *                 (scenes of fewer than 4,096 times as many tags take shorter
+ *                 ones, of 64 or more), or 0: by the scene's size (2,048
+ *                 waves, then 64 tags a wave, then 8,192 waves, then 256
+ *                 tags a wave);
  *   bisect_waves  2, 3 or 4 (0 = 2): waves per SIMD of the bisection kernels.
- * Defaults {2, 16, 256, 2}.  Errors: SX_EINVAL (out of range). */
+ * Defaults {2, 16, 0, 2}.  Errors: SX_EINVAL (out of range). */
 typedef struct {
     uint32_t piece_waves;
     uint32_t chunk_k;

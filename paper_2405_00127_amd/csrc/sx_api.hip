@@ -177,7 +177,7 @@ struct sx_ctx {
     int device = 0;
     sx_config cfg = {SX_FIT_OFFSET, SX_DENSITY_APPROX, SX_CONSTANTS_VERSION, 0u};
     std::string err;
-    sx_tuning tune = {2u, 16u, 256u, 2u};
+    sx_tuning tune = {2u, 16u, 0u, 2u};
     sx::WsCtl* pinned = nullptr;       // host-pinned counters of the last synchronous expansion
     std::shared_ptr<DevPool> pool;
     sx::HostEncoding enc{{pinned_get, pinned_put}};  // a scene's host streams while it is encoded (memory reused)
@@ -556,7 +556,7 @@ hipError_t run_one(const sx_ctx* ctx, const sx_scene* s, const sx::Cfg& conf, in
             return sx::launch_scan_tags(s->d_tags, s->n_tags, s->d_mon, ctl_block(s, 0), s->d_status_tags, s->d_ws_ctl,
                                         st);
         case kPhBisectCount:
-            return sx::launch_bisect(view(s), cfg, t.bisect_range, sx::keep_codes_of(s->n_tags), (int)t.bisect_waves,
+            return sx::launch_bisect(view(s), cfg, sx::bisect_range_of(s->n_tags, t.bisect_range), sx::keep_codes_of(s->n_tags), (int)t.bisect_waves,
                                      s->d_nslots, s->d_codes, s->d_ordered, s->slot_cap, s->d_ws_ctl, stats, st);
         case kPhScanSlots:
             // (a small scene's bases are part of the next phase)
@@ -684,11 +684,10 @@ int sx_set_tuning(sx_ctx* ctx, const sx_tuning* t) {
     if (t->piece_waves < 1 || t->piece_waves > 3) return fail(ctx, SX_EINVAL, "piece_waves must be 1, 2 or 3");
     if (t->chunk_k < 1 || t->chunk_k > 255) return fail(ctx, SX_EINVAL, "chunk_k must be in [1, 255]");
     if (t->bisect_range != 0 && (t->bisect_range % 64 || t->bisect_range > 1024))
-        return fail(ctx, SX_EINVAL, "bisect_range must be a multiple of 64 up to 1024 (0: 256)");
+        return fail(ctx, SX_EINVAL, "bisect_range must be a multiple of 64 up to 1024 (0: by size)");
     if (t->bisect_waves != 0 && (t->bisect_waves < 2 || t->bisect_waves > 4))
         return fail(ctx, SX_EINVAL, "bisect_waves must be 2, 3 or 4 (0: 2)");
     ctx->tune = *t;
-    if (ctx->tune.bisect_range == 0) ctx->tune.bisect_range = 256;
     if (ctx->tune.bisect_waves == 0) ctx->tune.bisect_waves = 2;
     return SX_OK;
 }

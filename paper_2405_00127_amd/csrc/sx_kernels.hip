@@ -421,7 +421,6 @@ __device__ __forceinline__ void scan_u32_body(const uint32_t* __restrict__ in, u
 // kept at codes[i * keep + q] (the first `keep` of each tag), and the write
 // pass orders them by their start.
 constexpr int kBisectBlock = 64;
-constexpr uint32_t kBisectMaxRange = 1024;  // tags per wave (the autotuner's largest range)
 constexpr uint32_t kRefillLanes = 16;       // idle lanes that trigger a refill
 constexpr uint32_t kNodeSegs = 64;          // curves with open nodes (a refilling wave holds fewer than 64 nodes)
 // Open nodes of a wave.  The stack is ordered by depth (deepest on top) and a
@@ -1587,14 +1586,6 @@ hipError_t launch_scan_counts_dev(const uint32_t* in, const uint64_t* n_dev, uin
     return hipGetLastError();
 }
 
-// Longest range of a scene of n tags: a small one is spread over kFillWaves
-// waves (more of them cost their dispatch, about 4 ns each: 20,011 segments
-// 25 us on 4,096 waves, 17 us on 2,048) until a wave has kFillRange tags,
-// a large one over 8,192 (1M segments: 119 us on 4,096 waves, 97 us on 8,192).
-constexpr uint32_t kFillWaves = 2048, kFillRange = 64;
-static uint32_t bisect_fill(uint32_t n) {
-    return std::max((n + 8191u) / 8192u, std::min((n + kFillWaves - 1u) / kFillWaves, kFillRange));
-}
 template <bool Stats>
 static void bisect_launch(uint32_t g, hipStream_t s, int waves, const SceneView& sv, const Cfg& cfg, uint32_t range,
                           uint32_t keep, uint32_t* nslots, uint32_t* codes, uint32_t* ordered, uint64_t ordered_cap,
@@ -1606,10 +1597,8 @@ hipError_t launch_bisect(const SceneView& sv, const Cfg& cfg, uint32_t range, ui
                          uint32_t* nslots, uint32_t* codes, uint32_t* ordered, uint64_t ordered_cap, WsCtl* ctl,
                          unsigned long long* stats, hipStream_t s) {
     if (sv.n_tags == 0) return hipSuccess;
-    if (range == 0 || range % 64u || range > kBisectMaxRange || keep < (uint32_t)kKeepCodes || keep % 16u)
+    if (range == 0 || range > kBisectMaxRange || keep < (uint32_t)kKeepCodes || keep % 16u)
         return hipErrorInvalidValue;
-    const uint32_t fill = bisect_fill(sv.n_tags);
-    if (fill < range) range = fill;
     const uint32_t g = (sv.n_tags + range - 1) / range;
     if (stats)
         bisect_launch<true>(g, s, waves, sv, cfg, range, keep, nslots, codes, ordered, ordered_cap, ctl, stats);

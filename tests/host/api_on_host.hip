@@ -202,6 +202,7 @@ hipError_t launch_dash(const SceneView& sv, const DashBufs& b, int phase, uint8_
 
 extern "C" {
 int ah_zero_ok(void* a, size_t na, void* b, size_t nb) { return sx::ZeroList{{a, na}, {b, nb}}.ok(); }
+uint32_t ah_range(uint32_t n, uint32_t asked) { return sx::bisect_range_of(n, asked); }
 void ah_fail(long k) { g_calls = 0, g_fail = k; }
 long ah_calls() { return g_calls; }
 void ah_limit(size_t n) { g_limit = n; }

@@ -272,3 +272,20 @@ def test_host_allocations_that_fail(api, dashed):
             break
     assert left >= 0 and k > 10
     assert api.ah_live() == live
+
+
+def test_a_bisection_range_that_is_set_acts(api):
+    """The ranges that the tuner times on the 1M-segment map scene are different
+    launches, up to the 256 tags that 4,096 waves have; larger scenes take all
+    of them.  0 goes by the size."""
+    ask = lambda n, r: api.ah_range(C.c_uint32(n), C.c_uint32(r))  # noqa: E731
+    assert [ask(1_012_923, r) for r in (64, 128, 192, 256, 512)] == [64, 128, 192, 256, 256]
+    assert [ask(4_300_000, r) for r in (64, 256, 384, 1024)] == [64, 256, 384, 1024]
+    assert [ask(n, 192) for n in (1, 20_011, 262_144, 600_000)] == [64, 64, 64, 192]
+    assert [ask(n, 0) for n in (1, 20_011, 110_000, 131_072, 1_012_923, 2**32 - 1)] == [1, 10, 54, 64, 124, 256]
+    ctx, t = Ctx(api), B._Tuning()
+    assert api.sx_get_tuning(ctx.h, C.byref(t)) == 0 and t.bisect_range == 0
+    t.bisect_range = 192
+    assert api.sx_set_tuning(ctx.h, C.byref(t)) == 0
+    assert api.sx_get_tuning(ctx.h, C.byref(t)) == 0 and t.bisect_range == 192
+    ctx.close()

@@ -75,6 +75,28 @@ def test_every_tuning_gives_identical_records(ctx, name):
         ctx.set_tuning(*GRID[0])
 
 
+def test_bisection_ranges_give_identical_records(ctx):
+    """Ranges of 64 to 1,024 tags and the one by size on 4.3M tags, where each
+    of them is launched as it is (a wave refills over up to 16 windows of 64
+    tags), curves of many pieces among them."""
+    import torch
+
+    sc = S.scene_map(7, 4_240_000, 34_000)
+    assert sc.n_segments() + sc.n_paths > 4096 * 1000
+    scene = ctx.encode(sc)
+    assert scene.n_tags > 4096 * 960
+    ref = None
+    try:
+        for r in (0, 64, 256, 384, 1024):
+            n, buf = _run(ctx, scene, sc.tolerance, sc.output_mode, (2, 16, r, 2))
+            _say("  range", r, "records", n)
+            got = buf[: n * 20]
+            assert ref is None or torch.equal(got, ref), r
+            ref = got.clone() if ref is None else ref
+    finally:
+        ctx.set_tuning(*GRID[0])
+
+
 @pytest.mark.parametrize("mode", [S.OUT_LINES, S.OUT_ARCS])
 def test_c1_parity_at_every_tuning(ctx, mode):
     from paper_2405_00127_amd import binding as B
