@@ -215,7 +215,7 @@ struct sx_scene {
     void* d_status_nslots = nullptr;
     void* d_status_rc = nullptr;
     // item workspace of the slot / record kernels
-    sx::Unit* d_items = nullptr;
+    uint4* d_items = nullptr;  // (four to a unit)
     uint4* d_es = nullptr;  // per-slot spiral records (their two halves, an array each)
     uint32_t* d_tile_n = nullptr;
     sx::WsCtl* d_ws_ctl = nullptr;
@@ -389,7 +389,7 @@ uint64_t overflow_units(const sx_scene* s) {
 
 sx::ItemWs workspace(const sx_scene* s) {
     sx::ItemWs w;
-    w.units = reinterpret_cast<uint4*>(s->d_items);
+    w.units = s->d_items;
     w.es_lo = s->d_es;
     w.es_hi = s->d_es + s->slot_cap;
     w.tile_n = s->d_tile_n;
@@ -444,7 +444,7 @@ hipError_t size_slots(sx_scene* s, uint64_t slot_cap, uint32_t region_per_piece,
     dfree(s->d_items);
     s->region_per_piece = region_per_piece;
     s->ovf_cap = ovf;
-    return dalloc(&s->d_items, (region_units(s) + overflow_units(s)) * sizeof(sx::Unit));
+    return dalloc(&s->d_items, (region_units(s) + overflow_units(s)) * sx::kUnitWords * sizeof(uint32_t));
 }
 
 // Grow the scene's device buffers to hold at least the given sizes (the

@@ -668,13 +668,10 @@ enum { kInNone = 0, kInPivot = 1, kInSmooth = 2 };
 // Items live in 64-byte units.  Offset items take one unit; evolute, join
 // and cap items two (their payload keeps word 16 at zero, so a scan over
 // units reads the second unit as an empty slot), or one when they are a
-// single chunk (short_unit, in the workspace of the launches).  The Euler
+// single chunk (short_unit).  The Euler
 // spiral of a piece is stored once per slot (the slot's ES record), not per
 // item.
 constexpr uint32_t kUnitWords = 16;
-struct __align__(16) Unit {
-    uint32_t w[kUnitWords];
-};
 struct ItemHdr {
     uint32_t hdr;    // kind | flags | outer kind << 16 | inner kind << 20 | records in this chunk << 24
     uint32_t path;   // output path id of the records
@@ -742,35 +739,17 @@ struct Cfg {
     double xinc[5];                         // F increments between the branch breaks
 };
 
-// Item sink: writes a tag's items into slots handed out by the allocator and
-// counts the tag's records.  Alloc::alloc(nc) returns the first of nc
-// consecutive slots owned by the caller, or ~0 when the workspace is full
-// (the items are then dropped; the caller sees the overflow count).
-// With Stats, the sink also counts the work done (fit trials, accepted
-// pieces, items by kind) for the algorithmic-work figures of the roofline.
+// What an item sink with kStats counts (fit trials, accepted pieces, items by
+// kind), for the algorithmic-work figures of the roofline.
 enum { kStTrials = 0, kStPieces = 1, kStRanges = 2, kStEvolutes = 3, kStJoins = 4, kStLines = 5, kStN = 6 };
 
-// An item of nrec records as chunks of at most K records, each chunk a copy
-// of the header (with its own count and position) and the payload, at unit
-// `base` of the workspace; n0 = the item's first record within its slot.
-template <class P>
-SX_HD void write_item(Unit* units, uint64_t base, uint32_t hdr, uint32_t path, uint32_t slot, uint32_t n0,
-                      uint32_t nrec, uint32_t K, const P& p) {
-    constexpr uint32_t U = Units<P>::n;
-    const uint32_t nc = chunks(nrec, K);
-    for (uint32_t c = 0; c < nc; c++) {
-        uint32_t* dst = units[base + (uint64_t)c * U].w;
-        const uint32_t nchunk = (c + 1 < nc) ? K : nrec - c * K;
-        *reinterpret_cast<uint4*>(dst) = make_uint4(hdr | (nchunk << 24), path, slot, n0 + c * K);
-        *reinterpret_cast<uint2*>(dst + 4) = make_uint2(c * K, nrec);
-        *reinterpret_cast<P*>(dst + kHdrWords) = p;
-    }
-}
-
-// The same into units laid out by their 16-byte quarters: quarter v of unit u
-// of a region of `stride` units at p[v * stride + u], so that neighbouring
-// lanes, which hold neighbouring units, read and write consecutive addresses
-// (64-byte units one after another took a cache line per lane and quarter).
+// An item of nrec records as chunks of at most K records, each chunk a copy of
+// the header (with its own count and position) and the payload; n0 = the
+// item's first record within its slot.  Units are laid out by their 16-byte
+// quarters: quarter v of unit u of a region of `stride` units at p[v * stride
+// + u], so that neighbouring lanes, which hold neighbouring units, read and
+// write consecutive addresses (64-byte units one after another took a cache
+// line per lane and quarter).
 // Quarters past the payload are left as they are.  An item of one chunk takes
 // one unit whatever its kind: evolutes and joins leave out the words that say
 // which chunk they are and those that their kind does not use.  The record
@@ -882,26 +861,44 @@ SX_FN void write_item_q(const UnitAt& at, uint32_t hdr, uint32_t path, uint32_t 
     }
 }
 
-template <class Alloc, bool Stats = false>
-struct ItemSink {
-    Unit* units;
-    float* es_tab;  // 8 floats per slot
-    Alloc al;
-    uint32_t path, slot;  // output path id, slot index
-    uint32_t n;           // records of the slot so far
-    uint32_t st[Stats ? kStN : 1];
-    static constexpr bool kStats = Stats;
-    template <class P>
-    SX_HD void put(uint32_t hdr, uint32_t nrec, uint32_t K, const P& p) {
-        if constexpr (Stats) {
-            const uint32_t kind = hdr & 15u;
-            st[kind == kItemOffset ? kStRanges : (kind == kItemEvolute ? kStEvolutes : kStJoins)]++;
-        }
-        const uint64_t base = al.alloc(chunks(nrec, K) * Units<P>::n);
-        if (base != ~0ull) write_item(units, base, hdr, path, slot, n, nrec, K, p);
-        n += nrec;
+// Reads the item chunk that starts at a unit into the 28 words of its two-unit
+// form (w: 32 words, zero, 16-byte aligned); quarter(v, j): quarter v of the j-th unit from
+// there.  False: no chunk starts there.  Only the quarters that write_item_q
+// fills are read, in the record kernel beside the slot's record offset and
+// spiral (all four at once, in small scenes: 1 us slower).
+template <class Load>
+SX_FN bool read_item(const Load& quarter, uint32_t* w) {
+    uint4* const wq = reinterpret_cast<uint4*>(w);
+    wq[0] = quarter(0u, 0u);
+    wq[2] = quarter(2u, 0u);
+    const uint32_t kind = w[0] & 15u;
+    if (kind == 0u) return false;
+    const bool off = kind == kItemOffset, brief = (w[0] & kIfShort) != 0u;
+    const bool single = off && brief && item_n(w[0]) == 1u;
+    if (!off || !brief) wq[1] = quarter(1u, 0u);
+    if (!single) wq[3] = quarter(3u, 0u);
+    w[5] = off && brief ? item_n(w[0]) : w[5];
+    w[7] = off && brief ? f_bits(1.0f) : w[7];
+    if (!off && brief) {
+        uint32_t s[kUnitWords];
+#pragma unroll
+        for (uint32_t q = 0; q < kUnitWords; q++) s[q] = w[q];
+        long_item(s, w);
     }
-};
+    if (!off && !brief) {
+#pragma unroll
+        for (uint32_t q = 0; q < 3u; q++) wq[4 + q] = quarter(q, 1u);
+    }
+    return true;
+}
+// Whether an item's records need the slot's spiral (a single line's do not).
+SX_FN bool needs_spiral(uint32_t hdr, bool arcs) {
+    const uint32_t kind = hdr & 15u;
+    return kind == kItemEvolute ||
+           (kind == kItemOffset && (arcs || (hdr & kIfShort) == 0u || item_n(hdr) != 1u));
+}
+static_assert(kHdrWords + sizeof(JoinP) / 4 <= kUnitWords + 12 && kHdrWords + sizeof(EvoluteP) / 4 <= kUnitWords + 12,
+              "read_item reads three quarters of a second unit");
 
 // ----------------------------------------------- one range of one side
 // Section 4 (lines), Section 5 (arcs) and Section 6 (evolute for rho < 0).
@@ -1385,11 +1382,11 @@ SX_HD inline void emit_item(const uint32_t* it, const float* es_rec, const XIncF
     const bool arcs = (hdr & kIfArcs) != 0;
     if (kind == kItemOffset) {
         const OffsetP p = *reinterpret_cast<const OffsetP*>(pw);
+        const uint32_t n = h.ntot;
         const ES es = es_from_f(es_rec, (hdr & kIfPivot) != 0);
         Place pl;
         PlaceN pn;
         const bool newton = Newton && (hdr & kIfNewton) != 0;
-        const uint32_t n = h.ntot;
         if (newton) place_newton_init(pn, p);
         else place_init(pl, es, p, hdr, xi);
         pl.inv_n = 1.0f / (float)n;

@@ -1289,50 +1289,29 @@ __device__ __forceinline__ uint4 load_quarter(const uint4* p) {
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// One item chunk starting at a unit: loads its one or two units (the quarters
-// its kind fills) and writes its records.
+// One item chunk starting at a unit: reads it and writes its records.
 template <bool Newton, bool Stream>
 __device__ __forceinline__ void record_item(const SceneView& sv, const ItemWs& ws, const UnitAt& u,
                                             const uint64_t* roff, uint64_t n_slots, float* out, uint64_t cap,
                                             int arcs, const XIncF& xi, float* stage = nullptr, uint64_t lo = 0,
                                             uint64_t hi = 0) {
     uint32_t w[2 * kUnitWords] = {};
-    *reinterpret_cast<uint4*>(w) = load_quarter<Stream>(u.p);
-    *reinterpret_cast<uint4*>(w + 8) = load_quarter<Stream>(u.p + 2u * u.stride);
-    const uint32_t kind = w[0] & 15u;
-    if (kind == 0u) return;
-    // the quarters that the item has (write_item_q), beside the slot's record
-    // offset and spiral (all four at once, in small scenes: 1 us slower)
-    const bool off = kind == kItemOffset, brief = (w[0] & kIfShort) != 0u;
-    const bool single = off && brief && item_n(w[0]) == 1u;
-    if (!off || !brief) *reinterpret_cast<uint4*>(w + 4) = load_quarter<Stream>(u.p + u.stride);
-    if (!single) *reinterpret_cast<uint4*>(w + 12) = load_quarter<Stream>(u.p + 3u * u.stride);
-    if (off) {
-        w[5] = brief ? item_n(w[0]) : w[5];
-        w[7] = brief ? f_bits(1.0f) : w[7];
-    } else if (brief) {
-        uint32_t s[kUnitWords];
-#pragma unroll
-        for (uint32_t q = 0; q < kUnitWords; q++) s[q] = w[q];
-        long_item(s, w);
-    } else {
-#pragma unroll
-        for (int q = 0; q < 3; q++) reinterpret_cast<uint4*>(w)[4 + q] = u.p[q * u.stride + 1u];
-    }
+    auto quarter = [p0 = u.p, stride = u.stride](uint32_t v, uint32_t j) {
+        const uint4* p = p0 + v * stride + j;
+        return j ? *p : load_quarter<Stream>(p);
+    };
+    if (!read_item(quarter, w)) return;
     const uint32_t path = w[1], slot = w[2];
     if (slot >= n_slots) return;
     const uint64_t end = roff[slot + 1] < cap ? roff[slot + 1] : cap;
     RecOut o{out, roff[slot] + w[3], end, path, arcs, stage, lo, hi};
     __align__(16) float es[8];
-    if (kind == kItemEvolute || (off && (arcs || !single))) {  // (a single line needs no spiral)
+    if (needs_spiral(w[0], arcs != 0)) {
         *reinterpret_cast<uint4*>(es) = ws.es_lo[slot];
         *reinterpret_cast<uint4*>(es + 4) = ws.es_hi[slot];
     }
     emit_item<Newton>(w, es, xi, o);
 }
-static_assert(kHdrWords + sizeof(JoinP) / 4 <= kUnitWords + 12 && kHdrWords + sizeof(EvoluteP) / 4 <= kUnitWords + 12,
-              "record_item loads three quarters of a second unit");
-
 // Per item chunk, the FP32 per-point work: records at
 // roff[slot] + the chunk's position within its slot.  A tile is one block's
 // turn; a scene of few tiles gives each to several blocks (every split-th

@@ -4,11 +4,28 @@
 // the slots' record counts, each item's records -- so the CPU suite can check
 // the kernels' arithmetic against the oracle without a GPU.  Serial, test
 // infrastructure only.
-#include <vector>
+#include <cmath>
 #include <cstring>
+#include <vector>
 #include "sx_device.h"
 #include "sx_encode.h"
 using namespace sx;
+// Items as the launches write and read them, in a region of all units.
+struct Sink {
+    static constexpr bool kStats = false;
+    UnitAt at;  // null: only count the units
+    float* es_tab;
+    uint32_t path, slot, n, units;
+    template <class P>
+    SX_HD void put(uint32_t hdr, uint32_t nrec, uint32_t K, const P& p) {
+        if (at.p) {
+            write_item_q(at, hdr, path, slot, n, nrec, K, p);
+            at.p += item_units<P>(nrec, K);
+        }
+        units += item_units<P>(nrec, K);
+        n += nrec;
+    }
+};
 static uint32_t g_K = 16;
 extern "C" void dh_set_k(uint32_t k) { g_K = k; }
 // counts: per-tag record counts (cap_tags entries); recs: records (cap_recs,
@@ -45,10 +62,6 @@ extern "C" int dh_expand(const sx_paths* paths, const sx_style* styles, uint32_t
     cfg.K = g_K;
     set_break_increments(cfg.xinc);
     // slot pipeline on the host: bisection -> slots, slots -> items, scan, records
-    struct Fix {
-        uint64_t next, cap;
-        SX_HD uint64_t alloc(uint32_t nc) { if (next + nc > cap) { next += nc; return ~0ull; } uint64_t b = next; next += nc; return b; }
-    };
     std::vector<Slot> slots;
     std::vector<uint64_t> tag_first(n + 1);
     for (uint32_t i = 0; i < n; i++) {
@@ -68,22 +81,26 @@ extern "C" int dh_expand(const sx_paths* paths, const sx_style* styles, uint32_t
         slots.push_back(Slot{i, kSlotTail});
     }
     tag_first[n] = slots.size();
-    std::vector<Unit> items, st(1024);
+    std::vector<uint4> region;
+    uint64_t stride = 0;
     std::vector<float> es_tab(8 * slots.size() + 8);
     std::vector<uint32_t> rc(slots.size());
-    for (size_t j = 0; j < slots.size(); j++) {
-        const Slot sl = slots[j];
-        for (;;) {
-            ItemSink<Fix> kw{st.data(), es_tab.data(), Fix{0, st.size()}, enc.path_map[mon[ms + sl.tag]], (uint32_t)j, 0};
+    for (int write = 0; write < 2; write++) {
+        uint64_t at = 0;
+        for (size_t j = 0; j < slots.size(); j++) {
+            const Slot sl = slots[j];
+            Sink k{{write ? region.data() + at : nullptr, stride}, es_tab.data(), enc.path_map[mon[ms + sl.tag]],
+                   (uint32_t)j, 0u, 0u};
             TagInfo ti; Seg sg;
             fetch_tag(sv, sl.tag, ti, sg);
-            if (sl.code == kSlotTail) emit_tail(kw, cfg, sv, sl.tag, ti, sg);
-            else emit_piece(kw, cfg, sg, ti.line, code_t0u(sl.code), code_depth(sl.code), code_pivot(sl.code));
-            if (kw.al.next > st.size()) { st.resize(kw.al.next); continue; }
-            items.insert(items.end(), st.begin(), st.begin() + kw.al.next);
-            rc[j] = kw.n;
-            break;
+            if (sl.code == kSlotTail) emit_tail(k, cfg, sv, sl.tag, ti, sg);
+            else emit_piece(k, cfg, sg, ti.line, code_t0u(sl.code), code_depth(sl.code), code_pivot(sl.code));
+            at += k.units;
+            rc[j] = k.n;
         }
+        stride = at;
+        // (what is not written reads as a bad item, path and slot)
+        if (!write) region.assign(4 * stride, make_uint4(0xfffffff5u, ~0u, ~0u, ~0u));
     }
     std::vector<uint64_t> roff(slots.size() + 1);
     uint64_t acc = 0;
@@ -95,19 +112,18 @@ extern "C" int dh_expand(const sx_paths* paths, const sx_style* styles, uint32_t
     for (uint32_t i = 0; i < n; i++) counts[i] = (uint32_t)(offs[i + 1] - offs[i]);
     *n_recs_out = total;
     if (!recs || total > cap_recs) return 0;
-    for (size_t u = 0; u < items.size(); u++) {
-        const uint32_t* w = items[u].w;
-        const uint32_t kind = w[0] & 15u;
-        if (kind == 0) continue;
-        uint32_t buf[32];
-        memcpy(buf, w, 64);
-        if (kind != kItemOffset) memcpy(buf + 16, items[u + 1].w, 64);
+    for (uint64_t u = 0; u < stride; u++) {
+        alignas(16) uint32_t w[2 * kUnitWords] = {};
+        if (!read_item([&](uint32_t v, uint32_t j) { return region[v * stride + u + j]; }, w)) continue;
         const uint32_t path = w[1], slot = w[2];
+        if (slot >= slots.size()) return -11;
         RecOut o{recs, roff[slot] + w[3], roff[slot + 1], path, cfg.arcs};
         XIncF xi;
         for (int q = 0; q < 5; q++) xi.v[q] = (float)cfg.xinc[q];
-        if (cfg.newton) emit_item<true>(buf, es_tab.data() + 8 * (size_t)slot, xi, o);
-        else emit_item<false>(buf, es_tab.data() + 8 * (size_t)slot, xi, o);
+        const float none[8] = {NAN, NAN, NAN, NAN, NAN, NAN, NAN, NAN};
+        const float* es = needs_spiral(w[0], cfg.arcs != 0) ? es_tab.data() + 8 * (size_t)slot : none;
+        if (cfg.newton) emit_item<true>(w, es, xi, o);
+        else emit_item<false>(w, es, xi, o);
         if (o.idx != roff[slot] + w[3] + item_n(w[0])) return -10;
     }
     return 0;

@@ -107,3 +107,26 @@ def test_exact_density_mode_on_host_matches_the_oracle(dev, name):
     assert rep.bad_path_ids == 0
     assert P.closed_per_path(recs) == 0
     assert counts.sum() != O.expand(sc, emit=False).counts.sum()  # the mode changes the counts
+
+
+@pytest.mark.parametrize("mode,flags", [(S.OUT_LINES, 0), (S.OUT_ARCS, 0), (S.OUT_LINES, 2)])
+def test_item_forms_give_the_same_records(dev, mode, flags):
+    """Items as the launches lay them out: in one unit or two, with and without
+    their quarters.  Chunks of 1 to 255 records, so that every kind of item
+    comes in each of its forms, give the same bytes."""
+    from test_gpu_items import _scene
+
+    sc = _scene(1)
+    sc.output_mode = mode
+    try:
+        got = []
+        for k in (16, 1, 2, 3, 4, 7, 255):
+            dev.dh_set_k(C.c_uint32(k))
+            got.append(_run(dev, sc, flags))
+    finally:
+        dev.dh_set_k(C.c_uint32(16))
+    for counts, recs in got[1:]:
+        assert np.array_equal(counts, got[0][0])
+        assert np.array_equal(recs, got[0][1])
+    rep = P.compare(*got[0], O.expand(sc, fit_mode=O.DENSITY_NEWTON) if flags else O.expand(sc), mode)
+    assert rep.ok(), rep
