@@ -1383,6 +1383,11 @@ SX_HD inline void emit_item(const uint32_t* it, const float* es_rec, const XIncF
     if (kind == kItemOffset) {
         const OffsetP p = *reinterpret_cast<const OffsetP*>(pw);
         const uint32_t n = h.ntot;
+        if (n == 1u && !arcs) {  // (read_item: neither a spiral nor a placement)
+            const V2 Pa = v2(p.Pax, p.Pay), Pb = v2(p.Pbx, p.Pby);
+            if (!(hdr & kIfDirNeg)) o.line(Pa, Pb); else o.line(Pb, Pa);
+            return;
+        }
         const ES es = es_from_f(es_rec, (hdr & kIfPivot) != 0);
         Place pl;
         PlaceN pn;

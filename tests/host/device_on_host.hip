@@ -120,8 +120,7 @@ extern "C" int dh_expand(const sx_paths* paths, const sx_style* styles, uint32_t
         RecOut o{recs, roff[slot] + w[3], roff[slot + 1], path, cfg.arcs};
         XIncF xi;
         for (int q = 0; q < 5; q++) xi.v[q] = (float)cfg.xinc[q];
-        const float none[8] = {NAN, NAN, NAN, NAN, NAN, NAN, NAN, NAN};
-        const float* es = needs_spiral(w[0], cfg.arcs != 0) ? es_tab.data() + 8 * (size_t)slot : none;
+        const float* es = needs_spiral(w[0], cfg.arcs != 0) ? es_tab.data() + 8 * (size_t)slot : nullptr;
         if (cfg.newton) emit_item<true>(w, es, xi, o);
         else emit_item<false>(w, es, xi, o);
         if (o.idx != roff[slot] + w[3] + item_n(w[0])) return -10;
