@@ -958,7 +958,10 @@ SX_FN RangeRes range_count(const Cfg& cfg, const XTab& T, const PieceK& p, int s
                 // the exact integral (counts) and the range's x in FP64 (placement)
                 r.place = kIfNewton;
                 const double xa = -1.0 - 2.0 * (hL * kna), xb = -1.0 - 2.0 * (hL * knb);
-                const double D = dens_int_d(xa, xb);
+                // (xb - xa is rounding alone where the curvature is nearly
+                // constant: the density is then too)
+                const double xm = 0.5 * (xa + xb);
+                const double D = fabs(dx) < 1e-9 ? sqrt_d(fabs(xm * xm - 1.0)) * dx : dens_int_d(xa, xb);
                 uint64_t xw;
                 memcpy(&xw, &xa, 8);
                 r.len0 = bits_f((uint32_t)xw);

@@ -13,6 +13,11 @@ def scale(s):
     return np.array([[s, 0, 0, s, 0, 0]], np.float32)
 
 
+def rotation(degrees):
+    c, s = np.cos(np.radians(degrees)), np.sin(np.radians(degrees))
+    return np.array([[c, s, -s, c, 0, 0]], np.float32)
+
+
 def polygons(join, turn=90, closed=False, xform=None):
     """Polylines of equal sides that turn by the same angle, to and fro (or
     round and round when closed)."""

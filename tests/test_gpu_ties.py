@@ -50,3 +50,27 @@ def test_perpendicular_hodographs_have_the_oracles_counts(size, w, mode):
         sc.tolerance, sc.output_mode = 1.0, mode
         print("hodographs", size, w, mode, s, flush=True)
         _same_as_the_oracle(sc)
+
+
+@pytest.mark.parametrize("degrees", [10, 30, 77])
+def test_nearly_constant_curvature_in_exact_density(degrees):
+    """Turned circles: their curvature changes by rounding alone along a piece,
+    and the exact integral over it is that of a constant density (the GPU's
+    rounding is its own: at the parity bars)."""
+    import torch
+
+    from paper_2405_00127_amd import binding as B
+
+    torch.cuda.set_device(0)
+    ctx = B.Context(0, density=B.DENSITY_NEWTON)
+    for radius, w, tol in ((1.0, 2.46, 0.0198), (3.0, 1.0, 0.25), (3.0, 2.46, 0.0198), (10.0, 4.0, 0.25)):
+        sc = shapes.circles(radius, w, xform=shapes.rotation(degrees))
+        sc.tolerance = tol
+        scene = ctx.encode(sc)
+        recs, _, _ = ctx.expand(scene, tol, 0)
+        counts = ctx.counts(scene, tol, 0).cpu().numpy().astype(np.uint32)
+        ref = O.expand(sc, fit_mode=O.DENSITY_NEWTON)
+        assert np.abs(counts.astype(int) - ref.counts.astype(int)).max() <= 2  # (one a side)
+        rep = P.compare(counts, B.records_to_numpy(recs, 0), ref, 0)
+        assert rep.ok(), rep
+    ctx.close()

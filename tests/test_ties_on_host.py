@@ -31,3 +31,15 @@ def test_perpendicular_hodographs_have_the_oracles_counts(dev, size, w, mode):  
         counts, _ = _run(dev, sc)
         ref = O.expand(sc)
         assert np.array_equal(counts, ref.counts), (s, int((counts != ref.counts).sum()))
+
+
+@pytest.mark.parametrize("degrees", [10, 30, 77])
+def test_nearly_constant_curvature_in_exact_density(dev, degrees):  # noqa: F811
+    """Turned circles: their curvature changes by rounding alone along a piece,
+    and the exact integral over it is that of a constant density."""
+    for radius, w, tol in ((1.0, 2.46, 0.0198), (3.0, 1.0, 0.25), (3.0, 2.46, 0.0198), (10.0, 4.0, 0.25)):
+        sc = shapes.circles(radius, w, xform=shapes.rotation(degrees))
+        sc.tolerance = tol
+        counts, _ = _run(dev, sc, 2)
+        ref = O.expand(sc, fit_mode=O.DENSITY_NEWTON)
+        assert np.array_equal(counts, ref.counts), (radius, w, int((counts != ref.counts).sum()))
