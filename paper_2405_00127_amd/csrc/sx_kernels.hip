@@ -409,14 +409,14 @@ __device__ __forceinline__ void scan_u32_body(const uint32_t* __restrict__ in, u
 // try the 64 deepest open nodes, and idle lanes take the range's next curves
 // once there are kRefillLanes of them.  A curve's trials run side by side, so
 // the wave's time follows its number of trials and the depth of its trees,
-// not its longest curve's trials in sequence: with one curve per lane and its
-// trials in order, 24 random cubics took 293 us (one lane's 180 trials), now
-// 28 us; 1,000 of them 371 -> 41 us; 20,000 stress cubics 1,154 us, 10,007 of
-// them now 129 us; the map scene of 1M segments 277 -> 178 us (23 of 64 lanes
-// were active).  A trial on unit vectors with its own reciprocals, square
-// roots and arctangents (node_accepted), instead of the library's: 28 -> 20.5
-// us, 41 -> 28 us, 129 -> 78 us, 178 -> 123 us.  Bound by the FP64 latency of
-// a trial on small scenes and by FP64 issue on large ones.
+// not its longest curve's trials in sequence.  With one curve per lane and its
+// trials in order (and the library's divisions, square roots and arctangents
+// in the trial): 24 random cubics 293 us (one lane's 180 trials), 1,000 of them
+// 371 us, 10,007 stress cubics 680 us, 1M map segments 257 us (23 of 64 lanes
+// active).  Side by side: 28, 41, 129 and 178 us; with a trial on unit vectors
+// and reciprocals, roots and arctangents of its own (node_accepted) 20.5, 28, 68
+// and 92 us (with shorter ranges too).  Bound by the FP64 latency of a trial on
+// small scenes and by FP64 issue on large ones.
 // Pieces are found in no particular order: the q-th one found of tag i is
 // kept at codes[i * keep + q] (the first `keep` of each tag), and the write
 // pass orders them by their start.
@@ -732,9 +732,9 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
 // them in order elsewhere.
 constexpr int kListBlock = 256;
 // pieces of a block's turn (list_kernel), by the slots it is launched for: a
-// thread's pieces follow one another (20,011 segments: 256 a turn 5.8 us, 512
-// 7.8, 1,024 13), a large scene's turns share their searches (1M segments:
-// 48, 42 and 44 us)
+// thread's pieces follow one another (20,011 segments: 256 a turn 7.7 us, 512
+// 9.4, 1,024 13), a large scene's turns share their searches (1M segments:
+// 38, 36 and 39 us)
 constexpr uint32_t kListPieces = 512, kListPiecesSmall = 256;
 constexpr uint32_t kListSmallSlots = 1u << 20;
 constexpr uint32_t kListSpan = 1024;        // tags of a turn whose bases are staged in LDS
@@ -746,8 +746,8 @@ __device__ __forceinline__ uint32_t code_start(uint32_t code) {
 }
 // Piece q of the np pieces of tag i, whose first piece has ordinal `first`.
 // Ahead: turns of the row loop unrolled (long rows: four loads in flight; 10,007
-// stress cubics: 40 -> 24.5 us; 1M map segments, of five pieces a curve, 42 us
-// without, 45 with).
+// stress cubics: 25.9 -> 24.4 us; 1M map segments, of five pieces a curve, 36 us
+// without, 42 with).
 template <int Ahead>
 __device__ __forceinline__ void list_piece(uint32_t keep, const uint32_t* __restrict__ codes,
                                            const uint32_t* __restrict__ ordered, uint64_t ordered_cap, bool line,
@@ -1002,7 +1002,8 @@ __device__ __forceinline__ uint64_t tail_tile(const uint64_t* base, uint32_t i) 
 // items written after it.  With the library's divisions, square roots and
 // arctangents, separate multiplies and adds in the polynomials, and all six
 // branch breaks walked per range: 362 us; with whole items of one or two
-// units: 279 us.
+// units: 279 us; 248 us with the tangents, chord and end angles of a piece in
+// the oracle's operations.
 template <int MinWaves, bool Stats, bool Newton>
 __global__ __launch_bounds__(kSlotBlock, MinWaves) void slot_kernel(SceneView sv, Cfg cfg, ItemWs ws,
                                                                     const Slot* __restrict__ pcs,
@@ -1224,7 +1225,8 @@ struct TailSink {
 // when the block spans more than kTailWin tiles).  Bound by a block's chain of
 // dependent loads, its tiles' atomics and the write: 43 us for 1M tags with
 // blocks of 128 or 256, 50 us with 1,024, whose few blocks also leave a small
-// scene on few CUs (1,000 cubics: 6.9, 7.7, 12 and 18 us with 128 to 1,024).
+// scene on few CUs (1,000 cubics: 6.9, 7.7, 12 and 18 us with 128 to 1,024);
+// 45 us with a join's unit vectors and turn correctly rounded.
 template <bool Stats>
 __global__ __launch_bounds__(kTailBlock, 3) void tail_kernel(SceneView sv, Cfg cfg, ItemWs ws,
                                                             const uint64_t* __restrict__ base, uint64_t slot_cap,
@@ -1317,13 +1319,14 @@ __device__ __forceinline__ void record_item(const SceneView& sv, const ItemWs& w
 // turn; a scene of few tiles gives each to several blocks (every split-th
 // round of 256 units), since a block's rounds of records follow one another
 // and a chunk's records too: 24 cubics (10 tiles of about 750 units) took 27
-// us with a block per tile and chunks of 16, 14 us with 4 blocks a tile and
-// chunks of 4.  The first block also publishes dst[0] = records and dst[1] =
-// 0 when everything fit, else 1 (slots or items were dropped: the workspace
-// must grow; the counters stay in ws.ctl), for which a launch of its own
-// took 4.6 us.  Bound by its bytes and by waiting for them, not by the points:
-// 1M map segments, 210 us; of 243 us before the items shrank, 237 were left
-// with every point's computation taken out, 222 without the copy out.
+// us with a block per tile and chunks of 16, 24 us with chunks of 4, and 15 us
+// with 4 or 8 blocks a tile besides (1,000 cubics: 32 and 17 us).  The first
+// block also publishes dst[0] = records and dst[1] = 0 when everything fit, else
+// 1 (slots or items were dropped: the workspace must grow; the counters stay in
+// ws.ctl), for which a launch of its own took 4.6 us.  Bound by its bytes and by
+// waiting for them, not by the points: 1M map segments, 198 us; of 243 us before
+// the items shrank, 237 were left with every point's computation taken out, 222
+// without the copy out.
 template <bool Newton>
 __global__ __launch_bounds__(kRecBlock, Newton ? 3 : 6) void record_kernel(SceneView sv, ItemWs ws, int arcs,
                                                            const uint64_t* __restrict__ roff,
