@@ -21,11 +21,14 @@ from paper_2405_00127_amd import scenes as S
 pytestmark = pytest.mark.gpu
 
 # (piece_waves, chunk_k, bisect_range, bisect_waves): every slot-kernel and
-# bisection instantiation, chunk sizes and ranges across the tuner's grid,
-# including the committed tunings of the 1M-segment map scene (lines and
-# arcs (1, 16, 192, 4)) and of the 256-scene batch (2, 16, 512, 2)
+# bisection instantiation, chunk sizes and ranges across the tuner's grid
+# (ranges up to 256 differ on the 1M-segment scene, and chunk sizes only in
+# scenes past 2^17 slots), including the committed tunings of the 1M-segment
+# map scene (lines (3, 32, 0, 2), arcs (3, 16, 128, 3)) and of the 256-scene
+# batch (1, 32, 128, 2)
 GRID = [(2, 16, 256, 2), (1, 4, 1024, 2), (2, 8, 128, 3), (3, 32, 128, 4), (3, 16, 192, 3), (3, 64, 384, 2),
-        (1, 32, 256, 4), (3, 4, 128, 2), (1, 16, 192, 4), (2, 16, 512, 2)]
+        (1, 32, 256, 4), (3, 4, 128, 2), (1, 16, 192, 4), (2, 16, 512, 2), (3, 32, 0, 2), (3, 16, 128, 3),
+        (1, 32, 128, 2)]
 
 
 def _say(*a):
