@@ -30,6 +30,12 @@ struct SubpathState {
 };
 
 inline bool same(float ax, float ay, float bx, float by) { return ax == bx && ay == by; }
+// the verbs at v and v + 1 have a point or more each
+inline bool both_have_points(const uint8_t* v) {
+    uint16_t u;
+    memcpy(&u, v, 2);
+    return (u & 0xfcfcu) == 0u;
+}
 inline bool finite_f(float v) {
     uint32_t u;
     memcpy(&u, &v, 4);
@@ -64,13 +70,6 @@ bool encode_paths(const sx_paths& in, const sx_style* styles, uint32_t n_styles,
         const bool fill = (styles[in.style_ix[k]].flags & SX_STYLE_FILL) != 0;
         const float* P = in.pts + 2 * (size_t)in.pt_off[k];
         const uint32_t np = in.pt_off[k + 1] - in.pt_off[k];
-        // (points that the verbs have: with other offsets nothing is read ahead)
-        uint32_t has = 0;
-        for (uint32_t vi = in.verb_off[k]; vi < in.verb_off[k + 1]; vi++) {
-            const uint32_t v = in.verbs[vi];
-            has += v > 3u ? 0u : (v ? v : 1u);
-        }
-        const bool ahead = has == np;
         uint32_t pi = 0;
         SubpathState sp;
         auto close_line = [&]() {
@@ -93,17 +92,19 @@ bool encode_paths(const sx_paths& in, const sx_style* styles, uint32_t n_styles,
                 put_pt(sp.dx, sp.dy);
             }
         };
-        for (uint32_t vi = in.verb_off[k]; vi < in.verb_off[k + 1]; vi++) {
+        const uint32_t vend = in.verb_off[k + 1];
+        for (uint32_t vi = in.verb_off[k]; vi < vend; vi++) {
             const uint8_t v = in.verbs[vi];
             // a verb adds at most a closing line and a marker, or its own points and a start
             out.tags.room(4);
             out.data.room(16);
-            if (v - 1u < 3u && ahead && pi + 3 <= np && sp.has_dir) {
+            if (v - 1u < 3u && vend - vi > 2u && both_have_points(in.verbs + vi + 1u) && pi + 3 <= np && sp.has_dir) {
                 const uint32_t c = v;
                 // inside a path every segment reads three points and
                 // advances by its own, with no branch on its degree (the
                 // degrees of a drawing are not predictable: 13 ns a
-                // segment with a loop over its points)
+                // segment with a loop over its points).  The points are its
+                // own and the next two verbs', whatever the offsets say.
                 const float* q = P + 2 * (size_t)pi;
                 const bool two = c >= 2, three = c == 3;
                 const bool f1 = finite_f(q[0]) & finite_f(q[1]), f2 = finite_f(q[2]) & finite_f(q[3]),
