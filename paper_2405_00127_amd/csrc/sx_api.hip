@@ -205,6 +205,7 @@ struct sx_scene {
     uint32_t* d_nslots = nullptr;
     uint32_t* d_codes = nullptr;  // the first piece codes of each tag
     uint32_t* d_ordered = nullptr;  // all piece codes of tags with more (slot_cap words)
+    uint32_t* d_rich = nullptr;     // per bisection wave, where they start; the tags (a word per tag each)
     uint64_t* d_base = nullptr;
     // per slot: the slot, its record count and record offset
     sx::Slot* d_slots = nullptr;
@@ -320,6 +321,7 @@ void free_scene(sx_scene* s) {
     dfree(s->d_nslots);
     dfree(s->d_codes);
     dfree(s->d_ordered);
+    dfree(s->d_rich);
     dfree(s->d_base);
     dfree(s->d_slots);
     dfree(s->d_rc);
@@ -479,6 +481,7 @@ hipError_t reserve_scene(sx_scene* s, uint32_t n_tags, uint32_t n_pts, uint32_t 
             regrow(s->d_codes, std::min<size_t>(std::max<size_t>((size_t)1 << 25, (size_t)c * sx::kKeepCodes),
                                                 (size_t)c * 1024) * sizeof(uint32_t));
             regrow(s->d_base, ((size_t)c + 1) * sizeof(uint64_t));
+            regrow(s->d_rich, 2 * (size_t)c * sizeof(uint32_t));
             regrow(s->d_status_nslots, sx::scan_status_bytes(c));
         }
         if (first) {
@@ -551,20 +554,23 @@ hipError_t run_one(const sx_ctx* ctx, const sx_scene* s, const sx::Cfg& conf, in
     sx::Cfg cfg = conf;
     cfg.K_ovf = cfg.K;
     if (s->slot_cap <= kSmallSlots) cfg.K = std::min(cfg.K, kSmallChunk);
+    const uint32_t keep = sx::keep_codes_of(s->n_tags);
+    const sx::OrderedCodes oc{s->d_ordered, s->slot_cap, s->d_rich, s->d_rich + s->cap_tags, s->d_ws_ctl,
+                              sx::bisect_range_of(s->n_tags, t.bisect_range)};
     switch (ph) {
         case kPhScanTags:
             return sx::launch_scan_tags(s->d_tags, s->n_tags, s->d_mon, ctl_block(s, 0), s->d_status_tags, s->d_ws_ctl,
                                         st);
         case kPhBisectCount:
-            return sx::launch_bisect(view(s), cfg, sx::bisect_range_of(s->n_tags, t.bisect_range), sx::keep_codes_of(s->n_tags), (int)t.bisect_waves,
-                                     s->d_nslots, s->d_codes, s->d_ordered, s->slot_cap, s->d_ws_ctl, stats, st);
+            return sx::launch_bisect(view(s), cfg, keep, (int)t.bisect_waves, s->d_nslots, s->d_codes, oc, stats, st);
         case kPhScanSlots:
             // (a small scene's bases are part of the next phase)
             if (sx::list_is_small(s->n_tags)) return hipSuccess;
-            return sx::launch_scan_slots(s->d_nslots, s->n_tags, s->d_base, ctl_block(s, 1), s->d_status_nslots, st);
+            return sx::launch_scan_slots(view(s), cfg, keep, s->d_nslots, s->d_codes, oc, s->d_base, ctl_block(s, 1),
+                                         s->d_status_nslots, st);
         case kPhBisectWrite:
-            return sx::launch_list(s->n_tags, sx::keep_codes_of(s->n_tags), s->d_nslots, s->d_codes, s->d_ordered,
-                                   s->slot_cap, s->d_base, s->d_slots, s->slot_cap, st);
+            return sx::launch_list(s->n_tags, keep, s->d_nslots, s->d_codes, oc, s->d_base, s->d_slots, s->slot_cap,
+                                   st);
         case kPhPieces:
             return sx::launch_slots(view(s), cfg, workspace(s), s->d_slots, n_slots_dev(s), s->slot_cap, s->d_rc,
                                     (int)t.piece_waves, stats, st);
@@ -1157,7 +1163,10 @@ int sx_run_phase(sx_ctx* ctx, const sx_scene* s, int phase, float tolerance, int
     const uint64_t rec = output_mode == SX_OUT_ARCS ? sizeof(sx_arc) : sizeof(sx_line);
     hipError_t e = hipSuccess;
     // (the bisection alone, again and again: its codes go to the same place)
-    if (phase == kPhBisectCount) e = sx::launch_zero({{&s->d_ws_ctl->ordered_n, sizeof(s->d_ws_ctl->ordered_n)}}, st);
+    if (phase == kPhBisectCount)
+        e = sx::launch_zero({{&s->d_ws_ctl->ordered_n, sizeof(s->d_ws_ctl->ordered_n)},
+                             {&s->d_ws_ctl->rich_n, sizeof(s->d_ws_ctl->rich_n)}},
+                            st);
     if (e == hipSuccess) e = run_one(ctx, s, cfg, phase, out_dev, out_capacity_bytes / rec, nullptr, st);
     return e == hipSuccess ? SX_OK : hip_fail(ctx, e, "phase launch");
 }

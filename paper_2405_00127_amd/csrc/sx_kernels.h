@@ -20,6 +20,7 @@ struct WsCtl {
     unsigned long long items_total;  // units requested by all tiles (of a run that dropped some)
     unsigned long long slots_total;  // slots of the last expansion
     unsigned long long ordered_n;    // piece codes of tags with more than are kept
+    unsigned long long rich_n;       // such tags listed
     unsigned long long result[2];    // records and status, for synchronous readback
 };
 struct ItemWs {
@@ -106,22 +107,32 @@ inline uint32_t bisect_range_of(uint32_t n, uint32_t asked) {
     const uint32_t few = std::min((n + kFillWaves - 1u) / kFillWaves, kFillRange);
     return std::min(std::max(n / 8192u + (n % 8192u != 0u), few), kMostRange);
 }
-// Slots per tag (pieces + 1; bit 31 marks a line) and, in no defined order,
-// the codes of its pieces; a tag with more than `keep` has them in order in
-// `ordered` from the index that its row starts with (ctl->ordered_n of
-// ordered_cap words are taken).
-hipError_t launch_bisect(const SceneView& sv, const Cfg& cfg, uint32_t range, uint32_t keep, int waves,
-                         uint32_t* nslots, uint32_t* codes, uint32_t* ordered, uint64_t ordered_cap, WsCtl* ctl,
-                         unsigned long long* stats, hipStream_t s);
-// Slot bases: exclusive scan of the slot counts (base[n] the total).
-hipError_t launch_scan_slots(const uint32_t* nslots, uint32_t n, uint64_t* base, void* ctl, void* st, hipStream_t s);
+// The codes of tags with more pieces than are kept, in order: `codes` has cap
+// words, of which ctl->ordered_n are taken; wave_base (per bisection wave of
+// `range` tags) and the first word of a tag's row say where its are; rich lists
+// the ctl->rich_n tags (both arrays have a word per tag).
+struct OrderedCodes {
+    uint32_t* codes;
+    uint64_t cap;
+    uint32_t *wave_base, *rich;
+    WsCtl* ctl;
+    uint32_t range;
+};
+// Slots per tag (pieces + 1; bit 31 marks a line) and, in no defined order, the
+// codes of its pieces, or its place among the ordered ones.
+hipError_t launch_bisect(const SceneView& sv, const Cfg& cfg, uint32_t keep, int waves, uint32_t* nslots,
+                         uint32_t* codes, const OrderedCodes& oc, unsigned long long* stats, hipStream_t s);
+// Slot bases: exclusive scan of the slot counts (base[n] the total); and the
+// ordered codes (of a small scene, list_is_small, launch_bisect writes them).
+hipError_t launch_scan_slots(const SceneView& sv, const Cfg& cfg, uint32_t keep, const uint32_t* nslots,
+                             const uint32_t* codes, const OrderedCodes& oc, uint64_t* base, void* ctl, void* st,
+                             hipStream_t s);
 // The piece list pcs: piece p of the scene (canonical order) as {tag, code},
 // its slot being p + tag.  Small scenes (list_is_small): computes the slot
 // bases too.
 bool list_is_small(uint32_t n_tags);
 hipError_t launch_list(uint32_t n_tags, uint32_t keep, const uint32_t* nslots, const uint32_t* codes,
-                       const uint32_t* ordered, uint64_t ordered_cap, uint64_t* base, Slot* pcs, uint64_t slot_cap,
-                       hipStream_t s);
+                       const OrderedCodes& oc, uint64_t* base, Slot* pcs, uint64_t slot_cap, hipStream_t s);
 // pieces (one thread per piece, tiles of slot_block() pieces)
 hipError_t launch_slots(const SceneView& sv, const Cfg& cfg, const ItemWs& ws, const Slot* pcs,
                         const uint64_t* n_slots_dev, uint64_t slot_cap, uint32_t* rc, int waves,

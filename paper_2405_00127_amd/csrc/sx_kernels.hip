@@ -207,16 +207,18 @@ __device__ __forceinline__ Pair tag_inc(uint32_t t) {
 // memset.
 // (The next launch reads these words after the kernel boundary, which
 // makes them visible; no fence is needed here.)
-__device__ __forceinline__ void finish_scan(ScanCtl* ctl, uint32_t epoch_used) {
-    if (atomicAdd(&ctl->done, 1u) == gridDim.x - 1) {
+__device__ __forceinline__ void finish_scan(ScanCtl* ctl, uint32_t epoch_used, uint32_t blocks) {
+    if (atomicAdd(&ctl->done, 1u) == blocks - 1) {
         ctl->ticket = 0;
         ctl->done = 0;
         ctl->epoch = epoch_used;
     }
 }
 
+// blocks: those of the grid that come here.
 template <int Items, class Load, class Store>
-__device__ void scan_tile(Load load, Store store, uint32_t n, ScanCtl* ctl, TileStatus* st) {
+__device__ void scan_tile(Load load, Store store, uint32_t n, ScanCtl* ctl, TileStatus* st,
+                          uint32_t blocks = gridDim.x) {
     constexpr uint32_t kTile = kScanBlock * Items;
     __shared__ uint32_t s_tile, s_epoch;
     __shared__ Pair s_wave[kScanBlock / 64];
@@ -233,7 +235,7 @@ __device__ void scan_tile(Load load, Store store, uint32_t n, ScanCtl* ctl, Tile
     const uint32_t ntiles = (n + kTile - 1) / kTile;
     if (tile >= ntiles) {
         // a grid sized for a capacity larger than this launch's n: nothing to scan
-        if (tid == 0) finish_scan(ctl, s_epoch);
+        if (tid == 0) finish_scan(ctl, s_epoch, blocks);
         return;
     }
     const uint64_t base = (uint64_t)tile * kTile + (uint64_t)tid * Items;
@@ -272,7 +274,7 @@ __device__ void scan_tile(Load load, Store store, uint32_t n, ScanCtl* ctl, Tile
     Pair pre = s_excl + texcl;
     store(base, item, pre);
     __syncthreads();
-    if (tid == 0) finish_scan(ctl, s_epoch);
+    if (tid == 0) finish_scan(ctl, s_epoch, blocks);
 }
 
 template <int Items>
@@ -284,6 +286,7 @@ __global__ __launch_bounds__(kScanBlock) void scan_tags_kernel(const uint8_t* __
         ws_reset->ovf_n = 0;
         ws_reset->items_total = 0;
         ws_reset->ordered_n = 0;
+        ws_reset->rich_n = 0;
     }
     auto load = [&](uint64_t base, Pair* item) {
         if (base + Items <= n) {
@@ -348,17 +351,11 @@ __global__ __launch_bounds__(kScanBlock) void scan_tags_kernel(const uint8_t* __
 // (Mask: the bits of an input word that count)
 template <int Items, uint32_t Mask = ~0u>
 __device__ __forceinline__ void scan_u32_body(const uint32_t* __restrict__ in, uint32_t n, uint64_t* __restrict__ out,
-                                              ScanCtl* ctl, TileStatus* st);
+                                              ScanCtl* ctl, TileStatus* st, uint32_t blocks = gridDim.x);
 __global__ __launch_bounds__(kScanBlock) void scan_counts_kernel(const uint32_t* __restrict__ in, uint32_t n,
                                                                  uint64_t* __restrict__ out, ScanCtl* ctl,
                                                                  TileStatus* st) {
     scan_u32_body<kCountItems>(in, n, out, ctl, st);
-}
-template <int Items>
-__global__ __launch_bounds__(kScanBlock) void scan_slots_kernel(const uint32_t* __restrict__ in, uint32_t n,
-                                                                uint64_t* __restrict__ out, ScanCtl* ctl,
-                                                                TileStatus* st) {
-    scan_u32_body<Items, ~kCountLine>(in, n, out, ctl, st);
 }
 // the same with n read from device memory (clamped to the buffers' capacity);
 // the grid covers the capacity
@@ -373,7 +370,7 @@ __global__ __launch_bounds__(kScanBlock) void scan_counts_dev_kernel(const uint3
 }
 template <int Items, uint32_t Mask>
 __device__ __forceinline__ void scan_u32_body(const uint32_t* __restrict__ in, uint32_t n, uint64_t* __restrict__ out,
-                                              ScanCtl* ctl, TileStatus* st) {
+                                              ScanCtl* ctl, TileStatus* st, uint32_t blocks) {
     auto load = [&](uint64_t base, Pair* item) {
         if (base + Items <= n) {
 #pragma unroll
@@ -397,7 +394,7 @@ __device__ __forceinline__ void scan_u32_body(const uint32_t* __restrict__ in, u
             if (base + j == (uint64_t)n - 1u) out[n] = pre.a + incl[j].a;
         }
     };
-    scan_tile<Items>(load, store, n, ctl, st);
+    scan_tile<Items>(load, store, n, ctl, st, blocks);
 }
 
 // --------------------------------------------------------- bisection
@@ -434,16 +431,20 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// A tag with more pieces than codes kept runs its bisection once more, at the
-// end of its wave's range, by the whole wave, and its codes go to `ordered` in
-// parameter order.  Their starts are marked in a bitmap of the 2^kMaxDepth
-// parameters (over the LDS of the first part), so that their order is that of
-// the bits and a piece's depth follows from the next one's start.  The first
-// round tries every node above depth 6, of which the ones below an accepted
-// node are then dropped.  (With one lane per tag and the trials in order, in
-// the list launch, 400,000 stress cubics with 80 codes kept took 24.5 ms there,
-// 2.9 ms this way; 1M map segments, 32 kept, 68 us and 20 us; without that code
-// the list kernel needs 24 VGPRs instead of 93.)
+// A tag with more pieces than codes kept (a rich one) runs its bisection once
+// more, by a whole wave, and its codes go to `ordered` in parameter order.
+// Their starts are marked in a bitmap of the 2^kMaxDepth parameters, so that
+// their order is that of the bits and a piece's depth follows from the next
+// one's start.  The first round tries every node above depth 6, of which the
+// ones below an accepted node are then dropped.  Who does it: blocks of the slot
+// scan that have no tile, from a list (rich tags come in clusters, and one
+// wave's range of them would be the launch's length); in a small scene, which
+// has no such scan, and ranges of one or two tags, the wave that has bisected
+// the tag.  300 stress cubics beside 1M map segments, 32 codes kept: the pass is
+// 1.72 ms with one lane per tag in the list launch, 3.28 with the tags of each
+// wave's range at its end, 1.09 this way.  400,000 stress cubics, 80 kept: 24.5 ms
+// with one lane per tag, 2.9 either other way.  (The list kernel needs 25 VGPRs
+// without that code, 93 with it.)
 constexpr uint32_t kMarkWords = 1u << (kMaxDepth - 5);
 struct BisectLds {
     double seg[13][kNodeSegs];      // NodeSeg
@@ -454,6 +455,7 @@ struct BisectLds {
     uint32_t curve[128];            // ring of curves not yet taken
     uint32_t node[kNodeStack];      // segment << 21 | depth << 16 | t0
     uint32_t rich[kBisectMaxRange / 32];  // tags with more pieces than codes kept
+    uint32_t n_rich;                      // and their pieces
 };
 static_assert(offsetof(BisectLds, node) >= kMarkWords * 4, "the bitmap ends before the node stack");
 static_assert(kMarkWords == 32u * kBisectBlock, "32 words per lane");
@@ -474,7 +476,7 @@ __device__ __forceinline__ bool try_node(const SceneView& sv, const Cfg& cfg, co
 // their number.
 __device__ __forceinline__ uint32_t order_codes(const SceneView& sv, const Cfg& cfg, uint32_t i, uint32_t* mark,
                                                 uint32_t* node, uint32_t* __restrict__ out, uint64_t room) {
-    const uint32_t lane = threadIdx.x;
+    const uint32_t lane = threadIdx.x & 63u;
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     constexpr uint32_t D = (uint32_t)kMaxDepth;
     NodeSeg e;
@@ -563,12 +565,19 @@ __device__ __forceinline__ uint32_t order_codes(const SceneView& sv, const Cfg& 
     return total;
 }
 
-template <bool Stats, int MinWaves>
-__global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneView sv, Cfg cfg, uint32_t range,
-                                                                        uint32_t keep, uint32_t* __restrict__ nslots,
-                                                                        uint32_t* __restrict__ codes,
-                                                                        uint32_t* __restrict__ ordered,
-                                                                        uint64_t ordered_cap, WsCtl* ctl,
+// Where a rich tag's pieces are: from wave_base[tag / range] + its row's first
+// word (its place among its wave's) on in `ordered`; past its end when full (the
+// scene then has more slots than the buffers hold).
+__device__ __forceinline__ uint64_t ordered_at(const OrderedCodes& oc, uint32_t keep, const uint32_t* codes, uint32_t i) {
+    const uint32_t w = oc.wave_base[i / oc.range];
+    return w == ~0u ? ~0ull >> 1 : (uint64_t)w + codes[(size_t)i * keep];
+}
+
+// Small: the wave orders its rich tags itself.
+template <bool Stats, bool Small, int MinWaves>
+__global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneView sv, Cfg cfg, uint32_t keep,
+                                                                        uint32_t* __restrict__ nslots,
+                                                                        uint32_t* __restrict__ codes, OrderedCodes oc,
                                                                         unsigned long long* __restrict__ stats) {
     __shared__ BisectLds lds;
     auto& s_seg = lds.seg;
@@ -578,7 +587,7 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
     auto& s_found = lds.found;
     auto& s_free = lds.free_;
     auto& s_curve = lds.curve;
-    const uint32_t lane = threadIdx.x;
+    const uint32_t lane = threadIdx.x, range = oc.range;
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const uint32_t a = blockIdx.x * range;
     const uint32_t b = min(sv.n_tags, a + range);
@@ -588,7 +597,7 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
     uint32_t n_free = kNodeSegs, n_node = 0;
     s_free[lane] = lane;
     if (lane < kBisectMaxRange / 32u) lds.rich[lane] = 0u;
-    uint32_t more = 0;  // pieces of this lane's tags with more than are kept
+    if (lane == 0u) lds.n_rich = 0u;
     wave_lds_sync();
     for (;;) {
         // this turn's nodes: the top of the stack on the first lanes
@@ -675,7 +684,7 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
                 const uint32_t np = s_found[sg], k = s_tag[sg] - a;
                 nslots[a + k] = np + 1u;
                 if (np > keep) {
-                    more += np;
+                    codes[(size_t)(a + k) * keep] = atomicAdd(&lds.n_rich, np);
                     atomicOr(&lds.rich[k >> 5], 1u << (k & 31u));
                 }
             }
@@ -696,28 +705,65 @@ __global__ __launch_bounds__(kBisectBlock, MinWaves) void bisect_kernel(SceneVie
         n_free += (uint32_t)__popcll(m_done);
         wave_lds_sync();
     }
-    if (__ballot(more != 0u)) {
-        for (int d = 32; d >= 1; d >>= 1) more += __shfl_xor(more, d, 64);
+    const uint32_t more = lds.n_rich;
+    if (more) {
+        const uint32_t bits = lane < kBisectMaxRange / 32u ? lds.rich[lane] : 0u, cnt = (uint32_t)__popc(bits);
+        uint32_t pre = cnt;
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t u = __shfl_up(pre, d, 64);
+            if ((int)lane >= d) pre += u;
+        }
         unsigned long long at = 0;
-        if (lane == 0u) at = atomicAdd(&ctl->ordered_n, (unsigned long long)more);
-        at = __shfl(at, 0, 64);
-        // (none when full: the scene then has more slots than the buffers hold)
-        const bool fits = at + more <= ordered_cap;
-        uint32_t off = fits ? (uint32_t)at : ~0u;
-        for (uint32_t w = 0; w < (b - a + 31u) / 32u; w++) {
-            uint32_t bits = lds.rich[w];
-            while (bits) {
-                const uint32_t i = a + w * 32u + (uint32_t)__builtin_ctz(bits);
-                bits &= bits - 1u;
-                if (lane == 0u) codes[(size_t)i * keep] = off;
-                if (fits) off += order_codes(sv, cfg, i, reinterpret_cast<uint32_t*>(&lds), s_node, ordered + off,
-                                              ordered_cap - off);
+        if (lane == 0u) at = atomicAdd(&oc.ctl->ordered_n, (unsigned long long)more);
+        if (!Small && lane == 63u) at = atomicAdd(&oc.ctl->rich_n, (unsigned long long)pre);
+        const unsigned long long first = __shfl(at, 0, 64);
+        const bool fits = first + more <= oc.cap;
+        if (lane == 0u) oc.wave_base[blockIdx.x] = fits ? (uint32_t)first : ~0u;
+        if (Small && fits) {
+            uint32_t off = 0;
+            for (uint32_t w = 0; w < (b - a + 31u) / 32u; w++) {
+                uint32_t m = __shfl(bits, (int)w, 64);
+                while (m) {
+                    const uint32_t i = a + w * 32u + (uint32_t)__builtin_ctz(m);
+                    m &= m - 1u;
+                    if (lane == 0u) codes[(size_t)i * keep] = off;
+                    off += order_codes(sv, cfg, i, reinterpret_cast<uint32_t*>(&lds), s_node,
+                                       oc.codes + first + off, oc.cap - first - off);
+                }
             }
+        } else if (!Small) {
+            uint32_t m = bits;
+            for (unsigned long long k = __shfl(at, 63, 64) + pre - cnt; m; m &= m - 1u)
+                oc.rich[k++] = a + lane * 32u + (uint32_t)__builtin_ctz(m);
         }
     }
     if (Stats) {
         atomicAdd(&stats[kStTrials], (unsigned long long)n_trials);
         atomicAdd(&stats[kStLines], (unsigned long long)n_lines);
+    }
+}
+
+// Slot bases: the scan of the slot counts, by the first blocks; the others put
+// the rich tags' codes in order, a wave at a time (without a ticket: 768 more of
+// them, all on one word, were 45 us).
+template <int Items>
+__global__ __launch_bounds__(kScanBlock, 3) void scan_slots_kernel(const uint32_t* __restrict__ nslots,
+                                                                uint64_t* __restrict__ base, ScanCtl* ctl,
+                                                                TileStatus* st, SceneView sv, Cfg cfg, uint32_t keep,
+                                                                const uint32_t* __restrict__ codes, OrderedCodes oc) {
+    __shared__ uint32_t s_order[kScanBlock / 64][kMarkWords + kNodeStack];
+    const uint32_t n = sv.n_tags, n_tiles = (n + kScanBlock * Items - 1u) / (kScanBlock * Items);
+    if (blockIdx.x < n_tiles) {
+        scan_u32_body<Items, ~kCountLine>(nslots, n, base, ctl, st, n_tiles);
+        return;
+    }
+    const uint32_t wv = threadIdx.x >> 6, n_rich = (uint32_t)oc.ctl->rich_n;
+    for (uint32_t k = (blockIdx.x - n_tiles) * (kScanBlock / 64u) + wv; k < n_rich;
+         k += (gridDim.x - n_tiles) * (kScanBlock / 64u)) {
+        const uint32_t i = oc.rich[k];
+        const uint64_t at = ordered_at(oc, keep, codes, i);
+        if (at < oc.cap)
+            order_codes(sv, cfg, i, s_order[wv], s_order[wv] + kMarkWords, oc.codes + at, oc.cap - at);
     }
 }
 
@@ -749,13 +795,13 @@ __device__ __forceinline__ uint32_t code_start(uint32_t code) {
 // stress cubics: 25.9 -> 24.4 us; 1M map segments, of five pieces a curve, 36 us
 // without, 42 with).
 template <int Ahead>
-__device__ __forceinline__ void list_piece(uint32_t keep, const uint32_t* __restrict__ codes,
-                                           const uint32_t* __restrict__ ordered, uint64_t ordered_cap, bool line,
+__device__ __forceinline__ void list_piece(uint32_t keep, const uint32_t* __restrict__ codes, const OrderedCodes& oc,
+                                           bool line,
                                            uint32_t i, uint32_t q, uint32_t np, uint64_t first,
                                            Slot* __restrict__ pcs, uint64_t slot_cap) {
     if (np > keep) {
-        const uint64_t at = (uint64_t)codes[(size_t)i * keep] + q;
-        if (first + q < slot_cap) pcs[first + q] = Slot{i, at < ordered_cap ? ordered[at] : slot_code(0u, 0u, false)};
+        const uint64_t at = ordered_at(oc, keep, codes, i) + q;
+        if (first + q < slot_cap) pcs[first + q] = Slot{i, at < oc.cap ? oc.codes[at] : slot_code(0u, 0u, false)};
         return;
     }
     uint32_t code = slot_code(0u, 0u, false) | kCodeLine, rank = 0;
@@ -778,8 +824,7 @@ __device__ __forceinline__ void list_piece(uint32_t keep, const uint32_t* __rest
 template <int Ahead>
 __global__ __launch_bounds__(kListBlock) void list_kernel(uint32_t n, uint32_t keep,
                                                           const uint32_t* __restrict__ nslots,
-                                                          const uint32_t* __restrict__ codes,
-                                                          const uint32_t* __restrict__ ordered, uint64_t ordered_cap,
+                                                          const uint32_t* __restrict__ codes, OrderedCodes oc,
                                                           const uint64_t* __restrict__ base, Slot* __restrict__ pcs,
                                                           uint64_t slot_cap, uint32_t turn) {
     __shared__ uint32_t s_tag[2];
@@ -823,7 +868,7 @@ __global__ __launch_bounds__(kListBlock) void list_kernel(uint32_t n, uint32_t k
             }
             const uint32_t i = tag0 + lo, w = nslots[i];
             const uint64_t first = staged ? f0 + s_off[lo] : base[i] - i;
-            list_piece<Ahead>(keep, codes, ordered, ordered_cap, (w & kCountLine) != 0u, i, (uint32_t)(p - first),
+            list_piece<Ahead>(keep, codes, oc, (w & kCountLine) != 0u, i, (uint32_t)(p - first),
                               (w & ~kCountLine) - 1u, first, pcs, slot_cap);
         }
         __syncthreads();  // s_tag and s_off are reused
@@ -836,9 +881,8 @@ __global__ __launch_bounds__(kListBlock) void list_kernel(uint32_t n, uint32_t k
 // take 30 us, this 35).
 __global__ __launch_bounds__(kListBlock) void list_small_kernel(uint32_t n, uint32_t keep,
                                                                 const uint32_t* __restrict__ nslots,
-                                                                const uint32_t* __restrict__ codes,
-                                                                const uint32_t* __restrict__ ordered,
-                                                                uint64_t ordered_cap, uint64_t* __restrict__ base, Slot* __restrict__ pcs,
+                                                                const uint32_t* __restrict__ codes, OrderedCodes oc,
+                                                                uint64_t* __restrict__ base, Slot* __restrict__ pcs,
                                                                 uint64_t slot_cap) {
     extern __shared__ uint32_t s_end[];  // pieces of tags 0..i; bit 31: a line
     __shared__ uint32_t s_wave[kListBlock / 64];
@@ -886,7 +930,7 @@ __global__ __launch_bounds__(kListBlock) void list_small_kernel(uint32_t n, uint
             cnt = le ? cnt - half : half;
         }
         const uint32_t first = i ? s_end[i - 1u] & ~kCountLine : 0u, e = s_end[i];
-        list_piece<4>(keep, codes, ordered, ordered_cap, (e & kCountLine) != 0u, i, p - first,
+        list_piece<4>(keep, codes, oc, (e & kCountLine) != 0u, i, p - first,
                       (e & ~kCountLine) - first, first, pcs, slot_cap);
     }
 }
@@ -1534,16 +1578,6 @@ hipError_t launch_scan_counts(const uint32_t* in, uint32_t n, uint64_t* out, voi
     scan_counts_kernel<<<count_scan_tiles(n), kScanBlock, 0, s>>>(in, n, out, (ScanCtl*)ctl, (TileStatus*)st);
     return hipGetLastError();
 }
-hipError_t launch_scan_slots(const uint32_t* nslots, uint32_t n, uint64_t* base, void* ctl, void* st, hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    if (n <= kCountSmall)
-        scan_slots_kernel<kCountItemsSmall><<<count_scan_tiles(n, kCountItemsSmall), kScanBlock, 0, s>>>(
-            nslots, n, base, (ScanCtl*)ctl, (TileStatus*)st);
-    else
-        scan_slots_kernel<kCountItems><<<count_scan_tiles(n), kScanBlock, 0, s>>>(nslots, n, base, (ScanCtl*)ctl,
-                                                                                  (TileStatus*)st);
-    return hipGetLastError();
-}
 __global__ void zero_u64_kernel(uint64_t* out) {
     if (threadIdx.x == 0) out[0] = 0ull;
 }
@@ -1569,40 +1603,56 @@ hipError_t launch_scan_counts_dev(const uint32_t* in, const uint64_t* n_dev, uin
 }
 
 template <bool Stats>
-static void bisect_launch(uint32_t g, hipStream_t s, int waves, const SceneView& sv, const Cfg& cfg, uint32_t range,
-                          uint32_t keep, uint32_t* nslots, uint32_t* codes, uint32_t* ordered, uint64_t ordered_cap,
-                          WsCtl* ctl, unsigned long long* stats) {
-    auto* k = waves <= 2 ? bisect_kernel<Stats, 2> : (waves == 3 ? bisect_kernel<Stats, 3> : bisect_kernel<Stats, 4>);
-    k<<<g, kBisectBlock, 0, s>>>(sv, cfg, range, keep, nslots, codes, ordered, ordered_cap, ctl, stats);
+static void bisect_launch(uint32_t g, hipStream_t s, int waves, const SceneView& sv, const Cfg& cfg, uint32_t keep,
+                          uint32_t* nslots, uint32_t* codes, const OrderedCodes& oc, unsigned long long* stats) {
+    auto* k = list_is_small(sv.n_tags) ? bisect_kernel<Stats, true, 2>
+              : waves <= 2             ? bisect_kernel<Stats, false, 2>
+              : waves == 3             ? bisect_kernel<Stats, false, 3>
+                                       : bisect_kernel<Stats, false, 4>;
+    k<<<g, kBisectBlock, 0, s>>>(sv, cfg, keep, nslots, codes, oc, stats);
 }
-hipError_t launch_bisect(const SceneView& sv, const Cfg& cfg, uint32_t range, uint32_t keep, int waves,
-                         uint32_t* nslots, uint32_t* codes, uint32_t* ordered, uint64_t ordered_cap, WsCtl* ctl,
-                         unsigned long long* stats, hipStream_t s) {
+hipError_t launch_bisect(const SceneView& sv, const Cfg& cfg, uint32_t keep, int waves, uint32_t* nslots,
+                         uint32_t* codes, const OrderedCodes& oc, unsigned long long* stats, hipStream_t s) {
     if (sv.n_tags == 0) return hipSuccess;
-    if (range == 0 || range > kBisectMaxRange || keep < (uint32_t)kKeepCodes || keep % 16u)
+    if (oc.range == 0 || oc.range > kBisectMaxRange || keep < (uint32_t)kKeepCodes || keep % 16u)
         return hipErrorInvalidValue;
-    const uint32_t g = (sv.n_tags + range - 1) / range;
+    const uint32_t g = (uint32_t)(((uint64_t)sv.n_tags + oc.range - 1) / oc.range);
     if (stats)
-        bisect_launch<true>(g, s, waves, sv, cfg, range, keep, nslots, codes, ordered, ordered_cap, ctl, stats);
+        bisect_launch<true>(g, s, waves, sv, cfg, keep, nslots, codes, oc, stats);
     else
-        bisect_launch<false>(g, s, waves, sv, cfg, range, keep, nslots, codes, ordered, ordered_cap, ctl, stats);
+        bisect_launch<false>(g, s, waves, sv, cfg, keep, nslots, codes, oc, stats);
+    return hipGetLastError();
+}
+hipError_t launch_scan_slots(const SceneView& sv, const Cfg& cfg, uint32_t keep, const uint32_t* nslots,
+                             const uint32_t* codes, const OrderedCodes& oc, uint64_t* base, void* ctl, void* st,
+                             hipStream_t s) {
+    const uint32_t n = sv.n_tags;
+    if (n == 0) return hipSuccess;
+    // blocks for rich tags: a wave for 64 tags, up to what the chip holds (they
+    // leave at once when there are none)
+    const uint32_t more = std::min(768u, n / 256u);
+    if (n <= kCountSmall)
+        scan_slots_kernel<kCountItemsSmall><<<count_scan_tiles(n, kCountItemsSmall) + more, kScanBlock, 0, s>>>(
+            nslots, base, (ScanCtl*)ctl, (TileStatus*)st, sv, cfg, keep, codes, oc);
+    else
+        scan_slots_kernel<kCountItems><<<count_scan_tiles(n) + more, kScanBlock, 0, s>>>(
+            nslots, base, (ScanCtl*)ctl, (TileStatus*)st, sv, cfg, keep, codes, oc);
     return hipGetLastError();
 }
 bool list_is_small(uint32_t n_tags) { return n_tags <= kSmallTags; }
 hipError_t launch_list(uint32_t n_tags, uint32_t keep, const uint32_t* nslots, const uint32_t* codes,
-                       const uint32_t* ordered, uint64_t ordered_cap, uint64_t* base, Slot* pcs, uint64_t slot_cap,
-                       hipStream_t s) {
+                       const OrderedCodes& oc, uint64_t* base, Slot* pcs, uint64_t slot_cap, hipStream_t s) {
     if (n_tags == 0) return hipSuccess;
     if (list_is_small(n_tags)) {
         const uint32_t g = (uint32_t)std::min<uint64_t>(kSmallBlocks, (slot_cap + kListBlock - 1) / kListBlock);
-        list_small_kernel<<<g, kListBlock, n_tags * sizeof(uint32_t), s>>>(n_tags, keep, nslots, codes, ordered,
-                                                                          ordered_cap, base, pcs, slot_cap);
+        list_small_kernel<<<g, kListBlock, n_tags * sizeof(uint32_t), s>>>(n_tags, keep, nslots, codes, oc, base, pcs,
+                                                                          slot_cap);
     } else {
         const uint32_t turn = slot_cap <= kListSmallSlots ? kListPiecesSmall : kListPieces;
         const uint32_t g = (uint32_t)std::min<uint64_t>(8192, (slot_cap + turn - 1) / turn);
         // (many pieces per tag: long rows)
         auto* k = slot_cap > 8ull * n_tags ? list_kernel<4> : list_kernel<1>;
-        k<<<g, kListBlock, 0, s>>>(n_tags, keep, nslots, codes, ordered, ordered_cap, base, pcs, slot_cap, turn);
+        k<<<g, kListBlock, 0, s>>>(n_tags, keep, nslots, codes, oc, base, pcs, slot_cap, turn);
     }
     return hipGetLastError();
 }

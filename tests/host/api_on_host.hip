@@ -140,16 +140,17 @@ hipError_t launch_scan_counts_dev(const uint32_t* in, const uint64_t* n, uint32_
                                   hipStream_t) {
     return need({in, n, o, ctl, st}), launched();
 }
-hipError_t launch_bisect(const SceneView& sv, const Cfg&, uint32_t, uint32_t, int, uint32_t* nslots, uint32_t* codes,
-                         uint32_t* ordered, uint64_t, WsCtl* ctl, unsigned long long*, hipStream_t) {
-    return need({sv.tags, sv.pts, sv.mon, nslots, codes, ordered, ctl}), launched();
+hipError_t launch_bisect(const SceneView& sv, const Cfg&, uint32_t, int, uint32_t* nslots, uint32_t* codes,
+                         const OrderedCodes& oc, unsigned long long*, hipStream_t) {
+    return need({sv.tags, sv.pts, sv.mon, nslots, codes, oc.codes, oc.wave_base, oc.rich, oc.ctl}), launched();
 }
-hipError_t launch_scan_slots(const uint32_t* nslots, uint32_t, uint64_t* base, void* ctl, void* st, hipStream_t) {
-    return need({nslots, base, ctl, st}), launched();
+hipError_t launch_scan_slots(const SceneView& sv, const Cfg&, uint32_t, const uint32_t* nslots, const uint32_t* codes,
+                             const OrderedCodes& oc, uint64_t* base, void* ctl, void* st, hipStream_t) {
+    return need({sv.tags, nslots, codes, oc.codes, oc.wave_base, oc.rich, base, ctl, st}), launched();
 }
-hipError_t launch_list(uint32_t, uint32_t, const uint32_t* nslots, const uint32_t* codes, const uint32_t* ordered,
-                       uint64_t, uint64_t* base, Slot* pcs, uint64_t, hipStream_t) {
-    return need({nslots, codes, ordered, base, pcs}), launched();
+hipError_t launch_list(uint32_t, uint32_t, const uint32_t* nslots, const uint32_t* codes, const OrderedCodes& oc,
+                       uint64_t* base, Slot* pcs, uint64_t, hipStream_t) {
+    return need({nslots, codes, oc.codes, oc.wave_base, base, pcs}), launched();
 }
 hipError_t launch_slots(const SceneView& sv, const Cfg&, const ItemWs& ws, const Slot* pcs, const uint64_t* n, uint64_t,
                         uint32_t* rc, int, unsigned long long*, hipStream_t) {

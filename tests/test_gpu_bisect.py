@@ -69,7 +69,8 @@ def test_tag_counts_at_the_edges(ctx, n_tags):
 @pytest.mark.parametrize("n_cubics,extra", [(6, 0), (6, SMALL_TAGS)])
 def test_more_pieces_than_codes_kept(ctx, n_cubics, extra):
     """About 1,400 pieces per cubic (1,024 codes are kept at most): the
-    tag's bisection runs again, from the list kernels, small and general."""
+    tag's bisection runs again, by its wave (small scenes) or beside the slot
+    scan."""
     sc = S.scene_c1(5, n_paths=2, n_cubics=n_cubics, tolerance=1e-5)
     if extra:
         b = S.SceneBuilder()
