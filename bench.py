@@ -668,7 +668,7 @@ def phase_of_kernel(name: str):
             return phase
     if re.search(r"sx::record_kernel(<(true|false)>)?\(", name):
         return "records"
-    m = re.search(r"sx::bisect_kernel<(true|false), \d+>", name)
+    m = re.search(r"sx::bisect_kernel<(true|false), (true|false), \d+>", name)
     if m:
         return None if m.group(1) == "true" else "bisect_count"
     m = re.search(r"sx::slot_kernel<\d+, (true|false)(, (true|false))?>", name)
